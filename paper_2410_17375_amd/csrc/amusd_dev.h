@@ -66,6 +66,49 @@ struct DevLayer {
     void* vcache;        // [slot][Hkv][ctx_pad/BK][hd/16][64 lanes][EPL] elements (matrix-core operand order)
 };
 
+// ---- prefill pass: many prompt rows of one sequence at a time
+constexpr int kPfMaxRows = 2048;     // rows of one pass
+constexpr int kPfMinRows = 17;       // prompts up to 16 tokens go through the verify pass's kernels
+constexpr int kPfBlockRows = 128;    // rows that share a stretch of the activation buffers
+constexpr int kPfTileGroup = 16;     // column tiles of the widest workgroup
+constexpr int kPfPartBytes = 96 << 20;   // attention partials in flight (they stay in the memory-side cache between the two kernels)
+enum { kPfQKV = 0, kPfOproj = 1, kPfGateUp = 2, kPfDown = 3, kPfLMHead = 4, kPfStages = 5 };
+
+struct PfTiles {
+    const int* order;     // column tiles by the start of their K walk, each start's filled up with -1 to whole groups
+    int n;                // entries
+    int wgs;              // workgroups of the stage in the verify pass (the walk of tile t is that of workgroup t mod wgs)
+};
+
+// Workspace of the prefill pass; rows padded to cap.
+struct PrefillBufs {
+    int cap;              // rows, a multiple of kPfBlockRows
+    int cus;
+    int att_tiles;        // 16-row tiles whose attention partials fit att_part
+    float* X;             // residual stream [cap][d]
+    void* A;              // norm-fed GEMM input, operand order
+    void* O;              // attention output, operand order
+    void* H;              // SwiGLU output, operand order
+    void* Q_hi;           // [cap][qdim]
+    void* Q_lo;
+    float* ssq;           // [d/16][cap]
+    float* rstd;          // [cap]
+    float* att_part;
+    float* xch;           // [cap x d] first K range's totals of the down projection, in the order of the threads that own them
+    float* best_val;      // [workgroup column halves][cap]
+    int* best_idx;
+    const int* tokens;    // [cap] pinned host memory
+    int* greedy;          // [cap] pinned host memory
+    PfTiles tiles[kPfStages];
+};
+
+struct PrefillArgs {
+    int n;                // rows
+    int L0;               // position of row 0
+    int slot;             // which key-value cache
+    int keep0;            // logits of rows keep0 .. n-1 are stored (n: none)
+};
+
 struct DevModel {
     int n_layers, d, Hq, Hkv, hd, F, V, G;
     int qdim, kvdim, nqkv;

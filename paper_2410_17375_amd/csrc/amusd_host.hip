@@ -104,6 +104,8 @@ struct amusd_model {
     size_t static_bytes = 0;               // bytes of the array that workspace takes
     uint64_t id = 0;
     HostStage* hstage = nullptr;
+    PrefillBufs pf{};                      // workspace of the prefill pass; cap 0: prompts go through the verify pass
+    int* pf_host = nullptr;                // pinned: tokens of a prefill pass, then its greedy tokens
     void* staging = nullptr;               // device staging for host-provided tensors
     size_t staging_bytes = 0;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
@@ -281,6 +283,88 @@ int run_pass(amusd_model* m, const SegReq* segs, int n_seg, bool force_accept, b
         q.kv_len = segs[i].L + h->res.accept_len[i];
         q.p_next = h->res.next_token[i];
     }
+    return AMUSD_OK;
+}
+
+// Workspace of the prefill pass, sized for the model's context.  A model that finds no memory for it (or whose context
+// is shorter than the smallest such pass) prefills through the verify pass.
+int alloc_prefill(amusd_model* m) {
+    const DevModel& D = m->dm;
+    if (D.max_ctx < kPfMinRows) return AMUSD_OK;
+    PrefillBufs T{};
+    T.cap = D.max_ctx >= kPfMaxRows ? kPfMaxRows : (D.max_ctx + kPfBlockRows - 1) / kPfBlockRows * kPfBlockRows;
+    T.cus = m->nwg;
+    const size_t cap = T.cap, d = D.d, q = D.qdim, F = D.F;
+    const size_t tile_bytes = (size_t)D.Hkv * D.max_chunks * D.G * kRows * (D.hd + 4) * 4;
+    T.att_tiles = (int)(kPfPartBytes / tile_bytes);
+    if (T.att_tiles < 1) T.att_tiles = 1;
+    if (T.att_tiles > T.cap / 16) T.att_tiles = T.cap / 16;
+    const size_t first = m->allocs.size();
+    std::vector<int> order;
+    int rc = AMUSD_OK;
+    void* p = nullptr;
+    auto get = [&](size_t bytes) -> void* {
+        if (rc == AMUSD_OK) rc = dev_alloc(m, &p, bytes, false);
+        return rc == AMUSD_OK ? p : nullptr;
+    };
+    for (int s = 0; s < kPfStages && rc == AMUSD_OK; ++s) {
+        prefill_tile_order(D, s, m->nwg, order, &T.tiles[s].wgs);
+        T.tiles[s].n = (int)order.size();
+        int* dst = static_cast<int*>(get(order.size() * 4));
+        T.tiles[s].order = dst;
+        if (dst && hipMemcpy(dst, order.data(), order.size() * 4, hipMemcpyHostToDevice) != hipSuccess)
+            rc = fail(AMUSD_E_HIP, "tile order upload");
+    }
+    T.X = static_cast<float*>(get(cap * d * 4));
+    T.A = get(cap * d * 4);
+    T.O = get(cap * q * 4);
+    T.H = get(cap * F * 4);
+    T.Q_hi = get(cap * q * 4);
+    T.Q_lo = get(cap * q * 4);
+    T.ssq = static_cast<float*>(get(d / 16 * cap * 4));
+    T.rstd = static_cast<float*>(get(cap * 4));
+    T.att_part = static_cast<float*>(get(T.att_tiles * tile_bytes));
+    T.xch = static_cast<float*>(get(D.split_down ? cap * T.tiles[kPfDown].n * 16 * 4 : 16));
+    T.best_val = static_cast<float*>(get(cap * T.tiles[kPfLMHead].n / 2 * 4));
+    T.best_idx = static_cast<int*>(get(cap * T.tiles[kPfLMHead].n / 2 * 4));
+    if (rc == AMUSD_OK && hipHostMalloc(reinterpret_cast<void**>(&m->pf_host), 2 * cap * 4, hipHostMallocDefault) != hipSuccess)
+        rc = fail(AMUSD_E_HIP, "pinned prefill buffer");
+    if (rc == AMUSD_OK) {
+        void* dev = nullptr;
+        if (hipHostGetDevicePointer(&dev, m->pf_host, 0) != hipSuccess) rc = fail(AMUSD_E_HIP, "device address of the pinned prefill buffer");
+        T.tokens = static_cast<const int*>(dev);
+        T.greedy = static_cast<int*>(dev) + cap;
+    }
+    if (rc != AMUSD_OK) {
+        for (size_t i = first; i < m->allocs.size(); ++i) (void)hipFree(m->allocs[i]);
+        m->allocs.resize(first);
+        (void)hipGetLastError();
+        return AMUSD_OK;
+    }
+    m->pf = T;
+    return AMUSD_OK;
+}
+
+// One prefill pass: n tokens of sequence seq appended at cache length L, all of them kept.  Of its rows the last `tail`
+// are what amusd_get_logits and amusd_get_greedy report.  Everything is already validated.
+int run_prefill(amusd_model* m, int seq, int L, const int32_t* tokens, int n, int tail) {
+    HostStage* h = m->hstage;
+    const PrefillArgs P{n, L, seq, m->keep_logits ? n - tail : n};
+    std::memcpy(m->pf_host, tokens, (size_t)n * 4);
+    HIP_TRY(hipEventRecord(m->ev0, m->stream));
+    HIP_TRY(launch_prefill(m->dm, m->layers_host.data(), m->pf, P, m->stream));
+    HIP_TRY(hipEventRecord(m->ev1, m->stream));
+    HIP_TRY(hipStreamSynchronize(m->stream));
+    HIP_TRY(hipEventElapsedTime(&m->last_ms, m->ev0, m->ev1));
+    const int* greedy = m->pf_host + m->pf.cap;
+    SeqState& q = m->seqs[seq];
+    std::memcpy(&q.greedy_at[L + 1], greedy, (size_t)n * 4);
+    std::memcpy(h->res.greedy, greedy + n - tail, (size_t)tail * 4);
+    q.kv_len = L + n;
+    q.p_next = greedy[n - 1];
+    m->last_positions = L + n;
+    m->logits_valid = m->keep_logits;
+    m->last_rows = tail;
     return AMUSD_OK;
 }
 
@@ -494,6 +578,7 @@ int amusd_model_create(const amusd_config* cfg, void* hip_stream, amusd_model** 
         S.best_idx = static_cast<int*>(place((size_t)m->nwg * kRows * 4));
         m->static_bytes = off;      // may exceed the array: amusd_verify_static then refuses the model
     }
+    if ((rc = alloc_prefill(m)) != AMUSD_OK) return bail(rc);
     if (hipStreamSynchronize(m->stream) != hipSuccess) return bail(fail(AMUSD_E_HIP, "create: stream sync"));
     *out = m;
     return AMUSD_OK;
@@ -618,6 +703,7 @@ int amusd_model_free(amusd_model* m) {
     for (void* p : m->allocs) (void)hipFree(p);
     if (m->staging) (void)hipFree(m->staging);
     if (m->hstage) (void)hipHostFree(m->hstage);
+    if (m->pf_host) (void)hipHostFree(m->pf_host);
     if (m->ev0) (void)hipEventDestroy(m->ev0);
     if (m->ev1) (void)hipEventDestroy(m->ev1);
     for (hipEvent_t e : m->tev_begin) if (e) (void)hipEventDestroy(e);
@@ -636,6 +722,22 @@ int amusd_seq_prefill(amusd_model* m, int32_t seq, const int32_t* tokens, int32_
     // 16-bit models run fastest with at most 8 rows per pass (hi and lo halves share one operand fragment)
     const int chunk = m->cfg.dtype == AMUSD_DTYPE_BF16 && m->cfg.max_k > 8 ? 8 : m->cfg.max_k;
     const int len_before = q.kv_len, next_before = q.p_next;
+    // Prompts go through the prefill pass, in stretches of about equal length; up to 16 tokens, and with a stage of the
+    // verify pass selected for timing, through the verify pass.  The last group of rows is the same either way.
+    if (n >= kPfMinRows && m->pf.cap && m->timer.stage < 0) {
+        const int tail = (n - 1) % chunk + 1, passes = (n + m->pf.cap - 1) / m->pf.cap;
+        const int per = passes == 1 ? n : ((n + passes - 1) / passes + kPfBlockRows - 1) / kPfBlockRows * kPfBlockRows;
+        for (int s = 0; s < n; s += per) {
+            const int k = n - s < per ? n - s : per;
+            if ((rc = run_prefill(m, seq, q.kv_len, tokens + s, k, tail < k ? tail : k))) {
+                q.kv_len = len_before;
+                q.p_next = next_before;
+                return rc;
+            }
+        }
+        if (next_token) *next_token = q.p_next;
+        return AMUSD_OK;
+    }
     for (int s = 0; s < n; s += chunk) {
         const int k = n - s < chunk ? n - s : chunk;
         if ((rc = run_pass(m, seq, q.kv_len, tokens + s, k, true))) {

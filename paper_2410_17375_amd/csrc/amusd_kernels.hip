@@ -18,185 +18,9 @@
 //     activation side; weights are exact bf16.
 // Every stage is a __device__ function over (workgroup id, workgroup count),
 // launched as one kernel per stage.
-#include <hip/hip_ext.h>
-#include <hip/hip_fp16.h>
-
-#include "amusd_launch.h"
+#include "amusd_attention.h"
 
 namespace amusd {
-
-typedef float v4f __attribute__((ext_vector_type(4)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef _Float16 v8h __attribute__((ext_vector_type(8)));
-
-// ---------------------------------------------------------------- dtype traits
-struct BF16 {
-    static constexpr int EPL = 8;         // elements in a lane's 16-byte fragment
-    static constexpr int KB = 32;         // contraction elements per fragment (4 lane groups x EPL)
-    static constexpr int ESZ = 2;
-    static constexpr int TPB = 2;         // 16-key score tiles per value block
-    static constexpr int BLOCK_KEYS = 32;
-    static constexpr bool HAS_LO = true;
-    static __device__ __forceinline__ v4f mfma(uint4 a, uint4 b, v4f c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
-    }
-    // Attention operands (cache, queries, probabilities) are IEEE half: the same 2 bytes per element as
-    // bf16 with three more mantissa bits; their magnitudes (keys, values, queries O(1), probabilities
-    // in [0,1]) sit well inside the half range, and stores clamp to it.
-    static __device__ __forceinline__ v4f mfma_att(uint4 a, uint4 b, v4f c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v8h, b), c, 0, 0, 0);
-    }
-    static __device__ __forceinline__ uint32_t att_bits(float x) {
-        const float c = fminf(fmaxf(x, -65504.f), 65504.f);
-        return (uint32_t)__half_as_ushort(__float2half_rn(c));
-    }
-    static __device__ __forceinline__ float att_float(uint32_t b) { return __half2float(__ushort_as_half((unsigned short)b)); }
-};
-struct FP32 {
-    static constexpr int EPL = 4;
-    static constexpr int KB = 16;
-    static constexpr int ESZ = 4;
-    static constexpr int TPB = 1;
-    static constexpr int BLOCK_KEYS = 16;
-    static constexpr bool HAS_LO = false;
-    static __device__ __forceinline__ v4f mfma(uint4 a, uint4 b, v4f c) {
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.x), __uint_as_float(b.x), c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.y), __uint_as_float(b.y), c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(b.z), c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
-        return c;
-    }
-    static __device__ __forceinline__ v4f mfma_att(uint4 a, uint4 b, v4f c) { return mfma(a, b, c); }
-    static __device__ __forceinline__ uint32_t att_bits(float x) { return __float_as_uint(x); }
-    static __device__ __forceinline__ float att_float(uint32_t b) { return __uint_as_float(b); }
-};
-
-__device__ __forceinline__ uint32_t bf16_rne(float x) {
-    uint32_t u = __float_as_uint(x);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return u >> 16;
-}
-__device__ __forceinline__ float bf16_to_f32(uint32_t b) { return __uint_as_float(b << 16); }
-
-// store a query element: fp32 as is; 16-bit models as hi + lo halves of the attention element type
-template <class DT>
-__device__ __forceinline__ void store_act(void* hi, void* lo, size_t idx, float x) {
-    if constexpr (DT::HAS_LO) {
-        uint32_t h = DT::att_bits(x);
-        uint32_t l = DT::att_bits(x - DT::att_float(h));
-        reinterpret_cast<uint16_t*>(hi)[idx] = (uint16_t)h;
-        reinterpret_cast<uint16_t*>(lo)[idx] = (uint16_t)l;
-    } else {
-        reinterpret_cast<float*>(hi)[idx] = x;
-    }
-}
-
-// GEMM inputs are kept in matrix-core operand order, so that a wave fetches the
-// 16 rows x one K block it needs with ONE contiguous 1 KiB load, exactly like
-// a weight fragment: buf[kb][part][lane = g*16 + slot][EPL elements], where g
-// selects the lane group's EPL columns of the K block.
-//   fp32        : one part, slot = row.
-//   bf16, k <= 8: one part; slots 0-7 hold the hi halves of rows 0-7 and slots
-//                 8-15 their lo halves (x = hi + lo), so one MFMA yields W.hi in
-//                 result columns 0-7 and W.lo in columns 8-15;
-//   bf16, k > 8 : two parts (hi, lo), slot = row.
-// In both bf16 forms a wave adds its W.hi and W.lo sums before the cross-wave
-// reduction, so a row's value does not depend on which form carried it.
-template <class DT>
-__device__ __forceinline__ void store_gemm_in(void* buf, int k_rows, int m, int col, float x) {
-    const int kb = col / DT::KB, g = (col % DT::KB) / DT::EPL, e = col % DT::EPL;
-    if constexpr (DT::HAS_LO) {
-        const uint32_t h = bf16_rne(x);
-        const uint32_t l = bf16_rne(x - bf16_to_f32(h));
-        uint16_t* b = reinterpret_cast<uint16_t*>(buf);
-        if (k_rows <= 8) {
-            const size_t base = ((size_t)kb * 64 + g * 16 + m) * 8 + e;
-            b[base] = (uint16_t)h;
-            b[base + 8 * 8] = (uint16_t)l;                 // slot m + 8
-        } else {
-            const size_t base = ((size_t)kb * 128 + g * 16 + m) * 8 + e;
-            b[base] = (uint16_t)h;
-            b[base + 64 * 8] = (uint16_t)l;                // part 1
-        }
-    } else {
-        reinterpret_cast<float*>(buf)[((size_t)kb * 64 + g * 16 + m) * 4 + e] = x;
-    }
-}
-
-// Element index of key `pos`, head_dim column `c` in a kv head's key cache.  Keys are kept in the operand
-// order of the score product: [16-key tile][fragment i][lane = g*16 + key%16][EPL], where lane group g owns
-// columns g*hd/4 .. (g+1)*hd/4 and fragment i its i-th run of EPL columns, so a wave fetches one
-// (tile, fragment) with a single contiguous 1 KiB load.
-template <class DT>
-__device__ __forceinline__ size_t kcache_index(int hd, int pos, int c) {
-    const int q = hd / 4, g = c / q, w = c % q;
-    return ((((size_t)(pos >> 4) * (q / DT::EPL) + w / DT::EPL) * 64) + g * 16 + (pos & 15)) * DT::EPL + w % DT::EPL;
-}
-
-// Weights are read once per pass: a non-temporal load keeps them from evicting
-// the (re-read) activations from L2.
-__device__ __forceinline__ uint4 load_stream(const uint4* p) {
-    typedef unsigned int u4 __attribute__((ext_vector_type(4)));
-    const u4 v = __builtin_nontemporal_load(reinterpret_cast<const u4*>(p));
-    return uint4{v.x, v.y, v.z, v.w};
-}
-
-template <class DT>
-__device__ __forceinline__ uint4 load_frag(const void* base, size_t elem_index) {
-    return *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(base) + elem_index * DT::ESZ);
-}
-
-// Forces a (wave-uniform) kernel argument into a scalar register at this point of the program.  Left to itself
-// the compiler loads an argument where it is first used, often behind a branch; a stage that starts by asking
-// for everything it needs waits for argument memory once instead of several times in a row.
-template <class T>
-__device__ __forceinline__ void pin_scalar(const T& x) { asm volatile("" ::"s"(x)); }
-
-// The value that lane (l ^ OFF) holds, without going through the LDS crossbar (`__shfl_xor` compiles to
-// ds_bpermute, 50-100 clocks each, and these exchanges sit in chains on the critical path of every stage's end):
-// data-parallel-primitive modifiers inside a row of 16 lanes, the gfx950 row and half-wave swaps across rows.
-template <int OFF>
-__device__ __forceinline__ uint32_t lane_xor_u(uint32_t v) {
-    static_assert(OFF == 1 || OFF == 2 || OFF == 4 || OFF == 8 || OFF == 16 || OFF == 32, "one bit of the lane index");
-    const int x = (int)v;
-    if constexpr (OFF == 1) {
-        return (uint32_t)__builtin_amdgcn_update_dpp(x, x, 0xB1, 0xf, 0xf, false);        // quad_perm:[1,0,3,2]
-    } else if constexpr (OFF == 2) {
-        return (uint32_t)__builtin_amdgcn_update_dpp(x, x, 0x4E, 0xf, 0xf, false);        // quad_perm:[2,3,0,1]
-    } else if constexpr (OFF == 4) {
-        const int t = __builtin_amdgcn_update_dpp(x, x, 0x104, 0xf, 0x5, false);          // row_shl:4 into lanes 0-3, 8-11
-        return (uint32_t)__builtin_amdgcn_update_dpp(t, x, 0x114, 0xf, 0xa, false);       // row_shr:4 into lanes 4-7, 12-15
-    } else if constexpr (OFF == 8) {
-        return (uint32_t)__builtin_amdgcn_update_dpp(x, x, 0x128, 0xf, 0xf, false);       // row_ror:8
-    } else if constexpr (OFF == 16) {
-        const auto p = __builtin_amdgcn_permlane16_swap(v, v, false, false);   // p[0]: rows 0,0,2,2   p[1]: rows 1,1,3,3
-        return (threadIdx.x & 16) ? p[0] : p[1];
-    } else {
-        const auto p = __builtin_amdgcn_permlane32_swap(v, v, false, false);   // p[0]: lanes 0-31 twice   p[1]: lanes 32-63 twice
-        return (threadIdx.x & 32) ? p[0] : p[1];
-    }
-}
-template <int OFF>
-__device__ __forceinline__ float lane_xor(float v) { return __uint_as_float(lane_xor_u<OFF>(__float_as_uint(v))); }
-template <int OFF>
-__device__ __forceinline__ int lane_xor(int v) { return (int)lane_xor_u<OFF>((uint32_t)v); }
-template <int OFF>
-__device__ __forceinline__ float wave_xor_add(float v) { return v + lane_xor<OFF>(v); }
-// all 64 lanes, offsets 32, 16, .., 1 in that order
-__device__ __forceinline__ float wave_max_all(float v) {
-    v = fmaxf(v, lane_xor<32>(v)); v = fmaxf(v, lane_xor<16>(v)); v = fmaxf(v, lane_xor<8>(v));
-    v = fmaxf(v, lane_xor<4>(v)); v = fmaxf(v, lane_xor<2>(v)); v = fmaxf(v, lane_xor<1>(v));
-    return v;
-}
-__device__ __forceinline__ float wave_sum_all(float v) {
-    v = wave_xor_add<32>(v); v = wave_xor_add<16>(v); v = wave_xor_add<8>(v);
-    v = wave_xor_add<4>(v); v = wave_xor_add<2>(v); v = wave_xor_add<1>(v);
-    return v;
-}
-// lane j's value in every lane (j the same in all lanes)
-__device__ __forceinline__ float lane_value(float v, int j) {
-    return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), j));
-}
 
 // ---------------------------------------------------------------- RMS scale of the 16 rows
 // The per-tile partial sums of squares are fetched at the start of a stage
@@ -258,7 +82,6 @@ struct RstdPrefetch {
 };
 
 // ---------------------------------------------------------------- LDS layout (dynamic shared memory, floats)
-constexpr int kAttPad = 4;    // row padding of the attention partials (spreads LDS banks)
 constexpr int kScratchFloats = kWaves * kRows * (128 + kAttPad) + kWaves * kRows * 2;   // attention partials; >= GEMM reduction area
 static_assert(kScratchFloats >= kWaves * kMaxTilesPerRound * 256, "GEMM reduction area must fit");
 constexpr int kOffRstd = kScratchFloats;
@@ -369,33 +192,6 @@ __device__ __forceinline__ void gemm_accumulate(v4f (&out)[kMaxTilesPerRound], c
     }
 }
 
-// A wave's share of the K blocks of a GEMM stage, and where in it the wave starts its walk: blocks
-// kb0 + stride * ((i + rot) mod S), i = 0 .. S-1.
-// K split: SIMD s hosts waves s and s+4; they share the K quarter of their SIMD, the first of them taking
-// old_share sixteenths (the first wave of a SIMD wins the issue arbitration and streams faster, but which split is
-// fastest was measured per stage, and it also shifts where the second wave's stream starts).
-// Interleaved form: the waves take every eighth block instead (the two waves of a SIMD neighbouring ones), so that a
-// workgroup's eight streams move through the tile as one window of 8 KiB.
-struct KSlice {
-    int kb0, S, rot, stride;
-};
-__device__ __forceinline__ KSlice k_slice(int kblocks, int wg, int wave, bool stagger, int rot_wg, int rot_wave,
-                                          bool interleave, int old_share) {
-    const int simd = wave & 3, young = wave >> 2;
-    const int q0 = (kblocks * simd) / 4, q1 = (kblocks * (simd + 1)) / 4;
-    const int cut = q0 + ((q1 - q0) * old_share + 8) / 16;
-    KSlice k;
-    k.kb0 = young ? cut : q0;
-    k.S = (young ? q1 : cut) - k.kb0;
-    k.stride = 1;
-    if (interleave) {
-        k.kb0 = simd * 2 + young;
-        k.S = (kblocks - k.kb0 + kWaves - 1) / kWaves;
-        k.stride = kWaves;
-    }
-    k.rot = stagger && k.S > 0 ? (int)(((unsigned)wg * (unsigned)rot_wg + (unsigned)wave * (unsigned)rot_wave) % (unsigned)k.S) : 0;
-    return k;
-}
 __device__ __forceinline__ int round_tiles(int left) { return left >= 8 ? 8 : left == 7 ? 7 : left >= 4 ? 4 : left >= 2 ? 2 : 1; }
 
 // Weights of a GEMM stage that runs later in the pass, fetched into L2 ahead of time.  The L2 of an XCD keeps what
@@ -408,18 +204,14 @@ __device__ __forceinline__ int round_tiles(int left) { return left >= 8 ? 8 : le
 struct NextWeights {
     const uint4* W;
     int n_tiles, kblocks;
-    bool stagger;
-    int rot_wg, rot_wave;   // the consumer's K-walk coefficients (k_slice)
-    bool interleave;
-    int old_share;
 };
 // Fragments [F0, F1) of consumer wave `cwave`, counted in the order the consumer's pipeline asks for them
 // (stage-major over the tiles of its first round); 8 fragments (8 KiB) per load instruction of the calling wave.
 // The loads deliver straight into LDS (64 words per wave that nobody reads), so they need no result registers.
-template <int F0, int F1>
+template <class Walk, int F0, int F1>
 __device__ __forceinline__ void prefetch_frags(const NextWeights& nx, int wg, int nwg, int cwave, int lane, float* lds_sink) {
     if (F1 <= F0 || wg >= nx.n_tiles) return;
-    const KSlice ks = k_slice(nx.kblocks, wg, cwave, nx.stagger, nx.rot_wg, nx.rot_wave, nx.interleave, nx.old_share);
+    const KSlice ks = k_slice_of<Walk>(nx.kblocks, wg, cwave);
     if (ks.S <= 0) return;
     const int nt = round_tiles((nx.n_tiles - wg + nwg - 1) / nwg);
 #pragma unroll
@@ -444,7 +236,7 @@ __device__ __forceinline__ void gemm_stage_m(const uint4* __restrict__ W, int n_
     constexpr int SLOTS = kMaxTilesPerRound;                  // partial tiles per wave per round
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int m = lane & 15, g = lane >> 4;
-    const KSlice ks = k_slice(kblocks, wg, wave, Epi::kStagger, Epi::kRotWg, Epi::kRotWave, Epi::kInterleave, Epi::kOldShare);
+    const KSlice ks = k_slice_of<typename Epi::Walk>(kblocks, wg, wave);
     const int kb0 = ks.kb0, S = ks.S, rot = ks.rot;
     const int mine = wg < n_tiles ? (n_tiles - wg + nwg - 1) / nwg : 0;
     const uint4* act = reinterpret_cast<const uint4*>(A);
@@ -553,7 +345,7 @@ __device__ __forceinline__ bool gemm_stage_split_m(const uint4* __restrict__ W, 
     const int groups = n_tiles / NT;
     const int grp = wg % groups, part = wg / groups;
     const int kh = kblocks / WAYS;
-    const KSlice ks = k_slice(kh, wg, wave, Epi::kStagger, Epi::kRotWg, Epi::kRotWave, Epi::kInterleave, Epi::kOldShare);
+    const KSlice ks = k_slice_of<typename Epi::Walk>(kh, wg, wave);
     const uint4* act = reinterpret_cast<const uint4*>(A);
     epi.prefetch(grp, groups, NT);
     v4f acc[SLOTS];
@@ -653,7 +445,7 @@ __device__ __forceinline__ void residual_pair(const DevModel& M, float g1, float
         M.X[(size_t)mm * M.d + c2] = x2;
         store_gemm_in<DT>(M.A, k_rows, mm, c1, x1 * g1);
         store_gemm_in<DT>(M.A, k_rows, mm, c2, x2 * g2);
-        sq = x1 * x1 + x2 * x2;
+        sq = square_pair(x1, x2);
     }
     sq = wave_xor_add<1>(sq);
     sq = wave_xor_add<2>(sq);
@@ -664,12 +456,7 @@ __device__ __forceinline__ void residual_pair(const DevModel& M, float g1, float
 template <class DT, int STAGE>
 struct EpiResidual {   // O-projection and down-projection: X += C, feed the next norm
     static constexpr int kStage = STAGE;
-    static constexpr bool kStagger = true;
-    // Where a wave starts its K walk (k_slice), swept per stage on the chip: the down projection is fastest when
-    // all workgroups start alike and only the waves differ, the O-projection when nobody is shifted by its wave.
-    static constexpr int kRotWg = STAGE == 6 ? 0 : 5, kRotWave = STAGE == 6 ? 5 : 0;
-    static constexpr bool kInterleave = STAGE == 6;   // down projection: 0.4 us per launch faster; the other stages equal or slower
-    static constexpr int kOldShare = 8;
+    using Walk = std::conditional_t<STAGE == 6, KWalkDown, KWalkOproj>;
     const DevModel& M;
     const float* gain_next;
     int k_rows;
@@ -702,10 +489,7 @@ struct EpiResidual {   // O-projection and down-projection: X += C, feed the nex
 template <class DT, bool ONE>
 struct EpiQKV {
     static constexpr int kStage = 1;        // RMS scale, rotary embedding on (i, i+hd/2) pairs, Q to its buffer, K/V appended to the cache
-    static constexpr bool kStagger = false; // measured slower with staggered K walks (short slices, two tile counts)
-    static constexpr int kRotWg = 0, kRotWave = 0;
-    static constexpr bool kInterleave = false;
-    static constexpr int kOldShare = 6;     // 12 + 20 of a SIMD's 32 K blocks: 0.4 us per launch faster than 16 + 16 (10 likewise; 4, 12, odd values not)
+    using Walk = KWalkQKV;
     const DevModel& M;
     const DevLayer& Ly;
     float* rstd;         // LDS
@@ -767,7 +551,8 @@ struct EpiQKV {
             const int tt = isq ? tile : tile - qt;
             const int head = tt / tph, i = (tt % tph) * 8 + r;
             const float c = pc[it], sn = ps[it];
-            const float y1 = x1 * c - x2 * sn, y2 = x1 * sn + x2 * c;
+            float y1, y2;
+            rotate_pair(x1, x2, c, sn, y1, y2);
             if (isq) {
                 const size_t o = (size_t)mm * M.qdim + head * hd + i;
                 store_act<DT>(M.Q_hi, M.Q_lo, o, y1);
@@ -786,12 +571,8 @@ struct EpiQKV {
         } else {
             const int tt = tile - qt - kt;
             const int head = tt / tph, j = tt % tph;   // value features j*16 + r and j*16 + r + 8
-            constexpr int BK = DT::BLOCK_KEYS;
-            const int b = pos / BK, q = pos % BK;
-            const int e = (q / 16) * 4 + (q % 4), gg = (q % 16) / 4;
-            const size_t blk = ((size_t)head * (M.ctx_pad / BK) + b) * tph + j;
-            const size_t o1 = slot_base + (blk * 64 + gg * 16 + r) * DT::EPL + e;
-            const size_t o2 = slot_base + (blk * 64 + gg * 16 + r + 8) * DT::EPL + e;
+            const size_t hb = slot_base + (size_t)head * M.ctx_pad * hd;
+            const size_t o1 = hb + vcache_index<DT>(hd, pos, j * 16 + r), o2 = hb + vcache_index<DT>(hd, pos, j * 16 + r + 8);
             if constexpr (DT::HAS_LO) {
                 reinterpret_cast<uint16_t*>(Ly.vcache)[o1] = (uint16_t)DT::att_bits(x1);
                 reinterpret_cast<uint16_t*>(Ly.vcache)[o2] = (uint16_t)DT::att_bits(x2);
@@ -807,10 +588,7 @@ struct EpiQKV {
 template <class DT>
 struct EpiSwiGLU {     // tile rows 0-7 are gate features, 8-15 the matching up features
     static constexpr int kStage = 5;
-    static constexpr bool kStagger = true;
-    static constexpr int kRotWg = 5, kRotWave = 11;   // an even wave coefficient costs 0.3-6 us per launch
-    static constexpr bool kInterleave = false;
-    static constexpr int kOldShare = 8;
+    using Walk = KWalkWide;
     const DevModel& M;
     float* rstd;
     int k_rows;
@@ -821,27 +599,15 @@ struct EpiSwiGLU {     // tile rows 0-7 are gate features, 8-15 the matching up 
         if (!valid || mm >= k_rows) return;
         const float sc = rstd[mm];
         const float gate = v1 * sc, up = v2 * sc;
-        const float h = gate / (1.0f + __expf(-gate)) * up;
+        const float h = swiglu(gate, up);
         store_gemm_in<DT>(M.H, k_rows, mm, tile * 8 + r, h);
     }
     __device__ __forceinline__ void round_end(int) {}
 };
 
-__device__ __forceinline__ bool better(float v, int i, float bv, int bi) { return v > bv || (v == bv && i < bi); }
-// keeps the better of this lane's (value, index) and lane (l ^ OFF)'s
-template <int OFF>
-__device__ __forceinline__ void keep_better_xor(float& bv, int& bi) {
-    const float ov = lane_xor<OFF>(bv);
-    const int oi = lane_xor<OFF>(bi);
-    if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
-}
-
 struct EpiLMHead {
     static constexpr int kStage = 7;     // logits (optionally stored); per-row arg-max over this workgroup's tiles, lowest id on ties
-    static constexpr bool kStagger = true;
-    static constexpr int kRotWg = 5, kRotWave = 11;
-    static constexpr bool kInterleave = false;
-    static constexpr int kOldShare = 8;
+    using Walk = KWalkWide;
     const DevModel& M;
     float* smem;
     int k_rows, keep;
@@ -1027,8 +793,6 @@ __device__ __forceinline__ void stage_lmhead(const DevModel& M, const PassArgs& 
 // order.  Block, run and chunk boundaries sit at fixed absolute positions, so a
 // row's result does not depend on how many rows the pass has or where it starts.
 // Output per (unit, head, row): numerator[hd], running max, denominator.
-constexpr int kPartRow = 4;   // floats appended to a partial's numerator: max, denominator, 2 pad (keeps 16-byte alignment)
-
 template <class DT, int HD, bool ONE>
 __device__ __forceinline__ void stage_attention(const DevModel& M, const DevLayer& Ly, const PassArgs& P, int wg, int nwg,
                                                 float* smem) {
@@ -1036,34 +800,22 @@ __device__ __forceinline__ void stage_attention(const DevModel& M, const DevLaye
     pin_scalar(Ly.wo); pin_scalar(M.d); pin_scalar(M.qdim); pin_scalar(M.Hkv); pin_scalar(M.ctx_pad);
     pin_scalar(M.att_scale); pin_scalar(M.G); pin_scalar(M.bpw); pin_scalar(P.L0); pin_scalar(P.k);
     pin_scalar(P.nchunks0); pin_scalar(P.slot0); pin_scalar(P.units); pin_scalar(P.n_seg); pin_scalar(nwg);
-    constexpr int FR = HD / 4 / DT::EPL;     // 16-byte fragments per lane along head_dim
-    constexpr int HT = HD / 16;              // 16-wide head_dim tiles
-    constexpr int BK = DT::BLOCK_KEYS, TPB = DT::TPB;
-    constexpr int HDP = HD + kAttPad;
     const int last = P.n_seg - 1;
     const int units = P.units;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int m = lane & 15, g = lane >> 4;
-    const int G = M.G, bpw = M.bpw;
-    const int lg = __builtin_ctz((unsigned)G);         // G is 1, 2, 4 or 8 (checked at model creation): shifts, no divisions
-    const int parts = kWaves >> lg, hq = wave & (G - 1), part = wave >> lg;
-    float* partO = smem;                               // [hq][part][16][HD + pad]
-    float* partML = smem + kWaves * kRows * HDP;       // [hq][part][16][2]
-    const int nblk = M.ctx_pad / BK;
-    const uint4 zero4 = uint4{0, 0, 0, 0};
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int G = M.G;
     // The O-projection's weights, fetched into L2 while this stage waits on latency, by the workgroups that have
     // no attention unit (at short contexts there are fewer units than compute units).  Such a workgroup serves the
     // O-projection workgroups of its own XCD in turn with the other idle workgroups of that XCD.
     if (kAttPf > 0 && wg >= units) {
-        const NextWeights wo{Ly.wo, M.d / 16, M.qdim / DT::KB, true, EpiResidual<DT, 4>::kRotWg, EpiResidual<DT, 4>::kRotWave,
-                              EpiResidual<DT, 4>::kInterleave, EpiResidual<DT, 4>::kOldShare};
+        const NextWeights wo{Ly.wo, M.d / 16, M.qdim / DT::KB};
         const int consumers = wo.n_tiles < nwg ? wo.n_tiles : nwg;      // workgroups of the O-projection
         const int x = wg & 7;
         const int first = units + ((x - units) & 7);                    // first idle workgroup of XCD x
         const int rank = (wg - first) >> 3, idle = (nwg - first + 7) >> 3;
         if (kAttPfSleep > 0) __builtin_amdgcn_s_sleep(kAttPfSleep);   // the units' own loads go first
         for (int t = rank, n = 0; x + 8 * t < consumers && n < kAttPfMax; t += idle, ++n)
-            prefetch_frags<0, kAttPf>(wo, x + 8 * t, consumers, wave, lane, smem + kOffPfSink + wave * 64);
+            prefetch_frags<KWalkOproj, 0, kAttPf>(wo, x + 8 * t, consumers, wave, lane, smem + kOffPfSink + wave * 64);
         prefetch_retire();
         return;
     }
@@ -1075,7 +827,6 @@ __device__ __forceinline__ void stage_attention(const DevModel& M, const DevLaye
             const PassSeg& S = P.seg[si];
             L = S.L; k = S.k; row0 = S.row0; nchunks = S.nchunks; cslot = S.slot; unit0 = S.unit0;
         }
-        const int T = L + k;
         const int ul = u - unit0;
         // Which (kv head, chunk) this unit is.  With a multiple of 8 kv heads, all chunks of a kv head go to
         // workgroups of one XCD (workgroup index mod 8 = kv head mod 8), and so do the merge waves of its query
@@ -1096,142 +847,8 @@ __device__ __forceinline__ void stage_attention(const DevModel& M, const DevLaye
         }
         const int ucanon = unit0 + kvh * nchunks + c;      // where the merge stage looks for this unit's partials
         const size_t slot_frags = (size_t)cslot * M.Hkv * M.ctx_pad * HD / DT::EPL;   // 16-byte fragments per cache
-        const bool mine = m >= row0 && m < row0 + k;     // tile row m belongs to this sequence
-        const int head = kvh * G + hq;
-        const int b0 = (c * parts + part) * bpw;       // first block of this wave's run
-        uint4 qh[FR], ql[FR];
-        {
-            const int mq = mine ? m : row0;            // other rows mirror row0; fully masked, never written out
-            const size_t q0 = (size_t)mq * M.qdim + head * HD + g * (HD / 4);
-#pragma unroll
-            for (int i = 0; i < FR; ++i) {
-                qh[i] = load_frag<DT>(M.Q_hi, q0 + i * DT::EPL);
-                ql[i] = zero4;
-                if constexpr (DT::HAS_LO) ql[i] = load_frag<DT>(M.Q_lo, q0 + i * DT::EPL);
-            }
-        }
-        uint4 kf[TPB][FR], vf[HT];
-        auto load_block = [&](int b, uint4 (&kd)[TPB][FR], uint4 (&vd)[HT]) {
-            const int bb = b < nblk ? b : nblk - 1;    // stay inside the cache allocation
-            const uint4* kb = reinterpret_cast<const uint4*>(Ly.kcache) + slot_frags +
-                              ((size_t)kvh * (M.ctx_pad / 16) + (size_t)bb * TPB) * FR * 64 + lane;
-#pragma unroll
-            for (int t = 0; t < TPB; ++t)
-#pragma unroll
-                for (int i = 0; i < FR; ++i) kd[t][i] = kb[(t * FR + i) * 64];
-            const uint4* vb = reinterpret_cast<const uint4*>(Ly.vcache) + slot_frags +
-                              (((size_t)kvh * nblk + bb) * HT) * 64 + lane;
-#pragma unroll
-            for (int j = 0; j < HT; ++j) vd[j] = vb[j * 64];
-        };
-        load_block(b0, kf, vf);
-        float mrun = -INFINITY, lrun = 0.f;
-        v4f o[HT];
-#pragma unroll
-        for (int j = 0; j < HT; ++j) o[j] = v4f{0.f, 0.f, 0.f, 0.f};
-        for (int ib = 0; ib < bpw; ++ib) {
-            const int p0 = (b0 + ib) * BK;
-            if (p0 >= T) break;                         // wave-uniform: later blocks of the run hold no visible key
-            uint4 kn[TPB][FR], vn[HT];
-            // next block of the run, fetched while this one is used; at the run's last useful block, that block
-            // again (a cache hit) rather than a block the neighbouring run owns: the fetch stays unconditional, so
-            // it is issued ahead of the matrix instructions, but nothing waits for the last one before the end
-            const bool more = ib + 1 < bpw && p0 + BK < T;
-            load_block(more ? b0 + ib + 1 : b0 + ib, kn, vn);
-            float sv[TPB][4];
-            float mx = -INFINITY;
-#pragma unroll
-            for (int t = 0; t < TPB; ++t) {
-                v4f sc = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int i = 0; i < FR; ++i) {
-                    sc = DT::mfma_att(kf[t][i], qh[i], sc);
-                    if constexpr (DT::HAS_LO) sc = DT::mfma_att(kf[t][i], ql[i], sc);
-                }
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int key = p0 + t * 16 + g * 4 + e;
-                    // causal: the sequence's j-th row (tile row row0+j) sees keys 0..L+j
-                    sv[t][e] = mine && key <= L + m - row0 ? sc[e] * M.att_scale : -INFINITY;
-                    mx = fmaxf(mx, sv[t][e]);
-                }
-            }
-            mx = fmaxf(mx, lane_xor<16>(mx));
-            mx = fmaxf(mx, lane_xor<32>(mx));
-            const float mnew = fmaxf(mrun, mx);
-            const float mref = mnew == -INFINITY ? 0.f : mnew;
-            const float alpha = __expf(mrun - mref);     // 0 for the first visible block
-            float pv[TPB][4], lsum = 0.f;
-#pragma unroll
-            for (int t = 0; t < TPB; ++t)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    pv[t][e] = __expf(sv[t][e] - mref);
-                    lsum += pv[t][e];
-                }
-            lsum = wave_xor_add<16>(lsum);
-            lsum = wave_xor_add<32>(lsum);
-            lrun = lrun * alpha + lsum;
-            mrun = mnew;
-            uint4 ph, pl = zero4;
-            if constexpr (DT::HAS_LO) {
-                uint32_t h[8], l[8];
-#pragma unroll
-                for (int t = 0; t < TPB; ++t)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        h[t * 4 + e] = DT::att_bits(pv[t][e]);
-                        l[t * 4 + e] = DT::att_bits(pv[t][e] - DT::att_float(h[t * 4 + e]));
-                    }
-                ph = uint4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
-                pl = uint4{l[0] | (l[1] << 16), l[2] | (l[3] << 16), l[4] | (l[5] << 16), l[6] | (l[7] << 16)};
-            } else {
-                ph = uint4{__float_as_uint(pv[0][0]), __float_as_uint(pv[0][1]), __float_as_uint(pv[0][2]), __float_as_uint(pv[0][3])};
-            }
-#pragma unroll
-            for (int j = 0; j < HT; ++j) {
-                o[j] = o[j] * alpha;
-                o[j] = DT::mfma_att(vf[j], ph, o[j]);
-                if constexpr (DT::HAS_LO) o[j] = DT::mfma_att(vf[j], pl, o[j]);
-            }
-            if (!more) break;     // wave-uniform; the look-ahead fetch is retired at the end of the stage
-#pragma unroll
-            for (int t = 0; t < TPB; ++t)
-#pragma unroll
-                for (int i = 0; i < FR; ++i) kf[t][i] = kn[t][i];
-#pragma unroll
-            for (int j = 0; j < HT; ++j) vf[j] = vn[j];
-        }
-        // run partial to LDS: o[j][e] is head_dim index 16j + 4g + e of row m
-        const int slot = hq * parts + part;
-#pragma unroll
-        for (int j = 0; j < HT; ++j)
-            *reinterpret_cast<v4f*>(partO + ((size_t)(slot * kRows + m) * HDP + j * 16 + g * 4)) = o[j];
-        if (g == 0) {
-            partML[(slot * kRows + m) * 2 + 0] = mrun;
-            partML[(slot * kRows + m) * 2 + 1] = lrun;
-        }
-        __syncthreads();
-        // merge the runs of each head in run order; item = (head, row, 4 consecutive head_dim entries)
-        for (int x = tid; x < G * kRows * (HD / 4); x += kThreads) {
-            const int c4 = x % (HD / 4), mm = (x / (HD / 4)) % kRows, hh = x / (kRows * (HD / 4));
-            if (mm < row0 || mm >= row0 + k) continue;
-            float Mx = -INFINITY;
-            for (int pp = 0; pp < parts; ++pp) Mx = fmaxf(Mx, partML[((hh * parts + pp) * kRows + mm) * 2]);
-            float den = 0.f;
-            v4f num = v4f{0.f, 0.f, 0.f, 0.f};
-            for (int pp = 0; pp < parts; ++pp) {
-                const int sl = hh * parts + pp;
-                const float mw = partML[(sl * kRows + mm) * 2];
-                const float wt = mw == -INFINITY ? 0.f : __expf(mw - Mx);
-                den += wt * partML[(sl * kRows + mm) * 2 + 1];
-                num += wt * *reinterpret_cast<const v4f*>(partO + ((size_t)(sl * kRows + mm) * HDP + c4 * 4));
-            }
-            float* out = M.att_part + (((size_t)ucanon * G + hh) * kRows + mm) * (HD + kPartRow);
-            *reinterpret_cast<v4f*>(out + c4 * 4) = num;
-            if (c4 == 0) { out[HD] = Mx; out[HD + 1] = den; }
-        }
-        __syncthreads();
+        attention_unit<DT, HD>(M, Ly, M.Q_hi, M.Q_lo, slot_frags, kvh, c, L, k, row0,
+                               M.att_part + (size_t)ucanon * G * kRows * (HD + kPartRow), smem);
     }
     prefetch_retire();
 }
@@ -1285,55 +902,11 @@ __device__ __forceinline__ void stage_attn_merge(const DevModel& M, const PassAr
         else nch = pos / CS + 1;
         const float* base = M.att_part + ((((size_t)unit0 + (size_t)kvh * nchunks) * M.G + hq) * kRows + mm) * ROW;
         const size_t cstride = (size_t)M.G * kRows * ROW;
-        float Mrun = -INFINITY, den = 0.f, num[PER];
-#pragma unroll
-        for (int i = 0; i < PER; ++i) num[i] = 0.f;
-        // numerators of the first chunks are fetched together with the maxima: one memory round trip
-        constexpr int CPRE = 24;
-        float pre[CPRE][PER];
-#pragma unroll
-        for (int j = 0; j < CPRE; ++j) {
-            const float* pj = base + (size_t)(j < nch ? j : nch - 1) * cstride;
-#pragma unroll
-            for (int i = 0; i < PER; ++i) pre[j][i] = pj[lane + 64 * i];
-        }
-        for (int c0 = 0; c0 < nch; c0 += 64) {        // groups of 64 chunks, in order
-            const int cc = c0 + lane;
-            const bool on = cc < nch;
-            const float* p = base + (size_t)(on ? cc : c0) * cstride;
-            const float mc = on ? p[HD] : -INFINITY;
-            const float dc = on ? p[HD + 1] : 0.f;
-            float Mg = mc;
-            Mg = wave_max_all(Mg);
-            const float Mnew = fmaxf(Mrun, Mg);       // finite: chunk 0 always holds key 0
-            const float scale_old = __expf(Mrun - Mnew);
-            const float wt = mc == -INFINITY ? 0.f : __expf(mc - Mnew);
-            float dsum = wt * dc;
-            dsum = wave_sum_all(dsum);
-            den = den * scale_old + dsum;
-#pragma unroll
-            for (int i = 0; i < PER; ++i) num[i] *= scale_old;
-            const int ng = nch - c0 < 64 ? nch - c0 : 64;
-            if (c0 == 0) {
-#pragma unroll
-                for (int j = 0; j < CPRE; ++j) {
-                    const float wj = j < ng ? lane_value(wt, j) : 0.f;
-#pragma unroll
-                    for (int i = 0; i < PER; ++i) num[i] += wj * pre[j][i];
-                }
-            }
-            for (int j = c0 == 0 ? CPRE : 0; j < ng; ++j) {
-                const float wj = lane_value(wt, j);
-                const float* pj = base + (size_t)(c0 + j) * cstride;
-#pragma unroll
-                for (int i = 0; i < PER; ++i) num[i] += wj * pj[lane + 64 * i];
-            }
-            Mrun = Mnew;
-        }
-        const float inv = 1.0f / den;
+        float num[PER];
+        merge_chunks<HD>(base, cstride, nch, lane, num);
 #pragma unroll
         for (int i = 0; i < PER; ++i)
-            store_gemm_in<DT>(M.O, k, mm, head * HD + lane + 64 * i, num[i] * inv);
+            store_gemm_in<DT>(M.O, k, mm, head * HD + lane + 64 * i, num[i]);
     }
 }
 

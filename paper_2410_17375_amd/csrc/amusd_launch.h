@@ -1,5 +1,7 @@
 // Host-callable launchers of the kernels in amusd_kernels.hip.
 #pragma once
+#include <vector>
+
 #include "amusd_dev.h"
 
 namespace amusd {
@@ -41,5 +43,11 @@ hipError_t launch_stream_chain(const uint4* buf, size_t buf_words, size_t words_
 // Enqueues one whole pass (all stages) on the stream.
 hipError_t launch_pass(const DevModel& M, const DevLayer* layers_host, const PassArgs& P, int nwg, hipStream_t stream,
                        StageTimer* timer);
+
+// One prefill pass: P.n rows (tokens in T.tokens) appended at P.L0; greedy tokens of all rows to T.greedy.
+hipError_t launch_prefill(const DevModel& M, const DevLayer* layers_host, const PrefillBufs& T, const PrefillArgs& P, hipStream_t stream);
+
+// Column tiles of a stage of the prefill pass in the order its workgroups take them, and *wgs (PfTiles).
+void prefill_tile_order(const DevModel& M, int stage, int nwg, std::vector<int>& order, int* wgs);
 
 }  // namespace amusd

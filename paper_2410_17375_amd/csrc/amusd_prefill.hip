@@ -1,0 +1,655 @@
+// Prefill pass for gfx950: up to kPfMaxRows prompt tokens of one sequence through the decoder at once.
+//
+// The verify pass serves 16 rows and is bound by streaming the weights; a prompt that goes through it 8 rows at a time
+// streams all weights n/8 times (8B shape: 3.07 ms per 8 tokens).  Here a weight fragment that has been fetched is used
+// for 64 rows of a wave, and the pass is bound by the matrix cores.
+//
+// A row gets the same bits as in the verify pass, whatever the number of rows: an output element is, as there, eight
+// chains of 16x16 matrix instructions over the same K slices in the same order (k_slice), each for the hi and the lo
+// halves of the activations, W.hi + W.lo added per slice, slices added in wave order.  What eight waves do there side by
+// side a wave does here one after the other, with the slice's two sums and the total in registers.  The order inside a
+// slice depends on the tile (its workgroup there), so a workgroup here takes tiles whose walks start alike: tile lists
+// ordered by that start are made once per model.
+#include <algorithm>
+#include <utility>
+#include <vector>
+
+#include "amusd_attention.h"
+
+namespace amusd {
+
+// ---------------------------------------------------------------- operand layout of the pass's activations
+// [128-row block][K block][16-row tile of the block][hi, lo][64 lanes][EPL]: what a workgroup stages per K block is
+// contiguous.
+template <class DT>
+struct PfAct {
+    static constexpr int AF = DT::HAS_LO ? 2 : 1;
+    static constexpr int kBlockTiles = kPfBlockRows / 16;
+    // 16-byte fragment index of lane 0 of (row tile, K block, part)
+    static __device__ __forceinline__ size_t frag(int kblocks, int rt, int kb, int part) {
+        return ((((size_t)(rt / kBlockTiles) * kblocks + kb) * kBlockTiles + rt % kBlockTiles) * AF + part) * 64;
+    }
+    // two neighbouring columns (col even) of one row
+    static __device__ __forceinline__ void store2(void* buf, int kblocks, int row, int col, float x0, float x1) {
+        const int kb = col / DT::KB, g = (col % DT::KB) / DT::EPL, e = col % DT::EPL;
+        const size_t at = (frag(kblocks, row >> 4, kb, 0) + g * 16 + (row & 15)) * DT::EPL + e;
+        if constexpr (DT::HAS_LO) {
+            const uint32_t h0 = bf16_rne(x0), h1 = bf16_rne(x1);
+            const uint32_t l0 = bf16_rne(x0 - bf16_to_f32(h0)), l1 = bf16_rne(x1 - bf16_to_f32(h1));
+            uint16_t* b = reinterpret_cast<uint16_t*>(buf);
+            *reinterpret_cast<uint32_t*>(b + at) = h0 | (h1 << 16);
+            *reinterpret_cast<uint32_t*>(b + at + 64 * DT::EPL) = l0 | (l1 << 16);
+        } else {
+            *reinterpret_cast<float2*>(reinterpret_cast<float*>(buf) + at) = float2{x0, x1};
+        }
+    }
+    static __device__ __forceinline__ void store1(void* buf, int kblocks, int row, int col, float x) {
+        const int kb = col / DT::KB, g = (col % DT::KB) / DT::EPL, e = col % DT::EPL;
+        const size_t at = (frag(kblocks, row >> 4, kb, 0) + g * 16 + (row & 15)) * DT::EPL + e;
+        if constexpr (DT::HAS_LO) {
+            const uint32_t h = bf16_rne(x), l = bf16_rne(x - bf16_to_f32(h));
+            reinterpret_cast<uint16_t*>(buf)[at] = (uint16_t)h;
+            reinterpret_cast<uint16_t*>(buf)[at + 64 * DT::EPL] = (uint16_t)l;
+        } else {
+            reinterpret_cast<float*>(buf)[at] = x;
+        }
+    }
+};
+
+// ---------------------------------------------------------------- contraction
+template <int STAGE>
+struct PfWalk;
+template <> struct PfWalk<kPfQKV> { using T = KWalkQKV; };
+template <> struct PfWalk<kPfOproj> { using T = KWalkOproj; };
+template <> struct PfWalk<kPfGateUp> { using T = KWalkWide; };
+template <> struct PfWalk<kPfDown> { using T = KWalkDown; };
+template <> struct PfWalk<kPfLMHead> { using T = KWalkWide; };
+
+// The K blocks of one contraction in order: slices of the eight waves of the verify pass one after the other, for each
+// of the K ranges (`ways`) that pairs of its workgroups share.
+template <class Walk>
+struct KSequence {
+    int kh, wg, ways;          // blocks per K range
+    int part = 0, w = -1, i = 0, kb = 0;
+    KSlice ks{0, 0, 0, 1};
+    bool at_end = false;
+    __device__ __forceinline__ KSequence(int kblocks, int wg_, int ways_) : kh(kblocks / ways_), wg(wg_), ways(ways_) { next_slice(); }
+    __device__ __forceinline__ void next_slice() {
+        i = 0;
+#pragma unroll 1
+        do {
+            if (++w == kWaves) {
+                w = 0;
+                if (++part == ways) { at_end = true; return; }
+            }
+            ks = k_slice_of<Walk>(kh, wg, w);
+        } while (ks.S <= 0);
+    }
+    // the next block; past the end the last one again
+    __device__ __forceinline__ int take() {
+        if (!at_end) {
+            const int x = i + ks.rot;
+            kb = part * kh + ks.kb0 + (x >= ks.S ? x - ks.S : x) * ks.stride;
+            if (++i == ks.S) next_slice();
+        }
+        return kb;
+    }
+};
+
+template <int N>
+__device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+
+// A workgroup of WN x WM waves computes WN*A column tiles x WM*B row tiles, a wave A x B of them.  Weight and activation
+// fragments of SLOTS K blocks go through a ring in LDS, filled by loads that deliver straight into it (SLOTS - 1 blocks
+// ahead; the loop has no other vector-memory instruction, so its waits can count them), and each fragment is read from
+// there by the waves of its row or column.
+//   4 x 2 waves of 4 x 4 tiles (256 columns x 128 rows, 32 KiB per K block): per K block 1024 clocks of matrix
+//       instructions on each SIMD, 96 KiB of LDS reads (768 clocks) and 32 KiB of loads (32 bytes per clock of the 64 that an
+//       L2 gives one of its compute units).  The three accumulators per output fill 192 of a wave's 256 registers.  8B shape,
+//       2048 rows: gate/up 908 us = 1.06 PFLOP/s of matrix instructions, hi and lo halves counted (a large library product
+//       on the same card: 1.29).
+//   smaller ones where that shape leaves compute units without a tile; they are bound by LDS reads.
+template <int WN_, int WM_, int A_, int B_, int SLOTS_>
+struct PfShape {
+    static constexpr int WN = WN_, WM = WM_, A = A_, B = B_, SLOTS = SLOTS_;
+    static constexpr int kTiles = WN * A, kRowTiles = WM * B, kThreads = WN * WM * 64;
+    // accumulators in vector registers proper: with fewer waves the compiler keeps them in accumulation registers and
+    // copies them back and forth around every slice
+    static constexpr int kMinWaves = A * B >= 8 ? 2 : 4;
+};
+template <class DT, int STAGE, class Sh>
+struct PfGemm {
+    static constexpr int WN = Sh::WN, WM = Sh::WM, A = Sh::A, B = Sh::B, SLOTS = Sh::SLOTS;
+    static constexpr int AF = PfAct<DT>::AF;
+    static constexpr int NF = WN * A + WM * B * AF;    // fragments per K block
+    static constexpr int NPW = NF / (WN * WM);         // loads per wave and K block
+    static_assert(NF % (WN * WM) == 0 && SLOTS >= 3 && A % 2 == 0, "");
+    static constexpr int kSlotBytes = NF * 1024;
+    static constexpr int kLdsBytes = SLOTS * kSlotBytes;
+    using Walk = typename PfWalk<STAGE>::T;
+
+    v4f tot[A][B], acc[A][B][AF];
+    uint4 wf[2], af[B][AF];
+
+    __device__ __forceinline__ uint4 lds_frag(const char* slot, int f, int lane) const {
+        return *reinterpret_cast<const uint4*>(slot + f * 1024 + lane * 16);
+    }
+    __device__ __forceinline__ void fold(int i, int j) {
+        if constexpr (AF == 2) tot[i][j] += acc[i][j][0] + acc[i][j][1];
+        else tot[i][j] += acc[i][j][0];
+    }
+
+    // One K block from slot `cur`; the following one is in `nxt` after the barrier in the middle, where the load of the
+    // block SLOTS - 1 ahead is issued (into the slot of the block before this one: every wave is past it).  At the first
+    // block of a slice (wave-uniform) the sums of the slice before are added to the total, tile by tile between the
+    // matrix instructions, and the new ones start at zero.
+    template <class Issue>
+    __device__ __forceinline__ void block(bool first, const char* cur, const char* nxt, int wn, int wm, int lane, Issue&& issue) {
+#pragma unroll
+        for (int i = 0; i < A; ++i) {
+            if (i == A / 2) {
+                wait_vm<(SLOTS - 3) * NPW>();
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                issue();
+            }
+            if (i + 1 < A) wf[(i + 1) & 1] = lds_frag(cur, wn * A + i + 1, lane);
+            else wf[(i + 1) & 1] = lds_frag(nxt, wn * A, lane);
+            if (first) {
+#pragma unroll
+                for (int j = 0; j < B; ++j) {
+                    fold(i, j);
+#pragma unroll
+                    for (int f = 0; f < AF; ++f) acc[i][j][f] = v4f{0.f, 0.f, 0.f, 0.f};
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < B; ++j) {
+#pragma unroll
+                for (int f = 0; f < AF; ++f) acc[i][j][f] = DT::mfma(wf[i & 1], af[j][f], acc[i][j][f]);
+                if (i == A - 1)
+#pragma unroll
+                    for (int f = 0; f < AF; ++f) af[j][f] = lds_frag(nxt, WN * A + (wm * B + j) * AF + f, lane);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+
+    __device__ __forceinline__ void contract(const uint4* __restrict__ W, const uint4* __restrict__ act, const int* tiles, int rt0,
+                                             int kblocks, int wgs, int ways, float* half_total, char* smem) {
+        const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const int wn = wave % Sh::WN, wm = wave / Sh::WN;
+        const int t0 = tiles[0];                        // all of the workgroup's tiles walk K alike
+        const char* src[NPW];
+        int step[NPW];
+#pragma unroll
+        for (int q = 0; q < NPW; ++q) {
+            const int f = wave * NPW + q;
+            if (f < WN * A) {
+                const int t = tiles[f];
+                src[q] = reinterpret_cast<const char*>(W + (size_t)(t < 0 ? t0 : t) * kblocks * 64);
+                step[q] = 1024;
+            } else {
+                const int x = f - WN * A;
+                src[q] = reinterpret_cast<const char*>(act + PfAct<DT>::frag(kblocks, rt0 + x / AF, 0, x % AF));
+                step[q] = PfAct<DT>::kBlockTiles * AF * 1024;
+            }
+        }
+        KSequence<Walk> ahead(kblocks, t0 % wgs, ways);
+        int islot = 0;
+        auto issue = [&]() {
+            const int kb = ahead.take();
+            char* dst = smem + islot * kSlotBytes + wave * (NPW * 1024);
+#pragma unroll
+            for (int q = 0; q < NPW; ++q)
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[q] + (size_t)kb * step[q] + lane * 16),
+                                                 (__attribute__((address_space(3))) void*)(dst + q * 1024), 16, 0, 0);
+            islot = islot + 1 == SLOTS ? 0 : islot + 1;
+        };
+#pragma unroll
+        for (int s = 0; s < SLOTS - 1; ++s) issue();
+#pragma unroll
+        for (int i = 0; i < A; ++i)
+#pragma unroll
+            for (int j = 0; j < B; ++j) {
+                tot[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int f = 0; f < AF; ++f) acc[i][j][f] = v4f{0.f, 0.f, 0.f, 0.f};
+            }
+        wait_vm<(SLOTS - 2) * NPW>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        wf[0] = lds_frag(smem, wn * A, lane);
+#pragma unroll
+        for (int j = 0; j < B; ++j)
+#pragma unroll
+            for (int f = 0; f < AF; ++f) af[j][f] = lds_frag(smem, WN * A + (wm * B + j) * AF + f, lane);
+        int cslot = 0;
+        auto slots = [&](const char*& cur, const char*& nxt) {
+            cur = smem + cslot * kSlotBytes;
+            cslot = cslot + 1 == SLOTS ? 0 : cslot + 1;
+            nxt = smem + cslot * kSlotBytes;
+        };
+        const int kh = kblocks / ways;
+#pragma unroll 1
+        for (int part = 0; part < ways; ++part) {
+            if (part) {                                 // the first K range's total waits in memory: this thread reads it back
+                float* hp = half_total + threadIdx.x * 4;
+                asm volatile("" : "+v"(hp));            // its addresses are not to be kept in registers from the start
+#pragma unroll
+                for (int i = 0; i < A; ++i)
+#pragma unroll
+                    for (int j = 0; j < B; ++j) {
+                        fold(i, j);
+                        *reinterpret_cast<v4f*>(hp + (i * B + j) * (Sh::kThreads * 4)) = tot[i][j];
+                        tot[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                        for (int f = 0; f < AF; ++f) acc[i][j][f] = v4f{0.f, 0.f, 0.f, 0.f};
+                    }
+            }
+#pragma unroll 1
+            for (int w = 0; w < kWaves; ++w) {
+                const int S = k_slice_of<Walk>(kh, t0 % wgs, w).S;
+                if (S <= 0) continue;
+#pragma unroll 1
+                for (int i = 0; i < S; ++i) {
+                    const char *cur, *nxt;
+                    slots(cur, nxt);
+                    block(i == 0, cur, nxt, wn, wm, lane, issue);
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < A; ++i)
+#pragma unroll
+            for (int j = 0; j < B; ++j) fold(i, j);
+        if (ways > 1) {
+            const float* hp = half_total + threadIdx.x * 4;
+            asm volatile("" : "+v"(hp));
+#pragma unroll
+            for (int i = 0; i < A; ++i)
+#pragma unroll
+                for (int j = 0; j < B; ++j) tot[i][j] = *reinterpret_cast<const v4f*>(hp + (i * B + j) * (Sh::kThreads * 4)) + tot[i][j];
+        }
+        wait_vm<0>();                                   // the blocks loaded past the end
+        __syncthreads();
+    }
+};
+
+// Position of a workgroup in the grid of (column group, row group).  Workgroups are dealt to the eight XCDs in turn; an
+// XCD takes a contiguous stretch of the column-major list, so the ones that run at a time on it share weight tiles and
+// activation rows in its L2.
+__device__ __forceinline__ int xcd_contiguous(int wg, int total) {
+    const int x = wg & 7, s = wg >> 3, per = total >> 3, rem = total & 7;
+    return x * per + (x < rem ? x : rem) + s;
+}
+
+template <class DT, int STAGE, class Sh>
+__global__ void __launch_bounds__(Sh::kThreads, Sh::kMinWaves) k_pf_gemm(DevModel M, DevLayer Ly, PrefillBufs T, PrefillArgs P, const float* gain_next) {
+    extern __shared__ char pf_smem[];
+    using G = PfGemm<DT, STAGE, Sh>;
+    constexpr int A = Sh::A, B = Sh::B;
+    const int row_groups = (P.n + Sh::kRowTiles * 16 - 1) / (Sh::kRowTiles * 16);
+    const int idx = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int cg = idx / row_groups, rg = idx % row_groups;
+    const PfTiles& L = T.tiles[STAGE];
+    const int* tiles = L.order + cg * Sh::kTiles;
+    if (tiles[0] < 0) {      // nothing but filling (it is at the end of a start's tiles): no K walk, no weights to point at
+        if constexpr (STAGE == kPfLMHead)
+            for (int x = threadIdx.x; x < Sh::WN * Sh::kRowTiles * 16; x += Sh::kThreads) {
+                const int row = rg * Sh::kRowTiles * 16 + x / Sh::WN;
+                if (row < P.n) {
+                    T.best_val[(size_t)(cg * Sh::WN + x % Sh::WN) * T.cap + row] = -INFINITY;
+                    T.best_idx[(size_t)(cg * Sh::WN + x % Sh::WN) * T.cap + row] = 0x7fffffff;
+                }
+            }
+        return;
+    }
+    const uint4* W;
+    const void* act;
+    int K;
+    if constexpr (STAGE == kPfQKV) { W = Ly.wqkv; act = T.A; K = M.d; }
+    else if constexpr (STAGE == kPfOproj) { W = Ly.wo; act = T.O; K = M.qdim; }
+    else if constexpr (STAGE == kPfGateUp) { W = Ly.wgu; act = T.A; K = M.d; }
+    else if constexpr (STAGE == kPfDown) { W = Ly.wd; act = T.H; K = M.F; }
+    else { W = M.wlm; act = T.A; K = M.d; }
+    const int ways = STAGE == kPfDown && M.split_down ? 2 : 1;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wn = wave % Sh::WN, wm = wave / Sh::WN;
+    const int rt0 = rg * Sh::kRowTiles;
+    G acc;
+    float* half = STAGE == kPfDown ? T.xch + (size_t)idx * (Sh::kThreads * A * B * 4) : nullptr;
+    acc.contract(W, reinterpret_cast<const uint4*>(act), tiles, rt0, K / DT::KB, L.wgs, ways, half, pf_smem);
+
+    // Lane (m = row, g) holds columns 4g .. 4g+3 of a tile.  After a swap between the half-waves it has columns r0, r0 + 1
+    // and their partners r0 + 8, r0 + 9, the pairs that the epilogues work on.
+    const int m = lane & 15, g = lane >> 4;
+    const int r0 = 4 * (g & 1) + 2 * (lane >> 5);
+    float best_v[B];
+    int best_i[B];
+#pragma unroll
+    for (int j = 0; j < B; ++j) { best_v[j] = -INFINITY; best_i[j] = 0x7fffffff; }
+#pragma unroll
+    for (int i = 0; i < A; ++i) {
+        const int tile = tiles[wn * A + i];
+        if (tile < 0) continue;
+#pragma unroll
+        for (int j = 0; j < B; ++j) {
+            const int row = (rt0 + wm * B + j) * 16 + m;
+            const bool on = row < P.n;
+            const v4f c = acc.tot[i][j];
+            const auto pa = __builtin_amdgcn_permlane32_swap(__float_as_uint(c.x), __float_as_uint(c.z), false, false);
+            const auto pb = __builtin_amdgcn_permlane32_swap(__float_as_uint(c.y), __float_as_uint(c.w), false, false);
+            const float u0 = __uint_as_float(pa[0]), u1 = __uint_as_float(pb[0]);      // columns r0, r0 + 1
+            const float w0 = __uint_as_float(pa[1]), w1 = __uint_as_float(pb[1]);      // columns r0 + 8, r0 + 9
+            if constexpr (STAGE == kPfOproj || STAGE == kPfDown) {
+                const int c1 = tile * 16 + r0;
+                float sq = 0.f;
+                if (on) {
+                    float2* x1 = reinterpret_cast<float2*>(T.X + (size_t)row * M.d + c1);
+                    float2* x2 = reinterpret_cast<float2*>(T.X + (size_t)row * M.d + c1 + 8);
+                    const float2 g1 = *reinterpret_cast<const float2*>(gain_next + c1), g2 = *reinterpret_cast<const float2*>(gain_next + c1 + 8);
+                    float2 a = *x1, b = *x2;
+                    a.x += u0; a.y += u1; b.x += w0; b.y += w1;
+                    *x1 = a;
+                    *x2 = b;
+                    PfAct<DT>::store2(T.A, M.d / DT::KB, row, c1, a.x * g1.x, a.y * g1.y);
+                    PfAct<DT>::store2(T.A, M.d / DT::KB, row, c1 + 8, b.x * g2.x, b.y * g2.y);
+                    sq = square_pair(a.x, b.x) + square_pair(a.y, b.y);
+                }
+                sq = wave_xor_add<32>(sq);
+                sq = wave_xor_add<16>(sq);
+                if (on && g == 0) T.ssq[(size_t)tile * T.cap + row] = sq;
+            } else if constexpr (STAGE == kPfGateUp) {
+                if (on) {
+                    const float sc = T.rstd[row];
+                    PfAct<DT>::store2(T.H, M.F / DT::KB, row, tile * 8 + r0, swiglu(u0 * sc, w0 * sc), swiglu(u1 * sc, w1 * sc));
+                }
+            } else if constexpr (STAGE == kPfQKV) {
+                if (!on) continue;
+                const float sc = T.rstd[row];
+                const int hd = M.hd, tph = hd / 16, qt = M.qdim / 16, kt = M.kvdim / 16, pos = P.L0 + row;
+                const float a0 = u0 * sc, a1 = u1 * sc, b0 = w0 * sc, b1 = w1 * sc;
+                const size_t slot_base = (size_t)P.slot * M.Hkv * M.ctx_pad * hd;
+                if (tile < qt + kt) {
+                    const bool isq = tile < qt;
+                    const int tt = isq ? tile : tile - qt;
+                    const int head = tt / tph, c1 = (tt % tph) * 8 + r0;
+                    const size_t ro = (size_t)pos * (hd / 2) + c1;
+                    const float2 cs = *reinterpret_cast<const float2*>(M.rope_cos + ro), sn = *reinterpret_cast<const float2*>(M.rope_sin + ro);
+                    float x0, x1, y0, y1;
+                    rotate_pair(a0, b0, cs.x, sn.x, x0, y0);
+                    rotate_pair(a1, b1, cs.y, sn.y, x1, y1);
+                    if (isq) {
+                        const size_t o = (size_t)row * M.qdim + head * hd + c1;
+                        if constexpr (DT::HAS_LO) {
+                            auto put = [&](size_t at, float p, float q) {
+                                const uint32_t h0 = DT::att_bits(p), h1 = DT::att_bits(q);
+                                const uint32_t l0 = DT::att_bits(p - DT::att_float(h0)), l1 = DT::att_bits(q - DT::att_float(h1));
+                                *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(T.Q_hi) + at) = h0 | (h1 << 16);
+                                *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(T.Q_lo) + at) = l0 | (l1 << 16);
+                            };
+                            put(o, x0, x1);
+                            put(o + hd / 2, y0, y1);
+                        } else {
+                            *reinterpret_cast<float2*>(reinterpret_cast<float*>(T.Q_hi) + o) = float2{x0, x1};
+                            *reinterpret_cast<float2*>(reinterpret_cast<float*>(T.Q_hi) + o + hd / 2) = float2{y0, y1};
+                        }
+                    } else {
+                        const size_t hb = slot_base + (size_t)head * M.ctx_pad * hd;
+                        auto put = [&](int col, float p, float q) {      // neighbouring columns are neighbours in the cache
+                            const size_t at = hb + kcache_index<DT>(hd, pos, col);
+                            if constexpr (DT::HAS_LO)
+                                *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(Ly.kcache) + at) = DT::att_bits(p) | (DT::att_bits(q) << 16);
+                            else
+                                *reinterpret_cast<float2*>(reinterpret_cast<float*>(Ly.kcache) + at) = float2{p, q};
+                        };
+                        put(c1, x0, x1);
+                        put(c1 + hd / 2, y0, y1);
+                    }
+                } else {
+                    const int tt = tile - qt - kt;
+                    const int head = tt / tph, c1 = (tt % tph) * 16 + r0;
+                    const size_t hb = slot_base + (size_t)head * M.ctx_pad * hd;
+                    auto put = [&](int col, float p) {
+                        const size_t at = hb + vcache_index<DT>(hd, pos, col);
+                        if constexpr (DT::HAS_LO) reinterpret_cast<uint16_t*>(Ly.vcache)[at] = (uint16_t)DT::att_bits(p);
+                        else reinterpret_cast<float*>(Ly.vcache)[at] = p;
+                    };
+                    put(c1, a0);
+                    put(c1 + 1, a1);
+                    put(c1 + 8, b0);
+                    put(c1 + 9, b1);
+                }
+            } else {                                   // LM head: logits of the rows that are kept, arg-max per row
+                if (on) {
+                    const float sc = T.rstd[row];
+                    const int c1 = tile * 16 + r0;
+                    const float z[4] = {u0 * sc, u1 * sc, w0 * sc, w1 * sc};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int col = c1 + (e & 1) + 8 * (e >> 1);
+                        if (better(z[e], col, best_v[j], best_i[j])) { best_v[j] = z[e]; best_i[j] = col; }
+                        if (row >= P.keep0) M.logits[(size_t)(row - P.keep0) * M.V + col] = z[e];
+                    }
+                }
+            }
+        }
+    }
+    if constexpr (STAGE == kPfLMHead) {
+#pragma unroll
+        for (int j = 0; j < B; ++j) {
+            const int row = (rt0 + wm * B + j) * 16 + m;
+            keep_better_xor<16>(best_v[j], best_i[j]);
+            keep_better_xor<32>(best_v[j], best_i[j]);
+            if (g == 0 && row < P.n) {
+                T.best_val[(size_t)(cg * Sh::WN + wn) * T.cap + row] = best_v[j];
+                T.best_idx[(size_t)(cg * Sh::WN + wn) * T.cap + row] = best_i[j];
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------- the stages around the contractions
+// Embedding rows -> residual stream, first norm input, sums of squares.  Thread -> (tile, row, column pair), as in the
+// verify pass; the sum over a tile's eight pairs is the same tree.
+template <class DT>
+__global__ void __launch_bounds__(256) k_pf_embed(DevModel M, PrefillBufs T, PrefillArgs P, const float* gain) {
+    const int ntiles = M.d / 16;
+    const int idx = blockIdx.x * 2 + (threadIdx.x >> 7);
+    const int tile = idx % ntiles, rt = idx / ntiles;
+    const int mm = (threadIdx.x >> 3) & 15, r = threadIdx.x & 7;
+    const int row = rt * 16 + mm;
+    const bool on = row < P.n;
+    float sq = 0.f;
+    const int c1 = tile * 16 + r;
+    if (on) {
+        const size_t o = (size_t)T.tokens[row] * M.d + c1;
+        float x1, x2;
+        if constexpr (DT::HAS_LO) {
+            x1 = bf16_to_f32(reinterpret_cast<const uint16_t*>(M.embed)[o]);
+            x2 = bf16_to_f32(reinterpret_cast<const uint16_t*>(M.embed)[o + 8]);
+        } else {
+            x1 = reinterpret_cast<const float*>(M.embed)[o];
+            x2 = reinterpret_cast<const float*>(M.embed)[o + 8];
+        }
+        T.X[(size_t)row * M.d + c1] = x1;
+        T.X[(size_t)row * M.d + c1 + 8] = x2;
+        PfAct<DT>::store1(T.A, M.d / DT::KB, row, c1, x1 * gain[c1]);
+        PfAct<DT>::store1(T.A, M.d / DT::KB, row, c1 + 8, x2 * gain[c1 + 8]);
+        sq = square_pair(x1, x2);
+    }
+    sq = wave_xor_add<1>(sq);
+    sq = wave_xor_add<2>(sq);
+    sq = wave_xor_add<4>(sq);
+    if (on && r == 0) T.ssq[(size_t)tile * T.cap + row] = sq;
+}
+
+// 1 / rms of each row; 32 lanes per row sum tiles s, s + 32, .. and then each other, in the verify pass's order.
+__global__ void __launch_bounds__(256) k_pf_rstd(DevModel M, PrefillBufs T, PrefillArgs P) {
+    const int row = blockIdx.x * 8 + (threadIdx.x >> 5), s = threadIdx.x & 31;
+    const int r = row < P.n ? row : P.n - 1;
+    const int ntp = M.d / 16;
+    float acc = 0.f;
+    for (int i = s; i < ntp; i += 32) acc += T.ssq[(size_t)i * T.cap + r];
+    acc = wave_xor_add<16>(acc);
+    acc = wave_xor_add<8>(acc);
+    acc = wave_xor_add<4>(acc);
+    acc = wave_xor_add<2>(acc);
+    acc = wave_xor_add<1>(acc);
+    if (s == 0 && row < P.n) T.rstd[row] = 1.0f / sqrtf(acc / (float)M.d + M.eps);
+}
+
+// Attention units of row tiles rt0 .. rt0 + nrt - 1 (16 rows each, at positions L0 + 16 rt ..): workgroup -> (row tile,
+// chunk, kv head).  With 8 kv heads (or a multiple) a kv head's units run on one XCD, and its cache stays in that L2.
+template <class DT, int HD>
+__global__ void __launch_bounds__(kThreads) k_pf_attention(DevModel M, DevLayer Ly, PrefillBufs T, PrefillArgs P, int rt0, int nch) {
+    extern __shared__ float att_smem[];
+    const int kvh = blockIdx.x % M.Hkv, rest = blockIdx.x / M.Hkv;
+    const int c = rest % nch, t = rest / nch, rt = rt0 + t;
+    const int L = P.L0 + 16 * rt;
+    const int k = P.n - 16 * rt < 16 ? P.n - 16 * rt : 16;
+    if (c * M.chunk >= L + k) return;
+    const size_t q0 = (size_t)rt * 16 * M.qdim * DT::ESZ;
+    const size_t slot_frags = (size_t)P.slot * M.Hkv * M.ctx_pad * HD / DT::EPL;
+    attention_unit<DT, HD>(M, Ly, reinterpret_cast<const char*>(T.Q_hi) + q0, reinterpret_cast<const char*>(T.Q_lo) + q0, slot_frags,
+                           kvh, c, L, k, 0, T.att_part + (((size_t)t * M.Hkv + kvh) * nch + c) * M.G * kRows * (HD + kPartRow), att_smem);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // a wave must not end while its look-ahead fetch is in flight
+}
+
+// One wave per (row, query head).
+template <class DT, int HD>
+__global__ void __launch_bounds__(256) k_pf_merge(DevModel M, PrefillBufs T, PrefillArgs P, int rt0, int rows, int nch) {
+    constexpr int ROW = HD + kPartRow, PER = HD / 64;
+    const int lane = threadIdx.x & 63;
+    const int x = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+    if (x >= rows * M.Hq) return;
+    // head fastest by kv head, so that with 8 of them a head's partials are merged where they were written
+    const int kvh = x % M.Hkv, y = x / M.Hkv, hq = y % M.G, rr = y / M.G;
+    const int row = rt0 * 16 + rr, t = rr >> 4, mm = rr & 15;
+    const int n = (P.L0 + row) / M.chunk + 1;
+    const float* base = T.att_part + ((((size_t)t * M.Hkv + kvh) * nch * M.G + hq) * kRows + mm) * ROW;
+    float num[PER];
+    merge_chunks<HD>(base, (size_t)M.G * kRows * ROW, n, lane, num);
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+        PfAct<DT>::store1(T.O, M.qdim / DT::KB, row, (kvh * M.G + hq) * HD + lane + 64 * i, num[i]);
+}
+
+// Arg-max of each row over the workgroups' partials: one wave per row.
+__global__ void __launch_bounds__(256) k_pf_greedy(PrefillBufs T, PrefillArgs P, int parts) {
+    const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (row >= P.n) return;
+    float bv = -INFINITY;
+    int bi = 0x7fffffff;
+    for (int w = lane; w < parts; w += 64) {
+        const float v = T.best_val[(size_t)w * T.cap + row];
+        const int i = T.best_idx[(size_t)w * T.cap + row];
+        if (better(v, i, bv, bi)) { bv = v; bi = i; }
+    }
+    keep_better_xor<32>(bv, bi);
+    keep_better_xor<16>(bv, bi);
+    keep_better_xor<8>(bv, bi);
+    keep_better_xor<4>(bv, bi);
+    keep_better_xor<2>(bv, bi);
+    keep_better_xor<1>(bv, bi);
+    if (lane == 0) T.greedy[row] = bi;
+}
+
+// ---------------------------------------------------------------- host side
+template <class Walk>
+static void order_tiles(int n_tiles, int kblocks, int wgs, std::vector<int>& out) {
+    // tiles by where their eight walks start; a class is filled up with -1 to whole groups of kPfTileGroup
+    std::vector<std::pair<std::vector<int>, int>> key(n_tiles);
+    for (int t = 0; t < n_tiles; ++t) {
+        key[t].second = t;
+        for (int w = 0; w < kWaves; ++w) key[t].first.push_back(k_slice_of<Walk>(kblocks, t % wgs, w).rot);
+    }
+    std::stable_sort(key.begin(), key.end());
+    out.clear();
+    for (int t = 0; t < n_tiles; ++t) {
+        if (t && key[t].first != key[t - 1].first)
+            while (out.size() % kPfTileGroup) out.push_back(-1);
+        out.push_back(key[t].second);
+    }
+    while (out.size() % kPfTileGroup) out.push_back(-1);
+}
+
+void prefill_tile_order(const DevModel& M, int stage, int nwg, std::vector<int>& order, int* wgs) {
+    const int kb = M.dtype ? BF16::KB : FP32::KB;
+    const int tiles = stage == kPfQKV ? M.nqkv / 16 : stage == kPfGateUp ? 2 * M.F / 16 : stage == kPfLMHead ? M.V / 16 : M.d / 16;
+    const int K = stage == kPfOproj ? M.qdim : stage == kPfDown ? M.F : M.d;
+    *wgs = tiles < nwg ? tiles : nwg;
+    switch (stage) {
+        case kPfQKV: order_tiles<KWalkQKV>(tiles, K / kb, *wgs, order); break;
+        case kPfOproj: order_tiles<KWalkOproj>(tiles, K / kb, *wgs, order); break;
+        case kPfDown: order_tiles<KWalkDown>(tiles, K / kb / (M.split_down ? 2 : 1), *wgs, order); break;
+        default: order_tiles<KWalkWide>(tiles, K / kb, *wgs, order); break;
+    }
+}
+
+template <class DT, int STAGE, class Sh>
+static hipError_t launch_pf_gemm_v(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PrefillArgs& P, const float* gain,
+                                   hipStream_t s, int* parts) {
+    const int lds = PfGemm<DT, STAGE, Sh>::kLdsBytes;
+    static const hipError_t set = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pf_gemm<DT, STAGE, Sh>),
+                                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (set != hipSuccess) return set;
+    const int groups = T.tiles[STAGE].n / Sh::kTiles;
+    const int grid = groups * ((P.n + Sh::kRowTiles * 16 - 1) / (Sh::kRowTiles * 16));
+    if (parts) *parts = groups * Sh::WN;
+    hipLaunchKernelGGL((k_pf_gemm<DT, STAGE, Sh>), dim3(grid), dim3(Sh::kThreads), lds, s, M, Ly, T, P, gain);
+    return hipSuccess;
+}
+
+template <class DT, int STAGE>
+static hipError_t launch_pf_gemm(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PrefillArgs& P, const float* gain,
+                                 hipStream_t s, int* parts = nullptr) {
+    const int nt = T.tiles[STAGE].n;
+    auto groups = [&](int tiles, int rows) { return nt / tiles * ((P.n + rows - 1) / rows); };
+    if (groups(16, 128) >= T.cus / 2) return launch_pf_gemm_v<DT, STAGE, PfShape<4, 2, 4, 4, 4>>(M, Ly, T, P, gain, s, parts);
+    if (groups(8, 64) >= T.cus / 2) return launch_pf_gemm_v<DT, STAGE, PfShape<2, 2, 4, 2, 4>>(M, Ly, T, P, gain, s, parts);
+    return launch_pf_gemm_v<DT, STAGE, PfShape<2, 2, 2, 2, 5>>(M, Ly, T, P, gain, s, parts);
+}
+
+template <class DT, int HD>
+static hipError_t launch_prefill_t(const DevModel& M, const DevLayer* Ls, const PrefillBufs& T, const PrefillArgs& P, hipStream_t s) {
+    constexpr int att_lds = (kWaves * kRows * (HD + kAttPad) + kWaves * kRows * 2) * 4;
+    static const hipError_t set = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pf_attention<DT, HD>),
+                                                      hipFuncAttributeMaxDynamicSharedMemorySize, att_lds);
+    if (set != hipSuccess) return set;
+    const int rts = (P.n + 15) / 16;
+    const int rstd_wgs = (P.n + 7) / 8;
+    hipError_t e;
+    hipLaunchKernelGGL((k_pf_embed<DT>), dim3((M.d / 16 * rts + 1) / 2), dim3(256), 0, s, M, T, P, Ls[0].g_attn);
+    for (int l = 0; l < M.n_layers; ++l) {
+        const float* gain_next = l + 1 < M.n_layers ? Ls[l + 1].g_attn : M.g_final;
+        hipLaunchKernelGGL(k_pf_rstd, dim3(rstd_wgs), dim3(256), 0, s, M, T, P);
+        if ((e = launch_pf_gemm<DT, kPfQKV>(M, Ls[l], T, P, nullptr, s)) != hipSuccess) return e;
+        for (int rt = 0; rt < rts; rt += T.att_tiles) {
+            const int nrt = rts - rt < T.att_tiles ? rts - rt : T.att_tiles;
+            const int last = P.n < (rt + nrt) * 16 ? P.n : (rt + nrt) * 16;     // rows below this one
+            const int nch = (P.L0 + last + M.chunk - 1) / M.chunk;
+            hipLaunchKernelGGL((k_pf_attention<DT, HD>), dim3(nrt * nch * M.Hkv), dim3(kThreads), att_lds, s, M, Ls[l], T, P, rt, nch);
+            const int rows = last - rt * 16;
+            hipLaunchKernelGGL((k_pf_merge<DT, HD>), dim3((rows * M.Hq + 3) / 4), dim3(256), 0, s, M, T, P, rt, rows, nch);
+        }
+        if ((e = launch_pf_gemm<DT, kPfOproj>(M, Ls[l], T, P, Ls[l].g_mlp, s)) != hipSuccess) return e;
+        hipLaunchKernelGGL(k_pf_rstd, dim3(rstd_wgs), dim3(256), 0, s, M, T, P);
+        if ((e = launch_pf_gemm<DT, kPfGateUp>(M, Ls[l], T, P, nullptr, s)) != hipSuccess) return e;
+        if ((e = launch_pf_gemm<DT, kPfDown>(M, Ls[l], T, P, gain_next, s)) != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(k_pf_rstd, dim3(rstd_wgs), dim3(256), 0, s, M, T, P);
+    int parts = 0;
+    if ((e = launch_pf_gemm<DT, kPfLMHead>(M, Ls[0], T, P, nullptr, s, &parts)) != hipSuccess) return e;
+    hipLaunchKernelGGL(k_pf_greedy, dim3((P.n + 3) / 4), dim3(256), 0, s, T, P, parts);
+    return hipGetLastError();
+}
+
+hipError_t launch_prefill(const DevModel& M, const DevLayer* Ls, const PrefillBufs& T, const PrefillArgs& P, hipStream_t stream) {
+    if (M.dtype)
+        return M.hd == 128 ? launch_prefill_t<BF16, 128>(M, Ls, T, P, stream) : launch_prefill_t<BF16, 64>(M, Ls, T, P, stream);
+    return M.hd == 128 ? launch_prefill_t<FP32, 128>(M, Ls, T, P, stream) : launch_prefill_t<FP32, 64>(M, Ls, T, P, stream);
+}
+
+}  // namespace amusd

@@ -1,0 +1,97 @@
+"""The prefill pass (prompts of 17 tokens and more) against the same tokens given in pieces of at most 8, which go through
+the verify pass: cache rows, greedy tokens of every position, kept logits and what a following window sees, bit for bit.
+The sizes put the edges of its row and column tiles, its workgroup shapes and the K ranges of the down projection in turn."""
+import numpy as np
+import pytest
+
+from workload import SHAPES, WeightStore, prompt_tokens
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # (shape, overrides, tokens cached before, prompt length)
+    ("tiny_verify", {}, 0, 17), ("tiny_verify", {}, 5, 130), ("tiny_draft", {}, 0, 33),
+    ("tiny_gqa_fp32", {}, 0, 300), ("tiny_wide_fp32", {}, 3, 65),
+    ("tiny_gqa_bf16", {}, 0, 17), ("tiny_gqa_bf16", {}, 7, 64), ("tiny_gqa_bf16", {}, 1, 300),
+    ("tiny_gqa128_bf16", {}, 33, 129), ("tiny_g8_bf16", {}, 0, 200), ("tiny_wide_bf16", {}, 2, 97),
+    ("tiny_gqa_bf16", {"d_model": 288, "d_ffn": 544, "vocab": 1008}, 0, 47),     # K blocks that do not split evenly over the waves
+    ("tiny_wide_bf16", {"d_model": 320, "d_ffn": 4160}, 0, 80),
+    ("tiny_gqa_bf16", {"d_model": 128, "n_q_heads": 2, "n_kv_heads": 1, "d_ffn": 96}, 0, 70),   # fewer K blocks than waves
+    ("one_layer_8b_width_bf16", {"vocab": 16000}, 0, 61), ("one_layer_8b_width_bf16", {"vocab": 16000}, 40, 400),
+    ("one_layer_8b_width_bf16", {"vocab": 16000}, 0, 1100), ("one_layer_8b_width_bf16", {}, 9, 2190),
+]
+
+
+def _models(shape, max_ctx):
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2410_17375_amd as A
+    from paper_2410_17375_amd.harness import load_model
+    store = WeightStore(shape)
+    out = []
+    for _ in range(2):
+        m = load_model(shape, max_ctx, store=store)
+        m.set_option(A.OPT_KEEP_LOGITS, 1)
+        out.append(m)
+    return out
+
+
+def _bits(x):
+    return np.ascontiguousarray(x, dtype=np.float32).view(np.uint32)
+
+
+@pytest.mark.parametrize("name,over,before,n", CASES)
+def test_prefill_pass_equals_short_passes(name, over, before, n):
+    shape = SHAPES[name].with_(**over)
+    total = before + n
+    a, b = _models(shape, total + 40)
+    toks = prompt_tokens(31, total + 16, shape.vocab)
+    for m in (a, b):
+        for s in range(0, before, 8):
+            m.prefill(toks[s:min(s + 8, before)])
+    group = 16 if shape.dtype == "fp32" else 8
+    tail = (n - 1) % group + 1
+    nxt = a.prefill(toks[before:total])                    # one prefill pass (or two)
+    for s in range(before, total, group):
+        ref = b.prefill(toks[s:min(s + group, total)])
+    assert a.kv_len() == b.kv_len() == total and nxt == ref
+    for layer in range(shape.n_layers):
+        for which in (0, 1):
+            assert np.array_equal(_bits(a.get_kv(layer, which, 0, total)), _bits(b.get_kv(layer, which, 0, total))), (layer, which)
+    assert np.array_equal(a.get_greedy(tail), b.get_greedy(tail))
+    assert np.array_equal(_bits(a.get_logits(tail)), _bits(b.get_logits(tail)))
+    with pytest.raises(Exception):
+        a.get_logits(tail + 1)
+    window = toks[total:total + 9]
+    res = []
+    for m in (a, b):
+        res.append((m.verify(total, window), _bits(m.get_logits(9))))
+    assert res[0][0] == res[1][0] and np.array_equal(res[0][1], res[1][1])
+    for pos in range(total, before, -1):                   # the model's own token is recorded for every position
+        for m in (a, b):
+            m.kv_rollback(pos)
+        assert a.get_next() == b.get_next(), pos
+    a.free()
+    b.free()
+
+
+def test_prefill_pass_into_second_sequence_and_stage_timing():
+    import paper_2410_17375_amd as A
+    from paper_2410_17375_amd.harness import load_model
+    shape = SHAPES["tiny_gqa128_bf16"]
+    store = WeightStore(shape)
+    ms = [load_model(shape, 200, store=store, max_seqs=3) for _ in range(2)]
+    toks = prompt_tokens(32, 120, shape.vocab)
+    ms[1].set_option(A.OPT_TIME_STAGE, A.STAGES["qkv"])     # a timed stage is one of the verify pass
+    for m in ms:
+        m.seq_prefill(1, toks[:90])
+        m.seq_prefill(2, toks[30:120])
+    assert ms[1].stage_time()[1] == 2 * shape.n_layers * 12   # 90 tokens are 12 passes of at most 8
+    for seq in (1, 2):
+        assert ms[0].seq_len(seq) == 90 and ms[0].seq_get_next(seq) == ms[1].seq_get_next(seq)
+        for which in (0, 1):
+            assert np.array_equal(ms[0].seq_get_kv(seq, 1, which, 0, 90), ms[1].seq_get_kv(seq, 1, which, 0, 90))
+    assert ms[0].seq_len(0) == 0 and ms[0].last_pass_ms() > 0
+    for m in ms:
+        m.free()
