@@ -9,6 +9,150 @@ namespace amusd {
 constexpr int kAttPad = 4;    // row padding of the attention partials (spreads LDS banks)
 constexpr int kPartRow = 4;   // floats appended to a partial's numerator: max, denominator, 2 pad (keeps 16-byte alignment)
 
+// Scores, maxima and weights are in units of log2: the score scale carries the factor log2(e), and every exponential is
+// the hardware's power of two.
+__device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// Running softmax of one wave: 16 rows of one query head, a run of key blocks.
+template <int HD>
+struct AttState {
+    float m, l;              // running maximum and denominator of row lane & 15
+    v4f o[HD / 16];          // numerator: o[j][e] is head_dim column 16 j + 4 (lane >> 4) + e
+    __device__ __forceinline__ void clear() {
+        m = -INFINITY;
+        l = 0.f;
+#pragma unroll
+        for (int j = 0; j < HD / 16; ++j) o[j] = v4f{0.f, 0.f, 0.f, 0.f};
+    }
+};
+
+// One step of a run: NB (two, or one at the end of a run of odd length) key blocks, keys p0 ...  Scores are computed
+// transposed (keys x rows), so that the result registers are, after the softmax numerator, the operand of the P.V product.
+// kf(b, t, i), vf(b, j): the blocks' fragments.  MASKED: the blocks may hold keys that some row does not see (lim: the row's
+// last visible key, -1 for a row that is not the sequence's); the other form gives the same values for rows that see all of
+// them.  first: the run's first step (the numerators are zero).
+// Two blocks per step: a block's 8 scores per lane cost one rescaling of all numerators and two reductions across lanes,
+// and its products are short chains; two share the former and fill the gaps of the latter.  Groups of 4 and 8 heads take
+// two (always the same two of a run, visible or not), groups of 1 and 2 one.
+template <class DT, int HD, int NB, bool MASKED, class KF, class VF>
+__device__ __forceinline__ void attention_step(AttState<HD>& s, const uint4* qh, const uint4* ql, KF&& kf, VF&& vf, int p0, int lim,
+                                               int g, float scale, bool first) {
+    constexpr int FR = HD / 4 / DT::EPL, HT = HD / 16, TPB = DT::TPB, NTL = NB * TPB;
+    // Products are issued so that those of one accumulator are not neighbours; its own order stays (hi, lo, next fragment).
+    v4f sc[NTL];
+#pragma unroll
+    for (int i = 0; i < FR; ++i) {
+        uint4 k[NTL];
+#pragma unroll
+        for (int t = 0; t < NTL; ++t) k[t] = kf(t / TPB, t % TPB, i);
+#pragma unroll
+        for (int t = 0; t < NTL; ++t) sc[t] = DT::mfma_att(k[t], qh[i], i ? sc[t] : v4f{0.f, 0.f, 0.f, 0.f});
+        if constexpr (DT::HAS_LO)
+#pragma unroll
+            for (int t = 0; t < NTL; ++t) sc[t] = DT::mfma_att(k[t], ql[i], sc[t]);
+    }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int t = 0; t < NTL; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            sc[t][e] = sc[t][e] * scale;
+            if (MASKED && p0 + t * 16 + g * 4 + e > lim) sc[t][e] = -INFINITY;
+            mx = fmaxf(mx, sc[t][e]);
+        }
+    mx = fmaxf(mx, lane_xor<16>(mx));
+    mx = fmaxf(mx, lane_xor<32>(mx));
+    const float mnew = fmaxf(s.m, mx);
+    const float mref = mnew == -INFINITY ? 0.f : mnew;
+    const float alpha = exp2_fast(s.m - mref);      // 0 for the first visible key
+    if (!first) {
+        // scaled where they stand, ahead of all products: left alone the compiler scales each into a temporary right
+        // before its product and waits for the temporary to be free again after every one
+#pragma unroll
+        for (int j = 0; j < HT; ++j) s.o[j] = s.o[j] * alpha;
+    }
+    float lsum = 0.f;
+#pragma unroll
+    for (int t = 0; t < NTL; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            sc[t][e] = exp2_fast(sc[t][e] - mref);
+            lsum += sc[t][e];
+        }
+    lsum = wave_xor_add<16>(lsum);
+    lsum = wave_xor_add<32>(lsum);
+    s.l = fmaf(s.l, alpha, lsum);
+    s.m = mnew;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        uint4 ph, pl = uint4{0, 0, 0, 0};
+        const v4f a0 = sc[b * TPB], a1 = sc[b * TPB + TPB - 1];
+        if constexpr (DT::HAS_LO) {
+            DT::att_split2(a0.x, a0.y, ph.x, pl.x);
+            DT::att_split2(a0.z, a0.w, ph.y, pl.y);
+            DT::att_split2(a1.x, a1.y, ph.z, pl.z);
+            DT::att_split2(a1.z, a1.w, ph.w, pl.w);
+        } else {
+            ph = uint4{__float_as_uint(a0.x), __float_as_uint(a0.y), __float_as_uint(a0.z), __float_as_uint(a0.w)};
+        }
+        constexpr int JG = 4;
+#pragma unroll
+        for (int j0 = 0; j0 < HT; j0 += JG) {
+            uint4 v[JG];
+#pragma unroll
+            for (int j = 0; j < JG; ++j) v[j] = vf(b, j0 + j);
+#pragma unroll
+            for (int j = 0; j < JG; ++j) s.o[j0 + j] = DT::mfma_att(v[j], ph, s.o[j0 + j]);
+            if constexpr (DT::HAS_LO)
+#pragma unroll
+                for (int j = 0; j < JG; ++j) s.o[j0 + j] = DT::mfma_att(v[j], pl, s.o[j0 + j]);
+        }
+    }
+}
+
+// The runs of a unit's heads, one per wave, through LDS to one partial per (head, row): [head][row][HD numerators, max,
+// denominator, pad] at part_out.  smem: kWaves * kRows * (HD + kAttPad + 2) floats, free to be written.
+template <int HD>
+__device__ __forceinline__ void merge_runs(const AttState<HD>& s, int G, int parts, int hq, int part, int row0, int k, float* part_out,
+                                           float* smem) {
+    constexpr int HT = HD / 16, HDP = HD + kAttPad;
+    const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, g = lane >> 4;
+    float* partO = smem;                               // [hq][part][16][HD + pad]
+    float* partML = smem + kWaves * kRows * HDP;       // [hq][part][16][2]
+    // run partial to LDS: o[j][e] is head_dim index 16j + 4g + e of row m
+    const int slot = hq * parts + part;
+#pragma unroll
+    for (int j = 0; j < HT; ++j)
+        *reinterpret_cast<v4f*>(partO + ((size_t)(slot * kRows + m) * HDP + j * 16 + g * 4)) = s.o[j];
+    if (g == 0) {
+        partML[(slot * kRows + m) * 2 + 0] = s.m;
+        partML[(slot * kRows + m) * 2 + 1] = s.l;
+    }
+    __syncthreads();
+    // merge the runs of each head in run order; item = (head, row, 4 consecutive head_dim entries)
+    for (int it = tid; it < G * kRows * (HD / 4); it += kThreads) {
+        const int c4 = it % (HD / 4), mm = (it / (HD / 4)) % kRows, hh = it / (kRows * (HD / 4));
+        if (mm < row0 || mm >= row0 + k) continue;
+        float Mx = -INFINITY;
+        for (int pp = 0; pp < parts; ++pp) Mx = fmaxf(Mx, partML[((hh * parts + pp) * kRows + mm) * 2]);
+        float den = 0.f;
+        v4f num = v4f{0.f, 0.f, 0.f, 0.f};
+        for (int pp = 0; pp < parts; ++pp) {
+            const int sl = hh * parts + pp;
+            const float mw = partML[(sl * kRows + mm) * 2];
+            const float wt = mw == -INFINITY ? 0.f : exp2_fast(mw - Mx);
+            den = fmaf(wt, partML[(sl * kRows + mm) * 2 + 1], den);
+            const v4f x = *reinterpret_cast<const v4f*>(partO + ((size_t)(sl * kRows + mm) * HDP + c4 * 4));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) num[e] = fmaf(wt, x[e], num[e]);
+        }
+        float* out = part_out + ((size_t)hh * kRows + mm) * (HD + kPartRow);
+        *reinterpret_cast<v4f*>(out + c4 * 4) = num;
+        if (c4 == 0) { out[HD] = Mx; out[HD + 1] = den; }
+    }
+    __syncthreads();
+}
+
 // One unit: chunk c of kv head kvh (the 8/G runs of bpw key blocks that the waves of a workgroup walk) against the tile
 // rows row0 .. row0+k-1, which stand at positions L .. L+k-1.  q_hi / q_lo: the tile's query rows, row-major.
 // slot_frags: start of the sequence's cache, in 16-byte fragments.  Writes [head of the group][row][HD numerators, max,
@@ -20,14 +164,11 @@ __device__ __forceinline__ void attention_unit(const DevModel& M, const DevLayer
     constexpr int FR = HD / 4 / DT::EPL;     // 16-byte fragments per lane along head_dim
     constexpr int HT = HD / 16;              // 16-wide head_dim tiles
     constexpr int BK = DT::BLOCK_KEYS, TPB = DT::TPB;
-    constexpr int HDP = HD + kAttPad;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int m = lane & 15, g = lane >> 4;
     const int G = M.G, bpw = M.bpw;
     const int lg = __builtin_ctz((unsigned)G);         // G is 1, 2, 4 or 8 (checked at model creation): shifts, no divisions
     const int parts = kWaves >> lg, hq = wave & (G - 1), part = wave >> lg;
-    float* partO = smem;                               // [hq][part][16][HD + pad]
-    float* partML = smem + kWaves * kRows * HDP;       // [hq][part][16][2]
     const int nblk = M.ctx_pad / BK;
     const uint4 zero4 = uint4{0, 0, 0, 0};
     const int T = L + k;
@@ -60,10 +201,11 @@ __device__ __forceinline__ void attention_unit(const DevModel& M, const DevLayer
         for (int j = 0; j < HT; ++j) vd[j] = vb[j * 64];
     };
     load_block(b0, kf, vf);
-    float mrun = -INFINITY, lrun = 0.f;
-    v4f o[HT];
-#pragma unroll
-    for (int j = 0; j < HT; ++j) o[j] = v4f{0.f, 0.f, 0.f, 0.f};
+    AttState<HD> s;
+    s.clear();
+    const int lim = mine ? L + m - row0 : -1;          // causal: the sequence's j-th row (tile row row0 + j) sees keys 0 .. L + j
+    auto kfrag = [&](int, int t, int i) { return kf[t][i]; };
+    auto vfrag = [&](int, int j) { return vf[j]; };
     for (int ib = 0; ib < bpw; ++ib) {
         const int p0 = (b0 + ib) * BK;
         if (p0 >= T) break;                         // wave-uniform: later blocks of the run hold no visible key
@@ -73,62 +215,8 @@ __device__ __forceinline__ void attention_unit(const DevModel& M, const DevLayer
         // it is issued ahead of the matrix instructions, but nothing waits for the last one before the end
         const bool more = ib + 1 < bpw && p0 + BK < T;
         load_block(more ? b0 + ib + 1 : b0 + ib, kn, vn);
-        float sv[TPB][4];
-        float mx = -INFINITY;
-#pragma unroll
-        for (int t = 0; t < TPB; ++t) {
-            v4f sc = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int i = 0; i < FR; ++i) {
-                sc = DT::mfma_att(kf[t][i], qh[i], sc);
-                if constexpr (DT::HAS_LO) sc = DT::mfma_att(kf[t][i], ql[i], sc);
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int key = p0 + t * 16 + g * 4 + e;
-                // causal: the sequence's j-th row (tile row row0+j) sees keys 0..L+j
-                sv[t][e] = mine && key <= L + m - row0 ? sc[e] * M.att_scale : -INFINITY;
-                mx = fmaxf(mx, sv[t][e]);
-            }
-        }
-        mx = fmaxf(mx, lane_xor<16>(mx));
-        mx = fmaxf(mx, lane_xor<32>(mx));
-        const float mnew = fmaxf(mrun, mx);
-        const float mref = mnew == -INFINITY ? 0.f : mnew;
-        const float alpha = __expf(mrun - mref);     // 0 for the first visible block
-        float pv[TPB][4], lsum = 0.f;
-#pragma unroll
-        for (int t = 0; t < TPB; ++t)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                pv[t][e] = __expf(sv[t][e] - mref);
-                lsum += pv[t][e];
-            }
-        lsum = wave_xor_add<16>(lsum);
-        lsum = wave_xor_add<32>(lsum);
-        lrun = fmaf(lrun, alpha, lsum);
-        mrun = mnew;
-        uint4 ph, pl = zero4;
-        if constexpr (DT::HAS_LO) {
-            uint32_t h[8], l[8];
-#pragma unroll
-            for (int t = 0; t < TPB; ++t)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    h[t * 4 + e] = DT::att_bits(pv[t][e]);
-                    l[t * 4 + e] = DT::att_bits(pv[t][e] - DT::att_float(h[t * 4 + e]));
-                }
-            ph = uint4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
-            pl = uint4{l[0] | (l[1] << 16), l[2] | (l[3] << 16), l[4] | (l[5] << 16), l[6] | (l[7] << 16)};
-        } else {
-            ph = uint4{__float_as_uint(pv[0][0]), __float_as_uint(pv[0][1]), __float_as_uint(pv[0][2]), __float_as_uint(pv[0][3])};
-        }
-#pragma unroll
-        for (int j = 0; j < HT; ++j) {
-            o[j] = o[j] * alpha;
-            o[j] = DT::mfma_att(vf[j], ph, o[j]);
-            if constexpr (DT::HAS_LO) o[j] = DT::mfma_att(vf[j], pl, o[j]);
-        }
+        if (p0 + BK - 1 > L) attention_step<DT, HD, 1, true>(s, qh, ql, kfrag, vfrag, p0, lim, g, M.att_scale, ib == 0);
+        else attention_step<DT, HD, 1, false>(s, qh, ql, kfrag, vfrag, p0, lim, g, M.att_scale, ib == 0);
         if (!more) break;     // wave-uniform; the look-ahead fetch is retired at the end of the stage
 #pragma unroll
         for (int t = 0; t < TPB; ++t)
@@ -137,38 +225,106 @@ __device__ __forceinline__ void attention_unit(const DevModel& M, const DevLayer
 #pragma unroll
         for (int j = 0; j < HT; ++j) vf[j] = vn[j];
     }
-    // run partial to LDS: o[j][e] is head_dim index 16j + 4g + e of row m
-    const int slot = hq * parts + part;
+    merge_runs<HD>(s, G, parts, hq, part, row0, k, part_out, smem);
+}
+
+// The same unit for groups of 4 or 8 heads: the blocks of a run are needed by all G waves that walk it, so they are staged
+// in LDS once, two blocks of every run per step, by loads that deliver straight into it; a step's successor is under way
+// while it is used.  (Fetched by each wave for itself a unit pulls G times the bytes through its compute unit's load path,
+// and a lane holds 128 registers of them.)  smem: at least kStagedBytes and merge_runs' area.
+template <class DT, int HD, int G>
+struct AttStaged {
+    static constexpr int FR = HD / 4 / DT::EPL, HT = HD / 16, TPB = DT::TPB;
+    static constexpr int PARTS = kWaves / G;
+    static constexpr int NF = TPB * FR + HT;             // fragments of a key block: keys, then values
+    static constexpr int NPW = PARTS * 2 * NF / kWaves;  // loads per wave and step of two blocks
+    static constexpr int kStepBytes = PARTS * 2 * NF * 1024, kStagedBytes = 2 * kStepBytes;
+    static_assert(PARTS * NF % kWaves == 0 && (G == 4 || G == 8), "");
+};
+template <class DT, int HD, int G>
+__device__ __forceinline__ void attention_unit_staged(const DevModel& M, const DevLayer& Ly, const void* q_hi, const void* q_lo,
+                                                      size_t slot_frags, int kvh, int c, int L, int k, int row0, float* part_out,
+                                                      float* smem) {
+    using C = AttStaged<DT, HD, G>;
+    constexpr int FR = C::FR, BK = DT::BLOCK_KEYS, PARTS = C::PARTS, NF = C::NF, NPW = C::NPW;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int m = lane & 15, g = lane >> 4;
+    const int hq = wave % G, part = wave / G, bpw = M.bpw;
+    const bool mine = m >= row0 && m < row0 + k;         // tile row m belongs to this sequence
+    const int T = L + k;
+    const int head = kvh * G + hq;
+    const int first = c * PARTS * bpw;                   // first block of the unit
+    const int b0 = first + part * bpw;                   // first block of this wave's run
+    uint4 qh[FR], ql[FR];
+    {
+        const int mq = mine ? m : row0;                  // other rows mirror row0; never written out
+        const size_t q0 = (size_t)mq * M.qdim + head * HD + g * (HD / 4);
 #pragma unroll
-    for (int j = 0; j < HT; ++j)
-        *reinterpret_cast<v4f*>(partO + ((size_t)(slot * kRows + m) * HDP + j * 16 + g * 4)) = o[j];
-    if (g == 0) {
-        partML[(slot * kRows + m) * 2 + 0] = mrun;
-        partML[(slot * kRows + m) * 2 + 1] = lrun;
-    }
-    __syncthreads();
-    // merge the runs of each head in run order; item = (head, row, 4 consecutive head_dim entries)
-    for (int it = tid; it < G * kRows * (HD / 4); it += kThreads) {
-        const int c4 = it % (HD / 4), mm = (it / (HD / 4)) % kRows, hh = it / (kRows * (HD / 4));
-        if (mm < row0 || mm >= row0 + k) continue;
-        float Mx = -INFINITY;
-        for (int pp = 0; pp < parts; ++pp) Mx = fmaxf(Mx, partML[((hh * parts + pp) * kRows + mm) * 2]);
-        float den = 0.f;
-        v4f num = v4f{0.f, 0.f, 0.f, 0.f};
-        for (int pp = 0; pp < parts; ++pp) {
-            const int sl = hh * parts + pp;
-            const float mw = partML[(sl * kRows + mm) * 2];
-            const float wt = mw == -INFINITY ? 0.f : __expf(mw - Mx);
-            den = fmaf(wt, partML[(sl * kRows + mm) * 2 + 1], den);
-            const v4f x = *reinterpret_cast<const v4f*>(partO + ((size_t)(sl * kRows + mm) * HDP + c4 * 4));
-#pragma unroll
-            for (int e = 0; e < 4; ++e) num[e] = fmaf(wt, x[e], num[e]);
+        for (int i = 0; i < FR; ++i) {
+            qh[i] = load_frag<DT>(q_hi, q0 + i * DT::EPL);
+            ql[i] = uint4{0, 0, 0, 0};
+            if constexpr (DT::HAS_LO) ql[i] = load_frag<DT>(q_lo, q0 + i * DT::EPL);
         }
-        float* out = part_out + ((size_t)hh * kRows + mm) * (HD + kPartRow);
-        *reinterpret_cast<v4f*>(out + c4 * 4) = num;
-        if (c4 == 0) { out[HD] = Mx; out[HD + 1] = den; }
     }
-    __syncthreads();
+    const char* kc = reinterpret_cast<const char*>(Ly.kcache) + slot_frags * 16 + (size_t)kvh * M.ctx_pad * HD * DT::ESZ;
+    const char* vc = reinterpret_cast<const char*>(Ly.vcache) + slot_frags * 16 + (size_t)kvh * M.ctx_pad * HD * DT::ESZ;
+    const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
+    const int steps_all = (bpw + 1) / 2;
+    int steps = (T - first * BK + 2 * BK - 1) / (2 * BK);    // the first run's steps with visible keys: it has the most
+    if (steps > steps_all) steps = steps_all;
+    auto fetch = [&](int b, int place, int f) {          // fragment f of block b to place (in fragments) of the ring
+        const char* src = f < C::TPB * FR ? kc + (size_t)b * (C::TPB * FR * 1024) + f * 1024
+                                          : vc + (size_t)b * (C::HT * 1024) + (f - C::TPB * FR) * 1024;
+        load_to_lds(src, lane * 16, lds0 + place * 1024);
+    };
+    // step s: [run][block of the step][fragment]; an odd run's last step has one block per run
+    auto issue = [&](int s) {
+        const int base = (s & 1) * (PARTS * 2 * NF);
+        if (2 * s + 1 < bpw) {
+#pragma unroll
+            for (int q = 0; q < NPW; ++q) {
+                const int x = wave * NPW + q;
+                fetch(first + x / (2 * NF) * bpw + 2 * s + x / NF % 2, base + x, x % NF);
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < NPW / 2; ++q) {
+                const int x = wave * (NPW / 2) + q;
+                fetch(first + x / NF * bpw + 2 * s, base + x / NF * (2 * NF) + x % NF, x % NF);
+            }
+        }
+    };
+    issue(0);
+    // the queries are used from here on as far as the compiler can tell: its wait for them is the first step's as well
+#pragma unroll
+    for (int i = 0; i < FR; ++i)
+        asm volatile("" : "+v"(qh[i].x), "+v"(qh[i].y), "+v"(qh[i].z), "+v"(qh[i].w), "+v"(ql[i].x), "+v"(ql[i].y), "+v"(ql[i].z), "+v"(ql[i].w));
+    wait_vm<0>();
+    AttState<HD> s;
+    s.clear();
+    const int lim = mine ? L + m - row0 : -1;            // causal: the sequence's j-th row (tile row row0 + j) sees keys 0 .. L + j
+    for (int st = 0; st < steps; ++st) {
+        // The loads of this step are the only ones under way.  Behind the barrier they are there for all waves, and all
+        // waves are done with the step before, whose place the next one takes.
+        if (st) {
+            __builtin_amdgcn_s_waitcnt(0xC07F);          // no LDS read is pending
+            wait_vm<0>();
+        }
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if (st + 1 < steps) issue(st + 1);
+        const char* at = reinterpret_cast<const char*>(smem) + ((st & 1) * PARTS + part) * (2 * NF * 1024) + lane * 16;
+        auto kf = [&](int b, int t, int i) { return *reinterpret_cast<const uint4*>(at + (b * NF + t * FR + i) * 1024); };
+        auto vf = [&](int b, int j) { return *reinterpret_cast<const uint4*>(at + (b * NF + C::TPB * FR + j) * 1024); };
+        const int p0 = (b0 + 2 * st) * BK;
+        if (p0 < T) {                                    // wave-uniform
+            if (2 * st + 1 >= bpw) attention_step<DT, HD, 1, true>(s, qh, ql, kf, vf, p0, lim, g, M.att_scale, st == 0);
+            else if (p0 + 2 * BK - 1 > L) attention_step<DT, HD, 2, true>(s, qh, ql, kf, vf, p0, lim, g, M.att_scale, st == 0);
+            else attention_step<DT, HD, 2, false>(s, qh, ql, kf, vf, p0, lim, g, M.att_scale, st == 0);
+        }
+    }
+    __syncthreads();                                     // the runs' sums take the place of the blocks
+    merge_runs<HD>(s, G, PARTS, hq, part, row0, k, part_out, smem);
 }
 
 // Merge of the chunk partials of one (head, row) in chunk order by one wave: lanes first hold one chunk each (max,
@@ -198,8 +354,8 @@ __device__ __forceinline__ void merge_chunks(const float* base, size_t cstride, 
         float Mg = mc;
         Mg = wave_max_all(Mg);
         const float Mnew = fmaxf(Mrun, Mg);       // finite: chunk 0 always holds key 0
-        const float scale_old = __expf(Mrun - Mnew);
-        const float wt = mc == -INFINITY ? 0.f : __expf(mc - Mnew);
+        const float scale_old = exp2_fast(Mrun - Mnew);
+        const float wt = mc == -INFINITY ? 0.f : exp2_fast(mc - Mnew);
         float dsum = wt * dc;
         dsum = wave_sum_all(dsum);
         den = fmaf(den, scale_old, dsum);

@@ -71,7 +71,7 @@ constexpr int kPfMaxRows = 2048;     // rows of one pass
 constexpr int kPfMinRows = 17;       // prompts up to 16 tokens go through the verify pass's kernels
 constexpr int kPfBlockRows = 128;    // rows that share a stretch of the activation buffers
 constexpr int kPfTileGroup = 16;     // column tiles of the widest workgroup
-constexpr int kPfPartBytes = 96 << 20;   // attention partials in flight (they stay in the memory-side cache between the two kernels)
+constexpr int kPfPartBytes = 256 << 20;  // attention partials in flight between the two kernels
 enum { kPfQKV = 0, kPfOproj = 1, kPfGateUp = 2, kPfDown = 3, kPfLMHead = 4, kPfStages = 5 };
 
 struct PfTiles {

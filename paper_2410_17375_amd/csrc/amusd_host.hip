@@ -458,7 +458,7 @@ int amusd_model_create(const amusd_config* cfg, void* hip_stream, amusd_model** 
     D.ctx_pad = (c.max_ctx + D.chunk - 1) / D.chunk * D.chunk;
     D.max_chunks = D.ctx_pad / D.chunk;
     D.eps = c.rms_eps;
-    D.att_scale = 1.0f / std::sqrt((float)c.head_dim);
+    D.att_scale = (float)(1.4426950408889634 / std::sqrt((double)c.head_dim));   // scores in units of log2
     {   // Down projection: pairs of workgroups share K ranges when the contraction is long enough to pay for the
         // hand-over: a tile per pair (tiles for at most half the compute units: every compute unit gets work) or
         // two tiles per pair (a tile per compute unit: half the activation bytes per weight byte).  The same

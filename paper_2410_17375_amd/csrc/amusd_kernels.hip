@@ -847,8 +847,10 @@ __device__ __forceinline__ void stage_attention(const DevModel& M, const DevLaye
         }
         const int ucanon = unit0 + kvh * nchunks + c;      // where the merge stage looks for this unit's partials
         const size_t slot_frags = (size_t)cslot * M.Hkv * M.ctx_pad * HD / DT::EPL;   // 16-byte fragments per cache
-        attention_unit<DT, HD>(M, Ly, M.Q_hi, M.Q_lo, slot_frags, kvh, c, L, k, row0,
-                               M.att_part + (size_t)ucanon * G * kRows * (HD + kPartRow), smem);
+        float* out = M.att_part + (size_t)ucanon * G * kRows * (HD + kPartRow);
+        if (G == 4) attention_unit_staged<DT, HD, 4>(M, Ly, M.Q_hi, M.Q_lo, slot_frags, kvh, c, L, k, row0, out, smem);
+        else if (G == 8) attention_unit_staged<DT, HD, 8>(M, Ly, M.Q_hi, M.Q_lo, slot_frags, kvh, c, L, k, row0, out, smem);
+        else attention_unit<DT, HD>(M, Ly, M.Q_hi, M.Q_lo, slot_frags, kvh, c, L, k, row0, out, smem);
     }
     prefetch_retire();
 }
@@ -1094,27 +1096,29 @@ hipError_t launch_stream_chain(const uint4* buf, size_t buf_words, size_t words_
 
 // ---------------------------------------------------------------- pass launch
 constexpr size_t kSmemBytes = (size_t)kSmemFloats * sizeof(float);
+template <class DT, int HD>
+constexpr size_t kAttSmemBytes = kSmemBytes > (size_t)AttStaged<DT, HD, 4>::kStagedBytes ? kSmemBytes : (size_t)AttStaged<DT, HD, 4>::kStagedBytes;
 
 template <class DT, int HD>
 static hipError_t configure_one() {
     hipError_t e;
-#define AMUSD_SET(kern)                                                                                          \
+#define AMUSD_SET(kern, bytes)                                                                                    \
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&kern<DT, HD>), hipFuncAttributeMaxDynamicSharedMemorySize, \
-                            (int)kSmemBytes);                                                                     \
+                            (int)(bytes));                                                                        \
     if (e != hipSuccess) return e;
-    AMUSD_SET(k_qkv)
-    AMUSD_SET(k_attention)
-#define AMUSD_SET_ONE(kern)                                                                                        \
+    AMUSD_SET(k_qkv, kSmemBytes)
+    AMUSD_SET(k_attention, (kAttSmemBytes<DT, HD>))
+#define AMUSD_SET_ONE(kern, bytes)                                                                                 \
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&kern<DT, HD, true>),                                     \
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSmemBytes);                           \
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)(bytes));                              \
     if (e != hipSuccess) return e;
-    AMUSD_SET_ONE(k_qkv)
-    AMUSD_SET_ONE(k_attention)
+    AMUSD_SET_ONE(k_qkv, kSmemBytes)
+    AMUSD_SET_ONE(k_attention, (kAttSmemBytes<DT, HD>))
 #undef AMUSD_SET_ONE
-    AMUSD_SET(k_oproj)
-    AMUSD_SET(k_gateup)
-    AMUSD_SET(k_down)
-    AMUSD_SET(k_lmhead)
+    AMUSD_SET(k_oproj, kSmemBytes)
+    AMUSD_SET(k_gateup, kSmemBytes)
+    AMUSD_SET(k_down, kSmemBytes)
+    AMUSD_SET(k_lmhead, kSmemBytes)
 #undef AMUSD_SET
     return hipSuccess;
 }
@@ -1170,7 +1174,7 @@ static hipError_t launch_pass_t(const DevModel& M, const DevLayer* Ls, const Pas
     for (int l = 0; l < M.n_layers; ++l) {
         const float* gain_next = l + 1 < M.n_layers ? Ls[l + 1].g_attn : M.g_final;
         AMUSD_LAUNCH_SEQ(1, k_qkv, qkv_wgs, blk, kSmemBytes, l)
-        AMUSD_LAUNCH_SEQ(2, k_attention, att_wgs, blk, kSmemBytes, l)
+        AMUSD_LAUNCH_SEQ(2, k_attention, att_wgs, blk, (kAttSmemBytes<DT, HD>), l)
         AMUSD_LAUNCH_SEQ(3, k_attn_merge, merge_wgs, dim3(64), 0, l)
         AMUSD_LAUNCH(4, k_oproj, d_wgs, kSmemBytes, l, nogain)
         AMUSD_LAUNCH(5, k_gateup, gu_wgs, kSmemBytes, l, nogain)

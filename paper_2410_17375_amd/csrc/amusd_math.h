@@ -40,6 +40,17 @@ struct BF16 {
         return (uint32_t)__half_as_ushort(__float2half_rn(c));
     }
     static __device__ __forceinline__ float att_float(uint32_t b) { return __half2float(__ushort_as_half((unsigned short)b)); }
+    // hi and lo halves of two probabilities (in [0, 1]: nothing to clamp), packed.  The subtraction of a half from its
+    // float is one mixed-precision instruction (an exact fused multiply-add by one; the compiler converts and subtracts).
+    static __device__ __forceinline__ void att_split2(float a, float b, uint32_t& hi, uint32_t& lo) {
+        typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+        typedef float f2 __attribute__((ext_vector_type(2)));
+        hi = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{a, b}, h2));
+        f2 r;
+        asm("v_fma_mix_f32 %0, -%1, 1.0, %2 op_sel_hi:[1,0,0]" : "=v"(r.x) : "v"(hi), "v"(a));
+        asm("v_fma_mix_f32 %0, -%1, 1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r.y) : "v"(hi), "v"(b));
+        lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, h2));
+    }
 };
 struct FP32 {
     static constexpr int EPL = 4;
@@ -186,6 +197,16 @@ __device__ __forceinline__ float wave_sum_all(float v) {
 __device__ __forceinline__ float lane_value(float v, int j) {
     return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), j));
 }
+
+// ---------------------------------------------------------------- loads that deliver into LDS
+// 16 bytes per lane from base + offset to LDS bytes dst + 16 lane.  In assembly, because the compiler takes the builtin
+// for an access to all of LDS and then waits for every LDS read at once (lgkmcnt(0)) throughout the loop; it has no result
+// registers, and every wait for it is written out (wait_vm).
+__device__ __forceinline__ void load_to_lds(const char* base, unsigned offset, unsigned dst) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(offset), "s"(base), "s"(dst) : "memory");
+}
+template <int N>
+__device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
 // ---------------------------------------------------------------- K walk of a contraction
 // A wave's share of the K blocks of a GEMM stage, and where in it the wave starts its walk: blocks

@@ -96,9 +96,6 @@ struct KSequence {
     }
 };
 
-template <int N>
-__device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
-
 // A workgroup of WN x WM waves computes WN*A column tiles x WM*B row tiles, a wave A x B of them.  Weight and activation
 // fragments of SLOTS K blocks go through a ring in LDS, filled by loads that deliver straight into it (SLOTS - 1 blocks
 // ahead; the loop has no other vector-memory instruction, so its waits can count them), and each fragment is read from
@@ -106,8 +103,9 @@ __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" :
 //   4 x 2 waves of 4 x 4 tiles (256 columns x 128 rows, 32 KiB per K block): per K block 1024 clocks of matrix
 //       instructions on each SIMD, 96 KiB of LDS reads (768 clocks) and 32 KiB of loads (32 bytes per clock of the 64 that an
 //       L2 gives one of its compute units).  The three accumulators per output fill 192 of a wave's 256 registers.  8B shape,
-//       2048 rows: gate/up 908 us = 1.06 PFLOP/s of matrix instructions, hi and lo halves counted (a large library product
-//       on the same card: 1.29).
+//       2048 rows: gate/up 845 us = 1.14 PFLOP/s of matrix instructions, hi and lo halves counted (a large library product
+//       on the same card: 1.29).  A fifth ring slot changes nothing; workgroups ordered column by column instead of in
+//       patches 887 us, with the loads through the compiler's builtin 908.
 //   smaller ones where that shape leaves compute units without a tile; they are bound by LDS reads.
 template <int WN_, int WM_, int A_, int B_, int SLOTS_>
 struct PfShape {
@@ -179,14 +177,14 @@ struct PfGemm {
                                              int kblocks, int wgs, int ways, float* half_total, char* smem) {
         const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         const int wn = wave % Sh::WN, wm = wave / Sh::WN;
-        const int t0 = tiles[0];                        // all of the workgroup's tiles walk K alike
+        const int t0 = __builtin_amdgcn_readfirstlane(tiles[0]);   // all of the workgroup's tiles walk K alike
         const char* src[NPW];
         int step[NPW];
 #pragma unroll
         for (int q = 0; q < NPW; ++q) {
             const int f = wave * NPW + q;
             if (f < WN * A) {
-                const int t = tiles[f];
+                const int t = __builtin_amdgcn_readfirstlane(tiles[f]);
                 src[q] = reinterpret_cast<const char*>(W + (size_t)(t < 0 ? t0 : t) * kblocks * 64);
                 step[q] = 1024;
             } else {
@@ -197,13 +195,13 @@ struct PfGemm {
         }
         KSequence<Walk> ahead(kblocks, t0 % wgs, ways);
         int islot = 0;
+        const unsigned lane16 = lane * 16;
+        const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
         auto issue = [&]() {
             const int kb = ahead.take();
-            char* dst = smem + islot * kSlotBytes + wave * (NPW * 1024);
+            const unsigned dst = lds0 + islot * kSlotBytes + wave * (NPW * 1024);
 #pragma unroll
-            for (int q = 0; q < NPW; ++q)
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[q] + (size_t)kb * step[q] + lane * 16),
-                                                 (__attribute__((address_space(3))) void*)(dst + q * 1024), 16, 0, 0);
+            for (int q = 0; q < NPW; ++q) load_to_lds(src[q] + (size_t)((unsigned)kb * (unsigned)step[q]), lane16, dst + q * 1024);
             islot = islot + 1 == SLOTS ? 0 : islot + 1;
         };
 #pragma unroll
@@ -217,6 +215,8 @@ struct PfGemm {
                 for (int f = 0; f < AF; ++f) acc[i][j][f] = v4f{0.f, 0.f, 0.f, 0.f};
             }
         wait_vm<(SLOTS - 2) * NPW>();
+        // no scalar load may be pending at the loop's entry: the compiler would then wait for all LDS reads at once in it
+        __builtin_amdgcn_s_waitcnt(0xC07F);             // lgkmcnt(0)
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         wf[0] = lds_frag(smem, wn * A, lane);
@@ -284,15 +284,28 @@ __device__ __forceinline__ int xcd_contiguous(int wg, int total) {
     return x * per + (x < rem ? x : rem) + s;
 }
 
+// idx-th (column group, row group) in patches of kPatchCols x kPatchRows, so that the workgroups an XCD runs at a time
+// (32 of them) read few different weight tiles and rows per K block.
+constexpr int kPatchCols = 4, kPatchRows = 8;
+__device__ __forceinline__ void patch_order(int idx, int cols, int rows, int& cg, int& rg) {
+    const int cb = idx / (kPatchCols * rows), x = idx - cb * kPatchCols * rows;
+    const int nc = cols - cb * kPatchCols < kPatchCols ? cols - cb * kPatchCols : kPatchCols;
+    const int rb = x / (kPatchRows * nc), y = x - rb * kPatchRows * nc;
+    const int nr = rows - rb * kPatchRows < kPatchRows ? rows - rb * kPatchRows : kPatchRows;
+    cg = cb * kPatchCols + y / nr;
+    rg = rb * kPatchRows + y % nr;
+}
+
 template <class DT, int STAGE, class Sh>
 __global__ void __launch_bounds__(Sh::kThreads, Sh::kMinWaves) k_pf_gemm(DevModel M, DevLayer Ly, PrefillBufs T, PrefillArgs P, const float* gain_next) {
     extern __shared__ char pf_smem[];
     using G = PfGemm<DT, STAGE, Sh>;
     constexpr int A = Sh::A, B = Sh::B;
     const int row_groups = (P.n + Sh::kRowTiles * 16 - 1) / (Sh::kRowTiles * 16);
-    const int idx = xcd_contiguous(blockIdx.x, gridDim.x);
-    const int cg = idx / row_groups, rg = idx % row_groups;
     const PfTiles& L = T.tiles[STAGE];
+    const int idx = xcd_contiguous(blockIdx.x, gridDim.x);
+    int cg, rg;
+    patch_order(idx, L.n / Sh::kTiles, row_groups, cg, rg);
     const int* tiles = L.order + cg * Sh::kTiles;
     if (tiles[0] < 0) {      // nothing but filling (it is at the end of a start's tiles): no K walk, no weights to point at
         if constexpr (STAGE == kPfLMHead)
@@ -500,10 +513,10 @@ __global__ void __launch_bounds__(256) k_pf_rstd(DevModel M, PrefillBufs T, Pref
     if (s == 0 && row < P.n) T.rstd[row] = 1.0f / sqrtf(acc / (float)M.d + M.eps);
 }
 
-// Attention units of row tiles rt0 .. rt0 + nrt - 1 (16 rows each, at positions L0 + 16 rt ..): workgroup -> (row tile,
-// chunk, kv head).  With 8 kv heads (or a multiple) a kv head's units run on one XCD, and its cache stays in that L2.
+// Attention of row tiles rt0 .. rt0 + nrt - 1 (16 rows each, at positions L0 + 16 rt ..) against all keys before them.
+// General form: one unit of the verify pass per workgroup -> (row tile, chunk, kv head).
 template <class DT, int HD>
-__global__ void __launch_bounds__(kThreads) k_pf_attention(DevModel M, DevLayer Ly, PrefillBufs T, PrefillArgs P, int rt0, int nch) {
+__global__ void __launch_bounds__(kThreads) k_pf_attention_unit(DevModel M, DevLayer Ly, PrefillBufs T, PrefillArgs P, int rt0, int nch) {
     extern __shared__ float att_smem[];
     const int kvh = blockIdx.x % M.Hkv, rest = blockIdx.x / M.Hkv;
     const int c = rest % nch, t = rest / nch, rt = rt0 + t;
@@ -516,6 +529,165 @@ __global__ void __launch_bounds__(kThreads) k_pf_attention(DevModel M, DevLayer 
                            kvh, c, L, k, 0, T.att_part + (((size_t)t * M.Hkv + kvh) * nch + c) * M.G * kRows * (HD + kPartRow), att_smem);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // a wave must not end while its look-ahead fetch is in flight
 }
+
+// Form for groups of 4 or 8 query heads (a chunk is two runs or one).  In the unit above every wave fetches the cache
+// blocks of its run for itself and a workgroup ends with its chunk.  Here the G waves of a workgroup (the heads of one kv
+// head) walk the blocks of `span` chunks together for one row tile, two blocks a step; a block is staged once, by loads
+// that deliver straight into an LDS ring, and read from there by all of them.  A wave does the runs of a chunk one after
+// the other and merges the two in registers, with the unit's operations in the unit's order.  8B shape, all launches of 2
+// layers, 12288 + 3 x 4000 tokens: 36.6 ms -> 18.7; 4 layers, 3 x 2048 tokens: 4.3 -> 1.7.  Matrix cores busy for a third
+// of the time, vector instructions for as much: the registers allow two waves per SIMD, and each is a chain of products,
+// softmax, products.  Measured slower: two row tiles per wave (22 % more time: one wave per SIMD less to fill the gaps),
+// eight waves on two row tiles (26 %), chunks before row tiles in the grid (9 %: the XCD's workgroups then read
+// different keys), longer stretches per workgroup at 2K context (uneven ends).
+template <class DT, int HD, int G>
+struct PfAtt {
+    static constexpr int FR = HD / 4 / DT::EPL, HT = HD / 16, TPB = DT::TPB;
+    static constexpr int NF = TPB * FR + HT;             // fragments of a key block: keys, then values
+    static constexpr int NPW = NF / G, SLOTS = 5;
+    static constexpr int kSlotBytes = NF * 1024, kLdsBytes = SLOTS * kSlotBytes;
+    static_assert(NF % G == 0 && (G == 4 || G == 8), "");
+};
+template <class DT, int HD, int G>
+__global__ void __launch_bounds__(64 * G, 2) k_pf_attention(DevModel M, DevLayer Ly, PrefillBufs T, PrefillArgs P, int rt0, int nrt,
+                                                             int nch, int span) {
+    using C = PfAtt<DT, HD, G>;
+    constexpr int FR = C::FR, HT = C::HT, BK = DT::BLOCK_KEYS, NPW = C::NPW, SLOTS = C::SLOTS;
+    constexpr int PARTS = kWaves / G;
+    extern __shared__ float att_smem[];
+    char* smem = reinterpret_cast<char*>(att_smem);
+    const int lane = threadIdx.x & 63, hq = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int m = lane & 15, g = lane >> 4;
+    // row tiles fastest: the workgroups that run together on an XCD (its kv head's, with 8 of them) walk the same keys
+    const int kvh = blockIdx.x % M.Hkv, rest = blockIdx.x / M.Hkv;
+    const int t = rest % nrt, sp = rest / nrt;            // row tile, from rt0; stretch of chunks
+    const int row0 = 16 * (rt0 + t);
+    const int L = P.L0 + row0, k = P.n - row0 < 16 ? P.n - row0 : 16;
+    const int key0 = sp * span * M.chunk;
+    if (key0 >= L + k) return;
+    const int key1 = key0 + span * M.chunk < L + k ? key0 + span * M.chunk : L + k;
+    const int b0 = key0 / BK, nb = (key1 - key0 + BK - 1) / BK;   // blocks with visible keys
+    const int lim = m < k ? L + m : -1;
+
+    const size_t slot_bytes = (size_t)P.slot * M.Hkv * M.ctx_pad * HD * DT::ESZ, head_bytes = (size_t)M.ctx_pad * HD * DT::ESZ;
+    const char* kc = reinterpret_cast<const char*>(Ly.kcache) + slot_bytes + kvh * head_bytes;
+    const char* vc = reinterpret_cast<const char*>(Ly.vcache) + slot_bytes + kvh * head_bytes;
+    const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
+    const int last_in_run = (nb - 1) % M.bpw;
+    const int total = nb + (last_in_run % 2 == 0 && last_in_run + 1 < M.bpw);   // blocks to fetch: steps are whole
+    int next = 0, nslot = 0;
+    auto issue = [&]() {                                  // block b0 + next
+        const int b = b0 + next;
+        const unsigned dst = lds0 + nslot * C::kSlotBytes;
+#pragma unroll
+        for (int q = 0; q < NPW; ++q) {
+            const int f = hq * NPW + q;
+            const char* src = f < C::TPB * FR ? kc + (size_t)b * (C::TPB * FR * 1024) + f * 1024
+                                              : vc + (size_t)b * (HT * 1024) + (f - C::TPB * FR) * 1024;
+            load_to_lds(src, lane * 16, dst + f * 1024);
+        }
+        ++next;
+        nslot = nslot + 1 == SLOTS ? 0 : nslot + 1;
+    };
+    uint4 qh[FR], ql[FR];
+    const size_t q0 = (size_t)(row0 + (m < k ? m : 0)) * M.qdim + (kvh * G + hq) * HD + g * (HD / 4);
+#pragma unroll
+    for (int i = 0; i < FR; ++i) {
+        qh[i] = load_frag<DT>(T.Q_hi, q0 + i * DT::EPL);
+        ql[i] = uint4{0, 0, 0, 0};
+        if constexpr (DT::HAS_LO) ql[i] = load_frag<DT>(T.Q_lo, q0 + i * DT::EPL);
+    }
+    // the loop's waits count its own loads: everything else arrives before it
+    wait_vm<0>();
+#pragma unroll
+    for (int i = 0; i < FR; ++i)
+        asm volatile("" : "+v"(qh[i].x), "+v"(qh[i].y), "+v"(qh[i].z), "+v"(qh[i].w), "+v"(ql[i].x), "+v"(ql[i].y), "+v"(ql[i].z), "+v"(ql[i].w));
+    for (int s = 0; s < SLOTS && s < total; ++s) issue();
+
+    AttState<HD> s, s0;                                   // the run at hand; the chunk's first run once it is done
+    s.clear();
+    s0.clear();
+    int run = 0, part = 0, c = sp * span, cslot = 0;     // run: blocks of it that are done
+    // A chunk's result leaves in kStores stores.  They are younger than the loads that are under way, and the waits for
+    // those must not include them (a store takes as long as a load).
+    constexpr int kStores = HT + 1;
+    int older = 0;                                        // blocks under way whose loads are older than the last stores
+    auto wait_blocks = [&](int newer, bool slack) {       // at most `newer` blocks (and the stores) are still under way
+        if (slack) {
+            if (newer >= 4) wait_vm<4 * NPW + kStores>();
+            else if (newer == 3) wait_vm<3 * NPW + kStores>();
+            else if (newer == 2) wait_vm<2 * NPW + kStores>();
+            else if (newer == 1) wait_vm<NPW + kStores>();
+            else wait_vm<kStores>();
+        } else {
+            if (newer >= 4) wait_vm<4 * NPW>();
+            else if (newer == 3) wait_vm<3 * NPW>();
+            else if (newer == 2) wait_vm<2 * NPW>();
+            else if (newer == 1) wait_vm<NPW>();
+            else wait_vm<0>();
+        }
+    };
+    int freed = 0;                                        // ring slots whose blocks the step before used
+    for (int ib = 0; ib < nb;) {
+        const int two = run + 1 < M.bpw ? 2 : 1;          // blocks of this step
+        __builtin_amdgcn_s_waitcnt(0xC07F);               // no LDS read of the step before is pending
+        wait_blocks(next - ib - two, older >= two);
+        older -= two;
+        __builtin_amdgcn_s_barrier();                     // .. of all waves; and all are done with the step before
+        asm volatile("" ::: "memory");
+        for (int x = 0; x < freed && next < total; ++x) issue();
+        freed = two;
+        const char* slot0 = smem + cslot * C::kSlotBytes + lane * 16;
+        cslot = cslot + 1 == SLOTS ? 0 : cslot + 1;
+        const char* slot1 = smem + cslot * C::kSlotBytes + lane * 16;
+        auto kf = [&](int bb, int tt, int i) { return *reinterpret_cast<const uint4*>((bb ? slot1 : slot0) + (tt * FR + i) * 1024); };
+        auto vf = [&](int bb, int j) { return *reinterpret_cast<const uint4*>((bb ? slot1 : slot0) + (C::TPB * FR + j) * 1024); };
+        const int p0 = (b0 + ib) * BK;
+        if (two == 2) {
+            cslot = cslot + 1 == SLOTS ? 0 : cslot + 1;
+            if (p0 + 2 * BK - 1 > L) attention_step<DT, HD, 2, true>(s, qh, ql, kf, vf, p0, lim, g, M.att_scale, run == 0);
+            else attention_step<DT, HD, 2, false>(s, qh, ql, kf, vf, p0, lim, g, M.att_scale, run == 0);
+        } else {
+            attention_step<DT, HD, 1, true>(s, qh, ql, kf, vf, p0, lim, g, M.att_scale, run == 0);
+        }
+        ib += two;
+        run += two;
+        if (run == M.bpw || ib >= nb) {
+            run = 0;
+            if (PARTS == 2 && part == 0 && ib < nb) {     // the chunk's second run follows
+                s0 = s;
+                s.clear();
+                part = 1;
+                continue;
+            }
+            // a chunk that ends with its first run: the second, without keys, counts for nothing
+            float Mx = s.m, den = s.l;
+            if (PARTS == 2 && part == 1) {
+                Mx = fmaxf(s0.m, s.m);
+                const float w0 = s0.m == -INFINITY ? 0.f : exp2_fast(s0.m - Mx);
+                const float w1 = s.m == -INFINITY ? 0.f : exp2_fast(s.m - Mx);
+                den = fmaf(w1, s.l, fmaf(w0, s0.l, 0.f));
+#pragma unroll
+                for (int j = 0; j < HT; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) s.o[j][e] = fmaf(w1, s.o[j][e], fmaf(w0, s0.o[j][e], 0.f));
+            }
+            // rows past the tile's last one are written too (their places are there and nobody reads them), so that every
+            // wave issues all its stores
+            float* out = T.att_part + ((((size_t)t * M.Hkv + kvh) * nch + c) * G + hq) * (kRows * (HD + kPartRow)) + m * (HD + kPartRow);
+#pragma unroll
+            for (int j = 0; j < HT; ++j) *reinterpret_cast<v4f*>(out + j * 16 + g * 4) = s.o[j];
+            if (g == 0) *reinterpret_cast<float2*>(out + HD) = float2{Mx, den};
+            older = next - ib;
+            s.clear();
+            part = 0;
+            ++c;
+        }
+    }
+    wait_vm<0>();
+}
+
+constexpr int kPfSpanKeys = 256;     // keys a workgroup walks at least (whole chunks)
 
 // One wave per (row, query head).
 template <class DT, int HD>
@@ -612,12 +784,34 @@ static hipError_t launch_pf_gemm(const DevModel& M, const DevLayer& Ly, const Pr
     return launch_pf_gemm_v<DT, STAGE, PfShape<2, 2, 2, 2, 5>>(M, Ly, T, P, gain, s, parts);
 }
 
+template <class DT, int HD, int G>
+static hipError_t launch_pf_attention_g(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PrefillArgs& P, int rt0, int nrt,
+                                        int nch, hipStream_t s) {
+    constexpr int lds = PfAtt<DT, HD, G>::kLdsBytes;
+    static const hipError_t set = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pf_attention<DT, HD, G>),
+                                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (set != hipSuccess) return set;
+    const int span = kPfSpanKeys > M.chunk ? kPfSpanKeys / M.chunk : 1;
+    hipLaunchKernelGGL((k_pf_attention<DT, HD, G>), dim3(nrt * ((nch + span - 1) / span) * M.Hkv), dim3(64 * G), lds, s, M, Ly, T, P, rt0,
+                       nrt, nch, span);
+    return hipSuccess;
+}
+
+template <class DT, int HD>
+static hipError_t launch_pf_attention(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PrefillArgs& P, int rt0, int nrt,
+                                      int nch, hipStream_t s) {
+    if (M.G == 4) return launch_pf_attention_g<DT, HD, 4>(M, Ly, T, P, rt0, nrt, nch, s);
+    if (M.G == 8) return launch_pf_attention_g<DT, HD, 8>(M, Ly, T, P, rt0, nrt, nch, s);
+    constexpr int lds = (kWaves * kRows * (HD + kAttPad) + kWaves * kRows * 2) * 4;
+    static const hipError_t set = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pf_attention_unit<DT, HD>),
+                                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (set != hipSuccess) return set;
+    hipLaunchKernelGGL((k_pf_attention_unit<DT, HD>), dim3(nrt * nch * M.Hkv), dim3(kThreads), lds, s, M, Ly, T, P, rt0, nch);
+    return hipSuccess;
+}
+
 template <class DT, int HD>
 static hipError_t launch_prefill_t(const DevModel& M, const DevLayer* Ls, const PrefillBufs& T, const PrefillArgs& P, hipStream_t s) {
-    constexpr int att_lds = (kWaves * kRows * (HD + kAttPad) + kWaves * kRows * 2) * 4;
-    static const hipError_t set = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pf_attention<DT, HD>),
-                                                      hipFuncAttributeMaxDynamicSharedMemorySize, att_lds);
-    if (set != hipSuccess) return set;
     const int rts = (P.n + 15) / 16;
     const int rstd_wgs = (P.n + 7) / 8;
     hipError_t e;
@@ -630,7 +824,7 @@ static hipError_t launch_prefill_t(const DevModel& M, const DevLayer* Ls, const 
             const int nrt = rts - rt < T.att_tiles ? rts - rt : T.att_tiles;
             const int last = P.n < (rt + nrt) * 16 ? P.n : (rt + nrt) * 16;     // rows below this one
             const int nch = (P.L0 + last + M.chunk - 1) / M.chunk;
-            hipLaunchKernelGGL((k_pf_attention<DT, HD>), dim3(nrt * nch * M.Hkv), dim3(kThreads), att_lds, s, M, Ls[l], T, P, rt, nch);
+            if ((e = launch_pf_attention<DT, HD>(M, Ls[l], T, P, rt, nrt, nch, s)) != hipSuccess) return e;
             const int rows = last - rt * 16;
             hipLaunchKernelGGL((k_pf_merge<DT, HD>), dim3((rows * M.Hq + 3) / 4), dim3(256), 0, s, M, T, P, rt, rows, nch);
         }
