@@ -72,6 +72,8 @@ constexpr int kPfMinRows = 17;       // prompts up to 16 tokens go through the v
 constexpr int kPfBlockRows = 128;    // rows that share a stretch of the activation buffers
 constexpr int kPfTileGroup = 16;     // column tiles of the widest workgroup
 constexpr int kPfPartBytes = 256 << 20;  // attention partials in flight between the two kernels
+constexpr int kPfTickets = 4096;     // tiles whose K slices several workgroups share, at most
+constexpr size_t kPfShareBytes = 64u << 20;   // their sums, at most
 enum { kPfQKV = 0, kPfOproj = 1, kPfGateUp = 2, kPfDown = 3, kPfLMHead = 4, kPfStages = 5 };
 
 struct PfTiles {
@@ -94,7 +96,10 @@ struct PrefillBufs {
     float* ssq;           // [d/16][cap]
     float* rstd;          // [cap]
     float* att_part;
-    float* xch;           // [cap x d] first K range's totals of the down projection, in the order of the threads that own them
+    float* xch;           // sums of tiles that are not complete: the down projection's totals over its first K range, or one
+                          // per K range or slice where several workgroups share a tile; in the order of the threads that own them
+    size_t xch_bytes;
+    int* ticket;          // [kPfTickets] workgroups that have delivered their sums of a tile
     float* best_val;      // [workgroup column halves][cap]
     int* best_idx;
     const int* tokens;    // [cap] pinned host memory

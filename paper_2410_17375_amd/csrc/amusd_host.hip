@@ -5,6 +5,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <chrono>
 #include <cmath>
 #include <cstdio>
@@ -324,7 +325,12 @@ int alloc_prefill(amusd_model* m) {
     T.ssq = static_cast<float*>(get(d / 16 * cap * 4));
     T.rstd = static_cast<float*>(get(cap * 4));
     T.att_part = static_cast<float*>(get(T.att_tiles * tile_bytes));
-    T.xch = static_cast<float*>(get(D.split_down ? cap * T.tiles[kPfDown].n * 16 * 4 : 16));
+    // the down projection's first totals; beyond that room for shared tiles, as far as 16 sums per element of a small pass go
+    T.xch_bytes = D.split_down ? cap * T.tiles[kPfDown].n * 16 * 4 : 0;
+    const size_t widest = (size_t)std::max(T.tiles[kPfQKV].n, T.tiles[kPfDown].n) * 16;
+    T.xch_bytes = std::max(T.xch_bytes, std::min(kPfShareBytes, 16 * cap * widest * 4));
+    T.xch = static_cast<float*>(get(T.xch_bytes));
+    T.ticket = static_cast<int*>(get(kPfTickets * 4));
     T.best_val = static_cast<float*>(get(cap * T.tiles[kPfLMHead].n / 2 * 4));
     T.best_idx = static_cast<int*>(get(cap * T.tiles[kPfLMHead].n / 2 * 4));
     if (rc == AMUSD_OK && hipHostMalloc(reinterpret_cast<void**>(&m->pf_host), 2 * cap * 4, hipHostMallocDefault) != hipSuccess)

@@ -65,31 +65,26 @@ template <> struct PfWalk<kPfGateUp> { using T = KWalkWide; };
 template <> struct PfWalk<kPfDown> { using T = KWalkDown; };
 template <> struct PfWalk<kPfLMHead> { using T = KWalkWide; };
 
-// The K blocks of one contraction in order: slices of the eight waves of the verify pass one after the other, for each
-// of the K ranges (`ways`) that pairs of its workgroups share.
+// Slices first .. last - 1 of a contraction, block by block: slice s is that of wave s mod 8 of the verify pass, in K range
+// s / 8 of those that pairs of its workgroups share (kh blocks each).
 template <class Walk>
 struct KSequence {
-    int kh, wg, ways;          // blocks per K range
-    int part = 0, w = -1, i = 0, kb = 0;
+    int kh, wg, s, last, i = 0, kb = 0;
     KSlice ks{0, 0, 0, 1};
-    bool at_end = false;
-    __device__ __forceinline__ KSequence(int kblocks, int wg_, int ways_) : kh(kblocks / ways_), wg(wg_), ways(ways_) { next_slice(); }
+    __device__ __forceinline__ KSequence(int kh_, int wg_, int first, int last_) : kh(kh_), wg(wg_), s(first - 1), last(last_) { next_slice(); }
     __device__ __forceinline__ void next_slice() {
         i = 0;
 #pragma unroll 1
         do {
-            if (++w == kWaves) {
-                w = 0;
-                if (++part == ways) { at_end = true; return; }
-            }
-            ks = k_slice_of<Walk>(kh, wg, w);
+            if (++s == last) return;
+            ks = k_slice_of<Walk>(kh, wg, s % kWaves);
         } while (ks.S <= 0);
     }
     // the next block; past the end the last one again
     __device__ __forceinline__ int take() {
-        if (!at_end) {
+        if (s < last) {
             const int x = i + ks.rot;
-            kb = part * kh + ks.kb0 + (x >= ks.S ? x - ks.S : x) * ks.stride;
+            kb = s / kWaves * kh + ks.kb0 + (x >= ks.S ? x - ks.S : x) * ks.stride;
             if (++i == ks.S) next_slice();
         }
         return kb;
@@ -118,10 +113,11 @@ struct PfShape {
 template <class DT, int STAGE, class Sh>
 struct PfGemm {
     static constexpr int WN = Sh::WN, WM = Sh::WM, A = Sh::A, B = Sh::B, SLOTS = Sh::SLOTS;
+    using Shape = Sh;
     static constexpr int AF = PfAct<DT>::AF;
     static constexpr int NF = WN * A + WM * B * AF;    // fragments per K block
     static constexpr int NPW = NF / (WN * WM);         // loads per wave and K block
-    static_assert(NF % (WN * WM) == 0 && SLOTS >= 3 && A % 2 == 0, "");
+    static_assert(NF % (WN * WM) == 0 && SLOTS >= 3, "");
     static constexpr int kSlotBytes = NF * 1024;
     static constexpr int kLdsBytes = SLOTS * kSlotBytes;
     using Walk = typename PfWalk<STAGE>::T;
@@ -171,49 +167,28 @@ struct PfGemm {
             }
             __builtin_amdgcn_sched_barrier(0);
         }
+        if (A & 1) wf[0] = wf[1];
     }
 
-    __device__ __forceinline__ void contract(const uint4* __restrict__ W, const uint4* __restrict__ act, const int* tiles, int rt0,
-                                             int kblocks, int wgs, int ways, float* half_total, char* smem) {
-        const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        const int wn = wave % Sh::WN, wm = wave / Sh::WN;
-        const int t0 = __builtin_amdgcn_readfirstlane(tiles[0]);   // all of the workgroup's tiles walk K alike
-        const char* src[NPW];
-        int step[NPW];
-#pragma unroll
-        for (int q = 0; q < NPW; ++q) {
-            const int f = wave * NPW + q;
-            if (f < WN * A) {
-                const int t = __builtin_amdgcn_readfirstlane(tiles[f]);
-                src[q] = reinterpret_cast<const char*>(W + (size_t)(t < 0 ? t0 : t) * kblocks * 64);
-                step[q] = 1024;
-            } else {
-                const int x = f - WN * A;
-                src[q] = reinterpret_cast<const char*>(act + PfAct<DT>::frag(kblocks, rt0 + x / AF, 0, x % AF));
-                step[q] = PfAct<DT>::kBlockTiles * AF * 1024;
-            }
-        }
-        KSequence<Walk> ahead(kblocks, t0 % wgs, ways);
-        int islot = 0;
-        const unsigned lane16 = lane * 16;
-        const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
-        auto issue = [&]() {
-            const int kb = ahead.take();
-            const unsigned dst = lds0 + islot * kSlotBytes + wave * (NPW * 1024);
-#pragma unroll
-            for (int q = 0; q < NPW; ++q) load_to_lds(src[q] + (size_t)((unsigned)kb * (unsigned)step[q]), lane16, dst + q * 1024);
-            islot = islot + 1 == SLOTS ? 0 : islot + 1;
-        };
-#pragma unroll
-        for (int s = 0; s < SLOTS - 1; ++s) issue();
+    // The first K range is done: its total waits in memory, and this thread reads it back at the end.
+    __device__ __forceinline__ void spill_total(float* spill) {
+        float* hp = spill + threadIdx.x * 4;
+        asm volatile("" : "+v"(hp));                    // its addresses are not to be kept in registers from the start
 #pragma unroll
         for (int i = 0; i < A; ++i)
 #pragma unroll
             for (int j = 0; j < B; ++j) {
+                fold(i, j);
+                *reinterpret_cast<v4f*>(hp + (i * B + j) * (Sh::kThreads * 4)) = tot[i][j];
                 tot[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int f = 0; f < AF; ++f) acc[i][j][f] = v4f{0.f, 0.f, 0.f, 0.f};
             }
+    }
+
+    template <class Issue>
+    __device__ __forceinline__ void run_blocks(int kh, int wg, int first, int last, int wn, int wm, int lane, float* spill, char* smem,
+                                               Issue&& issue) {
         wait_vm<(SLOTS - 2) * NPW>();
         // no scalar load may be pending at the loop's entry: the compiler would then wait for all LDS reads at once in it
         __builtin_amdgcn_s_waitcnt(0xC07F);             // lgkmcnt(0)
@@ -230,41 +205,69 @@ struct PfGemm {
             cslot = cslot + 1 == SLOTS ? 0 : cslot + 1;
             nxt = smem + cslot * kSlotBytes;
         };
-        const int kh = kblocks / ways;
 #pragma unroll 1
-        for (int part = 0; part < ways; ++part) {
-            if (part) {                                 // the first K range's total waits in memory: this thread reads it back
-                float* hp = half_total + threadIdx.x * 4;
-                asm volatile("" : "+v"(hp));            // its addresses are not to be kept in registers from the start
-#pragma unroll
-                for (int i = 0; i < A; ++i)
-#pragma unroll
-                    for (int j = 0; j < B; ++j) {
-                        fold(i, j);
-                        *reinterpret_cast<v4f*>(hp + (i * B + j) * (Sh::kThreads * 4)) = tot[i][j];
-                        tot[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                        for (int f = 0; f < AF; ++f) acc[i][j][f] = v4f{0.f, 0.f, 0.f, 0.f};
-                    }
-            }
+        for (int s = first; s < last; ++s) {
+            if (spill && s == kWaves) spill_total(spill);
+            const int S = k_slice_of<Walk>(kh, wg, s % kWaves).S;
+            if (S <= 0) continue;
 #pragma unroll 1
-            for (int w = 0; w < kWaves; ++w) {
-                const int S = k_slice_of<Walk>(kh, t0 % wgs, w).S;
-                if (S <= 0) continue;
-#pragma unroll 1
-                for (int i = 0; i < S; ++i) {
-                    const char *cur, *nxt;
-                    slots(cur, nxt);
-                    block(i == 0, cur, nxt, wn, wm, lane, issue);
-                }
+            for (int i = 0; i < S; ++i) {
+                const char *cur, *nxt;
+                slots(cur, nxt);
+                block(i == 0, cur, nxt, wn, wm, lane, issue);
             }
         }
+    }
+
+    // Slices first .. last - 1.  spill: where the total over the first K range waits while the second is summed (null:
+    // there is only one range in first .. last).
+    __device__ __forceinline__ void contract(const uint4* __restrict__ W, const uint4* __restrict__ act, const int* tiles, int rt0,
+                                             int kblocks, int kh, int wgs, int first, int last, float* spill, char* smem) {
+        const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const int wn = wave % Sh::WN, wm = wave / Sh::WN;
+        const int t0 = __builtin_amdgcn_readfirstlane(tiles[0]);   // all of the workgroup's tiles walk K alike
+        const char* src[NPW];
+#pragma unroll
+        for (int q = 0; q < NPW; ++q) {
+            const int f = wave * NPW + q;
+            if (f < WN * A) {
+                const int t = __builtin_amdgcn_readfirstlane(tiles[f]);
+                src[q] = reinterpret_cast<const char*>(W + (size_t)(t < 0 ? t0 : t) * kblocks * 64);
+            } else {
+                const int x = f - WN * A;
+                src[q] = reinterpret_cast<const char*>(act + PfAct<DT>::frag(kblocks, rt0 + x / AF, 0, x % AF));
+            }
+        }
+        KSequence<Walk> ahead(kh, t0 % wgs, first, last);
+        int islot = 0;
+        const unsigned lane16 = lane * 16;
+        const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
+        auto issue = [&]() {
+            const int kb = ahead.take();
+            const unsigned dst = lds0 + islot * kSlotBytes + wave * (NPW * 1024);
+            // byte offsets of the block in a weight tile and in the activations (below 4 GiB: K up to 8 million)
+            const unsigned ow = (unsigned)kb * 1024u + lane16, oa = (unsigned)kb * (unsigned)(PfAct<DT>::kBlockTiles * AF * 1024) + lane16;
+#pragma unroll
+            for (int q = 0; q < NPW; ++q) load_to_lds(src[q], wave * NPW + q < WN * A ? ow : oa, dst + q * 1024);
+            islot = islot + 1 == SLOTS ? 0 : islot + 1;
+        };
+#pragma unroll 1
+        for (int s = 0; s < SLOTS - 1; ++s) issue();
+#pragma unroll
+        for (int i = 0; i < A; ++i)
+#pragma unroll
+            for (int j = 0; j < B; ++j) {
+                tot[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int f = 0; f < AF; ++f) acc[i][j][f] = v4f{0.f, 0.f, 0.f, 0.f};
+            }
+        run_blocks(kh, t0 % wgs, first, last, wn, wm, lane, spill, smem, issue);
 #pragma unroll
         for (int i = 0; i < A; ++i)
 #pragma unroll
             for (int j = 0; j < B; ++j) fold(i, j);
-        if (ways > 1) {
-            const float* hp = half_total + threadIdx.x * 4;
+        if (spill) {
+            const float* hp = spill + threadIdx.x * 4;
             asm volatile("" : "+v"(hp));
 #pragma unroll
             for (int i = 0; i < A; ++i)
@@ -275,6 +278,70 @@ struct PfGemm {
         __syncthreads();
     }
 };
+
+// The sums of `ranges` K ranges, PER each, added in order: all loads of a range first, then the additions (one trip to
+// memory per range and two fragments instead of one per sum).
+template <int PER, class G>
+__device__ __forceinline__ void add_shares(G& acc, const float* xch, int ranges) {
+    using Sh = typename G::Shape;
+    constexpr int N = Sh::A * Sh::B, XB = N % 2 == 0 ? 2 : 1;
+    constexpr size_t kFloats = (size_t)Sh::kThreads * N * 4;
+#pragma unroll
+    for (int x0 = 0; x0 < N; x0 += XB) {
+        for (int r = 0; r < ranges; ++r) {
+            uint64_t raw[XB][PER][2];
+#pragma unroll
+            for (int s = 0; s < PER; ++s)
+#pragma unroll
+                for (int x = 0; x < XB; ++x)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        raw[x][s][h] = __hip_atomic_load(reinterpret_cast<const uint64_t*>(xch + (r * PER + s) * kFloats + (x0 + x) * (Sh::kThreads * 4) + threadIdx.x * 4) + h,
+                                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int x = 0; x < XB; ++x) {
+                v4f v = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int s = 0; s < PER; ++s)
+                    v += v4f{__uint_as_float((uint32_t)raw[x][s][0]), __uint_as_float((uint32_t)(raw[x][s][0] >> 32)),
+                             __uint_as_float((uint32_t)raw[x][s][1]), __uint_as_float((uint32_t)(raw[x][s][1] >> 32))};
+                v4f& t = acc.tot[(x0 + x) / Sh::B][(x0 + x) % Sh::B];
+                t = r ? t + v : v;
+            }
+        }
+    }
+}
+
+// Adds the sums that `shares` workgroups have of the same tiles: each writes its own to device memory and counts itself;
+// the one that counts last adds all of them in the order of the slices and goes on (returns true).  per_range: sums per K
+// range (8: one per slice; 1: the range's total).  Nobody waits for anybody.  Relaxed device-scope accesses, counted after
+// every wave has seen its stores acknowledged, as in the verify pass's down projection.
+template <class G>
+__device__ __forceinline__ bool combine_shares(G& acc, float* xch, int* ticket, int share, int shares, int per_range, char* smem) {
+    using Sh = typename G::Shape;
+    constexpr int kFloats = Sh::kThreads * Sh::A * Sh::B * 4;
+    auto at = [&](int sh, int x) { return reinterpret_cast<uint64_t*>(xch + (size_t)sh * kFloats + x * (Sh::kThreads * 4) + threadIdx.x * 4); };
+#pragma unroll
+    for (int x = 0; x < Sh::A * Sh::B; ++x) {
+        const v4f v = acc.tot[x / Sh::B][x % Sh::B];
+        uint64_t* p = at(share, x);
+        __hip_atomic_store(p, (uint64_t)__float_as_uint(v.x) | (uint64_t)__float_as_uint(v.y) << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(p + 1, (uint64_t)__float_as_uint(v.z) | (uint64_t)__float_as_uint(v.w) << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    int* flag = reinterpret_cast<int*>(smem);
+    if (threadIdx.x == 0) {
+        const int seen = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (seen == shares - 1) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next stage
+        *flag = seen == shares - 1;
+    }
+    __syncthreads();
+    if (!*flag) return false;
+    if (per_range == 1) add_shares<1>(acc, xch, shares);
+    else add_shares<kWaves>(acc, xch, shares / kWaves);
+    return true;
+}
 
 // Position of a workgroup in the grid of (column group, row group).  Workgroups are dealt to the eight XCDs in turn; an
 // XCD takes a contiguous stretch of the column-major list, so the ones that run at a time on it share weight tiles and
@@ -297,18 +364,21 @@ __device__ __forceinline__ void patch_order(int idx, int cols, int rows, int& cg
 }
 
 template <class DT, int STAGE, class Sh>
-__global__ void __launch_bounds__(Sh::kThreads, Sh::kMinWaves) k_pf_gemm(DevModel M, DevLayer Ly, PrefillBufs T, PrefillArgs P, const float* gain_next) {
+__global__ void __launch_bounds__(Sh::kThreads, Sh::kMinWaves) k_pf_gemm(DevModel M, DevLayer Ly, PrefillBufs T, PrefillArgs P, const float* gain_next,
+                                                                                 int shares) {
     extern __shared__ char pf_smem[];
     using G = PfGemm<DT, STAGE, Sh>;
     constexpr int A = Sh::A, B = Sh::B;
     const int row_groups = (P.n + Sh::kRowTiles * 16 - 1) / (Sh::kRowTiles * 16);
     const PfTiles& L = T.tiles[STAGE];
-    const int idx = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int tiles_wg = gridDim.x / shares;              // (column group, row group) pairs
+    const int share = blockIdx.x / tiles_wg;
+    const int idx = xcd_contiguous(blockIdx.x % tiles_wg, tiles_wg);
     int cg, rg;
     patch_order(idx, L.n / Sh::kTiles, row_groups, cg, rg);
     const int* tiles = L.order + cg * Sh::kTiles;
     if (tiles[0] < 0) {      // nothing but filling (it is at the end of a start's tiles): no K walk, no weights to point at
-        if constexpr (STAGE == kPfLMHead)
+        if (STAGE == kPfLMHead && share == 0)
             for (int x = threadIdx.x; x < Sh::WN * Sh::kRowTiles * 16; x += Sh::kThreads) {
                 const int row = rg * Sh::kRowTiles * 16 + x / Sh::WN;
                 if (row < P.n) {
@@ -330,9 +400,12 @@ __global__ void __launch_bounds__(Sh::kThreads, Sh::kMinWaves) k_pf_gemm(DevMode
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn = wave % Sh::WN, wm = wave / Sh::WN;
     const int rt0 = rg * Sh::kRowTiles;
+    const int kblocks = K / DT::KB, slices = ways * kWaves, per = slices / shares;   // shares: 1, `ways` or `slices`
+    float* xch = T.xch + (size_t)idx * shares * (Sh::kThreads * A * B * 4);
     G acc;
-    float* half = STAGE == kPfDown ? T.xch + (size_t)idx * (Sh::kThreads * A * B * 4) : nullptr;
-    acc.contract(W, reinterpret_cast<const uint4*>(act), tiles, rt0, K / DT::KB, L.wgs, ways, half, pf_smem);
+    acc.contract(W, reinterpret_cast<const uint4*>(act), tiles, rt0, kblocks, kblocks / ways, L.wgs, share * per, share * per + per,
+                 per > kWaves ? xch : nullptr, pf_smem);
+    if (shares > 1 && !combine_shares<G>(acc, xch, T.ticket + idx, share, shares, shares == ways ? 1 : kWaves, pf_smem)) return;
 
     // Lane (m = row, g) holds columns 4g .. 4g+3 of a tile.  After a swap between the half-waves it has columns r0, r0 + 1
     // and their partners r0 + 8, r0 + 9, the pairs that the epilogues work on.
@@ -469,6 +542,9 @@ __global__ void __launch_bounds__(Sh::kThreads, Sh::kMinWaves) k_pf_gemm(DevMode
 template <class DT>
 __global__ void __launch_bounds__(256) k_pf_embed(DevModel M, PrefillBufs T, PrefillArgs P, const float* gain) {
     const int ntiles = M.d / 16;
+    // counts of the stages whose tiles several workgroups share: each returns to 0 by itself; a pass still starts clean
+    if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < kPfTickets; i += 256) __hip_atomic_store(T.ticket + i, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int idx = blockIdx.x * 2 + (threadIdx.x >> 7);
     const int tile = idx % ntiles, rt = idx / ntiles;
     const int mm = (threadIdx.x >> 3) & 15, r = threadIdx.x & 7;
@@ -762,26 +838,67 @@ void prefill_tile_order(const DevModel& M, int stage, int nwg, std::vector<int>&
 
 template <class DT, int STAGE, class Sh>
 static hipError_t launch_pf_gemm_v(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PrefillArgs& P, const float* gain,
-                                   hipStream_t s, int* parts) {
+                                   hipStream_t s, int* parts, int shares) {
     const int lds = PfGemm<DT, STAGE, Sh>::kLdsBytes;
     static const hipError_t set = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pf_gemm<DT, STAGE, Sh>),
                                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (set != hipSuccess) return set;
     const int groups = T.tiles[STAGE].n / Sh::kTiles;
-    const int grid = groups * ((P.n + Sh::kRowTiles * 16 - 1) / (Sh::kRowTiles * 16));
+    const int grid = groups * ((P.n + Sh::kRowTiles * 16 - 1) / (Sh::kRowTiles * 16)) * shares;
     if (parts) *parts = groups * Sh::WN;
-    hipLaunchKernelGGL((k_pf_gemm<DT, STAGE, Sh>), dim3(grid), dim3(Sh::kThreads), lds, s, M, Ly, T, P, gain);
+    hipLaunchKernelGGL((k_pf_gemm<DT, STAGE, Sh>), dim3(grid), dim3(Sh::kThreads), lds, s, M, Ly, T, P, gain, shares);
     return hipSuccess;
+}
+
+// Workgroup shapes; the two smaller ones run two to a compute unit.
+using PfLarge = PfShape<4, 2, 4, 4, 4>;   // 256 columns x 128 rows
+using PfMid = PfShape<2, 2, 4, 2, 4>;     // 128 x 64
+using PfSmall = PfShape<2, 2, 2, 2, 6>;   // 64 x 64
+
+// Which shape a stage takes, and over how many workgroups the K slices of a tile are shared: the smallest estimate of
+// rounds x K blocks x time of a block, plus what the sharing costs.  The times were fitted to measurements of all choices
+// on the 8B and 1B shapes at 24 to 1000 rows: 0.93 us per K block of a large tile; 0.45 and 0.31 us of the smaller ones,
+// 0.545 and 0.40 when two share a compute unit; sharing 1.6 us per workgroup of a tile (its sums are written, counted and
+// read back through the memory side) and its bytes at 4 TB/s each way.  For instance at 61 rows of the 8B shape the down
+// projection takes 123 us on 64 small tiles, 71 with its two K ranges shared, 57 with all sixteen slices; the QKV
+// projection 40 and 36; at 250 rows 40 us on 384 small tiles and 99 on 48 large ones, gate/up 145 on small and 72 less on
+// large ones.
+struct PfPlan { int shape, shares; };
+static PfPlan plan_pf_gemm(const DevModel& M, const PrefillBufs& T, int n, int stage) {
+    struct Shape { int tiles, rows, per_cu; double alone, full; };
+    static const Shape shapes[3] = {{PfLarge::kTiles, PfLarge::kRowTiles * 16, 1, 0.93, 0.93},
+                                    {PfMid::kTiles, PfMid::kRowTiles * 16, 2, 0.45, 0.545},
+                                    {PfSmall::kTiles, PfSmall::kRowTiles * 16, 2, 0.31, 0.40}};
+    const int K = stage == kPfOproj ? M.qdim : stage == kPfDown ? M.F : M.d;
+    const int kblocks = K / (M.dtype ? BF16::KB : FP32::KB), ways = stage == kPfDown && M.split_down ? 2 : 1;
+    PfPlan best{0, 1};
+    double least = 0;
+    for (int s = 0; s < 3; ++s)
+        for (int shares : {1, ways, ways * kWaves}) {
+            const Shape& h = shapes[s];
+            const size_t tiles = (size_t)T.tiles[stage].n / h.tiles * ((n + h.rows - 1) / h.rows);
+            const size_t sum_bytes = tiles * h.tiles * h.rows * 16 * 4 * shares;
+            if (shares > 1 && (tiles > (size_t)kPfTickets || sum_bytes > T.xch_bytes)) continue;
+            const size_t wgs = tiles * shares, round = (size_t)T.cus * h.per_cu, rest = wgs % round;
+            const double rounds = wgs / round * h.full + (rest > (size_t)T.cus ? h.full : rest ? h.alone : 0.);
+            const double us = rounds * kblocks / shares + (shares > 1 ? 1.6 * shares + 2e-6 / 4 * sum_bytes : 0.);
+            if (least == 0 || us < least) {
+                least = us;
+                best = PfPlan{s, shares};
+            }
+        }
+    return best;
 }
 
 template <class DT, int STAGE>
 static hipError_t launch_pf_gemm(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PrefillArgs& P, const float* gain,
                                  hipStream_t s, int* parts = nullptr) {
-    const int nt = T.tiles[STAGE].n;
-    auto groups = [&](int tiles, int rows) { return nt / tiles * ((P.n + rows - 1) / rows); };
-    if (groups(16, 128) >= T.cus / 2) return launch_pf_gemm_v<DT, STAGE, PfShape<4, 2, 4, 4, 4>>(M, Ly, T, P, gain, s, parts);
-    if (groups(8, 64) >= T.cus / 2) return launch_pf_gemm_v<DT, STAGE, PfShape<2, 2, 4, 2, 4>>(M, Ly, T, P, gain, s, parts);
-    return launch_pf_gemm_v<DT, STAGE, PfShape<2, 2, 2, 2, 5>>(M, Ly, T, P, gain, s, parts);
+    const PfPlan p = plan_pf_gemm(M, T, P.n, STAGE);
+    switch (p.shape) {
+        case 0: return launch_pf_gemm_v<DT, STAGE, PfLarge>(M, Ly, T, P, gain, s, parts, p.shares);
+        case 1: return launch_pf_gemm_v<DT, STAGE, PfMid>(M, Ly, T, P, gain, s, parts, p.shares);
+        default: return launch_pf_gemm_v<DT, STAGE, PfSmall>(M, Ly, T, P, gain, s, parts, p.shares);
+    }
 }
 
 template <class DT, int HD, int G>
