@@ -363,6 +363,126 @@ __device__ __forceinline__ void patch_order(int idx, int cols, int rows, int& cg
     rg = rb * kPatchRows + y % nr;
 }
 
+// Weights, activations, contraction length and K ranges of a stage.
+template <int STAGE>
+__device__ __forceinline__ void pf_inputs(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const uint4*& W, const void*& act,
+                                          int& K, int& ways) {
+    if constexpr (STAGE == kPfQKV) { W = Ly.wqkv; act = T.A; K = M.d; }
+    else if constexpr (STAGE == kPfOproj) { W = Ly.wo; act = T.O; K = M.qdim; }
+    else if constexpr (STAGE == kPfGateUp) { W = Ly.wgu; act = T.A; K = M.d; }
+    else if constexpr (STAGE == kPfDown) { W = Ly.wd; act = T.H; K = M.F; }
+    else { W = M.wlm; act = T.A; K = M.d; }
+    ways = STAGE == kPfDown && M.split_down ? 2 : 1;
+}
+
+// What a stage does with a finished 16 x 16 fragment (column tile `tile`, row tile rt).  Lane (m = row, g) brings columns
+// 4g .. 4g+3.  After a swap between the half-waves it has columns r0, r0 + 1 and their partners r0 + 8, r0 + 9, the pairs that
+// the verify pass's epilogues work on.  LM head: the lane's best of the columns it has seen so far goes to best_v, best_i.
+template <class DT, int STAGE>
+__device__ __forceinline__ void pf_epilogue(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PrefillArgs& P,
+                                            const float* gain_next, int tile, int rt, v4f c, float& best_v, int& best_i) {
+    const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
+    const int r0 = 4 * (g & 1) + 2 * (lane >> 5);
+    const int row = rt * 16 + m;
+    const bool on = row < P.n;
+    const auto pa = __builtin_amdgcn_permlane32_swap(__float_as_uint(c.x), __float_as_uint(c.z), false, false);
+    const auto pb = __builtin_amdgcn_permlane32_swap(__float_as_uint(c.y), __float_as_uint(c.w), false, false);
+    const float u0 = __uint_as_float(pa[0]), u1 = __uint_as_float(pb[0]);      // columns r0, r0 + 1
+    const float w0 = __uint_as_float(pa[1]), w1 = __uint_as_float(pb[1]);      // columns r0 + 8, r0 + 9
+    if constexpr (STAGE == kPfOproj || STAGE == kPfDown) {
+        const int c1 = tile * 16 + r0;
+        float sq = 0.f;
+        if (on) {
+            float2* x1 = reinterpret_cast<float2*>(T.X + (size_t)row * M.d + c1);
+            float2* x2 = reinterpret_cast<float2*>(T.X + (size_t)row * M.d + c1 + 8);
+            const float2 g1 = *reinterpret_cast<const float2*>(gain_next + c1), g2 = *reinterpret_cast<const float2*>(gain_next + c1 + 8);
+            float2 a = *x1, b = *x2;
+            a.x += u0; a.y += u1; b.x += w0; b.y += w1;
+            *x1 = a;
+            *x2 = b;
+            PfAct<DT>::store2(T.A, M.d / DT::KB, row, c1, a.x * g1.x, a.y * g1.y);
+            PfAct<DT>::store2(T.A, M.d / DT::KB, row, c1 + 8, b.x * g2.x, b.y * g2.y);
+            sq = square_pair(a.x, b.x) + square_pair(a.y, b.y);
+        }
+        sq = wave_xor_add<32>(sq);
+        sq = wave_xor_add<16>(sq);
+        if (on && g == 0) T.ssq[(size_t)tile * T.cap + row] = sq;
+    } else if constexpr (STAGE == kPfGateUp) {
+        if (on) {
+            const float sc = T.rstd[row];
+            PfAct<DT>::store2(T.H, M.F / DT::KB, row, tile * 8 + r0, swiglu(u0 * sc, w0 * sc), swiglu(u1 * sc, w1 * sc));
+        }
+    } else if constexpr (STAGE == kPfQKV) {
+        if (!on) return;
+        const float sc = T.rstd[row];
+        const int hd = M.hd, tph = hd / 16, qt = M.qdim / 16, kt = M.kvdim / 16, pos = P.L0 + row;
+        const float a0 = u0 * sc, a1 = u1 * sc, b0 = w0 * sc, b1 = w1 * sc;
+        const size_t slot_base = (size_t)P.slot * M.Hkv * M.ctx_pad * hd;
+        if (tile < qt + kt) {
+            const bool isq = tile < qt;
+            const int tt = isq ? tile : tile - qt;
+            const int head = tt / tph, c1 = (tt % tph) * 8 + r0;
+            const size_t ro = (size_t)pos * (hd / 2) + c1;
+            const float2 cs = *reinterpret_cast<const float2*>(M.rope_cos + ro), sn = *reinterpret_cast<const float2*>(M.rope_sin + ro);
+            float x0, x1, y0, y1;
+            rotate_pair(a0, b0, cs.x, sn.x, x0, y0);
+            rotate_pair(a1, b1, cs.y, sn.y, x1, y1);
+            if (isq) {
+                const size_t o = (size_t)row * M.qdim + head * hd + c1;
+                if constexpr (DT::HAS_LO) {
+                    auto put = [&](size_t at, float p, float q) {
+                        const uint32_t h0 = DT::att_bits(p), h1 = DT::att_bits(q);
+                        const uint32_t l0 = DT::att_bits(p - DT::att_float(h0)), l1 = DT::att_bits(q - DT::att_float(h1));
+                        *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(T.Q_hi) + at) = h0 | (h1 << 16);
+                        *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(T.Q_lo) + at) = l0 | (l1 << 16);
+                    };
+                    put(o, x0, x1);
+                    put(o + hd / 2, y0, y1);
+                } else {
+                    *reinterpret_cast<float2*>(reinterpret_cast<float*>(T.Q_hi) + o) = float2{x0, x1};
+                    *reinterpret_cast<float2*>(reinterpret_cast<float*>(T.Q_hi) + o + hd / 2) = float2{y0, y1};
+                }
+            } else {
+                const size_t hb = slot_base + (size_t)head * M.ctx_pad * hd;
+                auto put = [&](int col, float p, float q) {      // neighbouring columns are neighbours in the cache
+                    const size_t at = hb + kcache_index<DT>(hd, pos, col);
+                    if constexpr (DT::HAS_LO)
+                        *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(Ly.kcache) + at) = DT::att_bits(p) | (DT::att_bits(q) << 16);
+                    else
+                        *reinterpret_cast<float2*>(reinterpret_cast<float*>(Ly.kcache) + at) = float2{p, q};
+                };
+                put(c1, x0, x1);
+                put(c1 + hd / 2, y0, y1);
+            }
+        } else {
+            const int tt = tile - qt - kt;
+            const int head = tt / tph, c1 = (tt % tph) * 16 + r0;
+            const size_t hb = slot_base + (size_t)head * M.ctx_pad * hd;
+            auto put = [&](int col, float p) {
+                const size_t at = hb + vcache_index<DT>(hd, pos, col);
+                if constexpr (DT::HAS_LO) reinterpret_cast<uint16_t*>(Ly.vcache)[at] = (uint16_t)DT::att_bits(p);
+                else reinterpret_cast<float*>(Ly.vcache)[at] = p;
+            };
+            put(c1, a0);
+            put(c1 + 1, a1);
+            put(c1 + 8, b0);
+            put(c1 + 9, b1);
+        }
+    } else {                                   // LM head: logits of the rows that are kept, arg-max per row
+        if (on) {
+            const float sc = T.rstd[row];
+            const int c1 = tile * 16 + r0;
+            const float z[4] = {u0 * sc, u1 * sc, w0 * sc, w1 * sc};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int col = c1 + (e & 1) + 8 * (e >> 1);
+                if (better(z[e], col, best_v, best_i)) { best_v = z[e]; best_i = col; }
+                if (row >= P.keep0) M.logits[(size_t)(row - P.keep0) * M.V + col] = z[e];
+            }
+        }
+    }
+}
+
 template <class DT, int STAGE, class Sh>
 __global__ void __launch_bounds__(Sh::kThreads, Sh::kMinWaves) k_pf_gemm(DevModel M, DevLayer Ly, PrefillBufs T, PrefillArgs P, const float* gain_next,
                                                                                  int shares) {
@@ -382,21 +502,16 @@ __global__ void __launch_bounds__(Sh::kThreads, Sh::kMinWaves) k_pf_gemm(DevMode
             for (int x = threadIdx.x; x < Sh::WN * Sh::kRowTiles * 16; x += Sh::kThreads) {
                 const int row = rg * Sh::kRowTiles * 16 + x / Sh::WN;
                 if (row < P.n) {
-                    T.best_val[(size_t)(cg * Sh::WN + x % Sh::WN) * T.cap + row] = -INFINITY;
-                    T.best_idx[(size_t)(cg * Sh::WN + x % Sh::WN) * T.cap + row] = 0x7fffffff;
+                    T.best_val[(size_t)(cg * Sh::WN + x % Sh::WN) * P.n + row] = -INFINITY;
+                    T.best_idx[(size_t)(cg * Sh::WN + x % Sh::WN) * P.n + row] = 0x7fffffff;
                 }
             }
         return;
     }
     const uint4* W;
     const void* act;
-    int K;
-    if constexpr (STAGE == kPfQKV) { W = Ly.wqkv; act = T.A; K = M.d; }
-    else if constexpr (STAGE == kPfOproj) { W = Ly.wo; act = T.O; K = M.qdim; }
-    else if constexpr (STAGE == kPfGateUp) { W = Ly.wgu; act = T.A; K = M.d; }
-    else if constexpr (STAGE == kPfDown) { W = Ly.wd; act = T.H; K = M.F; }
-    else { W = M.wlm; act = T.A; K = M.d; }
-    const int ways = STAGE == kPfDown && M.split_down ? 2 : 1;
+    int K, ways;
+    pf_inputs<STAGE>(M, Ly, T, W, act, K, ways);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn = wave % Sh::WN, wm = wave / Sh::WN;
     const int rt0 = rg * Sh::kRowTiles;
@@ -407,10 +522,6 @@ __global__ void __launch_bounds__(Sh::kThreads, Sh::kMinWaves) k_pf_gemm(DevMode
                  per > kWaves ? xch : nullptr, pf_smem);
     if (shares > 1 && !combine_shares<G>(acc, xch, T.ticket + idx, share, shares, shares == ways ? 1 : kWaves, pf_smem)) return;
 
-    // Lane (m = row, g) holds columns 4g .. 4g+3 of a tile.  After a swap between the half-waves it has columns r0, r0 + 1
-    // and their partners r0 + 8, r0 + 9, the pairs that the epilogues work on.
-    const int m = lane & 15, g = lane >> 4;
-    const int r0 = 4 * (g & 1) + 2 * (lane >> 5);
     float best_v[B];
     int best_i[B];
 #pragma unroll
@@ -420,108 +531,10 @@ __global__ void __launch_bounds__(Sh::kThreads, Sh::kMinWaves) k_pf_gemm(DevMode
         const int tile = tiles[wn * A + i];
         if (tile < 0) continue;
 #pragma unroll
-        for (int j = 0; j < B; ++j) {
-            const int row = (rt0 + wm * B + j) * 16 + m;
-            const bool on = row < P.n;
-            const v4f c = acc.tot[i][j];
-            const auto pa = __builtin_amdgcn_permlane32_swap(__float_as_uint(c.x), __float_as_uint(c.z), false, false);
-            const auto pb = __builtin_amdgcn_permlane32_swap(__float_as_uint(c.y), __float_as_uint(c.w), false, false);
-            const float u0 = __uint_as_float(pa[0]), u1 = __uint_as_float(pb[0]);      // columns r0, r0 + 1
-            const float w0 = __uint_as_float(pa[1]), w1 = __uint_as_float(pb[1]);      // columns r0 + 8, r0 + 9
-            if constexpr (STAGE == kPfOproj || STAGE == kPfDown) {
-                const int c1 = tile * 16 + r0;
-                float sq = 0.f;
-                if (on) {
-                    float2* x1 = reinterpret_cast<float2*>(T.X + (size_t)row * M.d + c1);
-                    float2* x2 = reinterpret_cast<float2*>(T.X + (size_t)row * M.d + c1 + 8);
-                    const float2 g1 = *reinterpret_cast<const float2*>(gain_next + c1), g2 = *reinterpret_cast<const float2*>(gain_next + c1 + 8);
-                    float2 a = *x1, b = *x2;
-                    a.x += u0; a.y += u1; b.x += w0; b.y += w1;
-                    *x1 = a;
-                    *x2 = b;
-                    PfAct<DT>::store2(T.A, M.d / DT::KB, row, c1, a.x * g1.x, a.y * g1.y);
-                    PfAct<DT>::store2(T.A, M.d / DT::KB, row, c1 + 8, b.x * g2.x, b.y * g2.y);
-                    sq = square_pair(a.x, b.x) + square_pair(a.y, b.y);
-                }
-                sq = wave_xor_add<32>(sq);
-                sq = wave_xor_add<16>(sq);
-                if (on && g == 0) T.ssq[(size_t)tile * T.cap + row] = sq;
-            } else if constexpr (STAGE == kPfGateUp) {
-                if (on) {
-                    const float sc = T.rstd[row];
-                    PfAct<DT>::store2(T.H, M.F / DT::KB, row, tile * 8 + r0, swiglu(u0 * sc, w0 * sc), swiglu(u1 * sc, w1 * sc));
-                }
-            } else if constexpr (STAGE == kPfQKV) {
-                if (!on) continue;
-                const float sc = T.rstd[row];
-                const int hd = M.hd, tph = hd / 16, qt = M.qdim / 16, kt = M.kvdim / 16, pos = P.L0 + row;
-                const float a0 = u0 * sc, a1 = u1 * sc, b0 = w0 * sc, b1 = w1 * sc;
-                const size_t slot_base = (size_t)P.slot * M.Hkv * M.ctx_pad * hd;
-                if (tile < qt + kt) {
-                    const bool isq = tile < qt;
-                    const int tt = isq ? tile : tile - qt;
-                    const int head = tt / tph, c1 = (tt % tph) * 8 + r0;
-                    const size_t ro = (size_t)pos * (hd / 2) + c1;
-                    const float2 cs = *reinterpret_cast<const float2*>(M.rope_cos + ro), sn = *reinterpret_cast<const float2*>(M.rope_sin + ro);
-                    float x0, x1, y0, y1;
-                    rotate_pair(a0, b0, cs.x, sn.x, x0, y0);
-                    rotate_pair(a1, b1, cs.y, sn.y, x1, y1);
-                    if (isq) {
-                        const size_t o = (size_t)row * M.qdim + head * hd + c1;
-                        if constexpr (DT::HAS_LO) {
-                            auto put = [&](size_t at, float p, float q) {
-                                const uint32_t h0 = DT::att_bits(p), h1 = DT::att_bits(q);
-                                const uint32_t l0 = DT::att_bits(p - DT::att_float(h0)), l1 = DT::att_bits(q - DT::att_float(h1));
-                                *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(T.Q_hi) + at) = h0 | (h1 << 16);
-                                *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(T.Q_lo) + at) = l0 | (l1 << 16);
-                            };
-                            put(o, x0, x1);
-                            put(o + hd / 2, y0, y1);
-                        } else {
-                            *reinterpret_cast<float2*>(reinterpret_cast<float*>(T.Q_hi) + o) = float2{x0, x1};
-                            *reinterpret_cast<float2*>(reinterpret_cast<float*>(T.Q_hi) + o + hd / 2) = float2{y0, y1};
-                        }
-                    } else {
-                        const size_t hb = slot_base + (size_t)head * M.ctx_pad * hd;
-                        auto put = [&](int col, float p, float q) {      // neighbouring columns are neighbours in the cache
-                            const size_t at = hb + kcache_index<DT>(hd, pos, col);
-                            if constexpr (DT::HAS_LO)
-                                *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(Ly.kcache) + at) = DT::att_bits(p) | (DT::att_bits(q) << 16);
-                            else
-                                *reinterpret_cast<float2*>(reinterpret_cast<float*>(Ly.kcache) + at) = float2{p, q};
-                        };
-                        put(c1, x0, x1);
-                        put(c1 + hd / 2, y0, y1);
-                    }
-                } else {
-                    const int tt = tile - qt - kt;
-                    const int head = tt / tph, c1 = (tt % tph) * 16 + r0;
-                    const size_t hb = slot_base + (size_t)head * M.ctx_pad * hd;
-                    auto put = [&](int col, float p) {
-                        const size_t at = hb + vcache_index<DT>(hd, pos, col);
-                        if constexpr (DT::HAS_LO) reinterpret_cast<uint16_t*>(Ly.vcache)[at] = (uint16_t)DT::att_bits(p);
-                        else reinterpret_cast<float*>(Ly.vcache)[at] = p;
-                    };
-                    put(c1, a0);
-                    put(c1 + 1, a1);
-                    put(c1 + 8, b0);
-                    put(c1 + 9, b1);
-                }
-            } else {                                   // LM head: logits of the rows that are kept, arg-max per row
-                if (on) {
-                    const float sc = T.rstd[row];
-                    const int c1 = tile * 16 + r0;
-                    const float z[4] = {u0 * sc, u1 * sc, w0 * sc, w1 * sc};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int col = c1 + (e & 1) + 8 * (e >> 1);
-                        if (better(z[e], col, best_v[j], best_i[j])) { best_v[j] = z[e]; best_i[j] = col; }
-                        if (row >= P.keep0) M.logits[(size_t)(row - P.keep0) * M.V + col] = z[e];
-                    }
-                }
-            }
-        }
+        for (int j = 0; j < B; ++j)
+            pf_epilogue<DT, STAGE>(M, Ly, T, P, gain_next, tile, rt0 + wm * B + j, acc.tot[i][j], best_v[j], best_i[j]);
     }
+    const int m = lane & 15, g = lane >> 4;
     if constexpr (STAGE == kPfLMHead) {
 #pragma unroll
         for (int j = 0; j < B; ++j) {
@@ -529,9 +542,136 @@ __global__ void __launch_bounds__(Sh::kThreads, Sh::kMinWaves) k_pf_gemm(DevMode
             keep_better_xor<16>(best_v[j], best_i[j]);
             keep_better_xor<32>(best_v[j], best_i[j]);
             if (g == 0 && row < P.n) {
-                T.best_val[(size_t)(cg * Sh::WN + wn) * T.cap + row] = best_v[j];
-                T.best_idx[(size_t)(cg * Sh::WN + wn) * T.cap + row] = best_i[j];
+                T.best_val[(size_t)(cg * Sh::WN + wn) * P.n + row] = best_v[j];
+                T.best_idx[(size_t)(cg * Sh::WN + wn) * P.n + row] = best_i[j];
             }
+        }
+    }
+}
+
+// Few rows: bound by streaming the weights, as the verify pass is, and built like its stages.  A workgroup owns NT column
+// tiles x RT row tiles; its eight waves contract over the eight K slices side by side, fetching weight and activation
+// fragments straight into registers D blocks ahead, and the slices' sums meet in LDS in wave order.  `shares` > 1: one
+// workgroup per K range.  Against the form above: no barrier per K block, eight streams per workgroup, and every compute
+// unit has weights to stream where that form has a few dozen tiles.
+template <int F>
+struct PfSums {                  // what combine_shares works on: F fragments per thread of eight waves
+    using Shape = PfShape<kWaves, 1, 1, F, 3>;
+    v4f tot[1][F];
+};
+template <class DT, int STAGE, int NT, int RT, int D>
+__global__ void __launch_bounds__(kThreads, 2) k_pf_stream(DevModel M, DevLayer Ly, PrefillBufs T, PrefillArgs P, const float* gain_next,
+                                                            int shares) {
+    extern __shared__ char pf_smem[];
+    constexpr int AF = PfAct<DT>::AF, F = (NT * RT + kWaves - 1) / kWaves;   // fragments a wave finishes
+    PfSums<F> sum;
+    using Walk = typename PfWalk<STAGE>::T;
+    const int row_groups = (P.n + RT * 16 - 1) / (RT * 16);
+    const PfTiles& L = T.tiles[STAGE];
+    const int groups = gridDim.x / shares;
+    const int share = blockIdx.x / groups, idx = blockIdx.x % groups;
+    const int cg = idx / row_groups, rg = idx % row_groups;
+    const int* tiles = L.order + cg * NT;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int t0 = __builtin_amdgcn_readfirstlane(tiles[0]);
+    const int rt0 = rg * RT;
+    static_assert(STAGE != kPfLMHead, "");
+    float best_v = 0.f;       // (the LM head's)
+    int best_i = 0;
+    if (t0 >= 0) {            // (else nothing but filling)
+        const uint4* W;
+        const void* act;
+        int K, ways;
+        pf_inputs<STAGE>(M, Ly, T, W, act, K, ways);
+        const int kblocks = K / DT::KB, kh = kblocks / ways;
+        v4f acc[NT][RT][AF], part[NT][RT];
+        // K ranges of this workgroup: all of them one after the other, or its own
+        for (int range = share; range < ways; range += shares) {
+            const KSlice ks = k_slice_of<Walk>(kh, t0 % L.wgs, wave);
+            const int S = ks.S;
+#pragma unroll
+            for (int i = 0; i < NT; ++i)
+#pragma unroll
+                for (int j = 0; j < RT; ++j)
+#pragma unroll
+                    for (int f = 0; f < AF; ++f) acc[i][j][f] = v4f{0.f, 0.f, 0.f, 0.f};
+            if (S > 0) {
+                const uint4* wp[NT];
+#pragma unroll
+                for (int i = 0; i < NT; ++i) {
+                    const int t = __builtin_amdgcn_readfirstlane(tiles[i]);
+                    wp[i] = W + ((size_t)(t < 0 ? t0 : t) * kblocks + range * kh + ks.kb0) * 64 + lane;
+                }
+                const uint4* ap = reinterpret_cast<const uint4*>(act) + PfAct<DT>::frag(kblocks, rt0, range * kh + ks.kb0, 0) + lane;
+                uint4 wb[D][NT], ab[D][RT][AF];
+                const int last = S - 1;
+                auto fetch = [&](int st, int to) {
+                    const int x = st + ks.rot;
+                    const int s = (x >= S ? x - S : x) * ks.stride;
+#pragma unroll
+                    for (int i = 0; i < NT; ++i) wb[to][i] = load_stream(wp[i] + (size_t)s * 64);
+#pragma unroll
+                    for (int j = 0; j < RT; ++j)
+#pragma unroll
+                        for (int f = 0; f < AF; ++f) ab[to][j][f] = ap[(size_t)s * (PfAct<DT>::kBlockTiles * AF * 64) + (j * AF + f) * 64];
+                    __builtin_amdgcn_sched_barrier(0);      // the loads stay in this order, and behind the products before them
+                };
+                auto multiply = [&](int from) {
+#pragma unroll
+                    for (int f = 0; f < AF; ++f)
+#pragma unroll
+                        for (int i = 0; i < NT; ++i)
+#pragma unroll
+                            for (int j = 0; j < RT; ++j) acc[i][j][f] = DT::mfma(wb[from][i], ab[from][j][f], acc[i][j][f]);
+                };
+#pragma unroll
+                for (int d = 0; d < D; ++d) fetch(d < last ? d : last, d);
+                int s0 = 0;
+                for (; s0 + D < S; s0 += D) {
+#pragma unroll
+                    for (int d = 0; d < D; ++d) {
+                        multiply(d);
+                        fetch(s0 + d + D < last ? s0 + d + D : last, d);
+                    }
+                }
+#pragma unroll
+                for (int d = 0; d < D; ++d)
+                    if (s0 + d < S) multiply(d);
+            }
+#pragma unroll
+            for (int i = 0; i < NT; ++i)
+#pragma unroll
+                for (int j = 0; j < RT; ++j) {
+                    if constexpr (AF == 2) part[i][j] = acc[i][j][0] + acc[i][j][1];
+                    else part[i][j] = acc[i][j][0];
+                }
+            if (range != share) __syncthreads();        // the sums of the range before have been read
+            v4f* lds = reinterpret_cast<v4f*>(pf_smem);   // [wave][fragment][lane]
+#pragma unroll
+            for (int i = 0; i < NT; ++i)
+#pragma unroll
+                for (int j = 0; j < RT; ++j) lds[(wave * (NT * RT) + i * RT + j) * 64 + lane] = part[i][j];
+            __syncthreads();
+#pragma unroll
+            for (int x = 0; x < F; ++x) {
+                const int f = wave + x * kWaves;
+                v4f v = v4f{0.f, 0.f, 0.f, 0.f};
+                if (f < NT * RT)
+#pragma unroll
+                    for (int w = 0; w < kWaves; ++w) v += lds[(w * (NT * RT) + f) * 64 + lane];
+                sum.tot[0][x] = range == share ? v : sum.tot[0][x] + v;
+            }
+        }
+        if (shares > 1) {
+            __syncthreads();
+            float* xch = T.xch + (size_t)idx * shares * (kThreads * F * 4);
+            if (!combine_shares<PfSums<F>>(sum, xch, T.ticket + idx, share, shares, 1, pf_smem)) return;
+        }
+#pragma unroll
+        for (int x = 0; x < F; ++x) {
+            const int f = wave + x * kWaves;
+            const int tile = f < NT * RT ? tiles[f / RT] : -1;
+            if (tile >= 0) pf_epilogue<DT, STAGE>(M, Ly, T, P, gain_next, tile, rt0 + f % RT, sum.tot[0][x], best_v, best_i);
         }
     }
 }
@@ -791,8 +931,8 @@ __global__ void __launch_bounds__(256) k_pf_greedy(PrefillBufs T, PrefillArgs P,
     float bv = -INFINITY;
     int bi = 0x7fffffff;
     for (int w = lane; w < parts; w += 64) {
-        const float v = T.best_val[(size_t)w * T.cap + row];
-        const int i = T.best_idx[(size_t)w * T.cap + row];
+        const float v = T.best_val[(size_t)w * P.n + row];
+        const int i = T.best_idx[(size_t)w * P.n + row];
         if (better(v, i, bv, bi)) { bv = v; bi = i; }
     }
     keep_better_xor<32>(bv, bi);
@@ -850,6 +990,43 @@ static hipError_t launch_pf_gemm_v(const DevModel& M, const DevLayer& Ly, const 
     return hipSuccess;
 }
 
+template <class DT, int STAGE, int NT, int RT, int D>
+static hipError_t launch_pf_stream_v(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PrefillArgs& P, const float* gain,
+                                     hipStream_t s, int shares) {
+    constexpr int lds = kWaves * NT * RT * 1024;
+    static const hipError_t set = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pf_stream<DT, STAGE, NT, RT, D>),
+                                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (set != hipSuccess) return set;
+    const int groups = T.tiles[STAGE].n / NT;
+    hipLaunchKernelGGL((k_pf_stream<DT, STAGE, NT, RT, D>), dim3(groups * ((P.n + RT * 16 - 1) / (RT * 16)) * shares), dim3(kThreads), lds, s,
+                       M, Ly, T, P, gain, shares);
+    return hipSuccess;
+}
+
+// The streaming form where it is the faster one: up to 64 rows, and up to 128 where one round of workgroups does the stage
+// (NT the smallest of 1, 2, 4 column tiles with that; at most 64 rows and still more workgroups: 4).  Measured against the
+// other form's best plan, us per launch: 8B shape, 24 rows QKV -18, O -8, gate/up -15, down -23; 61 rows -15, 0, -2, -9;
+// 128 rows -12, -8, (gate/up +38: 896 workgroups), -45; 250 rows +9, +22, +129, +33.  1B shape, 61 rows -6, -4, -5, 0; 128
+// rows -10, -11, (+6), -10.
+template <class DT, int STAGE>
+static bool launch_pf_stream(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PrefillArgs& P, const float* gain,
+                             hipStream_t s, hipError_t& e) {
+    if (P.n > 128) return false;
+    const int rt = P.n <= 32 ? 2 : 4, row_groups = (P.n + rt * 16 - 1) / (rt * 16), tiles = T.tiles[STAGE].n;
+    int shares = STAGE == kPfDown && M.split_down ? 2 : 1;
+    const int nt = tiles * row_groups * shares <= T.cus ? 1 : tiles / 2 * row_groups * shares <= T.cus ? 2 : 4;
+    if (tiles / nt * row_groups * shares > T.cus && P.n > 64) return false;
+    const size_t sums = (size_t)(tiles / nt * row_groups) * shares * (kThreads * ((nt * rt + kWaves - 1) / kWaves) * 16);
+    if (tiles / nt * row_groups > kPfTickets || sums > T.xch_bytes) shares = 1;
+    if (rt == 2) e = nt == 1 ? launch_pf_stream_v<DT, STAGE, 1, 2, 6>(M, Ly, T, P, gain, s, shares)
+                     : nt == 2 ? launch_pf_stream_v<DT, STAGE, 2, 2, 4>(M, Ly, T, P, gain, s, shares)
+                               : launch_pf_stream_v<DT, STAGE, 4, 2, 3>(M, Ly, T, P, gain, s, shares);
+    else e = nt == 1 ? launch_pf_stream_v<DT, STAGE, 1, 4, 3>(M, Ly, T, P, gain, s, shares)
+             : nt == 2 ? launch_pf_stream_v<DT, STAGE, 2, 4, 3>(M, Ly, T, P, gain, s, shares)
+                       : launch_pf_stream_v<DT, STAGE, 4, 4, 2>(M, Ly, T, P, gain, s, shares);
+    return true;
+}
+
 // Workgroup shapes; the two smaller ones run two to a compute unit.
 using PfLarge = PfShape<4, 2, 4, 4, 4>;   // 256 columns x 128 rows
 using PfMid = PfShape<2, 2, 4, 2, 4>;     // 128 x 64
@@ -893,6 +1070,10 @@ static PfPlan plan_pf_gemm(const DevModel& M, const PrefillBufs& T, int n, int s
 template <class DT, int STAGE>
 static hipError_t launch_pf_gemm(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PrefillArgs& P, const float* gain,
                                  hipStream_t s, int* parts = nullptr) {
+    if constexpr (STAGE != kPfLMHead) {      // (its partial maxima would outgrow best_val, and it gains nothing)
+        hipError_t e;
+        if (launch_pf_stream<DT, STAGE>(M, Ly, T, P, gain, s, e)) return e;
+    }
     const PfPlan p = plan_pf_gemm(M, T, P.n, STAGE);
     switch (p.shape) {
         case 0: return launch_pf_gemm_v<DT, STAGE, PfLarge>(M, Ly, T, P, gain, s, parts, p.shares);
