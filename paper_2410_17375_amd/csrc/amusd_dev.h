@@ -68,7 +68,6 @@ struct DevLayer {
 
 // ---- prefill pass: many prompt rows of one sequence at a time
 constexpr int kPfMaxRows = 2048;     // rows of one pass
-constexpr int kPfMinRows = 17;       // prompts up to 16 tokens go through the verify pass's kernels
 constexpr int kPfBlockRows = 128;    // rows that share a stretch of the activation buffers
 constexpr int kPfTileGroup = 16;     // column tiles of the widest workgroup
 constexpr int kPfPartBytes = 256 << 20;  // attention partials in flight between the two kernels

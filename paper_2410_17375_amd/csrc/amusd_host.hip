@@ -291,7 +291,7 @@ int run_pass(amusd_model* m, const SegReq* segs, int n_seg, bool force_accept, b
 // is shorter than the smallest such pass) prefills through the verify pass.
 int alloc_prefill(amusd_model* m) {
     const DevModel& D = m->dm;
-    if (D.max_ctx < kPfMinRows) return AMUSD_OK;
+    if (D.max_ctx <= 1) return AMUSD_OK;
     PrefillBufs T{};
     T.cap = D.max_ctx >= kPfMaxRows ? kPfMaxRows : (D.max_ctx + kPfBlockRows - 1) / kPfBlockRows * kPfBlockRows;
     T.cus = m->nwg;
@@ -728,9 +728,10 @@ int amusd_seq_prefill(amusd_model* m, int32_t seq, const int32_t* tokens, int32_
     // 16-bit models run fastest with at most 8 rows per pass (hi and lo halves share one operand fragment)
     const int chunk = m->cfg.dtype == AMUSD_DTYPE_BF16 && m->cfg.max_k > 8 ? 8 : m->cfg.max_k;
     const int len_before = q.kv_len, next_before = q.p_next;
-    // Prompts go through the prefill pass, in stretches of about equal length; up to 16 tokens, and with a stage of the
-    // verify pass selected for timing, through the verify pass.  The last group of rows is the same either way.
-    if (n >= kPfMinRows && m->pf.cap && m->timer.stage < 0) {
+    // Prompts go through the prefill pass, in stretches of about equal length; what one verify pass holds, and with a stage
+    // of the verify pass selected for timing everything, through the verify pass.  The last group of rows is the same either
+    // way.  (8B shape, 4 layers: 9 tokens 0.81 ms in two verify passes, 0.60 in one prefill pass.)
+    if (n > chunk && m->pf.cap && m->timer.stage < 0) {
         const int tail = (n - 1) % chunk + 1, passes = (n + m->pf.cap - 1) / m->pf.cap;
         const int per = passes == 1 ? n : ((n + passes - 1) / passes + kPfBlockRows - 1) / kPfBlockRows * kPfBlockRows;
         for (int s = 0; s < n; s += per) {

@@ -1,4 +1,4 @@
-"""The prefill pass (prompts of 17 tokens and more) against the same tokens given in pieces of at most 8, which go through
+"""The prefill pass (prompts of more tokens than a verify pass takes) against the same tokens given in pieces of at most 8, which go through
 the verify pass: cache rows, greedy tokens of every position, kept logits and what a following window sees, bit for bit.
 The sizes put the edges of its row and column tiles, its workgroup shapes and the K ranges of the down projection in turn."""
 import numpy as np
@@ -12,12 +12,14 @@ CASES = [
     # (shape, overrides, tokens cached before, prompt length)
     ("tiny_verify", {}, 0, 17), ("tiny_verify", {}, 5, 130), ("tiny_draft", {}, 0, 33),
     ("tiny_gqa_fp32", {}, 0, 300), ("tiny_wide_fp32", {}, 3, 65),
-    ("tiny_gqa_bf16", {}, 0, 17), ("tiny_gqa_bf16", {}, 7, 64), ("tiny_gqa_bf16", {}, 1, 300),
+    ("tiny_gqa_bf16", {}, 0, 9), ("tiny_g8_bf16", {}, 130, 16), ("tiny_gqa_bf16", {}, 0, 17), ("tiny_gqa_bf16", {}, 7, 64), ("tiny_gqa_bf16", {}, 1, 300),
     ("tiny_gqa128_bf16", {}, 33, 129), ("tiny_g8_bf16", {}, 0, 200), ("tiny_wide_bf16", {}, 2, 97),
     ("tiny_gqa_bf16", {"d_model": 288, "d_ffn": 544, "vocab": 1008}, 0, 47),     # K blocks that do not split evenly over the waves
     ("tiny_wide_bf16", {"d_model": 320, "d_ffn": 4160}, 0, 80),
     ("tiny_gqa_bf16", {"d_model": 128, "n_q_heads": 2, "n_kv_heads": 1, "d_ffn": 96}, 0, 70),   # fewer K blocks than waves
-    ("one_layer_8b_width_bf16", {"vocab": 16000}, 0, 61), ("one_layer_8b_width_bf16", {"vocab": 16000}, 40, 400),
+    ("one_layer_8b_width_bf16", {"vocab": 16000}, 3, 24),
+    ("one_layer_8b_width_bf16", {"vocab": 16000}, 0, 61), ("one_layer_8b_width_bf16", {}, 0, 128),
+    ("one_layer_8b_width_bf16", {"d_ffn": 14336}, 0, 250), ("one_layer_8b_width_bf16", {"vocab": 16000}, 40, 400),
     ("one_layer_8b_width_bf16", {"vocab": 16000}, 0, 1100), ("one_layer_8b_width_bf16", {}, 9, 2190),
 ]
 
