@@ -43,7 +43,6 @@ struct PassArgs {
     int slot0;          // seg[0].slot
     int nchunks0;       // seg[0].nchunks
     int units;          // attention work units of the pass, all sequences together
-    int serial;         // the pass's number, written to PassResult.done when its results are there
     int tokens[kRows];  // input token of each row
     int row_pos[kRows]; // position of each row in its sequence
     int row_seg[kRows]; // segment of each row
@@ -54,7 +53,6 @@ struct PassResult {
     int accept_len[kMaxSegs];   // per segment
     int next_token[kMaxSegs];
     int greedy[kRows];          // per row
-    int done;                   // number of the last pass whose results are complete
 };
 
 struct DevLayer {

@@ -6,7 +6,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdio>
@@ -110,9 +109,8 @@ struct amusd_model {
     int* pf_host = nullptr;                // pinned: tokens of a prefill pass, then its greedy tokens
     void* staging = nullptr;               // device staging for host-provided tensors
     size_t staging_bytes = 0;
-    hipEvent_t ev0 = nullptr, ev1 = nullptr;   // around the last pass
-    bool timed = false;                    // they have been recorded
-    int serial = 0;                        // number of the last pass
+    hipEvent_t ev0 = nullptr, ev1 = nullptr;
+    float last_ms = 0.f;
     StageTimer timer;
     std::vector<hipEvent_t> tev_begin, tev_end;
     double stage_ms = 0.0;
@@ -211,25 +209,6 @@ float half_bits_to_float(uint16_t h) {      // IEEE binary16 -> float
     return r;
 }
 
-// Waits for a pass's results: its number in the pinned result block.  The end of the last kernel reaches the host through
-// the runtime (stream synchronization, the second event's marker) 8 us later than this word, a tenth of a small model's
-// pass.  After 50 ms, or if the word never comes, the stream says what happened.
-hipError_t wait_results(amusd_model* m) {
-    const volatile int* done = &m->hstage->res.done;
-    const auto t0 = std::chrono::steady_clock::now();
-    for (unsigned i = 1;; ++i) {
-        if (*done == m->serial) {
-            std::atomic_thread_fence(std::memory_order_acquire);
-            return hipSuccess;
-        }
-        __builtin_ia32_pause();
-        if (i % 4096 == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(50)) break;
-    }
-    const hipError_t e = hipStreamSynchronize(m->stream);
-    if (e == hipSuccess && *done != m->serial) return hipErrorUnknown;
-    return e;
-}
-
 std::once_flag g_cfg_once;
 hipError_t g_cfg_err = hipSuccess;
 
@@ -280,16 +259,12 @@ int run_pass(amusd_model* m, const SegReq* segs, int n_seg, bool force_accept, b
     P.units = units;
     P.force_accept = force_accept ? 1 : 0;
     P.keep_logits = m->keep_logits ? 1 : 0;
-    P.serial = ++m->serial;
-    m->timed = false;
     HIP_TRY(hipEventRecord(m->ev0, m->stream));
     HIP_TRY(launch_pass(D, m->layers_host.data(), P, m->nwg, m->stream, m->timer.stage >= 0 ? &m->timer : nullptr));
     HIP_TRY(hipEventRecord(m->ev1, m->stream));
-    m->timed = true;
-    if (m->timer.stage < 0) {
-        HIP_TRY(wait_results(m));
-    } else {
-        HIP_TRY(hipStreamSynchronize(m->stream));
+    HIP_TRY(hipStreamSynchronize(m->stream));
+    HIP_TRY(hipEventElapsedTime(&m->last_ms, m->ev0, m->ev1));
+    if (m->timer.stage >= 0) {
         for (int i = 0; i < m->timer.used; ++i) {
             float ms = 0.f;
             HIP_TRY(hipEventElapsedTime(&ms, m->timer.begin[i], m->timer.end[i]));
@@ -382,12 +357,11 @@ int run_prefill(amusd_model* m, int seq, int L, const int32_t* tokens, int n, in
     HostStage* h = m->hstage;
     const PrefillArgs P{n, L, seq, m->keep_logits ? n - tail : n};
     std::memcpy(m->pf_host, tokens, (size_t)n * 4);
-    m->timed = false;
     HIP_TRY(hipEventRecord(m->ev0, m->stream));
     HIP_TRY(launch_prefill(m->dm, m->layers_host.data(), m->pf, P, m->stream));
     HIP_TRY(hipEventRecord(m->ev1, m->stream));
-    m->timed = true;
     HIP_TRY(hipStreamSynchronize(m->stream));
+    HIP_TRY(hipEventElapsedTime(&m->last_ms, m->ev0, m->ev1));
     const int* greedy = m->pf_host + m->pf.cap;
     SeqState& q = m->seqs[seq];
     std::memcpy(&q.greedy_at[L + 1], greedy, (size_t)n * 4);
@@ -550,7 +524,7 @@ int amusd_model_create(const amusd_config* cfg, void* hip_stream, amusd_model** 
     if (hipMemcpyAsync(const_cast<DevLayer*>(D.layers), m->layers_host.data(), sizeof(DevLayer) * c.n_layers,
                        hipMemcpyHostToDevice, m->stream) != hipSuccess)
         return bail(fail(AMUSD_E_HIP, "layer table upload"));
-    if (hipHostMalloc(reinterpret_cast<void**>(&m->hstage), sizeof(HostStage), hipHostMallocCoherent | hipHostMallocMapped) != hipSuccess)
+    if (hipHostMalloc(reinterpret_cast<void**>(&m->hstage), sizeof(HostStage), hipHostMallocDefault) != hipSuccess)
         return bail(fail(AMUSD_E_HIP, "pinned staging allocation"));
     std::memset(m->hstage, 0, sizeof(HostStage));
     // the acceptance kernel writes its 192-byte result straight into this pinned host block: no copy per pass
@@ -967,10 +941,7 @@ int amusd_get_greedy(amusd_model* m, int32_t* out, int32_t rows) {
 
 int amusd_last_pass_ms(amusd_model* m, float* ms) {
     if (!m || !ms) return fail(AMUSD_E_ARG, "null argument");
-    *ms = 0.f;
-    if (!m->timed) return AMUSD_OK;
-    HIP_TRY(hipEventSynchronize(m->ev1));
-    HIP_TRY(hipEventElapsedTime(ms, m->ev0, m->ev1));
+    *ms = m->last_ms;
     return AMUSD_OK;
 }
 

@@ -939,9 +939,7 @@ __device__ __forceinline__ void stage_accept(const DevModel& M, const PassArgs& 
     __syncthreads();
     if (row != 0) return;
     const int myg = lane < kRows ? sg[lane] : -1;
-    // results go to pinned host memory in system-scope stores; the host waits for the pass's number, written after them
-    auto put = [](int* p, int v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); };
-    if (lane < kRows) put(&M.res->greedy[lane], myg);
+    if (lane < kRows) M.res->greedy[lane] = myg;
     // lane r holds g[r]; for the sequence's first row the target is its p_ctx, else the previous row's g
     const int rl = lane < kRows ? lane : 0;
     const PassSeg& Sr = P.seg[P.row_seg[rl]];
@@ -957,11 +955,9 @@ __device__ __forceinline__ void stage_accept(const DevModel& M, const PassArgs& 
     const int gk = __shfl(myg, S.row0 + S.k - 1, 64);
     const int nxt_t = __shfl(target, S.row0 + (n < S.k ? n : 0), 64);
     if (lane < P.n_seg) {
-        put(&M.res->accept_len[lane], n);
-        put(&M.res->next_token[lane], n < S.k ? nxt_t : gk);
+        M.res->accept_len[lane] = n;
+        M.res->next_token[lane] = n < S.k ? nxt_t : gk;
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // acknowledged
-    if (lane == 0) put(&M.res->done, P.serial);
 }
 
 // ---------------------------------------------------------------- one kernel per stage
