@@ -287,8 +287,8 @@ int run_pass(amusd_model* m, const SegReq* segs, int n_seg, bool force_accept, b
     return AMUSD_OK;
 }
 
-// Workspace of the prefill pass, sized for the model's context.  A model that finds no memory for it (or whose context
-// is shorter than the smallest such pass) prefills through the verify pass.
+// Workspace of the prefill pass, sized for the model's context.  A model that finds no memory for it prefills through
+// the verify pass.
 int alloc_prefill(amusd_model* m) {
     const DevModel& D = m->dm;
     if (D.max_ctx <= 1) return AMUSD_OK;

@@ -98,7 +98,7 @@ struct KSequence {
 //   4 x 2 waves of 4 x 4 tiles (256 columns x 128 rows, 32 KiB per K block): per K block 1024 clocks of matrix
 //       instructions on each SIMD, 96 KiB of LDS reads (768 clocks) and 32 KiB of loads (32 bytes per clock of the 64 that an
 //       L2 gives one of its compute units).  The three accumulators per output fill 192 of a wave's 256 registers.  8B shape,
-//       2048 rows: gate/up 845 us = 1.14 PFLOP/s of matrix instructions, hi and lo halves counted (a large library product
+//       2048 rows: gate/up 845 us (774 on another card; the figures below are from the first) = 1.14 PFLOP/s of matrix instructions, hi and lo halves counted (a large library product
 //       on the same card: 1.29).  A fifth ring slot changes nothing; workgroups ordered column by column instead of in
 //       patches 887 us, with the loads through the compiler's builtin 908.
 //   smaller ones where that shape leaves compute units without a tile; they are bound by LDS reads.
