@@ -662,6 +662,9 @@ __global__ void __launch_bounds__(kThreads, 2) k_pf_stream(DevModel M, DevLayer 
                 sum.tot[0][x] = range == share ? v : sum.tot[0][x] + v;
             }
         }
+        // The last fetches are repeats of the last block that nothing multiplies, so nothing has waited for them, and a
+        // wave without a fragment to finish would end with them under way.
+        wait_vm<0>();
         if (shares > 1) {
             __syncthreads();
             float* xch = T.xch + (size_t)idx * shares * (kThreads * F * 4);
