@@ -201,10 +201,15 @@ __device__ __forceinline__ float lane_value(float v, int j) {
 // ---------------------------------------------------------------- loads that deliver into LDS
 // 16 bytes per lane from base + offset to LDS bytes dst + 16 lane.  In assembly, because the compiler takes the builtin
 // for an access to all of LDS and then waits for every LDS read at once (lgkmcnt(0)) throughout the loop; it has no result
-// registers, and every wait for it is written out (wait_vm).
+// registers, and every wait for it is written out (wait_vm).  m0 is named as overwritten: the compiler keeps it from one
+// of its own loads of this kind to the next, and a kernel may hold both.  (It warns that m0 is a reserved register; that
+// is why nothing of its own can be kept in it across the statement.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void load_to_lds(const char* base, unsigned offset, unsigned dst) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(offset), "s"(base), "s"(dst) : "memory");
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(offset), "s"(base), "s"(dst) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 template <int N>
 __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 

@@ -75,6 +75,33 @@ def test_reading_of_the_assembly():
     assert _ends_with_load_in_flight(code)
 
 
+MIXED_LOADS = """
+#include "%s"
+extern "C" __global__ void mixed_loads(const char* a, const char* b, float* out) {     // compiled, never run
+    extern __shared__ char smem[];
+    auto own = [&](int at) {
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(b + at + threadIdx.x * 4),
+                                         (__attribute__((address_space(3))) void*)(smem + 4096), 4, 0, 0);
+    };
+    own(0);
+    amusd::load_to_lds(a, threadIdx.x * 16, 0);
+    own(4096);
+    amusd::wait_vm<0>();
+    __syncthreads();
+    out[threadIdx.x] = reinterpret_cast<float*>(smem)[threadIdx.x] + reinterpret_cast<float*>(smem + 4096)[threadIdx.x];
+}
+"""
+
+
+def test_compiler_sets_m0_again_behind_the_written_out_load(tmp_path):
+    """m0 is where a load into LDS delivers to: the compiler's own loads must not go where load_to_lds sent its."""
+    src = tmp_path / "mixed.hip"
+    src.write_text(MIXED_LOADS % os.path.join(ROOT, "paper_2410_17375_amd", "csrc", "amusd_math.h"))
+    ops = [line for line in _compile(str(src), tmp_path / "mixed.s")["mixed_loads"] if re.search(r"\bm0\b|global_load_lds", line)]
+    kinds = ["set" if "m0" in op else op.split()[0] for op in ops]
+    assert kinds == ["set", "global_load_lds_dword", "set", "global_load_lds_dwordx4", "set", "global_load_lds_dword"], ops
+
+
 @pytest.fixture(scope="module")
 def prefill(tmp_path_factory):
     return _compile(os.path.join(ROOT, "paper_2410_17375_amd", "csrc", "amusd_prefill.hip"), tmp_path_factory.mktemp("asm") / "prefill.s")
