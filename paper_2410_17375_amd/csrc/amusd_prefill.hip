@@ -828,7 +828,8 @@ __global__ void __launch_bounds__(64 * G, 2) k_pf_attention(DevModel M, DevLayer
     s0.clear();
     int run = 0, part = 0, c = sp * span, cslot = 0;     // run: blocks of it that are done
     // A chunk's result leaves in kStores stores.  They are younger than the loads that are under way, and the waits for
-    // those must not include them (a store takes as long as a load).
+    // those must not include them (a store takes as long as a load).  The compiler must make exactly these stores of what
+    // is written below, and no other access to memory in the loop: tests/test_device_code.py reads that off its assembly.
     constexpr int kStores = HT + 1;
     int older = 0;                                        // blocks under way whose loads are older than the last stores
     auto wait_blocks = [&](int newer, bool slack) {       // at most `newer` blocks (and the stores) are still under way

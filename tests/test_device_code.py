@@ -110,3 +110,21 @@ def prefill(tmp_path_factory):
 def test_no_wave_ends_with_a_load_in_flight(prefill):
     assert len(prefill) > 50
     assert [k for k, body in prefill.items() if _ends_with_load_in_flight(body)] == []
+
+
+def test_stores_of_a_chunk_are_as_many_as_its_waits_count(prefill):
+    """k_pf_attention waits for loads that are older than a chunk's stores by a count that includes those (kStores): with
+    one store fewer it would read a block that has not arrived.  It has no other vector-memory instruction in the loop."""
+    seen = 0
+    for name, body in prefill.items():
+        m = re.search(r"14k_pf_attentionI.*ELi(64|128)ELi[48]E", name)
+        if not m:
+            continue
+        seen += 1
+        stores = [op.split()[0] for op in body if re.match(r"(global|buffer|flat|scratch)_(store|atomic)", op)]
+        assert sorted(stores) == ["global_store_dwordx2"] + ["global_store_dwordx4"] * (int(m.group(1)) // 16), name
+        assert not [op for op in body if op.startswith("scratch_")], name
+        first = next(i for i, op in enumerate(body) if op.startswith("global_load_lds"))
+        later = {op.split()[0] for op in body[first:] if re.match(r"(global|buffer|flat)_load", op)}
+        assert later == {"global_load_lds_dwordx4"}, name
+    assert seen == 8
