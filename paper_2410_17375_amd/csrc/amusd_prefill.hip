@@ -64,6 +64,9 @@ template <> struct PfWalk<kPfOproj> { using T = KWalkOproj; };
 template <> struct PfWalk<kPfGateUp> { using T = KWalkWide; };
 template <> struct PfWalk<kPfDown> { using T = KWalkDown; };
 template <> struct PfWalk<kPfLMHead> { using T = KWalkWide; };
+// A split stage of the verify pass walks by the index of its workgroup in the pair's K ranges, not by its tile's as here:
+// the two are the same walk only while the workgroup does not shift it.
+static_assert(KWalkDown::kRotWg == 0, "the prefill pass would start the down projection's slices elsewhere than the verify pass");
 
 // Slices first .. last - 1 of a contraction, block by block: slice s is that of wave s mod 8 of the verify pass, in K range
 // s / 8 of those that pairs of its workgroups share (kh blocks each).
