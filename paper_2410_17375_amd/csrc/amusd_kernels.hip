@@ -793,7 +793,7 @@ __device__ __forceinline__ void stage_lmhead(const DevModel& M, const PassArgs& 
 // order.  Block, run and chunk boundaries sit at fixed absolute positions, so a
 // row's result does not depend on how many rows the pass has or where it starts.
 // Output per (unit, head, row): numerator[hd], running max, denominator.
-template <class DT, int HD, bool ONE>
+template <class DT, int HD, bool ONE, int STAGED>
 __device__ __forceinline__ void stage_attention(const DevModel& M, const DevLayer& Ly, const PassArgs& P, int wg, int nwg,
                                                 float* smem) {
     pin_scalar(M.Q_hi); pin_scalar(M.Q_lo); pin_scalar(Ly.kcache); pin_scalar(Ly.vcache); pin_scalar(M.att_part);
@@ -848,8 +848,7 @@ __device__ __forceinline__ void stage_attention(const DevModel& M, const DevLaye
         const int ucanon = unit0 + kvh * nchunks + c;      // where the merge stage looks for this unit's partials
         const size_t slot_frags = (size_t)cslot * M.Hkv * M.ctx_pad * HD / DT::EPL;   // 16-byte fragments per cache
         float* out = M.att_part + (size_t)ucanon * G * kRows * (HD + kPartRow);
-        if (G == 4) attention_unit_staged<DT, HD, 4>(M, Ly, M.Q_hi, M.Q_lo, slot_frags, kvh, c, L, k, row0, out, smem);
-        else if (G == 8) attention_unit_staged<DT, HD, 8>(M, Ly, M.Q_hi, M.Q_lo, slot_frags, kvh, c, L, k, row0, out, smem);
+        if constexpr (STAGED != 0) attention_unit_staged<DT, HD, STAGED>(M, Ly, M.Q_hi, M.Q_lo, slot_frags, kvh, c, L, k, row0, out, smem);
         else attention_unit<DT, HD>(M, Ly, M.Q_hi, M.Q_lo, slot_frags, kvh, c, L, k, row0, out, smem);
     }
     prefetch_retire();
@@ -971,7 +970,13 @@ __device__ __forceinline__ void stage_accept(const DevModel& M, const PassArgs& 
 
 AMUSD_STAGE_KERNEL(k_embed, (stage_embed<DT>(M, gain, P, blockIdx.x, gridDim.x)))
 AMUSD_STAGE_KERNEL(k_qkv, (stage_qkv<DT, ONE>(M, Ly, P, blockIdx.x, gridDim.x, smem)))
-AMUSD_STAGE_KERNEL(k_attention, (stage_attention<DT, HD, ONE>(M, Ly, P, blockIdx.x, gridDim.x, smem)))
+// The three forms of the attention unit are a kernel each.  As branches of one kernel they gave each other the registers
+// and LDS of the largest (128 KiB for head_dim 128: nothing of another model's pass fits beside a workgroup of it): a group
+// of 8 heads, verify model of 8 layers beside a draft model on another stream, 300 tokens 652 ms against 647 apart (648.5
+// with all in the register form); 8 sequences of the 1B shape 912 us a pass against 898.
+AMUSD_STAGE_KERNEL(k_attention, (stage_attention<DT, HD, ONE, 0>(M, Ly, P, blockIdx.x, gridDim.x, smem)))
+AMUSD_STAGE_KERNEL(k_attention_g4, (stage_attention<DT, HD, ONE, 4>(M, Ly, P, blockIdx.x, gridDim.x, smem)))
+AMUSD_STAGE_KERNEL(k_attention_g8, (stage_attention<DT, HD, ONE, 8>(M, Ly, P, blockIdx.x, gridDim.x, smem)))
 AMUSD_STAGE_KERNEL(k_attn_merge, (stage_attn_merge<DT, HD, ONE>(M, P, blockIdx.x, gridDim.x)))
 AMUSD_STAGE_KERNEL(k_oproj, (stage_oproj<DT>(M, Ly, P, blockIdx.x, gridDim.x, smem)))
 AMUSD_STAGE_KERNEL(k_gateup, (stage_gateup<DT>(M, Ly, P, blockIdx.x, gridDim.x, smem)))
@@ -1096,8 +1101,8 @@ hipError_t launch_stream_chain(const uint4* buf, size_t buf_words, size_t words_
 
 // ---------------------------------------------------------------- pass launch
 constexpr size_t kSmemBytes = (size_t)kSmemFloats * sizeof(float);
-template <class DT, int HD>
-constexpr size_t kAttSmemBytes = kSmemBytes > (size_t)AttStaged<DT, HD, 4>::kStagedBytes ? kSmemBytes : (size_t)AttStaged<DT, HD, 4>::kStagedBytes;
+template <class DT, int HD, int G>
+constexpr size_t kAttSmemBytes = kSmemBytes > (size_t)AttStaged<DT, HD, G>::kStagedBytes ? kSmemBytes : (size_t)AttStaged<DT, HD, G>::kStagedBytes;
 
 template <class DT, int HD>
 static hipError_t configure_one() {
@@ -1107,13 +1112,17 @@ static hipError_t configure_one() {
                             (int)(bytes));                                                                        \
     if (e != hipSuccess) return e;
     AMUSD_SET(k_qkv, kSmemBytes)
-    AMUSD_SET(k_attention, (kAttSmemBytes<DT, HD>))
+    AMUSD_SET(k_attention, kSmemBytes)
+    AMUSD_SET(k_attention_g4, (kAttSmemBytes<DT, HD, 4>))
+    AMUSD_SET(k_attention_g8, (kAttSmemBytes<DT, HD, 8>))
 #define AMUSD_SET_ONE(kern, bytes)                                                                                 \
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&kern<DT, HD, true>),                                     \
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)(bytes));                              \
     if (e != hipSuccess) return e;
     AMUSD_SET_ONE(k_qkv, kSmemBytes)
-    AMUSD_SET_ONE(k_attention, (kAttSmemBytes<DT, HD>))
+    AMUSD_SET_ONE(k_attention, kSmemBytes)
+    AMUSD_SET_ONE(k_attention_g4, (kAttSmemBytes<DT, HD, 4>))
+    AMUSD_SET_ONE(k_attention_g8, (kAttSmemBytes<DT, HD, 8>))
 #undef AMUSD_SET_ONE
     AMUSD_SET(k_oproj, kSmemBytes)
     AMUSD_SET(k_gateup, kSmemBytes)
@@ -1174,7 +1183,9 @@ static hipError_t launch_pass_t(const DevModel& M, const DevLayer* Ls, const Pas
     for (int l = 0; l < M.n_layers; ++l) {
         const float* gain_next = l + 1 < M.n_layers ? Ls[l + 1].g_attn : M.g_final;
         AMUSD_LAUNCH_SEQ(1, k_qkv, qkv_wgs, blk, kSmemBytes, l)
-        AMUSD_LAUNCH_SEQ(2, k_attention, att_wgs, blk, (kAttSmemBytes<DT, HD>), l)
+        if (M.G == 4) { AMUSD_LAUNCH_SEQ(2, k_attention_g4, att_wgs, blk, (kAttSmemBytes<DT, HD, 4>), l) }
+        else if (M.G == 8) { AMUSD_LAUNCH_SEQ(2, k_attention_g8, att_wgs, blk, (kAttSmemBytes<DT, HD, 8>), l) }
+        else { AMUSD_LAUNCH_SEQ(2, k_attention, att_wgs, blk, kSmemBytes, l) }
         AMUSD_LAUNCH_SEQ(3, k_attn_merge, merge_wgs, dim3(64), 0, l)
         AMUSD_LAUNCH(4, k_oproj, d_wgs, kSmemBytes, l, nogain)
         AMUSD_LAUNCH(5, k_gateup, gu_wgs, kSmemBytes, l, nogain)

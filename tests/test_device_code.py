@@ -128,3 +128,17 @@ def test_stores_of_a_chunk_are_as_many_as_its_waits_count(prefill):
         later = {op.split()[0] for op in body[first:] if re.match(r"(global|buffer|flat)_load", op)}
         assert later == {"global_load_lds_dwordx4"}, name
     assert seen == 8
+
+
+def test_one_form_of_attention_per_kernel(tmp_path):
+    """Forms of the attention unit that share a kernel also share the largest one's registers and LDS."""
+    kernels = _compile(os.path.join(ROOT, "paper_2410_17375_amd", "csrc", "amusd_kernels.hip"), tmp_path / "kernels.s")
+    forms = {name: {m.group(0) for op in body for m in re.finditer(r"^global_load_lds_dwordx4|^global_load_dwordx4", op)}
+             for name, body in kernels.items() if re.search(r"\d+k_attention(_g[48])?I", name)}
+    assert len(forms) == 24                    # 3 forms x 2 types x 2 head dims x (one sequence, several)
+    for name, loads in forms.items():
+        staged = "global_load_lds_dwordx4" in loads
+        assert staged == ("k_attention_g" in name), name
+    units = {name: sum("ds_write_b128" in op for op in body) for name, body in kernels.items() if name in forms}
+    for name, writes in units.items():         # the runs' numerators go to LDS once, in the form's own merge
+        assert writes == (8 if "ELi128E" in name else 4), (name, writes)
