@@ -728,15 +728,17 @@ int amusd_seq_prefill(amusd_model* m, int32_t seq, const int32_t* tokens, int32_
     // 16-bit models run fastest with at most 8 rows per pass (hi and lo halves share one operand fragment)
     const int chunk = m->cfg.dtype == AMUSD_DTYPE_BF16 && m->cfg.max_k > 8 ? 8 : m->cfg.max_k;
     const int len_before = q.kv_len, next_before = q.p_next;
-    // Prompts go through the prefill pass, in stretches of about equal length; what one verify pass holds, and with a stage
-    // of the verify pass selected for timing everything, through the verify pass.  The last group of rows is the same either
-    // way.  (8B shape, 4 layers: 9 tokens 0.81 ms in two verify passes, 0.60 in one prefill pass.)
+    // Prompts go through the prefill pass, in stretches of whole row blocks; what one verify pass holds, and with a stage of
+    // the verify pass selected for timing everything, through the verify pass.  The last group of rows, the one whose logits
+    // and tokens can be asked for, is the verify pass's, so the last stretch holds at least that many.  (8B shape, 4 layers:
+    // 9 tokens 0.81 ms in two verify passes, 0.60 in one prefill pass.)
     if (n > chunk && m->pf.cap && m->timer.stage < 0) {
         const int tail = (n - 1) % chunk + 1, passes = (n + m->pf.cap - 1) / m->pf.cap;
         const int per = passes == 1 ? n : ((n + passes - 1) / passes + kPfBlockRows - 1) / kPfBlockRows * kPfBlockRows;
-        for (int s = 0; s < n; s += per) {
-            const int k = n - s < per ? n - s : per;
-            if ((rc = run_prefill(m, seq, q.kv_len, tokens + s, k, tail < k ? tail : k))) {
+        for (int s = 0, k; s < n; s += k) {
+            k = n - s < per ? n - s : per;
+            if (n - s - k > 0 && n - s - k < tail) k -= kRows;
+            if ((rc = run_prefill(m, seq, q.kv_len, tokens + s, k, tail))) {
                 q.kv_len = len_before;
                 q.p_next = next_before;
                 return rc;

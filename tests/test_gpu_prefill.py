@@ -97,3 +97,25 @@ def test_prefill_pass_into_second_sequence_and_stage_timing():
     assert ms[0].seq_len(0) == 0 and ms[0].last_pass_ms() > 0
     for m in ms:
         m.free()
+
+
+@pytest.mark.parametrize("max_k,n", [(7, 30721), (5, 32769), (3, 2050), (13, 61)])
+def test_last_group_of_rows_is_kept_whole_for_any_max_k(max_k, n):
+    """A long prompt goes through in stretches; its last group of rows, the last (n - 1) % group + 1 with groups of max_k,
+    is in one of them."""
+    import paper_2410_17375_amd as A
+    from paper_2410_17375_amd.harness import load_model
+    shape = SHAPES["tiny_draft"]
+    store = WeightStore(shape)
+    a, b = (load_model(shape, n + 20, max_k=max_k, store=store) for _ in range(2))
+    toks = prompt_tokens(33, n, shape.vocab)
+    rows = (n - 1) % max_k + 1
+    for m in (a, b):
+        m.set_option(A.OPT_KEEP_LOGITS, 1)
+    nxt = a.prefill(toks)
+    b.prefill(toks[:n - rows])
+    assert b.prefill(toks[n - rows:]) == nxt               # at most max_k tokens: one verify pass
+    assert np.array_equal(a.get_greedy(rows), b.get_greedy(rows))
+    assert np.array_equal(_bits(a.get_logits(rows)), _bits(b.get_logits(rows)))
+    a.free()
+    b.free()
