@@ -33,7 +33,8 @@ struct AttState {
 // them.  first: the run's first step (the numerators are zero).
 // Two blocks per step: a block's 8 scores per lane cost one rescaling of all numerators and two reductions across lanes,
 // and its products are short chains; two share the former and fill the gaps of the latter.  Groups of 4 and 8 heads take
-// two (always the same two of a run, visible or not), groups of 1 and 2 one.
+// two (always the same two of a run), groups of 1 and 2 one.  A second block without a visible key is left out: it would add
+// zeros, but what rolled-back rows have left in it may be no number, and zero times that is none either.
 template <class DT, int HD, int NB, bool MASKED, class KF, class VF>
 __device__ __forceinline__ void attention_step(AttState<HD>& s, const uint4* qh, const uint4* ql, KF&& kf, VF&& vf, int p0, int lim,
                                                int g, float scale, bool first) {
@@ -318,7 +319,7 @@ __device__ __forceinline__ void attention_unit_staged(const DevModel& M, const D
         auto vf = [&](int b, int j) { return *reinterpret_cast<const uint4*>(at + (b * NF + C::TPB * FR + j) * 1024); };
         const int p0 = (b0 + 2 * st) * BK;
         if (p0 < T) {                                    // wave-uniform
-            if (2 * st + 1 >= bpw) attention_step<DT, HD, 1, true>(s, qh, ql, kf, vf, p0, lim, g, M.att_scale, st == 0);
+            if (2 * st + 1 >= bpw || p0 + BK >= T) attention_step<DT, HD, 1, true>(s, qh, ql, kf, vf, p0, lim, g, M.att_scale, st == 0);
             else if (p0 + 2 * BK - 1 > L) attention_step<DT, HD, 2, true>(s, qh, ql, kf, vf, p0, lim, g, M.att_scale, st == 0);
             else attention_step<DT, HD, 2, false>(s, qh, ql, kf, vf, p0, lim, g, M.att_scale, st == 0);
         }

@@ -795,8 +795,6 @@ __global__ void __launch_bounds__(64 * G, 2) k_pf_attention(DevModel M, DevLayer
     const char* kc = reinterpret_cast<const char*>(Ly.kcache) + slot_bytes + kvh * head_bytes;
     const char* vc = reinterpret_cast<const char*>(Ly.vcache) + slot_bytes + kvh * head_bytes;
     const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
-    const int last_in_run = (nb - 1) % M.bpw;
-    const int total = nb + (last_in_run % 2 == 0 && last_in_run + 1 < M.bpw);   // blocks to fetch: steps are whole
     int next = 0, nslot = 0;
     auto issue = [&]() {                                  // block b0 + next
         const int b = b0 + next;
@@ -824,7 +822,7 @@ __global__ void __launch_bounds__(64 * G, 2) k_pf_attention(DevModel M, DevLayer
 #pragma unroll
     for (int i = 0; i < FR; ++i)
         asm volatile("" : "+v"(qh[i].x), "+v"(qh[i].y), "+v"(qh[i].z), "+v"(qh[i].w), "+v"(ql[i].x), "+v"(ql[i].y), "+v"(ql[i].z), "+v"(ql[i].w));
-    for (int s = 0; s < SLOTS && s < total; ++s) issue();
+    for (int s = 0; s < SLOTS && s < nb; ++s) issue();
 
     AttState<HD> s, s0;                                   // the run at hand; the chunk's first run once it is done
     s.clear();
@@ -852,13 +850,13 @@ __global__ void __launch_bounds__(64 * G, 2) k_pf_attention(DevModel M, DevLayer
     };
     int freed = 0;                                        // ring slots whose blocks the step before used
     for (int ib = 0; ib < nb;) {
-        const int two = run + 1 < M.bpw ? 2 : 1;          // blocks of this step
+        const int two = run + 1 < M.bpw && ib + 1 < nb ? 2 : 1;   // blocks of this step
         __builtin_amdgcn_s_waitcnt(0xC07F);               // no LDS read of the step before is pending
         wait_blocks(next - ib - two, older >= two);
         older -= two;
         __builtin_amdgcn_s_barrier();                     // .. of all waves; and all are done with the step before
         asm volatile("" ::: "memory");
-        for (int x = 0; x < freed && next < total; ++x) issue();
+        for (int x = 0; x < freed && next < nb; ++x) issue();
         freed = two;
         const char* slot0 = smem + cslot * C::kSlotBytes + lane * 16;
         cslot = cslot + 1 == SLOTS ? 0 : cslot + 1;

@@ -4,7 +4,7 @@ The sizes put the edges of its row and column tiles, its workgroup shapes and th
 import numpy as np
 import pytest
 
-from workload import SHAPES, WeightStore, prompt_tokens
+from workload import GLOBAL_TENSORS, LAYER_TENSORS, SHAPES, WeightStore, prompt_tokens
 
 pytestmark = pytest.mark.gpu
 
@@ -119,3 +119,45 @@ def test_last_group_of_rows_is_kept_whole_for_any_max_k(max_k, n):
     assert np.array_equal(_bits(a.get_logits(rows)), _bits(b.get_logits(rows)))
     a.free()
     b.free()
+
+
+def test_rolled_back_rows_without_a_value_do_not_reach_rows_before_their_block():
+    """A float32 cache may hold rolled-back rows that are not numbers.  A key block that no row of a pass sees is not
+    multiplied, be the block before it visible or not; the cache's blocks are 16 keys and the unit's steps two of them."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2410_17375_amd as A
+    shape = SHAPES["tiny_gqa_fp32"]
+    store = WeightStore(shape)
+    bad = 7
+    embed = np.array(store.bits("embed", None), copy=True)
+    embed[bad] = np.inf                                   # its keys and values are not numbers
+    toks = prompt_tokens(34, 100, shape.vocab)
+    toks[toks == bad] = bad + 1
+    seen = []
+    for poison in (False, True):
+        m = A.Model(n_layers=shape.n_layers, d_model=shape.d_model, n_q_heads=shape.n_q_heads, n_kv_heads=shape.n_kv_heads,
+                    head_dim=shape.head_dim, d_ffn=shape.d_ffn, vocab=shape.vocab, max_ctx=4200, dtype=A.DTYPE_FP32,
+                    rope_theta=shape.rope_theta, rms_eps=shape.rms_eps)      # runs of two blocks, chunks of 64 keys
+        for layer in [None] + list(range(shape.n_layers)):
+            for name in GLOBAL_TENSORS if layer is None else LAYER_TENSORS:
+                m.set_tensor(name, layer, embed if name == "embed" else store.bits(name, layer))
+        m.finalize()
+        m.set_option(A.OPT_KEEP_LOGITS, 1)
+        m.prefill(toks[:80])
+        if poison:
+            m.prefill(np.full(10, bad, dtype=np.int32))   # positions 80 .. 89
+            assert not np.isfinite(m.get_kv(1, 1, 80, 10)).any()
+        m.kv_rollback(60)
+        m.prefill(toks[60:80])                            # a prefill pass: rows 60 .. 75 and 76 .. 79
+        got = [_bits(m.get_logits(4))]
+        m.kv_rollback(64)
+        m.set_next(int(toks[64]))
+        m.verify(64, toks[64:72])
+        got.append(_bits(m.get_logits(8)))
+        seen.append(got)
+        m.free()
+    assert np.isfinite(seen[0][0].view(np.float32)).all() and np.isfinite(seen[0][1].view(np.float32)).all()
+    assert np.array_equal(seen[0][1], seen[1][1])         # the verify pass
+    assert np.array_equal(seen[0][0], seen[1][0])         # the prefill pass
