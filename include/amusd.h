@@ -78,7 +78,8 @@ enum {
 /* Options for amusd_set_option. */
 enum {
     AMUSD_OPT_KEEP_LOGITS = 0, /* 1: each pass also stores its fp32 logits (test hook), default 0 */
-    AMUSD_OPT_TIME_STAGE = 2    /* AMUSD_STAGE_* to bracket with HIP events in every pass, -1: none (default) */
+    AMUSD_OPT_TIME_STAGE = 2,   /* AMUSD_STAGE_* to bracket with HIP events in every pass, -1: none (default) */
+    AMUSD_OPT_PREFILL_WORKSPACE = 3 /* 0: gives the prefill workspace back (amusd_prefill), 1: takes it (default) */
 };
 
 /* Stages of a pass, for AMUSD_OPT_TIME_STAGE / amusd_stage_time. */
@@ -150,8 +151,14 @@ int amusd_model_free(amusd_model *m);
  * tokens (host array) at
  * positions kv_len .. kv_len+n-1 unconditionally, several rows per pass, and
  * returns in *next_token the greedy token after the last one.  next_token may
- * be NULL.  Errors: ARG, TOKEN, CAPACITY. */
+ * be NULL.  Errors: ARG, TOKEN, CAPACITY.
+ * A prompt of more tokens than a verify pass is given (max_k, with 16-bit weights at most 8) goes through up to
+ * 2048 rows at a time, in a workspace that the model holds (amusd_prefill_workspace_bytes).  A model that finds no
+ * memory for it, or is told to hold none, takes its prompts in verify passes instead: the same bits, 4 to 14 times
+ * the time.  So does a prompt while AMUSD_OPT_TIME_STAGE selects a stage. */
 int amusd_prefill(amusd_model *m, const int32_t *tokens, int32_t n, int32_t *next_token);
+/* Device memory of the model's prefill workspace (0: it holds none; a negative error code if m is NULL). */
+int64_t amusd_prefill_workspace_bytes(const amusd_model *m);
 
 /* VerifyTokens + mismatch test + cache update (Algorithm 1, VerifyProcess).
  * First truncates the cache to ctx_len (must be in [0, kv_len]; at ctx_len = 0 the model's token for

@@ -15,7 +15,7 @@ _LIB_PATH = os.environ.get("AMUSD_LIBRARY") or os.path.join(_HERE, "libamusd.so"
 
 DTYPE_FP32, DTYPE_BF16 = 0, 1
 MAX_K = 16
-OPT_KEEP_LOGITS, OPT_TIME_STAGE = 0, 2
+OPT_KEEP_LOGITS, OPT_TIME_STAGE, OPT_PREFILL_WORKSPACE = 0, 2, 3
 STAGES = {"embed": 0, "qkv": 1, "attention": 2, "attn_merge": 3, "oproj": 4, "gateup": 5, "down": 6,
           "lmhead": 7, "accept": 8}
 TENSOR_IDS = {"embed": 0, "lm_head": 1, "final_norm": 2, "wq": 3, "wk": 4, "wv": 5, "wo": 6,
@@ -75,6 +75,7 @@ def _load():
         "amusd_verify": (C.c_int, [vp, i32, i32p, i32, i32p, i32p]),
         "amusd_verify_static": (C.c_int, [vp, i32, i32p, i32, i32p, i32p]),
         "amusd_static_scratch_bytes": (C.c_int64, [vp]),
+        "amusd_prefill_workspace_bytes": (C.c_int64, [vp]),
         "amusd_draft_step": (C.c_int, [vp, i32p]),
         "amusd_kv_rollback": (C.c_int, [vp, i32]),
         "amusd_set_next": (C.c_int, [vp, i32]),
@@ -178,6 +179,9 @@ class Model:
 
     def static_scratch_bytes(self):
         return int(lib.amusd_static_scratch_bytes(self._h))
+
+    def prefill_workspace_bytes(self):
+        return int(lib.amusd_prefill_workspace_bytes(self._h))
 
     def draft_step(self):
         t = C.c_int32(-1)

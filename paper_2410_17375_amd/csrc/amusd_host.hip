@@ -106,6 +106,8 @@ struct amusd_model {
     uint64_t id = 0;
     HostStage* hstage = nullptr;
     PrefillBufs pf{};                      // workspace of the prefill pass; cap 0: prompts go through the verify pass
+    void* pf_mem = nullptr;                // the device allocation that its buffers are in
+    size_t pf_bytes = 0;
     int* pf_host = nullptr;                // pinned: tokens of a prefill pass, then its greedy tokens
     void* staging = nullptr;               // device staging for host-provided tensors
     size_t staging_bytes = 0;
@@ -287,11 +289,21 @@ int run_pass(amusd_model* m, const SegReq* segs, int n_seg, bool force_accept, b
     return AMUSD_OK;
 }
 
-// Workspace of the prefill pass, sized for the model's context.  A model that finds no memory for it prefills through
-// the verify pass.
-int alloc_prefill(amusd_model* m) {
+// Gives the prefill workspace back: prompts go through the verify pass from here on.
+void release_prefill(amusd_model* m) {
+    if (m->pf_mem) (void)hipFree(m->pf_mem);
+    if (m->pf_host) (void)hipHostFree(m->pf_host);
+    m->pf_mem = nullptr;
+    m->pf_host = nullptr;
+    m->pf_bytes = 0;
+    m->pf = PrefillBufs{};
+}
+
+// Takes the workspace of the prefill pass, sized for the model's context: one device allocation and a pinned block for
+// tokens.  Without the memory for it the model has none (m->pf.cap is 0); any other error is the caller's.
+int take_prefill(amusd_model* m) {
     const DevModel& D = m->dm;
-    if (D.max_ctx <= 1) return AMUSD_OK;
+    if (D.max_ctx <= 1 || m->pf.cap) return AMUSD_OK;
     PrefillBufs T{};
     T.cap = D.max_ctx >= kPfMaxRows ? kPfMaxRows : (D.max_ctx + kPfBlockRows - 1) / kPfBlockRows * kPfBlockRows;
     T.cus = m->nwg;
@@ -300,54 +312,65 @@ int alloc_prefill(amusd_model* m) {
     T.att_tiles = (int)(kPfPartBytes / tile_bytes);
     if (T.att_tiles < 1) T.att_tiles = 1;
     if (T.att_tiles > T.cap / 16) T.att_tiles = T.cap / 16;
-    const size_t first = m->allocs.size();
-    std::vector<int> order;
-    int rc = AMUSD_OK;
-    void* p = nullptr;
-    auto get = [&](size_t bytes) -> void* {
-        if (rc == AMUSD_OK) rc = dev_alloc(m, &p, bytes, false);
-        return rc == AMUSD_OK ? p : nullptr;
-    };
-    for (int s = 0; s < kPfStages && rc == AMUSD_OK; ++s) {
-        prefill_tile_order(D, s, m->nwg, order, &T.tiles[s].wgs);
-        T.tiles[s].n = (int)order.size();
-        int* dst = static_cast<int*>(get(order.size() * 4));
-        T.tiles[s].order = dst;
-        if (dst && hipMemcpy(dst, order.data(), order.size() * 4, hipMemcpyHostToDevice) != hipSuccess)
-            rc = fail(AMUSD_E_HIP, "tile order upload");
+    std::vector<int> orders, one;                  // the stages' tile orders back to back
+    size_t start[kPfStages];
+    try {
+        for (int s = 0; s < kPfStages; ++s) {
+            prefill_tile_order(D, s, m->nwg, one, &T.tiles[s].wgs);
+            T.tiles[s].n = (int)one.size();
+            start[s] = orders.size();
+            orders.insert(orders.end(), one.begin(), one.end());
+        }
+    } catch (const std::bad_alloc&) {
+        return fail(AMUSD_E_NOMEM, "tile orders of the prefill pass");
     }
-    T.X = static_cast<float*>(get(cap * d * 4));
-    T.A = get(cap * d * 4);
-    T.O = get(cap * q * 4);
-    T.H = get(cap * F * 4);
-    T.Q_hi = get(cap * q * 4);
-    T.Q_lo = get(cap * q * 4);
-    T.ssq = static_cast<float*>(get(d / 16 * cap * 4));
-    T.rstd = static_cast<float*>(get(cap * 4));
-    T.att_part = static_cast<float*>(get(T.att_tiles * tile_bytes));
     // the down projection's first totals; beyond that room for shared tiles, as far as 16 sums per element of a small pass go
     T.xch_bytes = D.split_down ? cap * T.tiles[kPfDown].n * 16 * 4 : 0;
     const size_t widest = (size_t)std::max(T.tiles[kPfQKV].n, T.tiles[kPfDown].n) * 16;
     T.xch_bytes = std::max(T.xch_bytes, std::min(kPfShareBytes, 16 * cap * widest * 4));
-    T.xch = static_cast<float*>(get(T.xch_bytes));
-    T.ticket = static_cast<int*>(get(kPfTickets * 4));
-    T.best_val = static_cast<float*>(get(cap * T.tiles[kPfLMHead].n / 2 * 4));
-    T.best_idx = static_cast<int*>(get(cap * T.tiles[kPfLMHead].n / 2 * 4));
-    if (rc == AMUSD_OK && hipHostMalloc(reinterpret_cast<void**>(&m->pf_host), 2 * cap * 4, hipHostMallocDefault) != hipSuccess)
-        rc = fail(AMUSD_E_HIP, "pinned prefill buffer");
-    if (rc == AMUSD_OK) {
-        void* dev = nullptr;
-        if (hipHostGetDevicePointer(&dev, m->pf_host, 0) != hipSuccess) rc = fail(AMUSD_E_HIP, "device address of the pinned prefill buffer");
-        T.tokens = static_cast<const int*>(dev);
-        T.greedy = static_cast<int*>(dev) + cap;
+    int* dev_orders = nullptr;
+    auto layout = [&](uintptr_t base) {            // sets the pointers, returns the bytes
+        size_t off = 0;
+        auto place = [&](size_t bytes) {
+            void* p = reinterpret_cast<void*>(base + off);
+            off += (bytes + 4095) & ~(size_t)4095;
+            return p;
+        };
+        dev_orders = static_cast<int*>(place(orders.size() * 4));
+        T.X = static_cast<float*>(place(cap * d * 4));
+        T.A = place(cap * d * 4);
+        T.O = place(cap * q * 4);
+        T.H = place(cap * F * 4);
+        T.Q_hi = place(cap * q * 4);
+        T.Q_lo = place(cap * q * 4);
+        T.ssq = static_cast<float*>(place(d / 16 * cap * 4));
+        T.rstd = static_cast<float*>(place(cap * 4));
+        T.att_part = static_cast<float*>(place(T.att_tiles * tile_bytes));
+        T.xch = static_cast<float*>(place(T.xch_bytes));
+        T.ticket = static_cast<int*>(place(kPfTickets * 4));
+        T.best_val = static_cast<float*>(place(cap * T.tiles[kPfLMHead].n / 2 * 4));
+        T.best_idx = static_cast<int*>(place(cap * T.tiles[kPfLMHead].n / 2 * 4));
+        return off;
+    };
+    const size_t bytes = layout(0);
+    hipError_t e = hipMalloc(&m->pf_mem, bytes);
+    if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&m->pf_host), 2 * cap * 4, hipHostMallocDefault);
+    void* host_dev = nullptr;
+    if (e == hipSuccess) e = hipHostGetDevicePointer(&host_dev, m->pf_host, 0);
+    if (e == hipSuccess) {
+        layout(reinterpret_cast<uintptr_t>(m->pf_mem));
+        e = hipMemcpy(dev_orders, orders.data(), orders.size() * 4, hipMemcpyHostToDevice);
     }
-    if (rc != AMUSD_OK) {
-        for (size_t i = first; i < m->allocs.size(); ++i) (void)hipFree(m->allocs[i]);
-        m->allocs.resize(first);
+    if (e != hipSuccess) {
+        release_prefill(m);
         (void)hipGetLastError();
-        return AMUSD_OK;
+        return e == hipErrorOutOfMemory ? AMUSD_OK : fail(AMUSD_E_HIP, std::string("prefill workspace: ") + hipGetErrorString(e));
     }
+    for (int s = 0; s < kPfStages; ++s) T.tiles[s].order = dev_orders + start[s];
+    T.tokens = static_cast<const int*>(host_dev);
+    T.greedy = static_cast<int*>(host_dev) + cap;
     m->pf = T;
+    m->pf_bytes = bytes;
     return AMUSD_OK;
 }
 
@@ -584,7 +607,7 @@ int amusd_model_create(const amusd_config* cfg, void* hip_stream, amusd_model** 
         S.best_idx = static_cast<int*>(place((size_t)m->nwg * kRows * 4));
         m->static_bytes = off;      // may exceed the array: amusd_verify_static then refuses the model
     }
-    if ((rc = alloc_prefill(m)) != AMUSD_OK) return bail(rc);
+    if ((rc = take_prefill(m)) != AMUSD_OK) return bail(rc);
     if (hipStreamSynchronize(m->stream) != hipSuccess) return bail(fail(AMUSD_E_HIP, "create: stream sync"));
     *out = m;
     return AMUSD_OK;
@@ -709,7 +732,7 @@ int amusd_model_free(amusd_model* m) {
     for (void* p : m->allocs) (void)hipFree(p);
     if (m->staging) (void)hipFree(m->staging);
     if (m->hstage) (void)hipHostFree(m->hstage);
-    if (m->pf_host) (void)hipHostFree(m->pf_host);
+    release_prefill(m);
     if (m->ev0) (void)hipEventDestroy(m->ev0);
     if (m->ev1) (void)hipEventDestroy(m->ev1);
     for (hipEvent_t e : m->tev_begin) if (e) (void)hipEventDestroy(e);
@@ -920,8 +943,22 @@ int amusd_set_option(amusd_model* m, int32_t option, int32_t value) {
             m->stage_launches = 0;
             return AMUSD_OK;
         }
+        case AMUSD_OPT_PREFILL_WORKSPACE: {
+            if (!value) {
+                release_prefill(m);
+                return AMUSD_OK;
+            }
+            const int rc = take_prefill(m);
+            if (rc == AMUSD_OK && !m->pf.cap && m->dm.max_ctx > 1) return fail(AMUSD_E_HIP, "no device memory for the prefill workspace");
+            return rc;
+        }
         default: return fail(AMUSD_E_ARG, "unknown option");
     }
+}
+
+int64_t amusd_prefill_workspace_bytes(const amusd_model* m) {
+    if (!m) return fail(AMUSD_E_ARG, "null model");
+    return (int64_t)m->pf_bytes;
 }
 
 int amusd_get_logits(amusd_model* m, float* out, int32_t rows) {

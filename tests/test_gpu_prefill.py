@@ -161,3 +161,30 @@ def test_rolled_back_rows_without_a_value_do_not_reach_rows_before_their_block()
     assert np.isfinite(seen[0][0].view(np.float32)).all() and np.isfinite(seen[0][1].view(np.float32)).all()
     assert np.array_equal(seen[0][1], seen[1][1])         # the verify pass
     assert np.array_equal(seen[0][0], seen[1][0])         # the prefill pass
+
+
+@pytest.mark.parametrize("name,over,before,n", [("tiny_gqa_bf16", {}, 7, 300), ("tiny_gqa_fp32", {}, 0, 70),
+                                                ("one_layer_8b_width_bf16", {"vocab": 4096}, 0, 45)])
+def test_prompts_without_the_workspace(name, over, before, n):
+    """What a model does that has no memory for the workspace: the same through verify passes; and back again."""
+    import paper_2410_17375_amd as A
+    shape = SHAPES[name].with_(**over)
+    m, other = _models(shape, before + n + 8)
+    other.free()
+    toks = prompt_tokens(35, before + n, shape.vocab)
+    if before:
+        m.prefill(toks[:before])
+    held = m.prefill_workspace_bytes()
+    assert held > 0
+    tail = (n - 1) % (16 if shape.dtype == "fp32" else 8) + 1
+    seen = []
+    for on in (1, 0, 0, 1):
+        m.set_option(A.OPT_PREFILL_WORKSPACE, on)
+        assert m.prefill_workspace_bytes() == (held if on else 0)
+        m.kv_rollback(before)
+        nxt = m.prefill(toks[before:])
+        seen.append([np.array([nxt]), m.get_greedy(tail), _bits(m.get_logits(tail))] +
+                    [_bits(m.get_kv(layer, which, 0, before + n)) for layer in range(shape.n_layers) for which in (0, 1)])
+    for other in seen[1:]:
+        assert all(np.array_equal(x, y) for x, y in zip(seen[0], other))
+    m.free()
