@@ -90,8 +90,8 @@ struct PrefillBufs {
     void* A;              // norm-fed GEMM input, operand order
     void* O;              // attention output, operand order
     void* H;              // SwiGLU output, operand order
-    void* Q_hi;           // [cap][qdim]
-    void* Q_lo;
+    void* Q_hi;           // [cap][qdim] elements of the attention's type
+    void* Q_lo;           // 16-bit models: the low halves
     float* ssq;           // [d/16][cap]
     float* rstd;          // [cap]
     float* att_part;

@@ -341,8 +341,8 @@ int take_prefill(amusd_model* m) {
         T.A = place(cap * d * 4);
         T.O = place(cap * q * 4);
         T.H = place(cap * F * 4);
-        T.Q_hi = place(cap * q * 4);
-        T.Q_lo = place(cap * q * 4);
+        T.Q_hi = place(cap * q * m->esz());
+        T.Q_lo = place(m->cfg.dtype == AMUSD_DTYPE_BF16 ? cap * q * m->esz() : 0);
         T.ssq = static_cast<float*>(place(d / 16 * cap * 4));
         T.rstd = static_cast<float*>(place(cap * 4));
         T.att_part = static_cast<float*>(place(T.att_tiles * tile_bytes));

@@ -188,3 +188,19 @@ def test_prompts_without_the_workspace(name, over, before, n):
     for other in seen[1:]:
         assert all(np.array_equal(x, y) for x, y in zip(seen[0], other))
     m.free()
+
+
+@pytest.mark.parametrize("name", ["tiny_gqa_bf16", "tiny_gqa_fp32"])
+def test_workspace_holds_no_more_than_its_buffers(name):
+    s = SHAPES[name]
+    m, other = _models(s, 360)
+    other.free()
+    cap, units = 384, 256 // s.n_kv_heads                  # rows in whole blocks of 128; chunks that a full context is cut into at most
+    runs, keys = 8 // s.group, 16 if s.dtype == "fp32" else 32
+    chunks = -(-360 // (runs * keys * -(-360 // (units * runs * keys))))
+    rows = 4 * (2 * s.d_model + s.q_dim + s.d_ffn) + 4 * s.q_dim + s.d_model // 4 + 4      # activations, queries, sums of squares
+    qkv, lm = -(-(s.q_dim + 2 * s.kv_dim) // 256) * 16, -(-s.vocab // 256) * 16              # column tiles, in groups of 16
+    sums = 16 * cap * max(qkv, -(-s.d_model // 256) * 16) * 64
+    expect = cap * rows + cap // 16 * s.n_kv_heads * chunks * s.group * 16 * (s.head_dim + 4) * 4 + min(sums, 64 << 20) + 4 * 4096 + 4 * cap * lm
+    assert m.prefill_workspace_bytes() <= expect + 20 * 4096       # alignment, and the tile orders
+    m.free()
