@@ -79,7 +79,8 @@ enum {
 enum {
     AMUSD_OPT_KEEP_LOGITS = 0, /* 1: each pass also stores its fp32 logits (test hook), default 0 */
     AMUSD_OPT_TIME_STAGE = 2,   /* AMUSD_STAGE_* to bracket with HIP events in every pass, -1: none (default) */
-    AMUSD_OPT_PREFILL_WORKSPACE = 3 /* 0: gives the prefill workspace back (amusd_prefill), 1: takes it (default) */
+    AMUSD_OPT_PREFILL_WORKSPACE = 3 /* 0: the prefill workspace (amusd_prefill) is given back, or not taken by finalize;
+                                       1: taken (default; HIP error if there is no memory for it) */
 };
 
 /* Stages of a pass, for AMUSD_OPT_TIME_STAGE / amusd_stage_time. */
@@ -136,7 +137,7 @@ int amusd_model_create(const amusd_config *cfg, void *hip_stream, amusd_model **
  * of exactly the tensor's size; it is not referenced after the call returns. */
 int amusd_model_set_tensor(amusd_model *m, int32_t tensor_id, int32_t layer, const void *data, int32_t on_device);
 
-/* Checks that every tensor has been set and makes the model usable.
+/* Checks that every tensor has been set, takes the prefill workspace (amusd_prefill) and makes the model usable.
  * AMUSD_E_STATE names a missing tensor through amusd_last_error. */
 int amusd_model_finalize(amusd_model *m);
 
@@ -153,9 +154,11 @@ int amusd_model_free(amusd_model *m);
  * returns in *next_token the greedy token after the last one.  next_token may
  * be NULL.  Errors: ARG, TOKEN, CAPACITY.
  * A prompt of more tokens than a verify pass is given (max_k, with 16-bit weights at most 8) goes through up to
- * 2048 rows at a time, in a workspace that the model holds (amusd_prefill_workspace_bytes).  A model that finds no
- * memory for it, or is told to hold none, takes its prompts in verify passes instead: the same bits, 4 to 14 times
- * the time.  So does a prompt while AMUSD_OPT_TIME_STAGE selects a stage. */
+ * 2048 rows at a time, in a workspace that amusd_model_finalize takes: about 0.4 GB for a 1B shape, 0.7 GB for an
+ * 8B shape, less for a max_ctx below 2048.  A model that finds no memory for it, or is told to hold none
+ * (AMUSD_OPT_PREFILL_WORKSPACE), takes its prompts in verify passes instead: the same bits, 4 to 14 times the time.
+ * So does a prompt while AMUSD_OPT_TIME_STAGE selects a stage.  When a model's weights or cache find no memory, the
+ * library gives back idle models' workspaces on that GPU; the option takes them again. */
 int amusd_prefill(amusd_model *m, const int32_t *tokens, int32_t n, int32_t *next_token);
 /* Device memory of the model's prefill workspace (0: it holds none; a negative error code if m is NULL). */
 int64_t amusd_prefill_workspace_bytes(const amusd_model *m);

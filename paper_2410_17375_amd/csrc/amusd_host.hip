@@ -108,6 +108,8 @@ struct amusd_model {
     PrefillBufs pf{};                      // workspace of the prefill pass; cap 0: prompts go through the verify pass
     void* pf_mem = nullptr;                // the device allocation that its buffers are in
     size_t pf_bytes = 0;
+    bool want_prefill = true;              // AMUSD_OPT_PREFILL_WORKSPACE
+    mutable std::mutex pf_mutex;                   // held while a prompt uses the workspace, and while it is taken or given back
     int* pf_host = nullptr;                // pinned: tokens of a prefill pass, then its greedy tokens
     void* staging = nullptr;               // device staging for host-provided tensors
     size_t staging_bytes = 0;
@@ -125,8 +127,39 @@ struct amusd_model {
 
 namespace {
 
+// Models that hold a prefill workspace.  It makes prompts faster but nothing needs it: when there is no memory for what a
+// model cannot do without, idle ones are given back, those of other models too.  (g_pf_mutex, then a model's pf_mutex, which
+// a prompt holds while it uses the workspace; a workspace in use is left alone.)
+std::mutex g_pf_mutex;
+std::vector<amusd_model*> g_pf_holders;
+
+void free_prefill(amusd_model* m) {          // with m->pf_mutex held, or no one else to use m
+    if (m->pf_mem) (void)hipFree(m->pf_mem);
+    if (m->pf_host) (void)hipHostFree(m->pf_host);
+    m->pf_mem = nullptr;
+    m->pf_host = nullptr;
+    m->pf_bytes = 0;
+    m->pf = PrefillBufs{};
+}
+
+hipError_t dev_malloc(int device, void** p, size_t bytes) {
+    hipError_t e = hipMalloc(p, bytes);
+    if (e != hipErrorOutOfMemory) return e;
+    std::lock_guard<std::mutex> lock(g_pf_mutex);
+    for (size_t i = g_pf_holders.size(); e == hipErrorOutOfMemory && i-- > 0;) {
+        amusd_model* h = g_pf_holders[i];
+        if (h->device != device || !h->pf_mutex.try_lock()) continue;
+        free_prefill(h);
+        h->pf_mutex.unlock();
+        g_pf_holders.erase(g_pf_holders.begin() + i);
+        (void)hipGetLastError();
+        e = hipMalloc(p, bytes);
+    }
+    return e;
+}
+
 int dev_alloc(amusd_model* m, void** p, size_t bytes, bool zero) {
-    HIP_TRY(hipMalloc(p, bytes ? bytes : 16));
+    HIP_TRY(dev_malloc(m->device, p, bytes ? bytes : 16));
     m->allocs.push_back(*p);
     if (zero) HIP_TRY(hipMemsetAsync(*p, 0, bytes ? bytes : 16, m->stream));
     return AMUSD_OK;
@@ -291,18 +324,18 @@ int run_pass(amusd_model* m, const SegReq* segs, int n_seg, bool force_accept, b
 
 // Gives the prefill workspace back: prompts go through the verify pass from here on.
 void release_prefill(amusd_model* m) {
-    if (m->pf_mem) (void)hipFree(m->pf_mem);
-    if (m->pf_host) (void)hipHostFree(m->pf_host);
-    m->pf_mem = nullptr;
-    m->pf_host = nullptr;
-    m->pf_bytes = 0;
-    m->pf = PrefillBufs{};
+    std::lock_guard<std::mutex> lock(g_pf_mutex);
+    std::lock_guard<std::mutex> mine(m->pf_mutex);
+    g_pf_holders.erase(std::remove(g_pf_holders.begin(), g_pf_holders.end(), m), g_pf_holders.end());
+    free_prefill(m);
 }
 
 // Takes the workspace of the prefill pass, sized for the model's context: one device allocation and a pinned block for
 // tokens.  Without the memory for it the model has none (m->pf.cap is 0); any other error is the caller's.
 int take_prefill(amusd_model* m) {
     const DevModel& D = m->dm;
+    std::lock_guard<std::mutex> lock(g_pf_mutex);
+    std::lock_guard<std::mutex> mine(m->pf_mutex);
     if (D.max_ctx <= 1 || m->pf.cap) return AMUSD_OK;
     PrefillBufs T{};
     T.cap = D.max_ctx >= kPfMaxRows ? kPfMaxRows : (D.max_ctx + kPfBlockRows - 1) / kPfBlockRows * kPfBlockRows;
@@ -321,6 +354,7 @@ int take_prefill(amusd_model* m) {
             start[s] = orders.size();
             orders.insert(orders.end(), one.begin(), one.end());
         }
+        g_pf_holders.reserve(g_pf_holders.size() + 1);
     } catch (const std::bad_alloc&) {
         return fail(AMUSD_E_NOMEM, "tile orders of the prefill pass");
     }
@@ -362,7 +396,7 @@ int take_prefill(amusd_model* m) {
         e = hipMemcpy(dev_orders, orders.data(), orders.size() * 4, hipMemcpyHostToDevice);
     }
     if (e != hipSuccess) {
-        release_prefill(m);
+        free_prefill(m);
         (void)hipGetLastError();
         return e == hipErrorOutOfMemory ? AMUSD_OK : fail(AMUSD_E_HIP, std::string("prefill workspace: ") + hipGetErrorString(e));
     }
@@ -371,6 +405,7 @@ int take_prefill(amusd_model* m) {
     T.greedy = static_cast<int*>(host_dev) + cap;
     m->pf = T;
     m->pf_bytes = bytes;
+    g_pf_holders.push_back(m);
     return AMUSD_OK;
 }
 
@@ -607,7 +642,6 @@ int amusd_model_create(const amusd_config* cfg, void* hip_stream, amusd_model** 
         S.best_idx = static_cast<int*>(place((size_t)m->nwg * kRows * 4));
         m->static_bytes = off;      // may exceed the array: amusd_verify_static then refuses the model
     }
-    if ((rc = take_prefill(m)) != AMUSD_OK) return bail(rc);
     if (hipStreamSynchronize(m->stream) != hipSuccess) return bail(fail(AMUSD_E_HIP, "create: stream sync"));
     *out = m;
     return AMUSD_OK;
@@ -650,7 +684,7 @@ int amusd_model_set_tensor(amusd_model* m, int32_t id, int32_t layer, const void
             if (m->staging) HIP_TRY(hipFree(m->staging));
             m->staging = nullptr;
             m->staging_bytes = 0;
-            HIP_TRY(hipMalloc(&m->staging, bytes));
+            HIP_TRY(dev_malloc(m->device, &m->staging, bytes));
             m->staging_bytes = bytes;
         }
         HIP_TRY(hipMemcpy(m->staging, data, bytes, hipMemcpyHostToDevice));
@@ -691,6 +725,10 @@ int amusd_model_finalize(amusd_model* m) {
         HIP_TRY(hipFree(m->staging));
         m->staging = nullptr;
         m->staging_bytes = 0;
+    }
+    if (!m->finalized && m->want_prefill) {       // last: it takes no memory that the tensors' way in needs
+        const int rc = take_prefill(m);
+        if (rc) return rc;
     }
     m->finalized = true;
     return AMUSD_OK;
@@ -755,6 +793,7 @@ int amusd_seq_prefill(amusd_model* m, int32_t seq, const int32_t* tokens, int32_
     // the verify pass selected for timing everything, through the verify pass.  The last group of rows, the one whose logits
     // and tokens can be asked for, is the verify pass's, so the last stretch holds at least that many.  (8B shape, 4 layers:
     // 9 tokens 0.81 ms in two verify passes, 0.60 in one prefill pass.)
+    std::unique_lock<std::mutex> use(m->pf_mutex);
     if (n > chunk && m->pf.cap && m->timer.stage < 0) {
         const int tail = (n - 1) % chunk + 1, passes = (n + m->pf.cap - 1) / m->pf.cap;
         const int per = passes == 1 ? n : ((n + passes - 1) / passes + kPfBlockRows - 1) / kPfBlockRows * kPfBlockRows;
@@ -770,6 +809,7 @@ int amusd_seq_prefill(amusd_model* m, int32_t seq, const int32_t* tokens, int32_
         if (next_token) *next_token = q.p_next;
         return AMUSD_OK;
     }
+    use.unlock();
     for (int s = 0; s < n; s += chunk) {
         const int k = n - s < chunk ? n - s : chunk;
         if ((rc = run_pass(m, seq, q.kv_len, tokens + s, k, true))) {
@@ -944,12 +984,14 @@ int amusd_set_option(amusd_model* m, int32_t option, int32_t value) {
             return AMUSD_OK;
         }
         case AMUSD_OPT_PREFILL_WORKSPACE: {
+            m->want_prefill = value != 0;
             if (!value) {
                 release_prefill(m);
                 return AMUSD_OK;
             }
+            if (!m->finalized) return AMUSD_OK;      // amusd_model_finalize takes it
             const int rc = take_prefill(m);
-            if (rc == AMUSD_OK && !m->pf.cap && m->dm.max_ctx > 1) return fail(AMUSD_E_HIP, "no device memory for the prefill workspace");
+            if (rc == AMUSD_OK && !amusd_prefill_workspace_bytes(m) && m->dm.max_ctx > 1) return fail(AMUSD_E_HIP, "no device memory for the prefill workspace");
             return rc;
         }
         default: return fail(AMUSD_E_ARG, "unknown option");
@@ -958,6 +1000,7 @@ int amusd_set_option(amusd_model* m, int32_t option, int32_t value) {
 
 int64_t amusd_prefill_workspace_bytes(const amusd_model* m) {
     if (!m) return fail(AMUSD_E_ARG, "null model");
+    std::lock_guard<std::mutex> lock(m->pf_mutex);
     return (int64_t)m->pf_bytes;
 }
 

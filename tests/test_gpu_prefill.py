@@ -204,3 +204,39 @@ def test_workspace_holds_no_more_than_its_buffers(name):
     expect = cap * rows + cap // 16 * s.n_kv_heads * chunks * s.group * 16 * (s.head_dim + 4) * 4 + min(sums, 64 << 20) + 4 * 4096 + 4 * cap * lm
     assert m.prefill_workspace_bytes() <= expect + 20 * 4096       # alignment, and the tile orders
     m.free()
+
+
+def test_a_model_that_needs_the_memory_gets_an_idle_models_workspace():
+    """Two models that fit the card fit it in any order of loading and prompting, whatever workspace the first one took."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2410_17375_amd as A
+    from paper_2410_17375_amd.harness import load_model
+    big, small = SHAPES["one_layer_8b_width_bf16"].with_(vocab=16000), SHAPES["tiny_gqa_bf16"]
+    first = load_model(big, 2200)
+    toks = prompt_tokens(36, 90, big.vocab)
+    nxt = first.prefill(toks)
+    held = first.prefill_workspace_bytes()
+    assert held > 400 << 20
+    fill = []                                              # the card is filled but for a gigabyte
+    while torch.cuda.mem_get_info()[0] > (3 << 29) + (1 << 30):
+        fill.append(torch.empty(min(torch.cuda.mem_get_info()[0] - (1 << 30), 16 << 30), dtype=torch.uint8, device="cuda"))
+    left = torch.cuda.mem_get_info()[0]
+    fill.append(torch.empty(left - (1 << 30), dtype=torch.uint8, device="cuda"))
+    seqs = 5 * (1 << 28) // (4096 * 1024)                  # 1.25 GB of cache: a kilobyte a position
+    try:
+        second = load_model(small, 4096, max_seqs=seqs)
+        assert first.prefill_workspace_bytes() == 0
+        first.kv_rollback(0)
+        assert first.prefill(toks) == nxt                  # through verify passes
+        assert second.prefill(toks % small.vocab) >= 0
+        second.free()
+        first.set_option(A.OPT_PREFILL_WORKSPACE, 1)
+        assert first.prefill_workspace_bytes() == held
+        first.kv_rollback(0)
+        assert first.prefill(toks) == nxt
+        first.free()
+    finally:
+        fill.clear()
+        torch.cuda.empty_cache()
