@@ -11,6 +11,7 @@
 // slice depends on the tile (its workgroup there), so a workgroup here takes tiles whose walks start alike: tile lists
 // ordered by that start are made once per model.
 #include <algorithm>
+#include <array>
 #include <utility>
 #include <vector>
 
@@ -952,20 +953,22 @@ __global__ void __launch_bounds__(256) k_pf_greedy(PrefillBufs T, PrefillArgs P,
 // ---------------------------------------------------------------- host side
 template <class Walk>
 static void order_tiles(int n_tiles, int kblocks, int wgs, std::vector<int>& out) {
-    // tiles by where their eight walks start; a class is filled up with -1 to whole groups of kPfTileGroup
-    std::vector<std::pair<std::vector<int>, int>> key(n_tiles);
-    for (int t = 0; t < n_tiles; ++t) {
-        key[t].second = t;
-        for (int w = 0; w < kWaves; ++w) key[t].first.push_back(k_slice_of<Walk>(kblocks, t % wgs, w).rot);
+    // tiles by where their eight walks start, which is the same for tiles of one workgroup of the verify pass; a class is
+    // filled up with -1 to whole groups of kPfTileGroup
+    std::vector<std::pair<std::array<int, kWaves>, int>> key(wgs);
+    for (int g = 0; g < wgs; ++g) {
+        key[g].second = g;
+        for (int w = 0; w < kWaves; ++w) key[g].first[w] = k_slice_of<Walk>(kblocks, g, w).rot;
     }
-    std::stable_sort(key.begin(), key.end());
+    std::sort(key.begin(), key.end());
     out.clear();
-    for (int t = 0; t < n_tiles; ++t) {
-        if (t && key[t].first != key[t - 1].first)
-            while (out.size() % kPfTileGroup) out.push_back(-1);
-        out.push_back(key[t].second);
+    for (int a = 0, b; a < wgs; a = b) {
+        for (b = a; b < wgs && key[b].first == key[a].first; ++b) {}
+        for (int t0 = 0; t0 < n_tiles; t0 += wgs)
+            for (int g = a; g < b; ++g)
+                if (t0 + key[g].second < n_tiles) out.push_back(t0 + key[g].second);
+        while (out.size() % kPfTileGroup) out.push_back(-1);
     }
-    while (out.size() % kPfTileGroup) out.push_back(-1);
 }
 
 void prefill_tile_order(const DevModel& M, int stage, int nwg, std::vector<int>& order, int* wgs) {
