@@ -1,5 +1,6 @@
-"""The prefill pass (prompts of more tokens than a verify pass takes) against the same tokens given in pieces of at most 8, which go through
-the verify pass: cache rows, greedy tokens of every position, kept logits and what a following window sees, bit for bit.
+"""The prefill pass (prompts of more tokens than a verify pass takes) against the same tokens given in pieces of at most 8
+(float32: 16), which go through the verify pass: cache rows, greedy tokens of every position, kept logits and what a
+following window sees, bit for bit.
 The sizes put the edges of its row and column tiles, its workgroup shapes and the K ranges of the down projection in turn."""
 import numpy as np
 import pytest
@@ -21,6 +22,18 @@ CASES = [
     ("one_layer_8b_width_bf16", {"vocab": 16000}, 0, 61), ("one_layer_8b_width_bf16", {}, 0, 128),
     ("one_layer_8b_width_bf16", {"d_ffn": 14336}, 0, 250), ("one_layer_8b_width_bf16", {"vocab": 16000}, 40, 400),
     ("one_layer_8b_width_bf16", {"vocab": 16000}, 0, 1100), ("one_layer_8b_width_bf16", {}, 9, 2190),
+    # Attention runs of several key blocks: ceil(context / (256 / kv heads * runs * block)) blocks, 8 / G runs a chunk, so that
+    # row tiles end after every number of blocks of the first and of the second run.  Odd runs end in a step of one block.
+    ("tiny_gqa_bf16", {"d_model": 128, "n_q_heads": 128, "n_kv_heads": 32, "d_ffn": 128}, 33, 1030),     # G = 4: 3 blocks
+    ("tiny_gqa_bf16", {"d_model": 128, "n_q_heads": 128, "n_kv_heads": 32, "d_ffn": 128}, 0, 2100),      # 5, two stretches
+    ("tiny_gqa128_bf16", {"d_model": 128, "n_q_heads": 64, "n_kv_heads": 16, "d_ffn": 128}, 7, 2050),    # head_dim 128: 3
+    ("tiny_g8_bf16", {"d_model": 128, "n_q_heads": 256, "n_kv_heads": 32, "d_ffn": 128}, 0, 400),        # G = 8, one run: 2
+    ("tiny_g8_bf16", {"d_model": 128, "n_q_heads": 256, "n_kv_heads": 32, "d_ffn": 128}, 40, 660),       # 3
+    ("tiny_g8_bf16", {"d_model": 128, "n_q_heads": 256, "n_kv_heads": 32, "d_ffn": 128}, 1, 1203),       # 5
+    ("tiny_gqa_fp32", {"d_model": 128, "n_q_heads": 128, "n_kv_heads": 32, "d_ffn": 128}, 5, 700),       # G = 4: 3
+    ("tiny_gqa_fp32", {"d_model": 128, "n_q_heads": 256, "n_kv_heads": 32, "d_ffn": 128}, 17, 300),      # G = 8: 3
+    # few column tiles and a long contraction: all K slices of a tile go to workgroups of their own, 16 (two K ranges) and 8
+    ("tiny_wide_bf16", {"d_ffn": 16384}, 0, 140), ("tiny_wide_bf16", {"d_ffn": 16416}, 0, 140),
 ]
 
 
