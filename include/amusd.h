@@ -275,14 +275,18 @@ int amusd_set_option(amusd_model *m, int32_t option, int32_t value);
 
 /* fp32 logits of the last pass, rows 0..rows-1, to host memory [rows, vocab]
  * (a batched pass keeps its sequences' rows back to back, in call order).
+ * After a prefill of n tokens: those of its last (n - 1) % group + 1 rows, with
+ * groups of max_k (16-bit weights: at most 8) rows.
  * Needs AMUSD_OPT_KEEP_LOGITS = 1 before that pass.  Errors: ARG, STATE. */
 int amusd_get_logits(amusd_model *m, float *out, int32_t rows);
 
-/* g[0..rows) of the last pass (arg-max token of each row) to host memory. */
+/* g[0..rows) of the last pass (arg-max token of each row; after a prefill the
+ * rows of amusd_get_logits) to host memory. */
 int amusd_get_greedy(amusd_model *m, int32_t *out, int32_t rows);
 
 /* Device time of the last pass in milliseconds, from HIP events recorded on
- * the model's stream around the pass's kernels (first launch to last end). */
+ * the model's stream around the pass's kernels (first launch to last end).
+ * After a prefill: of its last pass, up to 2048 rows. */
 int amusd_last_pass_ms(amusd_model *m, float *ms);
 
 /* Accumulated device time (HIP events on the model's stream, one pair around

@@ -782,15 +782,16 @@ __device__ __forceinline__ void stage_lmhead(const DevModel& M, const PassArgs& 
 
 // Causal grouped-query attention: every sequence of the pass has its k rows
 // checked against keys 0 .. L+k-1 of its own cache.
-// Work unit = (sequence, kv head, chunk of 8 key blocks; a block is 32 keys bf16 / 16 keys
-// fp32); tile rows of other sequences are masked out of the unit.  Wave w of the workgroup serves query head w % G of the group and the
-// w / G -th run of G consecutive blocks, walking them in order with a running
-// softmax (max, denominator, numerator) in registers; the next block's K and V
-// fragments are fetched while the current one is used.  Scores are computed
-// transposed (keys x rows) so that the matrix-core result registers are, after
-// the softmax numerator, already the operand of the P.V product: nothing is
-// transposed through LDS.  The 8/G runs of a head are merged through LDS in run
-// order.  Block, run and chunk boundaries sit at fixed absolute positions, so a
+// Work unit = (sequence, kv head, chunk of 8/G runs of bpw key blocks; a block is 32 keys
+// bf16 / 16 keys fp32); tile rows of other sequences are masked out of the unit.  Wave w of
+// the workgroup serves query head w % G of the group and the w / G -th run, walking its
+// blocks in order with a running softmax (max, denominator, numerator) in registers.
+// STAGED (the group's 4 or 8 heads): the blocks come through LDS, two a step, fetched once
+// for all waves of a run while the step before is used; 0: each wave fetches its own next
+// block into registers.  Scores are computed transposed (keys x rows) so that the
+// matrix-core result registers are, after the softmax numerator, already the operand of the
+// P.V product: nothing is transposed through LDS.  The 8/G runs of a head are merged through
+// LDS in run order.  Block, run and chunk boundaries sit at fixed absolute positions, so a
 // row's result does not depend on how many rows the pass has or where it starts.
 // Output per (unit, head, row): numerator[hd], running max, denominator.
 template <class DT, int HD, bool ONE, int STAGED>

@@ -1,4 +1,4 @@
-// Host-callable launchers of the kernels in amusd_kernels.hip.
+// Host-callable launchers of the kernels in amusd_kernels.hip and amusd_prefill.hip.
 #pragma once
 #include <vector>
 
@@ -13,7 +13,8 @@ enum RelayoutKind {
     kUp = 3         // tile t, rows 8-15 <- source row 8t + r - 8
 };
 
-// One-time per process: raises the dynamic-LDS limit of the stage kernels.
+// One-time per process: raises the dynamic-LDS limit of the verify pass's kernels (the prefill pass's raise theirs when first
+// launched).
 hipError_t configure_kernels();
 
 // Re-lays a row-major [rows, K] matrix into matrix-core operand order at

@@ -1014,8 +1014,10 @@ static hipError_t launch_pf_stream_v(const DevModel& M, const DevLayer& Ly, cons
 // The streaming form where it is the faster one: up to 64 rows, and up to 128 where one round of workgroups does the stage
 // (NT the smallest of 1, 2, 4 column tiles with that; at most 64 rows and still more workgroups: 4).  Measured against the
 // other form's best plan, us per launch: 8B shape, 24 rows QKV -18, O -8, gate/up -15, down -23; 61 rows -15, 0, -2, -9;
-// 128 rows -12, -8, (gate/up +38: 896 workgroups), -45; 250 rows +9, +22, +129, +33.  1B shape, 61 rows -6, -4, -5, 0; 128
-// rows -10, -11, (+6), -10.
+// 128 rows -12, -8, (gate/up +38: 896 workgroups), -45; 192 rows +8, -1, +86, +12; 250 rows +9, +22, +129, +33.  1B shape,
+// 61 rows -6, -4, -5, 0; 128 rows -10, -11, (+6), -10; 192 rows -5, -8, +16, -2; 250 rows -4, -8, +35, +2.  Above 128 rows the
+// line stands where the 8B shape needs it: on the 1B shape a prompt of 192 rows would take 2.38 ms instead of 2.63 with the
+// streaming form in all but gate/up, one of 250 rows 2.51 instead of 2.69.
 template <class DT, int STAGE>
 static bool launch_pf_stream(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PrefillArgs& P, const float* gain,
                              hipStream_t s, hipError_t& e) {
@@ -1044,10 +1046,12 @@ using PfSmall = PfShape<2, 2, 2, 2, 6>;   // 64 x 64
 // rounds x K blocks x time of a block, plus what the sharing costs.  The times were fitted to measurements of all choices
 // on the 8B and 1B shapes at 24 to 1000 rows: 0.93 us per K block of a large tile; 0.45 and 0.31 us of the smaller ones,
 // 0.545 and 0.40 when two share a compute unit; sharing 1.6 us per workgroup of a tile (its sums are written, counted and
-// read back through the memory side) and its bytes at 4 TB/s each way.  For instance at 61 rows of the 8B shape the down
-// projection takes 123 us on 64 small tiles, 71 with its two K ranges shared, 57 with all sixteen slices; the QKV
-// projection 40 and 36; at 250 rows 40 us on 384 small tiles and 99 on 48 large ones, gate/up 145 on small and 72 less on
-// large ones.
+// read back through the memory side) and its bytes at 4 TB/s each way.  For instance at 250 rows of the 8B shape the QKV
+// projection takes 40 us on 384 small tiles and 99 on 48 large ones, gate/up 145 on small and 72 less on large ones.  Sharing
+// all slices is for few tiles and a long contraction (up to 128 rows the streaming form has those).  4 layers of d = 512, F =
+// 16384, whole prompts with the down projection's sixteen slices shared against its two K ranges: 129 rows 479 us (633), 256
+// rows 514 (655), 400 rows 731 (790), 600 rows 1050 (954: the estimate is off there).  d = 1024, F = 8192: equal within 2 %.
+// d = 2048, F = 16384: 129 rows 937 (927), 256 rows 1140 (990).
 struct PfPlan { int shape, shares; };
 static PfPlan plan_pf_gemm(const DevModel& M, const PrefillBufs& T, int n, int stage) {
     struct Shape { int tiles, rows, per_cu; double alone, full; };
