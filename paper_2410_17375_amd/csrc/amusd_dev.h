@@ -69,7 +69,7 @@ struct DevLayer {
 // ---- prefill pass: many prompt rows of one sequence at a time
 constexpr int kPfMaxRows = 2048;     // rows of one pass
 constexpr int kPfBlockRows = 128;    // rows that share a stretch of the activation buffers
-constexpr int kPfTileGroup = 16;     // column tiles of the widest workgroup
+constexpr int kPfGroups = 5;         // column tiles of a workgroup: 1, 2, 4, 8 or 16
 constexpr int kPfPartBytes = 256 << 20;  // attention partials in flight between the two kernels
 constexpr int kPfTickets = 4096;     // tiles whose K slices several workgroups share, at most
 constexpr size_t kPfShareBytes = 64u << 20;   // their sums, at most
@@ -79,6 +79,9 @@ struct PfTiles {
     const int* order;     // column tiles by the start of their K walk, each start's filled up with -1 to whole groups
     int n;                // entries
     int wgs;              // workgroups of the stage in the verify pass (the walk of tile t is that of workgroup t mod wgs)
+};
+struct PfTileSet {        // a stage's, for groups of 1, 2, 4, 8 and 16 tiles
+    PfTiles groups[kPfGroups];
 };
 
 // Workspace of the prefill pass; rows padded to cap.
@@ -103,7 +106,6 @@ struct PrefillBufs {
     int* best_idx;
     const int* tokens;    // [cap] pinned host memory
     int* greedy;          // [cap] pinned host memory
-    PfTiles tiles[kPfStages];
 };
 
 struct PrefillArgs {

@@ -106,6 +106,7 @@ struct amusd_model {
     uint64_t id = 0;
     HostStage* hstage = nullptr;
     PrefillBufs pf{};                      // workspace of the prefill pass; cap 0: prompts go through the verify pass
+    PfTileSet pf_tiles[kPfStages];
     void* pf_mem = nullptr;                // the device allocation that its buffers are in
     size_t pf_bytes = 0;
     bool want_prefill = true;              // AMUSD_OPT_PREFILL_WORKSPACE
@@ -345,22 +346,17 @@ int take_prefill(amusd_model* m) {
     T.att_tiles = (int)(kPfPartBytes / tile_bytes);
     if (T.att_tiles < 1) T.att_tiles = 1;
     if (T.att_tiles > T.cap / 16) T.att_tiles = T.cap / 16;
-    std::vector<int> orders, one;                  // the stages' tile orders back to back
-    size_t start[kPfStages];
+    std::vector<int> orders;                       // the stages' tile orders back to back
     try {
-        for (int s = 0; s < kPfStages; ++s) {
-            prefill_tile_order(D, s, m->nwg, one, &T.tiles[s].wgs);
-            T.tiles[s].n = (int)one.size();
-            start[s] = orders.size();
-            orders.insert(orders.end(), one.begin(), one.end());
-        }
+        for (int s = 0; s < kPfStages; ++s) prefill_tile_orders(D, s, m->nwg, orders, m->pf_tiles[s]);
         g_pf_holders.reserve(g_pf_holders.size() + 1);
     } catch (const std::bad_alloc&) {
         return fail(AMUSD_E_NOMEM, "tile orders of the prefill pass");
     }
     // the down projection's first totals; beyond that room for shared tiles, as far as 16 sums per element of a small pass go
-    T.xch_bytes = D.split_down ? cap * T.tiles[kPfDown].n * 16 * 4 : 0;
-    const size_t widest = (size_t)std::max(T.tiles[kPfQKV].n, T.tiles[kPfDown].n) * 16;
+    auto places = [&](int s) { return (size_t)m->pf_tiles[s].groups[kPfGroups - 1].n; };   // the most that a form takes
+    T.xch_bytes = D.split_down ? cap * places(kPfDown) * 16 * 4 : 0;
+    const size_t widest = std::max(places(kPfQKV), places(kPfDown)) * 16;
     T.xch_bytes = std::max(T.xch_bytes, std::min(kPfShareBytes, 16 * cap * widest * 4));
     int* dev_orders = nullptr;
     auto layout = [&](uintptr_t base) {            // sets the pointers, returns the bytes
@@ -382,8 +378,8 @@ int take_prefill(amusd_model* m) {
         T.att_part = static_cast<float*>(place(T.att_tiles * tile_bytes));
         T.xch = static_cast<float*>(place(T.xch_bytes));
         T.ticket = static_cast<int*>(place(kPfTickets * 4));
-        T.best_val = static_cast<float*>(place(cap * T.tiles[kPfLMHead].n / 2 * 4));
-        T.best_idx = static_cast<int*>(place(cap * T.tiles[kPfLMHead].n / 2 * 4));
+        T.best_val = static_cast<float*>(place(cap * places(kPfLMHead) / 2 * 4));
+        T.best_idx = static_cast<int*>(place(cap * places(kPfLMHead) / 2 * 4));
         return off;
     };
     const size_t bytes = layout(0);
@@ -400,7 +396,8 @@ int take_prefill(amusd_model* m) {
         (void)hipGetLastError();
         return e == hipErrorOutOfMemory ? AMUSD_OK : fail(AMUSD_E_HIP, std::string("prefill workspace: ") + hipGetErrorString(e));
     }
-    for (int s = 0; s < kPfStages; ++s) T.tiles[s].order = dev_orders + start[s];
+    for (PfTileSet& set : m->pf_tiles)
+        for (PfTiles& t : set.groups) t.order = reinterpret_cast<const int*>(reinterpret_cast<uintptr_t>(dev_orders) + reinterpret_cast<uintptr_t>(t.order));
     T.tokens = static_cast<const int*>(host_dev);
     T.greedy = static_cast<int*>(host_dev) + cap;
     m->pf = T;
@@ -416,7 +413,7 @@ int run_prefill(amusd_model* m, int seq, int L, const int32_t* tokens, int n, in
     const PrefillArgs P{n, L, seq, m->keep_logits ? n - tail : n};
     std::memcpy(m->pf_host, tokens, (size_t)n * 4);
     HIP_TRY(hipEventRecord(m->ev0, m->stream));
-    HIP_TRY(launch_prefill(m->dm, m->layers_host.data(), m->pf, P, m->stream));
+    HIP_TRY(launch_prefill(m->dm, m->layers_host.data(), m->pf, m->pf_tiles, P, m->stream));
     HIP_TRY(hipEventRecord(m->ev1, m->stream));
     HIP_TRY(hipStreamSynchronize(m->stream));
     HIP_TRY(hipEventElapsedTime(&m->last_ms, m->ev0, m->ev1));

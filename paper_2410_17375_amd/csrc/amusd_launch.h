@@ -46,9 +46,12 @@ hipError_t launch_pass(const DevModel& M, const DevLayer* layers_host, const Pas
                        StageTimer* timer);
 
 // One prefill pass: P.n rows (tokens in T.tokens) appended at P.L0; greedy tokens of all rows to T.greedy.
-hipError_t launch_prefill(const DevModel& M, const DevLayer* layers_host, const PrefillBufs& T, const PrefillArgs& P, hipStream_t stream);
+// tiles: [kPfStages].
+hipError_t launch_prefill(const DevModel& M, const DevLayer* layers_host, const PrefillBufs& T, const PfTileSet* tiles, const PrefillArgs& P,
+                          hipStream_t stream);
 
-// Column tiles of a stage of the prefill pass in the order its workgroups take them, and *wgs (PfTiles).
-void prefill_tile_order(const DevModel& M, int stage, int nwg, std::vector<int>& order, int* wgs);
+// Column tiles of a stage of the prefill pass in the orders its workgroups take them, appended to `orders`; the order
+// pointers of `set` are left as offsets from the start of `orders`.
+void prefill_tile_orders(const DevModel& M, int stage, int nwg, std::vector<int>& orders, PfTileSet& set);
 
 }  // namespace amusd

@@ -488,30 +488,18 @@ __device__ __forceinline__ void pf_epilogue(const DevModel& M, const DevLayer& L
 }
 
 template <class DT, int STAGE, class Sh>
-__global__ void __launch_bounds__(Sh::kThreads, Sh::kMinWaves) k_pf_gemm(DevModel M, DevLayer Ly, PrefillBufs T, PrefillArgs P, const float* gain_next,
-                                                                                 int shares) {
+__global__ void __launch_bounds__(Sh::kThreads, Sh::kMinWaves) k_pf_gemm(DevModel M, DevLayer Ly, PrefillBufs T, PfTiles L, PrefillArgs P,
+                                                                          const float* gain_next, int shares) {
     extern __shared__ char pf_smem[];
     using G = PfGemm<DT, STAGE, Sh>;
     constexpr int A = Sh::A, B = Sh::B;
     const int row_groups = (P.n + Sh::kRowTiles * 16 - 1) / (Sh::kRowTiles * 16);
-    const PfTiles& L = T.tiles[STAGE];
     const int tiles_wg = gridDim.x / shares;              // (column group, row group) pairs
     const int share = blockIdx.x / tiles_wg;
     const int idx = xcd_contiguous(blockIdx.x % tiles_wg, tiles_wg);
     int cg, rg;
     patch_order(idx, L.n / Sh::kTiles, row_groups, cg, rg);
     const int* tiles = L.order + cg * Sh::kTiles;
-    if (tiles[0] < 0) {      // nothing but filling (it is at the end of a start's tiles): no K walk, no weights to point at
-        if (STAGE == kPfLMHead && share == 0)
-            for (int x = threadIdx.x; x < Sh::WN * Sh::kRowTiles * 16; x += Sh::kThreads) {
-                const int row = rg * Sh::kRowTiles * 16 + x / Sh::WN;
-                if (row < P.n) {
-                    T.best_val[(size_t)(cg * Sh::WN + x % Sh::WN) * P.n + row] = -INFINITY;
-                    T.best_idx[(size_t)(cg * Sh::WN + x % Sh::WN) * P.n + row] = 0x7fffffff;
-                }
-            }
-        return;
-    }
     const uint4* W;
     const void* act;
     int K, ways;
@@ -564,14 +552,13 @@ struct PfSums {                  // what combine_shares works on: F fragments pe
     v4f tot[1][F];
 };
 template <class DT, int STAGE, int NT, int RT, int D>
-__global__ void __launch_bounds__(kThreads, 2) k_pf_stream(DevModel M, DevLayer Ly, PrefillBufs T, PrefillArgs P, const float* gain_next,
-                                                            int shares) {
+__global__ void __launch_bounds__(kThreads, 2) k_pf_stream(DevModel M, DevLayer Ly, PrefillBufs T, PfTiles L, PrefillArgs P,
+                                                            const float* gain_next, int shares) {
     extern __shared__ char pf_smem[];
     constexpr int AF = PfAct<DT>::AF, F = (NT * RT + kWaves - 1) / kWaves;   // fragments a wave finishes
     PfSums<F> sum;
     using Walk = typename PfWalk<STAGE>::T;
     const int row_groups = (P.n + RT * 16 - 1) / (RT * 16);
-    const PfTiles& L = T.tiles[STAGE];
     const int groups = gridDim.x / shares;
     const int share = blockIdx.x / groups, idx = blockIdx.x % groups;
     const int cg = idx / row_groups, rg = idx % row_groups;
@@ -582,104 +569,102 @@ __global__ void __launch_bounds__(kThreads, 2) k_pf_stream(DevModel M, DevLayer 
     static_assert(STAGE != kPfLMHead, "");
     float best_v = 0.f;       // (the LM head's)
     int best_i = 0;
-    if (t0 >= 0) {            // (else nothing but filling)
-        const uint4* W;
-        const void* act;
-        int K, ways;
-        pf_inputs<STAGE>(M, Ly, T, W, act, K, ways);
-        const int kblocks = K / DT::KB, kh = kblocks / ways;
-        v4f acc[NT][RT][AF], part[NT][RT];
-        // K ranges of this workgroup: all of them one after the other, or its own
-        for (int range = share; range < ways; range += shares) {
-            const KSlice ks = k_slice_of<Walk>(kh, t0 % L.wgs, wave);
-            const int S = ks.S;
+    const uint4* W;
+    const void* act;
+    int K, ways;
+    pf_inputs<STAGE>(M, Ly, T, W, act, K, ways);
+    const int kblocks = K / DT::KB, kh = kblocks / ways;
+    v4f acc[NT][RT][AF], part[NT][RT];
+    // K ranges of this workgroup: all of them one after the other, or its own
+    for (int range = share; range < ways; range += shares) {
+        const KSlice ks = k_slice_of<Walk>(kh, t0 % L.wgs, wave);
+        const int S = ks.S;
 #pragma unroll
-            for (int i = 0; i < NT; ++i)
+        for (int i = 0; i < NT; ++i)
+#pragma unroll
+            for (int j = 0; j < RT; ++j)
+#pragma unroll
+                for (int f = 0; f < AF; ++f) acc[i][j][f] = v4f{0.f, 0.f, 0.f, 0.f};
+        if (S > 0) {
+            const uint4* wp[NT];
+#pragma unroll
+            for (int i = 0; i < NT; ++i) {
+                const int t = __builtin_amdgcn_readfirstlane(tiles[i]);
+                wp[i] = W + ((size_t)(t < 0 ? t0 : t) * kblocks + range * kh + ks.kb0) * 64 + lane;
+            }
+            const uint4* ap = reinterpret_cast<const uint4*>(act) + PfAct<DT>::frag(kblocks, rt0, range * kh + ks.kb0, 0) + lane;
+            uint4 wb[D][NT], ab[D][RT][AF];
+            const int last = S - 1;
+            auto fetch = [&](int st, int to) {
+                const int x = st + ks.rot;
+                const int s = (x >= S ? x - S : x) * ks.stride;
+#pragma unroll
+                for (int i = 0; i < NT; ++i) wb[to][i] = load_stream(wp[i] + (size_t)s * 64);
 #pragma unroll
                 for (int j = 0; j < RT; ++j)
 #pragma unroll
-                    for (int f = 0; f < AF; ++f) acc[i][j][f] = v4f{0.f, 0.f, 0.f, 0.f};
-            if (S > 0) {
-                const uint4* wp[NT];
+                    for (int f = 0; f < AF; ++f) ab[to][j][f] = ap[(size_t)s * (PfAct<DT>::kBlockTiles * AF * 64) + (j * AF + f) * 64];
+                __builtin_amdgcn_sched_barrier(0);      // the loads stay in this order, and behind the products before them
+            };
+            auto multiply = [&](int from) {
 #pragma unroll
-                for (int i = 0; i < NT; ++i) {
-                    const int t = __builtin_amdgcn_readfirstlane(tiles[i]);
-                    wp[i] = W + ((size_t)(t < 0 ? t0 : t) * kblocks + range * kh + ks.kb0) * 64 + lane;
+                for (int f = 0; f < AF; ++f)
+#pragma unroll
+                    for (int i = 0; i < NT; ++i)
+#pragma unroll
+                        for (int j = 0; j < RT; ++j) acc[i][j][f] = DT::mfma(wb[from][i], ab[from][j][f], acc[i][j][f]);
+            };
+#pragma unroll
+            for (int d = 0; d < D; ++d) fetch(d < last ? d : last, d);
+            int s0 = 0;
+            for (; s0 + D < S; s0 += D) {
+#pragma unroll
+                for (int d = 0; d < D; ++d) {
+                    multiply(d);
+                    fetch(s0 + d + D < last ? s0 + d + D : last, d);
                 }
-                const uint4* ap = reinterpret_cast<const uint4*>(act) + PfAct<DT>::frag(kblocks, rt0, range * kh + ks.kb0, 0) + lane;
-                uint4 wb[D][NT], ab[D][RT][AF];
-                const int last = S - 1;
-                auto fetch = [&](int st, int to) {
-                    const int x = st + ks.rot;
-                    const int s = (x >= S ? x - S : x) * ks.stride;
-#pragma unroll
-                    for (int i = 0; i < NT; ++i) wb[to][i] = load_stream(wp[i] + (size_t)s * 64);
-#pragma unroll
-                    for (int j = 0; j < RT; ++j)
-#pragma unroll
-                        for (int f = 0; f < AF; ++f) ab[to][j][f] = ap[(size_t)s * (PfAct<DT>::kBlockTiles * AF * 64) + (j * AF + f) * 64];
-                    __builtin_amdgcn_sched_barrier(0);      // the loads stay in this order, and behind the products before them
-                };
-                auto multiply = [&](int from) {
-#pragma unroll
-                    for (int f = 0; f < AF; ++f)
-#pragma unroll
-                        for (int i = 0; i < NT; ++i)
-#pragma unroll
-                            for (int j = 0; j < RT; ++j) acc[i][j][f] = DT::mfma(wb[from][i], ab[from][j][f], acc[i][j][f]);
-                };
-#pragma unroll
-                for (int d = 0; d < D; ++d) fetch(d < last ? d : last, d);
-                int s0 = 0;
-                for (; s0 + D < S; s0 += D) {
-#pragma unroll
-                    for (int d = 0; d < D; ++d) {
-                        multiply(d);
-                        fetch(s0 + d + D < last ? s0 + d + D : last, d);
-                    }
-                }
-#pragma unroll
-                for (int d = 0; d < D; ++d)
-                    if (s0 + d < S) multiply(d);
             }
 #pragma unroll
-            for (int i = 0; i < NT; ++i)
+            for (int d = 0; d < D; ++d)
+                if (s0 + d < S) multiply(d);
+        }
 #pragma unroll
-                for (int j = 0; j < RT; ++j) {
-                    if constexpr (AF == 2) part[i][j] = acc[i][j][0] + acc[i][j][1];
-                    else part[i][j] = acc[i][j][0];
-                }
-            if (range != share) __syncthreads();        // the sums of the range before have been read
-            v4f* lds = reinterpret_cast<v4f*>(pf_smem);   // [wave][fragment][lane]
+        for (int i = 0; i < NT; ++i)
 #pragma unroll
-            for (int i = 0; i < NT; ++i)
-#pragma unroll
-                for (int j = 0; j < RT; ++j) lds[(wave * (NT * RT) + i * RT + j) * 64 + lane] = part[i][j];
-            __syncthreads();
-#pragma unroll
-            for (int x = 0; x < F; ++x) {
-                const int f = wave + x * kWaves;
-                v4f v = v4f{0.f, 0.f, 0.f, 0.f};
-                if (f < NT * RT)
-#pragma unroll
-                    for (int w = 0; w < kWaves; ++w) v += lds[(w * (NT * RT) + f) * 64 + lane];
-                sum.tot[0][x] = range == share ? v : sum.tot[0][x] + v;
+            for (int j = 0; j < RT; ++j) {
+                if constexpr (AF == 2) part[i][j] = acc[i][j][0] + acc[i][j][1];
+                else part[i][j] = acc[i][j][0];
             }
-        }
-        // The last fetches are repeats of the last block that nothing multiplies, so nothing has waited for them, and a
-        // wave without a fragment to finish would end with them under way.
-        wait_vm<0>();
-        if (shares > 1) {
-            __syncthreads();
-            float* xch = T.xch + (size_t)idx * shares * (kThreads * F * 4);
-            if (!combine_shares<PfSums<F>>(sum, xch, T.ticket + idx, share, shares, 1, pf_smem)) return;
-        }
+        if (range != share) __syncthreads();        // the sums of the range before have been read
+        v4f* lds = reinterpret_cast<v4f*>(pf_smem);   // [wave][fragment][lane]
+#pragma unroll
+        for (int i = 0; i < NT; ++i)
+#pragma unroll
+            for (int j = 0; j < RT; ++j) lds[(wave * (NT * RT) + i * RT + j) * 64 + lane] = part[i][j];
+        __syncthreads();
 #pragma unroll
         for (int x = 0; x < F; ++x) {
             const int f = wave + x * kWaves;
-            const int tile = f < NT * RT ? tiles[f / RT] : -1;
-            if (tile >= 0) pf_epilogue<DT, STAGE>(M, Ly, T, P, gain_next, tile, rt0 + f % RT, sum.tot[0][x], best_v, best_i);
+            v4f v = v4f{0.f, 0.f, 0.f, 0.f};
+            if (f < NT * RT)
+#pragma unroll
+                for (int w = 0; w < kWaves; ++w) v += lds[(w * (NT * RT) + f) * 64 + lane];
+            sum.tot[0][x] = range == share ? v : sum.tot[0][x] + v;
         }
+    }
+    // The last fetches are repeats of the last block that nothing multiplies, so nothing has waited for them, and a
+    // wave without a fragment to finish would end with them under way.
+    wait_vm<0>();
+    if (shares > 1) {
+        __syncthreads();
+        float* xch = T.xch + (size_t)idx * shares * (kThreads * F * 4);
+        if (!combine_shares<PfSums<F>>(sum, xch, T.ticket + idx, share, shares, 1, pf_smem)) return;
+    }
+#pragma unroll
+    for (int x = 0; x < F; ++x) {
+        const int f = wave + x * kWaves;
+        const int tile = f < NT * RT ? tiles[f / RT] : -1;
+        if (tile >= 0) pf_epilogue<DT, STAGE>(M, Ly, T, P, gain_next, tile, rt0 + f % RT, sum.tot[0][x], best_v, best_i);
     }
 }
 
@@ -952,62 +937,83 @@ __global__ void __launch_bounds__(256) k_pf_greedy(PrefillBufs T, PrefillArgs P,
 
 // ---------------------------------------------------------------- host side
 template <class Walk>
-static void order_tiles(int n_tiles, int kblocks, int wgs, std::vector<int>& out) {
-    // tiles by where their eight walks start, which is the same for tiles of one workgroup of the verify pass; a class is
-    // filled up with -1 to whole groups of kPfTileGroup
+static void order_tiles(int n_tiles, int kblocks, int wgs, std::vector<int>& orders, PfTileSet& set) {
+    // tiles by where their eight walks start, which is the same for tiles of one workgroup of the verify pass
     std::vector<std::pair<std::array<int, kWaves>, int>> key(wgs);
     for (int g = 0; g < wgs; ++g) {
         key[g].second = g;
         for (int w = 0; w < kWaves; ++w) key[g].first[w] = k_slice_of<Walk>(kblocks, g, w).rot;
     }
     std::sort(key.begin(), key.end());
-    out.clear();
+    std::vector<int> tiles, ends;                  // the starts' tiles one after the other, and where each start's end
     for (int a = 0, b; a < wgs; a = b) {
         for (b = a; b < wgs && key[b].first == key[a].first; ++b) {}
         for (int t0 = 0; t0 < n_tiles; t0 += wgs)
             for (int g = a; g < b; ++g)
-                if (t0 + key[g].second < n_tiles) out.push_back(t0 + key[g].second);
-        while (out.size() % kPfTileGroup) out.push_back(-1);
+                if (t0 + key[g].second < n_tiles) tiles.push_back(t0 + key[g].second);
+        ends.push_back((int)tiles.size());
+    }
+    // Each start's are filled up with -1 to whole groups, for every size of group by itself: a filler is read and multiplied
+    // like a tile.  Where slices are of unequal length there are many starts: d = 3200 has 156, and filled to 16 the
+    // O-projection's 200 tiles took 2496 places, also in groups of one.
+    for (int g = kPfGroups - 1, n = -1; g >= 0; --g) {
+        const int size = 1 << g;
+        int filled = 0;
+        for (size_t c = 0, first = 0; c < ends.size(); first = ends[c++]) filled += (ends[c] - (int)first + size - 1) / size * size;
+        PfTiles& t = set.groups[g];
+        if (filled == n) {                         // no fewer than for the larger group: the same list
+            t = set.groups[g + 1];
+            continue;
+        }
+        t = PfTiles{reinterpret_cast<const int*>(orders.size() * sizeof(int)), n = filled, wgs};
+        for (size_t c = 0, first = 0; c < ends.size(); first = ends[c++]) {
+            orders.insert(orders.end(), tiles.begin() + first, tiles.begin() + ends[c]);
+            orders.insert(orders.end(), (size - (ends[c] - first) % size) % size, -1);
+        }
     }
 }
 
-void prefill_tile_order(const DevModel& M, int stage, int nwg, std::vector<int>& order, int* wgs) {
+void prefill_tile_orders(const DevModel& M, int stage, int nwg, std::vector<int>& orders, PfTileSet& set) {
     const int kb = M.dtype ? BF16::KB : FP32::KB;
     const int tiles = stage == kPfQKV ? M.nqkv / 16 : stage == kPfGateUp ? 2 * M.F / 16 : stage == kPfLMHead ? M.V / 16 : M.d / 16;
     const int K = stage == kPfOproj ? M.qdim : stage == kPfDown ? M.F : M.d;
-    *wgs = tiles < nwg ? tiles : nwg;
+    const int wgs = tiles < nwg ? tiles : nwg;
     switch (stage) {
-        case kPfQKV: order_tiles<KWalkQKV>(tiles, K / kb, *wgs, order); break;
-        case kPfOproj: order_tiles<KWalkOproj>(tiles, K / kb, *wgs, order); break;
-        case kPfDown: order_tiles<KWalkDown>(tiles, K / kb / (M.split_down ? 2 : 1), *wgs, order); break;
-        default: order_tiles<KWalkWide>(tiles, K / kb, *wgs, order); break;
+        case kPfQKV: order_tiles<KWalkQKV>(tiles, K / kb, wgs, orders, set); break;
+        case kPfOproj: order_tiles<KWalkOproj>(tiles, K / kb, wgs, orders, set); break;
+        case kPfDown: order_tiles<KWalkDown>(tiles, K / kb / (M.split_down ? 2 : 1), wgs, orders, set); break;
+        default: order_tiles<KWalkWide>(tiles, K / kb, wgs, orders, set); break;
     }
 }
 
+static const PfTiles& group_tiles(const PfTileSet& set, int size) { return set.groups[__builtin_ctz(size)]; }
+
 template <class DT, int STAGE, class Sh>
-static hipError_t launch_pf_gemm_v(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PrefillArgs& P, const float* gain,
-                                   hipStream_t s, int* parts, int shares) {
+static hipError_t launch_pf_gemm_v(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PfTileSet* tiles, const PrefillArgs& P,
+                                   const float* gain, hipStream_t s, int* parts, int shares) {
     const int lds = PfGemm<DT, STAGE, Sh>::kLdsBytes;
     static const hipError_t set = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pf_gemm<DT, STAGE, Sh>),
                                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (set != hipSuccess) return set;
-    const int groups = T.tiles[STAGE].n / Sh::kTiles;
+    const PfTiles& L = group_tiles(tiles[STAGE], Sh::kTiles);
+    const int groups = L.n / Sh::kTiles;
     const int grid = groups * ((P.n + Sh::kRowTiles * 16 - 1) / (Sh::kRowTiles * 16)) * shares;
     if (parts) *parts = groups * Sh::WN;
-    hipLaunchKernelGGL((k_pf_gemm<DT, STAGE, Sh>), dim3(grid), dim3(Sh::kThreads), lds, s, M, Ly, T, P, gain, shares);
+    hipLaunchKernelGGL((k_pf_gemm<DT, STAGE, Sh>), dim3(grid), dim3(Sh::kThreads), lds, s, M, Ly, T, L, P, gain, shares);
     return hipSuccess;
 }
 
 template <class DT, int STAGE, int NT, int RT, int D>
-static hipError_t launch_pf_stream_v(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PrefillArgs& P, const float* gain,
-                                     hipStream_t s, int shares) {
+static hipError_t launch_pf_stream_v(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PfTileSet* tiles, const PrefillArgs& P,
+                                     const float* gain, hipStream_t s, int shares) {
     constexpr int lds = kWaves * NT * RT * 1024;
     static const hipError_t set = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pf_stream<DT, STAGE, NT, RT, D>),
                                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (set != hipSuccess) return set;
-    const int groups = T.tiles[STAGE].n / NT;
+    const PfTiles& L = group_tiles(tiles[STAGE], NT);
+    const int groups = L.n / NT;
     hipLaunchKernelGGL((k_pf_stream<DT, STAGE, NT, RT, D>), dim3(groups * ((P.n + RT * 16 - 1) / (RT * 16)) * shares), dim3(kThreads), lds, s,
-                       M, Ly, T, P, gain, shares);
+                       M, Ly, T, L, P, gain, shares);
     return hipSuccess;
 }
 
@@ -1019,21 +1025,22 @@ static hipError_t launch_pf_stream_v(const DevModel& M, const DevLayer& Ly, cons
 // line stands where the 8B shape needs it: on the 1B shape a prompt of 192 rows would take 2.38 ms instead of 2.63 with the
 // streaming form in all but gate/up, one of 250 rows 2.51 instead of 2.69.
 template <class DT, int STAGE>
-static bool launch_pf_stream(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PrefillArgs& P, const float* gain,
-                             hipStream_t s, hipError_t& e) {
+static bool launch_pf_stream(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PfTileSet* tiles, const PrefillArgs& P,
+                             const float* gain, hipStream_t s, hipError_t& e) {
     if (P.n > 128) return false;
-    const int rt = P.n <= 32 ? 2 : 4, row_groups = (P.n + rt * 16 - 1) / (rt * 16), tiles = T.tiles[STAGE].n;
+    const int rt = P.n <= 32 ? 2 : 4, row_groups = (P.n + rt * 16 - 1) / (rt * 16);
     int shares = STAGE == kPfDown && M.split_down ? 2 : 1;
-    const int nt = tiles * row_groups * shares <= T.cus ? 1 : tiles / 2 * row_groups * shares <= T.cus ? 2 : 4;
-    if (tiles / nt * row_groups * shares > T.cus && P.n > 64) return false;
-    const size_t sums = (size_t)(tiles / nt * row_groups) * shares * (kThreads * ((nt * rt + kWaves - 1) / kWaves) * 16);
-    if (tiles / nt * row_groups > kPfTickets || sums > T.xch_bytes) shares = 1;
-    if (rt == 2) e = nt == 1 ? launch_pf_stream_v<DT, STAGE, 1, 2, 6>(M, Ly, T, P, gain, s, shares)
-                     : nt == 2 ? launch_pf_stream_v<DT, STAGE, 2, 2, 4>(M, Ly, T, P, gain, s, shares)
-                               : launch_pf_stream_v<DT, STAGE, 4, 2, 3>(M, Ly, T, P, gain, s, shares);
-    else e = nt == 1 ? launch_pf_stream_v<DT, STAGE, 1, 4, 3>(M, Ly, T, P, gain, s, shares)
-             : nt == 2 ? launch_pf_stream_v<DT, STAGE, 2, 4, 3>(M, Ly, T, P, gain, s, shares)
-                       : launch_pf_stream_v<DT, STAGE, 4, 4, 2>(M, Ly, T, P, gain, s, shares);
+    auto wgs = [&](int nt) { return group_tiles(tiles[STAGE], nt).n / nt * row_groups; };
+    const int nt = wgs(1) * shares <= T.cus ? 1 : wgs(2) * shares <= T.cus ? 2 : 4;
+    if (wgs(nt) * shares > T.cus && P.n > 64) return false;
+    const size_t sums = (size_t)wgs(nt) * shares * (kThreads * ((nt * rt + kWaves - 1) / kWaves) * 16);
+    if (wgs(nt) > kPfTickets || sums > T.xch_bytes) shares = 1;
+    if (rt == 2) e = nt == 1 ? launch_pf_stream_v<DT, STAGE, 1, 2, 6>(M, Ly, T, tiles, P, gain, s, shares)
+                     : nt == 2 ? launch_pf_stream_v<DT, STAGE, 2, 2, 4>(M, Ly, T, tiles, P, gain, s, shares)
+                               : launch_pf_stream_v<DT, STAGE, 4, 2, 3>(M, Ly, T, tiles, P, gain, s, shares);
+    else e = nt == 1 ? launch_pf_stream_v<DT, STAGE, 1, 4, 3>(M, Ly, T, tiles, P, gain, s, shares)
+             : nt == 2 ? launch_pf_stream_v<DT, STAGE, 2, 4, 3>(M, Ly, T, tiles, P, gain, s, shares)
+                       : launch_pf_stream_v<DT, STAGE, 4, 4, 2>(M, Ly, T, tiles, P, gain, s, shares);
     return true;
 }
 
@@ -1053,7 +1060,7 @@ using PfSmall = PfShape<2, 2, 2, 2, 6>;   // 64 x 64
 // rows 514 (655), 400 rows 731 (790), 600 rows 1050 (954: the estimate is off there).  d = 1024, F = 8192: equal within 2 %.
 // d = 2048, F = 16384: 129 rows 937 (927), 256 rows 1140 (990).
 struct PfPlan { int shape, shares; };
-static PfPlan plan_pf_gemm(const DevModel& M, const PrefillBufs& T, int n, int stage) {
+static PfPlan plan_pf_gemm(const DevModel& M, const PrefillBufs& T, const PfTileSet* sets, int n, int stage) {
     struct Shape { int tiles, rows, per_cu; double alone, full; };
     static const Shape shapes[3] = {{PfLarge::kTiles, PfLarge::kRowTiles * 16, 1, 0.93, 0.93},
                                     {PfMid::kTiles, PfMid::kRowTiles * 16, 2, 0.45, 0.545},
@@ -1065,7 +1072,7 @@ static PfPlan plan_pf_gemm(const DevModel& M, const PrefillBufs& T, int n, int s
     for (int s = 0; s < 3; ++s)
         for (int shares : {1, ways, ways * kWaves}) {
             const Shape& h = shapes[s];
-            const size_t tiles = (size_t)T.tiles[stage].n / h.tiles * ((n + h.rows - 1) / h.rows);
+            const size_t tiles = (size_t)group_tiles(sets[stage], h.tiles).n / h.tiles * ((n + h.rows - 1) / h.rows);
             const size_t sum_bytes = tiles * h.tiles * h.rows * 16 * 4 * shares;
             if (shares > 1 && (tiles > (size_t)kPfTickets || sum_bytes > T.xch_bytes)) continue;
             const size_t wgs = tiles * shares, round = (size_t)T.cus * h.per_cu, rest = wgs % round;
@@ -1080,17 +1087,17 @@ static PfPlan plan_pf_gemm(const DevModel& M, const PrefillBufs& T, int n, int s
 }
 
 template <class DT, int STAGE>
-static hipError_t launch_pf_gemm(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PrefillArgs& P, const float* gain,
-                                 hipStream_t s, int* parts = nullptr) {
+static hipError_t launch_pf_gemm(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PfTileSet* tiles, const PrefillArgs& P,
+                                 const float* gain, hipStream_t s, int* parts = nullptr) {
     if constexpr (STAGE != kPfLMHead) {      // (its partial maxima would outgrow best_val, and it gains nothing)
         hipError_t e;
-        if (launch_pf_stream<DT, STAGE>(M, Ly, T, P, gain, s, e)) return e;
+        if (launch_pf_stream<DT, STAGE>(M, Ly, T, tiles, P, gain, s, e)) return e;
     }
-    const PfPlan p = plan_pf_gemm(M, T, P.n, STAGE);
+    const PfPlan p = plan_pf_gemm(M, T, tiles, P.n, STAGE);
     switch (p.shape) {
-        case 0: return launch_pf_gemm_v<DT, STAGE, PfLarge>(M, Ly, T, P, gain, s, parts, p.shares);
-        case 1: return launch_pf_gemm_v<DT, STAGE, PfMid>(M, Ly, T, P, gain, s, parts, p.shares);
-        default: return launch_pf_gemm_v<DT, STAGE, PfSmall>(M, Ly, T, P, gain, s, parts, p.shares);
+        case 0: return launch_pf_gemm_v<DT, STAGE, PfLarge>(M, Ly, T, tiles, P, gain, s, parts, p.shares);
+        case 1: return launch_pf_gemm_v<DT, STAGE, PfMid>(M, Ly, T, tiles, P, gain, s, parts, p.shares);
+        default: return launch_pf_gemm_v<DT, STAGE, PfSmall>(M, Ly, T, tiles, P, gain, s, parts, p.shares);
     }
 }
 
@@ -1121,7 +1128,8 @@ static hipError_t launch_pf_attention(const DevModel& M, const DevLayer& Ly, con
 }
 
 template <class DT, int HD>
-static hipError_t launch_prefill_t(const DevModel& M, const DevLayer* Ls, const PrefillBufs& T, const PrefillArgs& P, hipStream_t s) {
+static hipError_t launch_prefill_t(const DevModel& M, const DevLayer* Ls, const PrefillBufs& T, const PfTileSet* tiles, const PrefillArgs& P,
+                                   hipStream_t s) {
     const int rts = (P.n + 15) / 16;
     const int rstd_wgs = (P.n + 7) / 8;
     hipError_t e;
@@ -1129,7 +1137,7 @@ static hipError_t launch_prefill_t(const DevModel& M, const DevLayer* Ls, const 
     for (int l = 0; l < M.n_layers; ++l) {
         const float* gain_next = l + 1 < M.n_layers ? Ls[l + 1].g_attn : M.g_final;
         hipLaunchKernelGGL(k_pf_rstd, dim3(rstd_wgs), dim3(256), 0, s, M, T, P);
-        if ((e = launch_pf_gemm<DT, kPfQKV>(M, Ls[l], T, P, nullptr, s)) != hipSuccess) return e;
+        if ((e = launch_pf_gemm<DT, kPfQKV>(M, Ls[l], T, tiles, P, nullptr, s)) != hipSuccess) return e;
         for (int rt = 0; rt < rts; rt += T.att_tiles) {
             const int nrt = rts - rt < T.att_tiles ? rts - rt : T.att_tiles;
             const int last = P.n < (rt + nrt) * 16 ? P.n : (rt + nrt) * 16;     // rows below this one
@@ -1138,22 +1146,23 @@ static hipError_t launch_prefill_t(const DevModel& M, const DevLayer* Ls, const 
             const int rows = last - rt * 16;
             hipLaunchKernelGGL((k_pf_merge<DT, HD>), dim3((rows * M.Hq + 3) / 4), dim3(256), 0, s, M, T, P, rt, rows, nch);
         }
-        if ((e = launch_pf_gemm<DT, kPfOproj>(M, Ls[l], T, P, Ls[l].g_mlp, s)) != hipSuccess) return e;
+        if ((e = launch_pf_gemm<DT, kPfOproj>(M, Ls[l], T, tiles, P, Ls[l].g_mlp, s)) != hipSuccess) return e;
         hipLaunchKernelGGL(k_pf_rstd, dim3(rstd_wgs), dim3(256), 0, s, M, T, P);
-        if ((e = launch_pf_gemm<DT, kPfGateUp>(M, Ls[l], T, P, nullptr, s)) != hipSuccess) return e;
-        if ((e = launch_pf_gemm<DT, kPfDown>(M, Ls[l], T, P, gain_next, s)) != hipSuccess) return e;
+        if ((e = launch_pf_gemm<DT, kPfGateUp>(M, Ls[l], T, tiles, P, nullptr, s)) != hipSuccess) return e;
+        if ((e = launch_pf_gemm<DT, kPfDown>(M, Ls[l], T, tiles, P, gain_next, s)) != hipSuccess) return e;
     }
     hipLaunchKernelGGL(k_pf_rstd, dim3(rstd_wgs), dim3(256), 0, s, M, T, P);
     int parts = 0;
-    if ((e = launch_pf_gemm<DT, kPfLMHead>(M, Ls[0], T, P, nullptr, s, &parts)) != hipSuccess) return e;
+    if ((e = launch_pf_gemm<DT, kPfLMHead>(M, Ls[0], T, tiles, P, nullptr, s, &parts)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_pf_greedy, dim3((P.n + 3) / 4), dim3(256), 0, s, T, P, parts);
     return hipGetLastError();
 }
 
-hipError_t launch_prefill(const DevModel& M, const DevLayer* Ls, const PrefillBufs& T, const PrefillArgs& P, hipStream_t stream) {
+hipError_t launch_prefill(const DevModel& M, const DevLayer* Ls, const PrefillBufs& T, const PfTileSet* tiles, const PrefillArgs& P,
+                          hipStream_t stream) {
     if (M.dtype)
-        return M.hd == 128 ? launch_prefill_t<BF16, 128>(M, Ls, T, P, stream) : launch_prefill_t<BF16, 64>(M, Ls, T, P, stream);
-    return M.hd == 128 ? launch_prefill_t<FP32, 128>(M, Ls, T, P, stream) : launch_prefill_t<FP32, 64>(M, Ls, T, P, stream);
+        return M.hd == 128 ? launch_prefill_t<BF16, 128>(M, Ls, T, tiles, P, stream) : launch_prefill_t<BF16, 64>(M, Ls, T, tiles, P, stream);
+    return M.hd == 128 ? launch_prefill_t<FP32, 128>(M, Ls, T, tiles, P, stream) : launch_prefill_t<FP32, 64>(M, Ls, T, tiles, P, stream);
 }
 
 }  // namespace amusd
