@@ -154,7 +154,7 @@ int amusd_model_free(amusd_model *m);
  * returns in *next_token the greedy token after the last one.  next_token may
  * be NULL.  Errors: ARG, TOKEN, CAPACITY.
  * A prompt of more tokens than a verify pass is given (max_k, with 16-bit weights at most 8) goes through up to
- * 2048 rows at a time, in a workspace that amusd_model_finalize takes: about 0.4 GB for a 1B shape, 0.7 GB for an
+ * 2048 rows at a time, in a workspace that amusd_model_finalize takes: about 0.5 GB for a 1B shape, 0.7 GB for an
  * 8B shape, less for a max_ctx below 2048.  A model that finds no memory for it, or is told to hold none
  * (AMUSD_OPT_PREFILL_WORKSPACE), takes its prompts in verify passes instead: the same bits, 4 to 14 times the time.
  * So does a prompt while AMUSD_OPT_TIME_STAGE selects a stage.  When a model's weights or cache find no memory, the
