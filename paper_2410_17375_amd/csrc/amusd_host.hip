@@ -903,7 +903,8 @@ int amusd_draft_step_batch(amusd_model* m, int32_t n_seq, const int32_t* seq_ids
         for (int j = 0; j < i; ++j)
             if (seq_ids[j] == seq_ids[i]) return fail(AMUSD_E_ARG, "draft_step: a sequence appears twice");
         const SeqState& q = m->seqs[seq_ids[i]];
-        if (q.p_next < 0) return fail(AMUSD_E_STATE, "draft_step: p_next unknown");
+        // (logits that are not numbers have no arg-max: the token is then past every vocabulary, and no row to read)
+        if (q.p_next < 0 || q.p_next >= m->cfg.vocab) return fail(AMUSD_E_STATE, "draft_step: p_next unknown");
         if (q.kv_len + 1 > m->cfg.max_ctx) return fail(AMUSD_E_CAPACITY, "draft_step: cache full");
         toks[i] = q.p_next;
         segs[i] = SegReq{seq_ids[i], q.kv_len, &toks[i], 1};

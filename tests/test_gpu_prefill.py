@@ -167,6 +167,9 @@ def test_rolled_back_rows_without_a_value_do_not_reach_rows_before_their_block()
         if poison:
             m.prefill(np.full(10, bad, dtype=np.int32))   # positions 80 .. 89
             assert not np.isfinite(m.get_kv(1, 1, 80, 10)).any()
+            with pytest.raises(A.AmusdError) as e:        # logits that are not numbers give no token to go on with
+                m.draft_step()
+            assert e.value.code == -5 and m.kv_len() == 90
         m.kv_rollback(60)
         m.prefill(toks[60:80])                            # a prefill pass: rows 60 .. 75 and 76 .. 79
         got = [_bits(m.get_logits(4))]
