@@ -110,7 +110,7 @@ struct amusd_model {
     void* pf_mem = nullptr;                // the device allocation that its buffers are in
     size_t pf_bytes = 0;
     bool want_prefill = true;              // AMUSD_OPT_PREFILL_WORKSPACE
-    mutable std::mutex pf_mutex;                   // held while a prompt uses the workspace, and while it is taken or given back
+    mutable std::mutex pf_mutex;           // held while a prompt uses the workspace, and while it is taken or given back
     int* pf_host = nullptr;                // pinned: tokens of a prefill pass, then its greedy tokens
     void* staging = nullptr;               // device staging for host-provided tensors
     size_t staging_bytes = 0;
@@ -132,7 +132,7 @@ namespace {
 // model cannot do without, idle ones are given back, those of other models too.  (g_pf_mutex, then a model's pf_mutex, which
 // a prompt holds while it uses the workspace; a workspace in use is left alone.)
 std::mutex g_pf_mutex;
-std::vector<amusd_model*> g_pf_holders;
+std::vector<amusd_model*>& g_pf_holders = *new std::vector<amusd_model*>();   // never destroyed: models may be freed at exit
 
 void free_prefill(amusd_model* m) {          // with m->pf_mutex held, or no one else to use m
     if (m->pf_mem) (void)hipFree(m->pf_mem);

@@ -77,3 +77,8 @@ def test_bad_configs_are_rejected_before_any_device_work(A):
         with pytest.raises(A.AmusdError) as e:      # a valid config fails loudly without a device: no CPU fallback
             A.Model(**good)
         assert e.value.code == -6
+
+
+def test_prefill_workspace_calls_check_their_model(A):
+    assert A.lib.amusd_prefill_workspace_bytes(None) == -1
+    assert A.lib.amusd_set_option(None, A.OPT_PREFILL_WORKSPACE, 0) == -1
