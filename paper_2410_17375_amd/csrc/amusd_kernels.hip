@@ -572,7 +572,7 @@ struct EpiQKV {
             const int tt = tile - qt - kt;
             const int head = tt / tph, j = tt % tph;   // value features j*16 + r and j*16 + r + 8
             // vcache_index of columns 16 j + r and 16 j + r + 8, which are known to be in tile j: from the column the compiler
-            // divides by 16 with its sign, 45 instructions more behind the contraction (8B shape: pass 3.070 ms, so 3.055)
+            // divides by 16 with its sign, 45 instructions more behind the contraction (8B shape: pass 3.061 ms, so 3.050-3.060)
             constexpr int BK = DT::BLOCK_KEYS;
             const int b = pos / BK, q = pos % BK;
             const int e = (q / 16) * 4 + (q % 4), gg = (q % 16) / 4;
@@ -978,9 +978,9 @@ __device__ __forceinline__ void stage_accept(const DevModel& M, const PassArgs& 
 AMUSD_STAGE_KERNEL(k_embed, (stage_embed<DT>(M, gain, P, blockIdx.x, gridDim.x)))
 AMUSD_STAGE_KERNEL(k_qkv, (stage_qkv<DT, ONE>(M, Ly, P, blockIdx.x, gridDim.x, smem)))
 // The three forms of the attention unit are a kernel each.  As branches of one kernel they gave each other the registers
-// and LDS of the largest (128 KiB for head_dim 128: nothing of another model's pass fits beside a workgroup of it): a group
-// of 8 heads, verify model of 8 layers beside a draft model on another stream, 300 tokens 652 ms against 647 apart (648.5
-// with all in the register form); 8 sequences of the 1B shape 912 us a pass against 898.
+// and LDS of the largest (128 KiB for head_dim 128, where a group of 8 heads needs 64 and groups of 1 and 2 what the other
+// stages have: nothing of another model's pass then fits beside a workgroup of it).  8 sequences of the 1B shape 912 us a
+// pass, apart 898; attention there 15.5 us a launch, apart 15.0, at 16K context of the 8B shape 21.0 and 20.6.
 AMUSD_STAGE_KERNEL(k_attention, (stage_attention<DT, HD, ONE, 0>(M, Ly, P, blockIdx.x, gridDim.x, smem)))
 AMUSD_STAGE_KERNEL(k_attention_g4, (stage_attention<DT, HD, ONE, 4>(M, Ly, P, blockIdx.x, gridDim.x, smem)))
 AMUSD_STAGE_KERNEL(k_attention_g8, (stage_attention<DT, HD, ONE, 8>(M, Ly, P, blockIdx.x, gridDim.x, smem)))
