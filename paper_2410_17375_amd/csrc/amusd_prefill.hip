@@ -5,9 +5,9 @@
 // for 64 rows of a wave, and the pass is bound by the matrix cores.
 //
 // A row gets the same bits as in the verify pass, whatever the number of rows: an output element is, as there, eight
-// chains of 16x16 matrix instructions over the same K slices in the same order (k_slice), each for the hi and the lo
-// halves of the activations, W.hi + W.lo added per slice, slices added in wave order.  What eight waves do there side by
-// side a wave does here one after the other, with the slice's two sums and the total in registers.  The order inside a
+// chains of 16x16 matrix instructions over the same K slices in the same order (k_slice), a block's product with the hi
+// halves of the activations and then with the lo halves, slices added in wave order.  What eight waves do there side by
+// side a wave does here one after the other, with the slice's sum and the total in registers.  The order inside a
 // slice depends on the tile (its workgroup there), so a workgroup here takes tiles whose walks start alike: tile lists
 // ordered by that start are made once per model.
 #include <algorithm>
@@ -44,6 +44,24 @@ struct PfAct {
             *reinterpret_cast<float2*>(reinterpret_cast<float*>(buf) + at) = float2{x0, x1};
         }
     }
+    // four neighbouring columns (col a multiple of 4) of one row
+    static __device__ __forceinline__ void store4(void* buf, int kblocks, int row, int col, v4f x) {
+        const int kb = col / DT::KB, g = (col % DT::KB) / DT::EPL, e = col % DT::EPL;
+        const size_t at = (frag(kblocks, row >> 4, kb, 0) + g * 16 + (row & 15)) * DT::EPL + e;
+        if constexpr (DT::HAS_LO) {
+            uint32_t h[4], l[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                h[i] = bf16_rne(x[i]);
+                l[i] = bf16_rne(x[i] - bf16_to_f32(h[i]));
+            }
+            uint16_t* b = reinterpret_cast<uint16_t*>(buf);
+            *reinterpret_cast<uint2*>(b + at) = uint2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
+            *reinterpret_cast<uint2*>(b + at + 64 * DT::EPL) = uint2{l[0] | (l[1] << 16), l[2] | (l[3] << 16)};
+        } else {
+            *reinterpret_cast<v4f*>(reinterpret_cast<float*>(buf) + at) = x;
+        }
+    }
     static __device__ __forceinline__ void store1(void* buf, int kblocks, int row, int col, float x) {
         const int kb = col / DT::KB, g = (col % DT::KB) / DT::EPL, e = col % DT::EPL;
         const size_t at = (frag(kblocks, row >> 4, kb, 0) + g * 16 + (row & 15)) * DT::EPL + e;
@@ -70,28 +88,43 @@ template <> struct PfWalk<kPfLMHead> { using T = KWalkWide; };
 static_assert(KWalkDown::kRotWg == 0, "the prefill pass would start the down projection's slices elsewhere than the verify pass");
 
 // Slices first .. last - 1 of a contraction, block by block: slice s is that of wave s mod 8 of the verify pass, in K range
-// s / 8 of those that pairs of its workgroups share (kh blocks each).
+// s / 8 of those that pairs of its workgroups share (kh blocks each).  Kept as straight stretches, so that the step to the
+// next block, which every block's loads wait for, is an addition.
 template <class Walk>
 struct KSequence {
-    int kh, wg, s, last, i = 0, kb = 0;
-    KSlice ks{0, 0, 0, 1};
-    __device__ __forceinline__ KSequence(int kh_, int wg_, int first, int last_) : kh(kh_), wg(wg_), s(first - 1), last(last_) { next_slice(); }
-    __device__ __forceinline__ void next_slice() {
-        i = 0;
-#pragma unroll 1
-        do {
-            if (++s == last) return;
-            ks = k_slice_of<Walk>(kh, wg, s % kWaves);
-        } while (ks.S <= 0);
-    }
-    // the next block; past the end the last one again
-    __device__ __forceinline__ int take() {
-        if (s < last) {
-            const int x = i + ks.rot;
-            kb = s / kWaves * kh + ks.kb0 + (x >= ks.S ? x - ks.S : x) * ks.stride;
-            if (++i == ks.S) next_slice();
+    int kh, wg, s, last, kb = 0, run = 1, stride = 0, rest = 0, kb0 = 0;   // run: blocks to the end of this straight stretch
+    __device__ __forceinline__ KSequence(int kh_, int wg_, int first, int last_) : kh(kh_), wg(wg_), s(first - 1), last(last_) { stretch(); }
+    // the slice's blocks from its start to its end, then those before its start
+    __device__ __forceinline__ void stretch() {
+        if (rest > 0) {
+            kb = kb0;
+            run = rest;
+            rest = 0;
+            return;
         }
-        return kb;
+#pragma unroll 1
+        for (;;) {
+            if (s + 1 >= last) {         // past the end the last block again
+                run = 1 << 30;
+                stride = 0;
+                return;
+            }
+            ++s;
+            const KSlice ks = k_slice_of<Walk>(kh, wg, s % kWaves);
+            if (ks.S <= 0) continue;
+            kb0 = s / kWaves * kh + ks.kb0;
+            stride = ks.stride;
+            kb = kb0 + ks.rot * stride;
+            run = ks.S - ks.rot;
+            rest = ks.rot;
+            return;
+        }
+    }
+    __device__ __forceinline__ int take() {
+        const int at = kb;
+        if (--run == 0) stretch();
+        else kb += stride;
+        return at;
     }
 };
 
@@ -99,20 +132,21 @@ struct KSequence {
 // fragments of SLOTS K blocks go through a ring in LDS, filled by loads that deliver straight into it (SLOTS - 1 blocks
 // ahead; the loop has no other vector-memory instruction, so its waits can count them), and each fragment is read from
 // there by the waves of its row or column.
-//   4 x 2 waves of 4 x 4 tiles (256 columns x 128 rows, 32 KiB per K block): per K block 1024 clocks of matrix
-//       instructions on each SIMD, 96 KiB of LDS reads (768 clocks) and 32 KiB of loads (32 bytes per clock of the 64 that an
-//       L2 gives one of its compute units).  The three accumulators per output fill 192 of a wave's 256 registers.  8B shape,
-//       2048 rows: gate/up 845 us (774 on another card; the figures below are from the first) = 1.14 PFLOP/s of matrix instructions, hi and lo halves counted (a large library product
-//       on the same card: 1.29).  A fifth ring slot changes nothing; workgroups ordered column by column instead of in
-//       patches 887 us, with the loads through the compiler's builtin 908.
-//   smaller ones where that shape leaves compute units without a tile; they are bound by LDS reads.
+//   4 x 2 waves of 4 x 4 tiles (256 columns x 128 rows, 32 KiB per K block): per K block 1024 clocks of matrix instructions
+//       on each SIMD, 96 KiB of LDS reads (768 clocks) and 32 KiB of loads.  8B shape, 2048 rows: gate/up 867 us -> 780, down
+//       475 -> 410, O-projection 155 -> 120 (one card; others are 10 % faster).  With data that is all zero gate/up takes 600:
+//       the rest is the power that random data costs, and a bare loop of these instructions reaches 1.78 PFLOP/s with it (2.37
+//       with zeros).  Four waves of 8 x 4 tiles read a third less from LDS and take the same time (810, with 5 slots 790).
+//   smaller ones where that shape leaves compute units without a tile.  They are bound by what a compute unit can have under
+//       way, about 64 KiB whatever the ring's depth: 58 GB/s from HBM, 110 from L2, i.e. 0.28 us per K block of 16 KiB.
+//       (Touching the lines of later blocks, so that the loads find them in L2, was 3 to 20 % slower.)
 template <int WN_, int WM_, int A_, int B_, int SLOTS_>
 struct PfShape {
     static constexpr int WN = WN_, WM = WM_, A = A_, B = B_, SLOTS = SLOTS_;
     static constexpr int kTiles = WN * A, kRowTiles = WM * B, kThreads = WN * WM * 64;
     // accumulators in vector registers proper: with fewer waves the compiler keeps them in accumulation registers and
     // copies them back and forth around every slice
-    static constexpr int kMinWaves = A * B >= 8 ? 2 : 4;
+    static constexpr int kMinWaves = A * B >= 32 ? 1 : A * B >= 8 ? 2 : 4;
 };
 template <class DT, int STAGE, class Sh>
 struct PfGemm {
@@ -126,52 +160,56 @@ struct PfGemm {
     static constexpr int kLdsBytes = SLOTS * kSlotBytes;
     using Walk = typename PfWalk<STAGE>::T;
 
-    v4f tot[A][B], acc[A][B][AF];
-    uint4 wf[2], af[B][AF];
+    // Weight fragments are read WD ahead of their use, the next block's activation fragments as this one's are used up.
+    static constexpr int WR = A >= 4 ? 4 : 2, WD = WR / 2;
+    static constexpr int MID = A / 2;
+    static_assert(A % WR == 0 && MID + WD <= A, "");
+    v4f tot[A][B], acc[A][B];
+    uint4 wf[WR], af[B][AF];
 
     __device__ __forceinline__ uint4 lds_frag(const char* slot, int f, int lane) const {
         return *reinterpret_cast<const uint4*>(slot + f * 1024 + lane * 16);
     }
-    __device__ __forceinline__ void fold(int i, int j) {
-        if constexpr (AF == 2) tot[i][j] += acc[i][j][0] + acc[i][j][1];
-        else tot[i][j] += acc[i][j][0];
-    }
 
-    // One K block from slot `cur`; the following one is in `nxt` after the barrier in the middle, where the load of the
-    // block SLOTS - 1 ahead is issued (into the slot of the block before this one: every wave is past it).  At the first
-    // block of a slice (wave-uniform) the sums of the slice before are added to the total, tile by tile between the
-    // matrix instructions, and the new ones start at zero.
-    template <class Issue>
-    __device__ __forceinline__ void block(bool first, const char* cur, const char* nxt, int wn, int wm, int lane, Issue&& issue) {
+    // One K block from slot `cur`; the following one is in `nxt` after the barrier in the middle, where the loads of the block
+    // SLOTS - 1 ahead begin (into the slot of the block before this one: every wave is past it).  They are issued a few per
+    // step, up to the middle of the next block: all at once they hold the wave up, and with it its matrix instructions (four
+    // waves of 8 x 4 tiles: 869 us, spread 810).  FIRST, at the first block of a slice: the sums of the slice before are
+    // added to the total, tile by tile between the matrix instructions, and the new ones start at zero.
+    template <bool FIRST, class Issue>
+    __device__ __forceinline__ void block(const char* cur, const char* nxt, int wn, int wm, int lane, Issue&& issue) {
 #pragma unroll
         for (int i = 0; i < A; ++i) {
-            if (i == A / 2) {
+            if (i == MID) {
                 wait_vm<(SLOTS - 3) * NPW>();
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
-                issue();
+                issue(-1);
             }
-            if (i + 1 < A) wf[(i + 1) & 1] = lds_frag(cur, wn * A + i + 1, lane);
-            else wf[(i + 1) & 1] = lds_frag(nxt, wn * A, lane);
-            if (first) {
+            {
+                const int k = (i - MID + A) % A;
+#pragma unroll
+                for (int q = k * NPW / A; q < (k + 1) * NPW / A; ++q) issue(q);
+            }
+            if (i + WD < A) wf[(i + WD) % WR] = lds_frag(cur, wn * A + i + WD, lane);
+            else wf[(i + WD) % WR] = lds_frag(nxt, wn * A + i + WD - A, lane);
+            if constexpr (FIRST) {
+#pragma unroll
+                for (int j = 0; j < B; ++j) { tot[i][j] += acc[i][j]; asm volatile("" : "+v"(tot[i][j])); acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f}; }
+            }
+#pragma unroll
+            for (int f = 0; f < AF; ++f)
 #pragma unroll
                 for (int j = 0; j < B; ++j) {
-                    fold(i, j);
-#pragma unroll
-                    for (int f = 0; f < AF; ++f) acc[i][j][f] = v4f{0.f, 0.f, 0.f, 0.f};
+                    acc[i][j] = DT::mfma(wf[i % WR], af[j][f], acc[i][j]);
+                    if (i == A - 1) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        af[j][f] = lds_frag(nxt, WN * A + (wm * B + j) * AF + f, lane);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
                 }
-            }
-#pragma unroll
-            for (int j = 0; j < B; ++j) {
-#pragma unroll
-                for (int f = 0; f < AF; ++f) acc[i][j][f] = DT::mfma(wf[i & 1], af[j][f], acc[i][j][f]);
-                if (i == A - 1)
-#pragma unroll
-                    for (int f = 0; f < AF; ++f) af[j][f] = lds_frag(nxt, WN * A + (wm * B + j) * AF + f, lane);
-            }
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (A & 1) wf[0] = wf[1];
     }
 
     // The first K range is done: its total waits in memory, and this thread reads it back at the end.
@@ -182,44 +220,38 @@ struct PfGemm {
         for (int i = 0; i < A; ++i)
 #pragma unroll
             for (int j = 0; j < B; ++j) {
-                fold(i, j);
-                *reinterpret_cast<v4f*>(hp + (i * B + j) * (Sh::kThreads * 4)) = tot[i][j];
-                tot[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int f = 0; f < AF; ++f) acc[i][j][f] = v4f{0.f, 0.f, 0.f, 0.f};
+                *reinterpret_cast<v4f*>(hp + (i * B + j) * (Sh::kThreads * 4)) = tot[i][j] + acc[i][j];
+                tot[i][j] = acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
             }
     }
 
     template <class Issue>
     __device__ __forceinline__ void run_blocks(int kh, int wg, int first, int last, int wn, int wm, int lane, float* spill, char* smem,
                                                Issue&& issue) {
-        wait_vm<(SLOTS - 2) * NPW>();
+        wait_vm<(SLOTS - 3) * NPW + NPW * (A - MID) / A>();
         // no scalar load may be pending at the loop's entry: the compiler would then wait for all LDS reads at once in it
         __builtin_amdgcn_s_waitcnt(0xC07F);             // lgkmcnt(0)
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        wf[0] = lds_frag(smem, wn * A, lane);
 #pragma unroll
-        for (int j = 0; j < B; ++j)
+        for (int i = 0; i < WD; ++i) wf[i] = lds_frag(smem, wn * A + i, lane);
 #pragma unroll
-            for (int f = 0; f < AF; ++f) af[j][f] = lds_frag(smem, WN * A + (wm * B + j) * AF + f, lane);
+        for (int x = 0; x < B * AF; ++x) af[x / AF][x % AF] = lds_frag(smem, WN * A + wm * (B * AF) + x, lane);
         int cslot = 0;
-        auto slots = [&](const char*& cur, const char*& nxt) {
-            cur = smem + cslot * kSlotBytes;
+        auto one = [&](auto begin) {
+            const char* cur = smem + cslot * kSlotBytes;
             cslot = cslot + 1 == SLOTS ? 0 : cslot + 1;
-            nxt = smem + cslot * kSlotBytes;
+            const char* nxt = smem + cslot * kSlotBytes;
+            block<decltype(begin)::value>(cur, nxt, wn, wm, lane, issue);
         };
 #pragma unroll 1
         for (int s = first; s < last; ++s) {
             if (spill && s == kWaves) spill_total(spill);
-            const int S = k_slice_of<Walk>(kh, wg, s % kWaves).S;
+            const int S = __builtin_amdgcn_readfirstlane(k_slice_of<Walk>(kh, wg, s % kWaves).S);
             if (S <= 0) continue;
+            one(std::true_type());
 #pragma unroll 1
-            for (int i = 0; i < S; ++i) {
-                const char *cur, *nxt;
-                slots(cur, nxt);
-                block(i == 0, cur, nxt, wn, wm, lane, issue);
-            }
+            for (int i = 1; i < S; ++i) one(std::false_type());
         }
     }
 
@@ -246,30 +278,39 @@ struct PfGemm {
         int islot = 0;
         const unsigned lane16 = lane * 16;
         const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
-        auto issue = [&]() {
-            const int kb = ahead.take();
-            const unsigned dst = lds0 + islot * kSlotBytes + wave * (NPW * 1024);
-            // byte offsets of the block in a weight tile and in the activations (below 4 GiB: K up to 8 million)
-            const unsigned ow = (unsigned)kb * 1024u + lane16, oa = (unsigned)kb * (unsigned)(PfAct<DT>::kBlockTiles * AF * 1024) + lane16;
-#pragma unroll
-            for (int q = 0; q < NPW; ++q) load_to_lds(src[q], wave * NPW + q < WN * A ? ow : oa, dst + q * 1024);
-            islot = islot + 1 == SLOTS ? 0 : islot + 1;
+        unsigned dst = 0, ow = 0, oa = 0;
+        auto issue = [&](int q) {
+            if (q < 0) {
+                const int kb = ahead.take();
+                dst = lds0 + islot * kSlotBytes + wave * (NPW * 1024);
+                // byte offsets of the block in a weight tile and in the activations (below 4 GiB: K up to 8 million)
+                ow = (unsigned)kb * 1024u + lane16;
+                oa = (unsigned)kb * (unsigned)(PfAct<DT>::kBlockTiles * AF * 1024) + lane16;
+                islot = islot + 1 == SLOTS ? 0 : islot + 1;
+            } else {
+                load_to_lds(src[q], wave * NPW + q < WN * A ? ow : oa, dst + q * 1024);
+            }
         };
 #pragma unroll 1
-        for (int s = 0; s < SLOTS - 1; ++s) issue();
+        for (int s = 0; s < SLOTS - 1; ++s) {
+            issue(-1);
+#pragma unroll
+            for (int q = 0; q < NPW * (A - MID) / A; ++q) issue(q);
+            if (s < SLOTS - 2)
+#pragma unroll
+                for (int q = NPW * (A - MID) / A; q < NPW; ++q) issue(q);
+        }
 #pragma unroll
         for (int i = 0; i < A; ++i)
 #pragma unroll
             for (int j = 0; j < B; ++j) {
-                tot[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int f = 0; f < AF; ++f) acc[i][j][f] = v4f{0.f, 0.f, 0.f, 0.f};
+                tot[i][j] = acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
             }
         run_blocks(kh, t0 % wgs, first, last, wn, wm, lane, spill, smem, issue);
 #pragma unroll
         for (int i = 0; i < A; ++i)
 #pragma unroll
-            for (int j = 0; j < B; ++j) fold(i, j);
+            for (int j = 0; j < B; ++j) tot[i][j] += acc[i][j];
         if (spill) {
             const float* hp = spill + threadIdx.x * 4;
             asm volatile("" : "+v"(hp));
@@ -379,104 +420,138 @@ __device__ __forceinline__ void pf_inputs(const DevModel& M, const DevLayer& Ly,
     ways = STAGE == kPfDown && M.split_down ? 2 : 1;
 }
 
-// What a stage does with a finished 16 x 16 fragment (column tile `tile`, row tile rt).  Lane (m = row, g) brings columns
-// 4g .. 4g+3.  After a swap between the half-waves it has columns r0, r0 + 1 and their partners r0 + 8, r0 + 9, the pairs that
-// the verify pass's epilogues work on.  LM head: the lane's best of the columns it has seen so far goes to best_v, best_i.
-template <class DT, int STAGE>
-__device__ __forceinline__ void pf_epilogue(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PrefillArgs& P,
-                                            const float* gain_next, int tile, int rt, v4f c, float& best_v, int& best_i) {
+// A 16 x 16 fragment's lane (m = row, g) has columns 4g .. 4g+3 of it.  After a swap between the half-waves it has columns
+// r0, r0 + 1 and their partners r0 + 8, r0 + 9, the pairs that the verify pass's epilogues work on.
+struct PfPairs {
+    float u0, u1, w0, w1;        // columns r0, r0 + 1, r0 + 8, r0 + 9
+    __device__ __forceinline__ explicit PfPairs(v4f c) {
+        const auto pa = __builtin_amdgcn_permlane32_swap(__float_as_uint(c.x), __float_as_uint(c.z), false, false);
+        const auto pb = __builtin_amdgcn_permlane32_swap(__float_as_uint(c.y), __float_as_uint(c.w), false, false);
+        u0 = __uint_as_float(pa[0]); u1 = __uint_as_float(pb[0]);
+        w0 = __uint_as_float(pa[1]); w1 = __uint_as_float(pb[1]);
+    }
+    static __device__ __forceinline__ int r0() { return 4 * ((threadIdx.x >> 4) & 1) + 2 * ((threadIdx.x & 63) >> 5); }
+};
+
+// The residual stream, fragment by fragment in the order of a wave's result registers: [row tile][column tile][64 lanes][4].
+__device__ __forceinline__ v4f* pf_x_frag(const DevModel& M, const PrefillBufs& T, int tile, int rt) {
+    return reinterpret_cast<v4f*>(T.X) + ((size_t)rt * (M.d / 16) + tile) * 64 + (threadIdx.x & 63);
+}
+// A fragment of the stream's new value: stored, times the next norm's gain as the next contraction's input, and its sum of
+// squares per row.  All lanes of a wave call it.
+template <class DT>
+__device__ __forceinline__ void pf_residual(const DevModel& M, const PrefillBufs& T, const PrefillArgs& P, int tile, int rt, v4f x, v4f gain) {
     const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
-    const int r0 = 4 * (g & 1) + 2 * (lane >> 5);
     const int row = rt * 16 + m;
     const bool on = row < P.n;
-    const auto pa = __builtin_amdgcn_permlane32_swap(__float_as_uint(c.x), __float_as_uint(c.z), false, false);
-    const auto pb = __builtin_amdgcn_permlane32_swap(__float_as_uint(c.y), __float_as_uint(c.w), false, false);
-    const float u0 = __uint_as_float(pa[0]), u1 = __uint_as_float(pb[0]);      // columns r0, r0 + 1
-    const float w0 = __uint_as_float(pa[1]), w1 = __uint_as_float(pb[1]);      // columns r0 + 8, r0 + 9
-    if constexpr (STAGE == kPfOproj || STAGE == kPfDown) {
-        const int c1 = tile * 16 + r0;
-        float sq = 0.f;
-        if (on) {
-            float2* x1 = reinterpret_cast<float2*>(T.X + (size_t)row * M.d + c1);
-            float2* x2 = reinterpret_cast<float2*>(T.X + (size_t)row * M.d + c1 + 8);
-            const float2 g1 = *reinterpret_cast<const float2*>(gain_next + c1), g2 = *reinterpret_cast<const float2*>(gain_next + c1 + 8);
-            float2 a = *x1, b = *x2;
-            a.x += u0; a.y += u1; b.x += w0; b.y += w1;
-            *x1 = a;
-            *x2 = b;
-            PfAct<DT>::store2(T.A, M.d / DT::KB, row, c1, a.x * g1.x, a.y * g1.y);
-            PfAct<DT>::store2(T.A, M.d / DT::KB, row, c1 + 8, b.x * g2.x, b.y * g2.y);
-            sq = square_pair(a.x, b.x) + square_pair(a.y, b.y);
+    if (on) {
+        *pf_x_frag(M, T, tile, rt) = x;
+        PfAct<DT>::store4(T.A, M.d / DT::KB, row, tile * 16 + 4 * g, x * gain);
+    }
+    const PfPairs p(x);
+    float sq = square_pair(p.u0, p.w0) + square_pair(p.u1, p.w1);
+    sq = wave_xor_add<32>(sq);
+    sq = wave_xor_add<16>(sq);
+    if (on && g == 0) T.ssq[(size_t)tile * T.cap + row] = sq;
+}
+
+// What a stage does with a finished fragment (column tile `tile`, row tile rt).  fetch() asks for what finish() needs from
+// memory: a wave fetches for all of its fragments before it finishes the first, because the compiler moves no load in front
+// of another fragment's stores and the wave then waits for memory once per fragment (16 of them, 8B shape, 2048 rows: 26 us
+// of the O-projection's 142, 9 us of each round of gate/up's).  fetch() stays inside the buffers for fillers and for rows past
+// the last one.  LM head: the lane's best of the columns it has seen so far goes to best_v, best_i.
+template <class DT, int STAGE>
+struct PfEpilogue {
+    v4f x, gain;                 // O-projection, down projection
+    float sc;                    // the others: the row's 1 / rms
+    float2 cs, sn;               // QKV: the rotation
+    __device__ __forceinline__ void fetch(const DevModel& M, const PrefillBufs& T, const PrefillArgs& P, const float* gain_next, int tile, int rt) {
+        const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
+        const int row = rt * 16 + m;
+        if (tile < 0) tile = 0;
+        if constexpr (STAGE == kPfOproj || STAGE == kPfDown) {
+            x = *pf_x_frag(M, T, tile, rt);
+            gain = *reinterpret_cast<const v4f*>(gain_next + tile * 16 + 4 * g);
+        } else {
+            sc = T.rstd[row];
         }
-        sq = wave_xor_add<32>(sq);
-        sq = wave_xor_add<16>(sq);
-        if (on && g == 0) T.ssq[(size_t)tile * T.cap + row] = sq;
-    } else if constexpr (STAGE == kPfGateUp) {
-        if (on) {
-            const float sc = T.rstd[row];
-            PfAct<DT>::store2(T.H, M.F / DT::KB, row, tile * 8 + r0, swiglu(u0 * sc, w0 * sc), swiglu(u1 * sc, w1 * sc));
+        if constexpr (STAGE == kPfQKV) {
+            const int hd = M.hd, tph = hd / 16;
+            if (tile < (M.qdim + M.kvdim) / 16) {
+                const size_t ro = (size_t)(P.L0 + (row < P.n ? row : 0)) * (hd / 2) + (tile % tph) * 8 + PfPairs::r0();
+                cs = *reinterpret_cast<const float2*>(M.rope_cos + ro);
+                sn = *reinterpret_cast<const float2*>(M.rope_sin + ro);
+            }
         }
-    } else if constexpr (STAGE == kPfQKV) {
-        if (!on) return;
-        const float sc = T.rstd[row];
-        const int hd = M.hd, tph = hd / 16, qt = M.qdim / 16, kt = M.kvdim / 16, pos = P.L0 + row;
-        const float a0 = u0 * sc, a1 = u1 * sc, b0 = w0 * sc, b1 = w1 * sc;
-        const size_t slot_base = (size_t)P.slot * M.Hkv * M.ctx_pad * hd;
-        if (tile < qt + kt) {
-            const bool isq = tile < qt;
-            const int tt = isq ? tile : tile - qt;
-            const int head = tt / tph, c1 = (tt % tph) * 8 + r0;
-            const size_t ro = (size_t)pos * (hd / 2) + c1;
-            const float2 cs = *reinterpret_cast<const float2*>(M.rope_cos + ro), sn = *reinterpret_cast<const float2*>(M.rope_sin + ro);
-            float x0, x1, y0, y1;
-            rotate_pair(a0, b0, cs.x, sn.x, x0, y0);
-            rotate_pair(a1, b1, cs.y, sn.y, x1, y1);
-            if (isq) {
-                const size_t o = (size_t)row * M.qdim + head * hd + c1;
-                if constexpr (DT::HAS_LO) {
-                    auto put = [&](size_t at, float p, float q) {
-                        const uint32_t h0 = DT::att_bits(p), h1 = DT::att_bits(q);
-                        const uint32_t l0 = DT::att_bits(p - DT::att_float(h0)), l1 = DT::att_bits(q - DT::att_float(h1));
-                        *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(T.Q_hi) + at) = h0 | (h1 << 16);
-                        *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(T.Q_lo) + at) = l0 | (l1 << 16);
-                    };
-                    put(o, x0, x1);
-                    put(o + hd / 2, y0, y1);
+    }
+    __device__ __forceinline__ void finish(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PrefillArgs& P, int tile, int rt,
+                                           v4f c, float& best_v, int& best_i) const {
+        if constexpr (STAGE == kPfOproj || STAGE == kPfDown) pf_residual<DT>(M, T, P, tile, rt, x + c, gain);
+        else finish_scaled(M, Ly, T, P, tile, rt, c, best_v, best_i);
+    }
+    __device__ __forceinline__ void finish_scaled(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PrefillArgs& P, int tile,
+                                                  int rt, v4f c, float& best_v, int& best_i) const {
+        const int lane = threadIdx.x & 63, m = lane & 15;
+        const int row = rt * 16 + m, r0 = PfPairs::r0();
+        const PfPairs p(c);
+        if (row >= P.n) return;
+        const float a0 = p.u0 * sc, a1 = p.u1 * sc, b0 = p.w0 * sc, b1 = p.w1 * sc;
+        if constexpr (STAGE == kPfGateUp) {
+            PfAct<DT>::store2(T.H, M.F / DT::KB, row, tile * 8 + r0, swiglu(a0, b0), swiglu(a1, b1));
+        } else if constexpr (STAGE == kPfQKV) {
+            const int hd = M.hd, tph = hd / 16, qt = M.qdim / 16, kt = M.kvdim / 16, pos = P.L0 + row;
+            const size_t slot_base = (size_t)P.slot * M.Hkv * M.ctx_pad * hd;
+            if (tile < qt + kt) {
+                const bool isq = tile < qt;
+                const int tt = isq ? tile : tile - qt;
+                const int head = tt / tph, c1 = (tt % tph) * 8 + r0;
+                float x0, x1, y0, y1;
+                rotate_pair(a0, b0, cs.x, sn.x, x0, y0);
+                rotate_pair(a1, b1, cs.y, sn.y, x1, y1);
+                if (isq) {
+                    const size_t o = (size_t)row * M.qdim + head * hd + c1;
+                    if constexpr (DT::HAS_LO) {
+                        auto put = [&](size_t at, float v, float w) {
+                            const uint32_t h0 = DT::att_bits(v), h1 = DT::att_bits(w);
+                            const uint32_t l0 = DT::att_bits(v - DT::att_float(h0)), l1 = DT::att_bits(w - DT::att_float(h1));
+                            *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(T.Q_hi) + at) = h0 | (h1 << 16);
+                            *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(T.Q_lo) + at) = l0 | (l1 << 16);
+                        };
+                        put(o, x0, x1);
+                        put(o + hd / 2, y0, y1);
+                    } else {
+                        *reinterpret_cast<float2*>(reinterpret_cast<float*>(T.Q_hi) + o) = float2{x0, x1};
+                        *reinterpret_cast<float2*>(reinterpret_cast<float*>(T.Q_hi) + o + hd / 2) = float2{y0, y1};
+                    }
                 } else {
-                    *reinterpret_cast<float2*>(reinterpret_cast<float*>(T.Q_hi) + o) = float2{x0, x1};
-                    *reinterpret_cast<float2*>(reinterpret_cast<float*>(T.Q_hi) + o + hd / 2) = float2{y0, y1};
+                    const size_t hb = slot_base + (size_t)head * M.ctx_pad * hd;
+                    auto put = [&](int col, float v, float w) {      // neighbouring columns are neighbours in the cache
+                        const size_t at = hb + kcache_index<DT>(hd, pos, col);
+                        if constexpr (DT::HAS_LO)
+                            *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(Ly.kcache) + at) = DT::att_bits(v) | (DT::att_bits(w) << 16);
+                        else
+                            *reinterpret_cast<float2*>(reinterpret_cast<float*>(Ly.kcache) + at) = float2{v, w};
+                    };
+                    put(c1, x0, x1);
+                    put(c1 + hd / 2, y0, y1);
                 }
             } else {
+                const int tt = tile - qt - kt;
+                const int head = tt / tph, c1 = (tt % tph) * 16 + r0;
                 const size_t hb = slot_base + (size_t)head * M.ctx_pad * hd;
-                auto put = [&](int col, float p, float q) {      // neighbouring columns are neighbours in the cache
-                    const size_t at = hb + kcache_index<DT>(hd, pos, col);
-                    if constexpr (DT::HAS_LO)
-                        *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(Ly.kcache) + at) = DT::att_bits(p) | (DT::att_bits(q) << 16);
-                    else
-                        *reinterpret_cast<float2*>(reinterpret_cast<float*>(Ly.kcache) + at) = float2{p, q};
+                auto put = [&](int col, float v) {
+                    const size_t at = hb + vcache_index<DT>(hd, pos, col);
+                    if constexpr (DT::HAS_LO) reinterpret_cast<uint16_t*>(Ly.vcache)[at] = (uint16_t)DT::att_bits(v);
+                    else reinterpret_cast<float*>(Ly.vcache)[at] = v;
                 };
-                put(c1, x0, x1);
-                put(c1 + hd / 2, y0, y1);
+                put(c1, a0);
+                put(c1 + 1, a1);
+                put(c1 + 8, b0);
+                put(c1 + 9, b1);
             }
-        } else {
-            const int tt = tile - qt - kt;
-            const int head = tt / tph, c1 = (tt % tph) * 16 + r0;
-            const size_t hb = slot_base + (size_t)head * M.ctx_pad * hd;
-            auto put = [&](int col, float p) {
-                const size_t at = hb + vcache_index<DT>(hd, pos, col);
-                if constexpr (DT::HAS_LO) reinterpret_cast<uint16_t*>(Ly.vcache)[at] = (uint16_t)DT::att_bits(p);
-                else reinterpret_cast<float*>(Ly.vcache)[at] = p;
-            };
-            put(c1, a0);
-            put(c1 + 1, a1);
-            put(c1 + 8, b0);
-            put(c1 + 9, b1);
-        }
-    } else {                                   // LM head: logits of the rows that are kept, arg-max per row
-        if (on) {
-            const float sc = T.rstd[row];
+        } else {                                   // LM head: logits of the rows that are kept, arg-max per row
             const int c1 = tile * 16 + r0;
-            const float z[4] = {u0 * sc, u1 * sc, w0 * sc, w1 * sc};
+            const float z[4] = {a0, a1, b0, b1};
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int col = c1 + (e & 1) + 8 * (e >> 1);
@@ -485,7 +560,7 @@ __device__ __forceinline__ void pf_epilogue(const DevModel& M, const DevLayer& L
             }
         }
     }
-}
+};
 
 template <class DT, int STAGE, class Sh>
 __global__ void __launch_bounds__(Sh::kThreads, Sh::kMinWaves) k_pf_gemm(DevModel M, DevLayer Ly, PrefillBufs T, PfTiles L, PrefillArgs P,
@@ -518,13 +593,18 @@ __global__ void __launch_bounds__(Sh::kThreads, Sh::kMinWaves) k_pf_gemm(DevMode
     int best_i[B];
 #pragma unroll
     for (int j = 0; j < B; ++j) { best_v[j] = -INFINITY; best_i[j] = 0x7fffffff; }
+    PfEpilogue<DT, STAGE> epi[A][B];
+#pragma unroll
+    for (int i = 0; i < A; ++i)
+#pragma unroll
+        for (int j = 0; j < B; ++j) epi[i][j].fetch(M, T, P, gain_next, tiles[wn * A + i], rt0 + wm * B + j);
+    wait_vm<0>();                                       // fillers and rows past the last use nothing of it
 #pragma unroll
     for (int i = 0; i < A; ++i) {
-        const int tile = tiles[wn * A + i];
+        const int tile = __builtin_amdgcn_readfirstlane(tiles[wn * A + i]);
         if (tile < 0) continue;
 #pragma unroll
-        for (int j = 0; j < B; ++j)
-            pf_epilogue<DT, STAGE>(M, Ly, T, P, gain_next, tile, rt0 + wm * B + j, acc.tot[i][j], best_v[j], best_i[j]);
+        for (int j = 0; j < B; ++j) epi[i][j].finish(M, Ly, T, P, tile, rt0 + wm * B + j, acc.tot[i][j], best_v[j], best_i[j]);
     }
     const int m = lane & 15, g = lane >> 4;
     if constexpr (STAGE == kPfLMHead) {
@@ -541,7 +621,7 @@ __global__ void __launch_bounds__(Sh::kThreads, Sh::kMinWaves) k_pf_gemm(DevMode
     }
 }
 
-// Few rows: bound by streaming the weights, as the verify pass is, and built like its stages.  A workgroup owns NT column
+// Few tiles: bound by streaming the weights, as the verify pass is, and built like its stages.  A workgroup owns NT column
 // tiles x RT row tiles; its eight waves contract over the eight K slices side by side, fetching weight and activation
 // fragments straight into registers D blocks ahead, and the slices' sums meet in LDS in wave order.  `shares` > 1: one
 // workgroup per K range.  Against the form above: no barrier per K block, eight streams per workgroup, and every compute
@@ -560,8 +640,9 @@ __global__ void __launch_bounds__(kThreads, 2) k_pf_stream(DevModel M, DevLayer 
     using Walk = typename PfWalk<STAGE>::T;
     const int row_groups = (P.n + RT * 16 - 1) / (RT * 16);
     const int groups = gridDim.x / shares;
-    const int share = blockIdx.x / groups, idx = blockIdx.x % groups;
-    const int cg = idx / row_groups, rg = idx % row_groups;
+    const int share = blockIdx.x / groups, idx = xcd_contiguous(blockIdx.x % groups, groups);
+    int cg, rg;
+    patch_order(idx, L.n / NT, row_groups, cg, rg);
     const int* tiles = L.order + cg * NT;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int t0 = __builtin_amdgcn_readfirstlane(tiles[0]);
@@ -574,7 +655,7 @@ __global__ void __launch_bounds__(kThreads, 2) k_pf_stream(DevModel M, DevLayer 
     int K, ways;
     pf_inputs<STAGE>(M, Ly, T, W, act, K, ways);
     const int kblocks = K / DT::KB, kh = kblocks / ways;
-    v4f acc[NT][RT][AF], part[NT][RT];
+    v4f acc[NT][RT];
     // K ranges of this workgroup: all of them one after the other, or its own
     for (int range = share; range < ways; range += shares) {
         const KSlice ks = k_slice_of<Walk>(kh, t0 % L.wgs, wave);
@@ -582,9 +663,7 @@ __global__ void __launch_bounds__(kThreads, 2) k_pf_stream(DevModel M, DevLayer 
 #pragma unroll
         for (int i = 0; i < NT; ++i)
 #pragma unroll
-            for (int j = 0; j < RT; ++j)
-#pragma unroll
-                for (int f = 0; f < AF; ++f) acc[i][j][f] = v4f{0.f, 0.f, 0.f, 0.f};
+            for (int j = 0; j < RT; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
         if (S > 0) {
             const uint4* wp[NT];
 #pragma unroll
@@ -612,7 +691,7 @@ __global__ void __launch_bounds__(kThreads, 2) k_pf_stream(DevModel M, DevLayer 
 #pragma unroll
                     for (int i = 0; i < NT; ++i)
 #pragma unroll
-                        for (int j = 0; j < RT; ++j) acc[i][j][f] = DT::mfma(wb[from][i], ab[from][j][f], acc[i][j][f]);
+                        for (int j = 0; j < RT; ++j) acc[i][j] = DT::mfma(wb[from][i], ab[from][j][f], acc[i][j]);
             };
 #pragma unroll
             for (int d = 0; d < D; ++d) fetch(d < last ? d : last, d);
@@ -628,19 +707,12 @@ __global__ void __launch_bounds__(kThreads, 2) k_pf_stream(DevModel M, DevLayer 
             for (int d = 0; d < D; ++d)
                 if (s0 + d < S) multiply(d);
         }
-#pragma unroll
-        for (int i = 0; i < NT; ++i)
-#pragma unroll
-            for (int j = 0; j < RT; ++j) {
-                if constexpr (AF == 2) part[i][j] = acc[i][j][0] + acc[i][j][1];
-                else part[i][j] = acc[i][j][0];
-            }
         if (range != share) __syncthreads();        // the sums of the range before have been read
         v4f* lds = reinterpret_cast<v4f*>(pf_smem);   // [wave][fragment][lane]
 #pragma unroll
         for (int i = 0; i < NT; ++i)
 #pragma unroll
-            for (int j = 0; j < RT; ++j) lds[(wave * (NT * RT) + i * RT + j) * 64 + lane] = part[i][j];
+            for (int j = 0; j < RT; ++j) lds[(wave * (NT * RT) + i * RT + j) * 64 + lane] = acc[i][j];
         __syncthreads();
 #pragma unroll
         for (int x = 0; x < F; ++x) {
@@ -660,50 +732,52 @@ __global__ void __launch_bounds__(kThreads, 2) k_pf_stream(DevModel M, DevLayer 
         float* xch = T.xch + (size_t)idx * shares * (kThreads * F * 4);
         if (!combine_shares<PfSums<F>>(sum, xch, T.ticket + idx, share, shares, 1, pf_smem)) return;
     }
+    PfEpilogue<DT, STAGE> epi[F];
+#pragma unroll
+    for (int x = 0; x < F; ++x) {
+        const int f = wave + x * kWaves < NT * RT ? wave + x * kWaves : 0;
+        epi[x].fetch(M, T, P, gain_next, tiles[f / RT], rt0 + f % RT);
+    }
+    wait_vm<0>();
 #pragma unroll
     for (int x = 0; x < F; ++x) {
         const int f = wave + x * kWaves;
-        const int tile = f < NT * RT ? tiles[f / RT] : -1;
-        if (tile >= 0) pf_epilogue<DT, STAGE>(M, Ly, T, P, gain_next, tile, rt0 + f % RT, sum.tot[0][x], best_v, best_i);
+        const int tile = f < NT * RT ? __builtin_amdgcn_readfirstlane(tiles[f / RT]) : -1;
+        if (tile >= 0) epi[x].finish(M, Ly, T, P, tile, rt0 + f % RT, sum.tot[0][x], best_v, best_i);
     }
 }
 
 // ---------------------------------------------------------------- the stages around the contractions
-// Embedding rows -> residual stream, first norm input, sums of squares.  Thread -> (tile, row, column pair), as in the
-// verify pass; the sum over a tile's eight pairs is the same tree.
+// Embedding rows -> residual stream, first norm input, sums of squares.  A wave takes kEmbedTiles column tiles of one row tile,
+// so that a row's token (host memory) is read a few times and not once per tile.
+constexpr int kEmbedTiles = 8;
 template <class DT>
 __global__ void __launch_bounds__(256) k_pf_embed(DevModel M, PrefillBufs T, PrefillArgs P, const float* gain) {
     const int ntiles = M.d / 16;
     // counts of the stages whose tiles several workgroups share: each returns to 0 by itself; a pass still starts clean
     if (blockIdx.x == 0)
         for (int i = threadIdx.x; i < kPfTickets; i += 256) __hip_atomic_store(T.ticket + i, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const int idx = blockIdx.x * 2 + (threadIdx.x >> 7);
-    const int tile = idx % ntiles, rt = idx / ntiles;
-    const int mm = (threadIdx.x >> 3) & 15, r = threadIdx.x & 7;
-    const int row = rt * 16 + mm;
-    const bool on = row < P.n;
-    float sq = 0.f;
-    const int c1 = tile * 16 + r;
-    if (on) {
-        const size_t o = (size_t)T.tokens[row] * M.d + c1;
-        float x1, x2;
+    const int per = (ntiles + 4 * kEmbedTiles - 1) / (4 * kEmbedTiles);       // workgroups of a row tile
+    const int rt = blockIdx.x / per, first = (blockIdx.x % per * 4 + (threadIdx.x >> 6)) * kEmbedTiles;
+    const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
+    const int row = rt * 16 + m;
+    const size_t at = (size_t)T.tokens[row < P.n ? row : P.n - 1] * M.d + 4 * g;
+    v4f x[kEmbedTiles], gn[kEmbedTiles];
+#pragma unroll
+    for (int t = 0; t < kEmbedTiles; ++t) {
+        const int tile = first + t < ntiles ? first + t : ntiles - 1;
         if constexpr (DT::HAS_LO) {
-            x1 = bf16_to_f32(reinterpret_cast<const uint16_t*>(M.embed)[o]);
-            x2 = bf16_to_f32(reinterpret_cast<const uint16_t*>(M.embed)[o + 8]);
+            const uint2 v = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(M.embed) + at + tile * 16);
+            x[t] = v4f{bf16_to_f32(v.x & 0xFFFFu), bf16_to_f32(v.x >> 16), bf16_to_f32(v.y & 0xFFFFu), bf16_to_f32(v.y >> 16)};
         } else {
-            x1 = reinterpret_cast<const float*>(M.embed)[o];
-            x2 = reinterpret_cast<const float*>(M.embed)[o + 8];
+            x[t] = *reinterpret_cast<const v4f*>(reinterpret_cast<const float*>(M.embed) + at + tile * 16);
         }
-        T.X[(size_t)row * M.d + c1] = x1;
-        T.X[(size_t)row * M.d + c1 + 8] = x2;
-        PfAct<DT>::store1(T.A, M.d / DT::KB, row, c1, x1 * gain[c1]);
-        PfAct<DT>::store1(T.A, M.d / DT::KB, row, c1 + 8, x2 * gain[c1 + 8]);
-        sq = square_pair(x1, x2);
+        gn[t] = *reinterpret_cast<const v4f*>(gain + tile * 16 + 4 * g);
     }
-    sq = wave_xor_add<1>(sq);
-    sq = wave_xor_add<2>(sq);
-    sq = wave_xor_add<4>(sq);
-    if (on && r == 0) T.ssq[(size_t)tile * T.cap + row] = sq;
+    wait_vm<0>();                                         // a wave past the last tile uses nothing of it
+#pragma unroll
+    for (int t = 0; t < kEmbedTiles; ++t)
+        if (first + t < ntiles) pf_residual<DT>(M, T, P, first + t, rt, x[t], gn[t]);
 }
 
 // 1 / rms of each row; 32 lanes per row sum tiles s, s + 32, .. and then each other, in the verify pass's order.
@@ -1017,54 +1091,51 @@ static hipError_t launch_pf_stream_v(const DevModel& M, const DevLayer& Ly, cons
     return hipSuccess;
 }
 
-// The streaming form where it is the faster one: up to 64 rows, and up to 128 where one round of workgroups does the stage
-// (NT the smallest of 1, 2, 4 column tiles with that; at most 64 rows and still more workgroups: 4).  Measured against the
-// other form's best plan, us per launch: 8B shape, 24 rows QKV -18, O -8, gate/up -15, down -23; 61 rows -15, 0, -2, -9;
-// 128 rows -12, -8, (gate/up +38: 896 workgroups), -45; 192 rows +8, -1, +86, +12; 250 rows +9, +22, +129, +33.  1B shape,
-// 61 rows -6, -4, -5, 0; 128 rows -10, -11, (+6), -10; 192 rows -5, -8, +16, -2; 250 rows -4, -8, +35, +2.  Above 128 rows the
-// line stands where the 8B shape needs it: on the 1B shape a prompt of 192 rows would take 2.38 ms instead of 2.63 with the
-// streaming form in all but gate/up, one of 250 rows 2.51 instead of 2.69.
+// The streaming form where one round of workgroups does the stage: with the fewest column tiles (1, 2, 4) x 2 row tiles that
+// does it, else 8 x 2 for prompts of at most 32 rows, else 4 x 4.  More work per workgroup means fewer bytes, less means more
+// compute units that load.  us per launch (with 6 of timing), this form / the best plan of the other, 8B shape: 17 rows
+// QKV 19 / 33, O 16 / 32, gate/up 44 / 55, down 34 / 58; 61 rows 23 / 33, 20 / 32, (gate/up: 448 workgroups, 67 / 55), 41 / 58;
+// 128 rows 31 / 35, 23 / 33, (115 / 86), 56 / 61; 250 rows (54 / 46), 31 / 34, (200 / 114), (95 / 81).  1B shape: 61 rows 12 / 22,
+// 11 / 21, 21 / 24, 22 / 37; 250 rows 19 / 23, 14 / 21, (60 / 45), 35 / 40; 509 rows (34 / 30), 19 / 23, (117 / 65), (57 / 53).
+// Between its own forms, 61 rows of the 8B shape: O with 1, 2, 4 column tiles 26, 20, 23, down 57, 57 (2), 41 (4).
 template <class DT, int STAGE>
 static bool launch_pf_stream(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PfTileSet* tiles, const PrefillArgs& P,
                              const float* gain, hipStream_t s, hipError_t& e) {
-    if (P.n > 128) return false;
-    const int rt = P.n <= 32 ? 2 : 4, row_groups = (P.n + rt * 16 - 1) / (rt * 16);
     int shares = STAGE == kPfDown && M.split_down ? 2 : 1;
-    auto wgs = [&](int nt) { return group_tiles(tiles[STAGE], nt).n / nt * row_groups; };
-    const int nt = wgs(1) * shares <= T.cus ? 1 : wgs(2) * shares <= T.cus ? 2 : 4;
-    if (wgs(nt) * shares > T.cus && P.n > 64) return false;
-    const size_t sums = (size_t)wgs(nt) * shares * (kThreads * ((nt * rt + kWaves - 1) / kWaves) * 16);
-    if (wgs(nt) > kPfTickets || sums > T.xch_bytes) shares = 1;
-    if (rt == 2) e = nt == 1 ? launch_pf_stream_v<DT, STAGE, 1, 2, 6>(M, Ly, T, tiles, P, gain, s, shares)
-                     : nt == 2 ? launch_pf_stream_v<DT, STAGE, 2, 2, 4>(M, Ly, T, tiles, P, gain, s, shares)
-                               : launch_pf_stream_v<DT, STAGE, 4, 2, 3>(M, Ly, T, tiles, P, gain, s, shares);
-    else e = nt == 1 ? launch_pf_stream_v<DT, STAGE, 1, 4, 3>(M, Ly, T, tiles, P, gain, s, shares)
-             : nt == 2 ? launch_pf_stream_v<DT, STAGE, 2, 4, 3>(M, Ly, T, tiles, P, gain, s, shares)
-                       : launch_pf_stream_v<DT, STAGE, 4, 4, 2>(M, Ly, T, tiles, P, gain, s, shares);
+    auto wgs = [&](int nt, int rt) { return group_tiles(tiles[STAGE], nt).n / nt * ((P.n + rt * 16 - 1) / (rt * 16)); };
+    auto round = [&](int nt, int rt) { return wgs(nt, rt) * shares <= T.cus; };
+    const int nt = round(1, 2) ? 1 : round(2, 2) ? 2 : round(4, 2) ? 4 : P.n <= 32 && round(8, 2) ? 8 : 4;
+    const int rt = round(nt, 2) ? 2 : 4;
+    if (!round(nt, rt)) return false;
+    const size_t sums = (size_t)wgs(nt, rt) * shares * (kThreads * ((nt * rt + kWaves - 1) / kWaves) * 16);
+    if (wgs(nt, rt) > kPfTickets || sums > T.xch_bytes) shares = 1;
+    e = nt == 1 ? launch_pf_stream_v<DT, STAGE, 1, 2, 8>(M, Ly, T, tiles, P, gain, s, shares)
+      : nt == 2 ? launch_pf_stream_v<DT, STAGE, 2, 2, 6>(M, Ly, T, tiles, P, gain, s, shares)
+      : nt == 8 ? launch_pf_stream_v<DT, STAGE, 8, 2, 2>(M, Ly, T, tiles, P, gain, s, shares)
+      : rt == 2 ? launch_pf_stream_v<DT, STAGE, 4, 2, 4>(M, Ly, T, tiles, P, gain, s, shares)
+                : launch_pf_stream_v<DT, STAGE, 4, 4, 2>(M, Ly, T, tiles, P, gain, s, shares);
     return true;
 }
 
 // Workgroup shapes; the two smaller ones run two to a compute unit.
 using PfLarge = PfShape<4, 2, 4, 4, 4>;   // 256 columns x 128 rows
-using PfMid = PfShape<2, 2, 4, 2, 4>;     // 128 x 64
+using PfMid = PfShape<2, 2, 4, 2, 5>;     // 128 x 64
 using PfSmall = PfShape<2, 2, 2, 2, 6>;   // 64 x 64
 
 // Which shape a stage takes, and over how many workgroups the K slices of a tile are shared: the smallest estimate of
-// rounds x K blocks x time of a block, plus what the sharing costs.  The times were fitted to measurements of all choices
-// on the 8B and 1B shapes at 24 to 1000 rows: 0.93 us per K block of a large tile; 0.45 and 0.31 us of the smaller ones,
-// 0.545 and 0.40 when two share a compute unit; sharing 1.6 us per workgroup of a tile (its sums are written, counted and
-// read back through the memory side) and its bytes at 4 TB/s each way.  For instance at 250 rows of the 8B shape the QKV
-// projection takes 40 us on 384 small tiles and 99 on 48 large ones, gate/up 145 on small and 72 less on large ones.  Sharing
-// all slices is for few tiles and a long contraction (up to 128 rows the streaming form has those).  4 layers of d = 512, F =
-// 16384, whole prompts with the down projection's sixteen slices shared against its two K ranges: 129 rows 479 us (633), 256
-// rows 514 (655), 400 rows 731 (790), 600 rows 1050 (954: the estimate is off there).  d = 1024, F = 8192: equal within 2 %.
-// d = 2048, F = 16384: 129 rows 937 (927), 256 rows 1140 (990).
+// rounds x (K blocks x time of a block + a workgroup's beginning and end), plus what the sharing costs.  The times were fitted
+// to measurements of all choices on the 8B and 1B shapes at 17 to 2048 rows: 0.82 us per K block of a large tile; 0.30 and
+// 0.20 us of the smaller ones, 0.50 and 0.35 when two share a compute unit; 12, 7.5 and 6 us at the ends, 4 more for the large
+// tile's rotations; sharing 1.6 us per workgroup of a tile (its sums are written, counted and read back through the memory
+// side) and its bytes at 5 TB/s each way.  The choice is within 6 % of the best everywhere there.  For instance at 250 rows of the
+// 8B shape gate/up takes 114 us on 224 large tiles and 150 on 896 of the middle ones, at 128 rows 97 and 86.  Sharing
+// all slices is for few tiles and a long contraction (mostly the streaming form has those).
 struct PfPlan { int shape, shares; };
 static PfPlan plan_pf_gemm(const DevModel& M, const PrefillBufs& T, const PfTileSet* sets, int n, int stage) {
-    struct Shape { int tiles, rows, per_cu; double alone, full; };
-    static const Shape shapes[3] = {{PfLarge::kTiles, PfLarge::kRowTiles * 16, 1, 0.93, 0.93},
-                                    {PfMid::kTiles, PfMid::kRowTiles * 16, 2, 0.45, 0.545},
-                                    {PfSmall::kTiles, PfSmall::kRowTiles * 16, 2, 0.31, 0.40}};
+    struct Shape { int tiles, rows, per_cu; double alone, full, ends; };
+    static const Shape shapes[3] = {{PfLarge::kTiles, PfLarge::kRowTiles * 16, 1, 0.82, 0.82, 12.},
+                                    {PfMid::kTiles, PfMid::kRowTiles * 16, 2, 0.30, 0.50, 7.5},
+                                    {PfSmall::kTiles, PfSmall::kRowTiles * 16, 2, 0.20, 0.35, 6.}};
     const int K = stage == kPfOproj ? M.qdim : stage == kPfDown ? M.F : M.d;
     const int kblocks = K / (M.dtype ? BF16::KB : FP32::KB), ways = stage == kPfDown && M.split_down ? 2 : 1;
     PfPlan best{0, 1};
@@ -1076,8 +1147,10 @@ static PfPlan plan_pf_gemm(const DevModel& M, const PrefillBufs& T, const PfTile
             const size_t sum_bytes = tiles * h.tiles * h.rows * 16 * 4 * shares;
             if (shares > 1 && (tiles > (size_t)kPfTickets || sum_bytes > T.xch_bytes)) continue;
             const size_t wgs = tiles * shares, round = (size_t)T.cus * h.per_cu, rest = wgs % round;
-            const double rounds = wgs / round * h.full + (rest > (size_t)T.cus ? h.full : rest ? h.alone : 0.);
-            const double us = rounds * kblocks / shares + (shares > 1 ? 1.6 * shares + 2e-6 / 4 * sum_bytes : 0.);
+            const double ends = h.ends + (s == 0 && stage == kPfQKV ? 4. : 0.), blocks = (double)kblocks / shares;
+            const double full = blocks * h.full + ends, alone = blocks * h.alone + ends;
+            const double us = wgs / round * full + (rest > (size_t)T.cus ? full : rest ? alone : 0.) +
+                              (shares > 1 ? 1.6 * shares + 2e-6 / 5 * sum_bytes : 0.);
             if (least == 0 || us < least) {
                 least = us;
                 best = PfPlan{s, shares};
@@ -1133,7 +1206,7 @@ static hipError_t launch_prefill_t(const DevModel& M, const DevLayer* Ls, const 
     const int rts = (P.n + 15) / 16;
     const int rstd_wgs = (P.n + 7) / 8;
     hipError_t e;
-    hipLaunchKernelGGL((k_pf_embed<DT>), dim3((M.d / 16 * rts + 1) / 2), dim3(256), 0, s, M, T, P, Ls[0].g_attn);
+    hipLaunchKernelGGL((k_pf_embed<DT>), dim3((M.d / 16 + 4 * kEmbedTiles - 1) / (4 * kEmbedTiles) * rts), dim3(256), 0, s, M, T, P, Ls[0].g_attn);
     for (int l = 0; l < M.n_layers; ++l) {
         const float* gain_next = l + 1 < M.n_layers ? Ls[l + 1].g_attn : M.g_final;
         hipLaunchKernelGGL(k_pf_rstd, dim3(rstd_wgs), dim3(256), 0, s, M, T, P);
