@@ -493,6 +493,16 @@ struct PfEpilogue {
                                                   int rt, v4f c, float& best_v, int& best_i) const {
         const int lane = threadIdx.x & 63, m = lane & 15;
         const int row = rt * 16 + m, r0 = PfPairs::r0();
+        if constexpr (STAGE == kPfLMHead) {        // logits of the rows that are kept, arg-max per row
+            if (row >= P.n) return;
+            const int c0 = tile * 16 + 4 * (lane >> 4);
+            const v4f z = c * sc;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (better(z[e], c0 + e, best_v, best_i)) { best_v = z[e]; best_i = c0 + e; }
+            if (row >= P.keep0) *reinterpret_cast<v4f*>(M.logits + (size_t)(row - P.keep0) * M.V + c0) = z;
+            return;
+        }
         const PfPairs p(c);
         if (row >= P.n) return;
         const float a0 = p.u0 * sc, a1 = p.u1 * sc, b0 = p.w0 * sc, b1 = p.w1 * sc;
@@ -548,15 +558,6 @@ struct PfEpilogue {
                 put(c1 + 1, a1);
                 put(c1 + 8, b0);
                 put(c1 + 9, b1);
-            }
-        } else {                                   // LM head: logits of the rows that are kept, arg-max per row
-            const int c1 = tile * 16 + r0;
-            const float z[4] = {a0, a1, b0, b1};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int col = c1 + (e & 1) + 8 * (e >> 1);
-                if (better(z[e], col, best_v, best_i)) { best_v = z[e]; best_i = col; }
-                if (row >= P.keep0) M.logits[(size_t)(row - P.keep0) * M.V + col] = z[e];
             }
         }
     }
