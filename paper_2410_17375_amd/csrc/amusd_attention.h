@@ -13,16 +13,47 @@ constexpr int kPartRow = 4;   // floats appended to a partial's numerator: max, 
 // the hardware's power of two.
 __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// Exponentials are taken against a reference that a row's maximum may exceed by up to 2^kAttSlack: sums are rescaled only
+// when it grows beyond.  (The true maximum grows in most steps of a run, for one of a wave's 16 rows or another.)  Numerators
+// stay far inside the half range, whose hi + lo pairs are as precise at 256 as at 1.
+constexpr float kAttSlack = 8.f;
+__device__ __forceinline__ bool att_outgrown(float m, float ref) { return m > ref + kAttSlack; }   // false for -inf against -inf
+
 // Running softmax of one wave: 16 rows of one query head, a run of key blocks.
 template <int HD>
 struct AttState {
-    float m, l;              // running maximum and denominator of row lane & 15
+    float m, l;              // reference and denominator of row lane & 15; l: this lane's part of it until close()
     v4f o[HD / 16];          // numerator: o[j][e] is head_dim column 16 j + 4 (lane >> 4) + e
     __device__ __forceinline__ void clear() {
         m = -INFINITY;
         l = 0.f;
 #pragma unroll
         for (int j = 0; j < HD / 16; ++j) o[j] = v4f{0.f, 0.f, 0.f, 0.f};
+    }
+    __device__ __forceinline__ void rescale(bool up, float to) {
+        const float a = up ? exp2_fast(m - to) : 1.f;
+        m = up ? to : m;
+        l *= a;
+        // scaled where they stand, ahead of all products: left alone the compiler scales each into a temporary right
+        // before its product and waits for the temporary to be free again after every one
+#pragma unroll
+        for (int j = 0; j < HD / 16; ++j) o[j] = o[j] * a;
+    }
+    // the end of a run: the denominator from the four lanes that share the row
+    __device__ __forceinline__ void close() {
+        l = wave_xor_add<16>(l);
+        l = wave_xor_add<32>(l);
+    }
+    // adds a later (closed) run or chunk of the same rows; the first is copied
+    __device__ __forceinline__ void add(const AttState& s) {
+        const bool up = att_outgrown(s.m, m);
+        if (__builtin_amdgcn_ballot_w64(up)) rescale(up, s.m);
+        const float w = s.m == -INFINITY ? 0.f : exp2_fast(s.m - m);
+        l = fmaf(w, s.l, l);
+#pragma unroll
+        for (int j = 0; j < HD / 16; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[j][e] = fmaf(w, s.o[j][e], o[j][e]);
     }
 };
 
@@ -31,8 +62,8 @@ struct AttState {
 // kf(b, t, i), vf(b, j): the blocks' fragments.  MASKED: the blocks may hold keys that some row does not see (lim: the row's
 // last visible key, -1 for a row that is not the sequence's); the other form gives the same values for rows that see all of
 // them.  first: the run's first step (the numerators are zero).
-// Two blocks per step: a block's 8 scores per lane cost one rescaling of all numerators and two reductions across lanes,
-// and its products are short chains; two share the former and fill the gaps of the latter.  Groups of 4 and 8 heads take
+// Two blocks per step: a block's 8 scores per lane cost two exchanges across lanes, and its products are short chains; two
+// share the former and fill the gaps of the latter.  Groups of 4 and 8 heads take
 // two (always the same two of a run), groups of 1 and 2 one.  A second block without a visible key is left out: it would add
 // zeros, but what rolled-back rows have left in it may be no number, and zero times that is none either.
 template <class DT, int HD, int NB, bool MASKED, class KF, class VF>
@@ -52,38 +83,36 @@ __device__ __forceinline__ void attention_step(AttState<HD>& s, const uint4* qh,
 #pragma unroll
             for (int t = 0; t < NTL; ++t) sc[t] = DT::mfma_att(k[t], ql[i], sc[t]);
     }
-    float mx = -INFINITY;
+    __builtin_amdgcn_sched_barrier(0);
+    // maxima and sums by tile: a chain over all of a lane's scores is as long as the products
+    float mt[NTL];
 #pragma unroll
-    for (int t = 0; t < NTL; ++t)
+    for (int t = 0; t < NTL; ++t) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            sc[t][e] = sc[t][e] * scale;
+        for (int e = 0; e < 4; ++e)
             if (MASKED && p0 + t * 16 + g * 4 + e > lim) sc[t][e] = -INFINITY;
-            mx = fmaxf(mx, sc[t][e]);
-        }
+        mt[t] = fmaxf(fmaxf(sc[t].x, sc[t].y), fmaxf(sc[t].z, sc[t].w));
+    }
+    float mx = mt[0];
+#pragma unroll
+    for (int t = 1; t < NTL; ++t) mx = fmaxf(mx, mt[t]);
     mx = fmaxf(mx, lane_xor<16>(mx));
     mx = fmaxf(mx, lane_xor<32>(mx));
-    const float mnew = fmaxf(s.m, mx);
-    const float mref = mnew == -INFINITY ? 0.f : mnew;
-    const float alpha = exp2_fast(s.m - mref);      // 0 for the first visible key
-    if (!first) {
-        // scaled where they stand, ahead of all products: left alone the compiler scales each into a temporary right
-        // before its product and waits for the temporary to be free again after every one
-#pragma unroll
-        for (int j = 0; j < HT; ++j) s.o[j] = s.o[j] * alpha;
+    const float top = mx * scale;
+    if (first) {
+        s.m = top;
+    } else {
+        const bool up = att_outgrown(top, s.m);
+        if (__builtin_amdgcn_ballot_w64(up)) s.rescale(up, top);
     }
-    float lsum = 0.f;
+    const float mref = s.m == -INFINITY ? 0.f : s.m;
 #pragma unroll
     for (int t = 0; t < NTL; ++t)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            sc[t][e] = exp2_fast(sc[t][e] - mref);
-            lsum += sc[t][e];
-        }
-    lsum = wave_xor_add<16>(lsum);
-    lsum = wave_xor_add<32>(lsum);
-    s.l = fmaf(s.l, alpha, lsum);
-    s.m = mnew;
+        for (int e = 0; e < 4; ++e) sc[t][e] = exp2_fast(fmaf(sc[t][e], scale, -mref));
+#pragma unroll
+    for (int t = 0; t < NTL; ++t) s.l += (sc[t].x + sc[t].y) + (sc[t].z + sc[t].w);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         uint4 ph, pl = uint4{0, 0, 0, 0};
@@ -114,7 +143,7 @@ __device__ __forceinline__ void attention_step(AttState<HD>& s, const uint4* qh,
 // The runs of a unit's heads, one per wave, through LDS to one partial per (head, row): [head][row][HD numerators, max,
 // denominator, pad] at part_out.  smem: kWaves * kRows * (HD + kAttPad + 2) floats, free to be written.
 template <int HD>
-__device__ __forceinline__ void merge_runs(const AttState<HD>& s, int G, int parts, int hq, int part, int row0, int k, float* part_out,
+__device__ __forceinline__ void merge_runs(AttState<HD>& s, int G, int parts, int hq, int part, int row0, int k, float* part_out,
                                            float* smem) {
     constexpr int HT = HD / 16, HDP = HD + kAttPad;
     const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, g = lane >> 4;
@@ -122,6 +151,7 @@ __device__ __forceinline__ void merge_runs(const AttState<HD>& s, int G, int par
     float* partML = smem + kWaves * kRows * HDP;       // [hq][part][16][2]
     // run partial to LDS: o[j][e] is head_dim index 16j + 4g + e of row m
     const int slot = hq * parts + part;
+    s.close();
 #pragma unroll
     for (int j = 0; j < HT; ++j)
         *reinterpret_cast<v4f*>(partO + ((size_t)(slot * kRows + m) * HDP + j * 16 + g * 4)) = s.o[j];
@@ -134,13 +164,17 @@ __device__ __forceinline__ void merge_runs(const AttState<HD>& s, int G, int par
     for (int it = tid; it < G * kRows * (HD / 4); it += kThreads) {
         const int c4 = it % (HD / 4), mm = (it / (HD / 4)) % kRows, hh = it / (kRows * (HD / 4));
         if (mm < row0 || mm >= row0 + k) continue;
-        float Mx = -INFINITY;
-        for (int pp = 0; pp < parts; ++pp) Mx = fmaxf(Mx, partML[((hh * parts + pp) * kRows + mm) * 2]);
-        float den = 0.f;
-        v4f num = v4f{0.f, 0.f, 0.f, 0.f};
-        for (int pp = 0; pp < parts; ++pp) {
+        float Mx = partML[(hh * parts * kRows + mm) * 2], den = partML[(hh * parts * kRows + mm) * 2 + 1];
+        v4f num = *reinterpret_cast<const v4f*>(partO + ((size_t)(hh * parts * kRows + mm) * HDP + c4 * 4));
+        for (int pp = 1; pp < parts; ++pp) {           // AttState::add
             const int sl = hh * parts + pp;
             const float mw = partML[(sl * kRows + mm) * 2];
+            if (att_outgrown(mw, Mx)) {
+                const float a = exp2_fast(Mx - mw);
+                Mx = mw;
+                den *= a;
+                num = num * a;
+            }
             const float wt = mw == -INFINITY ? 0.f : exp2_fast(mw - Mx);
             den = fmaf(wt, partML[(sl * kRows + mm) * 2 + 1], den);
             const v4f x = *reinterpret_cast<const v4f*>(partO + ((size_t)(sl * kRows + mm) * HDP + c4 * 4));
@@ -204,6 +238,7 @@ __device__ __forceinline__ void attention_unit(const DevModel& M, const DevLayer
     load_block(b0, kf, vf);
     AttState<HD> s;
     s.clear();
+
     const int lim = mine ? L + m - row0 : -1;          // causal: the sequence's j-th row (tile row row0 + j) sees keys 0 .. L + j
     auto kfrag = [&](int, int t, int i) { return kf[t][i]; };
     auto vfrag = [&](int, int j) { return vf[j]; };
@@ -303,6 +338,7 @@ __device__ __forceinline__ void attention_unit_staged(const DevModel& M, const D
     wait_vm<0>();
     AttState<HD> s;
     s.clear();
+
     const int lim = mine ? L + m - row0 : -1;            // causal: the sequence's j-th row (tile row row0 + j) sees keys 0 .. L + j
     for (int st = 0; st < steps; ++st) {
         // The loads of this step are the only ones under way.  Behind the barrier they are there for all waves, and all
@@ -328,16 +364,14 @@ __device__ __forceinline__ void attention_unit_staged(const DevModel& M, const D
     merge_runs<HD>(s, G, PARTS, hq, part, row0, k, part_out, smem);
 }
 
-// Merge of the chunk partials of one (head, row) in chunk order by one wave: lanes first hold one chunk each (max,
-// weight, denominator), then one slice of head_dim each.  base: the row's partial of chunk 0; cstride: floats from chunk
+// Merge of the chunk partials of one (head, row) in chunk order by one wave, with AttState::add's operations in its order:
+// lanes first hold one chunk each (reference, weight, denominator), then one slice of head_dim each.  base: the row's partial of chunk 0; cstride: floats from chunk
 // to chunk.  num[i]: normalised output of head_dim column lane + 64 i.
 template <int HD>
 __device__ __forceinline__ void merge_chunks(const float* base, size_t cstride, int nch, int lane, float (&num)[HD / 64]) {
     constexpr int PER = HD / 64;
-    float Mrun = -INFINITY, den = 0.f;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) num[i] = 0.f;
-    // numerators of the first chunks are fetched together with the maxima: one memory round trip
+    float ref = 0.f, den = 0.f;
+    // numerators of the first chunks are fetched together with the references: one memory round trip
     constexpr int CPRE = 24;
     float pre[CPRE][PER];
 #pragma unroll
@@ -352,32 +386,62 @@ __device__ __forceinline__ void merge_chunks(const float* base, size_t cstride, 
         const float* p = base + (size_t)(on ? cc : c0) * cstride;
         const float mc = on ? p[HD] : -INFINITY;
         const float dc = on ? p[HD + 1] : 0.f;
-        float Mg = mc;
-        Mg = wave_max_all(Mg);
-        const float Mnew = fmaxf(Mrun, Mg);       // finite: chunk 0 always holds key 0
-        const float scale_old = exp2_fast(Mrun - Mnew);
-        const float wt = mc == -INFINITY ? 0.f : exp2_fast(mc - Mnew);
-        float dsum = wt * dc;
-        dsum = wave_sum_all(dsum);
-        den = fmaf(den, scale_old, dsum);
-#pragma unroll
-        for (int i = 0; i < PER; ++i) num[i] *= scale_old;
         const int ng = nch - c0 < 64 ? nch - c0 : 64;
-        if (c0 == 0) {
+        int j0 = 0;
+        if (c0 == 0) {                            // the first chunk is copied
+            ref = lane_value(mc, 0);
+            den = lane_value(dc, 0);
 #pragma unroll
-            for (int j = 0; j < CPRE; ++j) {
-                const float wj = j < ng ? lane_value(wt, j) : 0.f;
+            for (int i = 0; i < PER; ++i) num[i] = pre[0][i];
+            j0 = 1;
+        }
+        if (__builtin_amdgcn_ballot_w64(att_outgrown(mc, ref)) == 0) {      // the usual case: all against one reference
+            const float wt = mc == -INFINITY ? 0.f : exp2_fast(mc - ref);
+            // (lanes past the last chunk hold weight and denominator 0, and what is fetched there is the last chunk's)
+            if (c0 == 0) {
 #pragma unroll
-                for (int i = 0; i < PER; ++i) num[i] = fmaf(wj, pre[j][i], num[i]);
+                for (int j = 1; j < CPRE; ++j) {
+                    const float wj = lane_value(wt, j);
+                    den = fmaf(wj, lane_value(dc, j), den);
+#pragma unroll
+                    for (int i = 0; i < PER; ++i) num[i] = fmaf(wj, pre[j][i], num[i]);
+                }
+                j0 = CPRE;
+            }
+            constexpr int CB = 8;                  // the others, CB at a time
+            for (int j = j0; j < ng; j += CB) {
+                float x[CB][PER];
+#pragma unroll
+                for (int u = 0; u < CB; ++u) {
+                    const float* pj = base + (size_t)(c0 + (j + u < ng ? j + u : ng - 1)) * cstride;
+#pragma unroll
+                    for (int i = 0; i < PER; ++i) x[u][i] = pj[lane + 64 * i];
+                }
+#pragma unroll
+                for (int u = 0; u < CB; ++u) {
+                    const float wj = lane_value(wt, j + u);
+                    den = fmaf(wj, lane_value(dc, j + u), den);
+#pragma unroll
+                    for (int i = 0; i < PER; ++i) num[i] = fmaf(wj, x[u][i], num[i]);
+                }
+            }
+        } else {
+            for (int j = j0; j < ng; ++j) {       // AttState::add
+                const float mj = lane_value(mc, j);
+                const float* pj = base + (size_t)(c0 + j) * cstride;
+                if (att_outgrown(mj, ref)) {
+                    const float a = exp2_fast(ref - mj);
+                    ref = mj;
+                    den *= a;
+#pragma unroll
+                    for (int i = 0; i < PER; ++i) num[i] *= a;
+                }
+                const float wj = mj == -INFINITY ? 0.f : exp2_fast(mj - ref);
+                den = fmaf(wj, lane_value(dc, j), den);
+#pragma unroll
+                for (int i = 0; i < PER; ++i) num[i] = fmaf(wj, pj[lane + 64 * i], num[i]);
             }
         }
-        for (int j = c0 == 0 ? CPRE : 0; j < ng; ++j) {
-            const float wj = lane_value(wt, j);
-            const float* pj = base + (size_t)(c0 + j) * cstride;
-#pragma unroll
-            for (int i = 0; i < PER; ++i) num[i] = fmaf(wj, pj[lane + 64 * i], num[i]);
-        }
-        Mrun = Mnew;
     }
     const float inv = 1.0f / den;
 #pragma unroll

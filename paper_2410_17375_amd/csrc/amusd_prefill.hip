@@ -817,38 +817,81 @@ __global__ void __launch_bounds__(kThreads) k_pf_attention_unit(DevModel M, DevL
 // blocks of its run for itself and a workgroup ends with its chunk.  Here the G waves of a workgroup (the heads of one kv
 // head) walk the blocks of `span` chunks together for one row tile, two blocks a step; a block is staged once, by loads
 // that deliver straight into an LDS ring, and read from there by all of them.  A wave does the runs of a chunk one after
-// the other and merges the two in registers, with the unit's operations in the unit's order.  8B shape, all launches of 2
-// layers, 12288 + 3 x 4000 tokens: 36.6 ms -> 18.7; 4 layers, 3 x 2048 tokens: 4.3 -> 1.7.  Matrix cores busy for a third
-// of the time, vector instructions for as much: the registers allow two waves per SIMD, and each is a chain of products,
-// softmax, products.  Measured slower: two row tiles per wave (22 % more time: one wave per SIMD less to fill the gaps),
-// eight waves on two row tiles (26 %), chunks before row tiles in the grid (9 %: the XCD's workgroups then read
-// different keys), longer stretches per workgroup at 2K context (uneven ends).
-template <class DT, int HD, int G>
+// the other and merges the two in registers, with the unit's operations in the unit's order.  8B heads, one layer: 2000 rows
+// behind 14288 keys 1560 us -> 1160-1190, 2048 rows 229 -> 105, 509 rows 44 -> 26; 1B heads, 509 rows 36 -> 16.  Matrix cores busy
+// for 36 % of the time, vector instructions for 32: the registers allow two waves per SIMD, and each is a chain of products,
+// softmax, products.  Measured slower: two heads or two row tiles per wave (no registers for either), eight waves on two row
+// tiles (26 %), fragments read a group ahead of their products (4 %), chunks before row tiles in the grid (9 %: the XCD's
+// workgroups then read different keys).
+template <class DT, int HD, int G, bool WHOLE = false>
 struct PfAtt {
     static constexpr int FR = HD / 4 / DT::EPL, HT = HD / 16, TPB = DT::TPB;
     static constexpr int NF = TPB * FR + HT;             // fragments of a key block: keys, then values
-    static constexpr int NPW = NF / G, SLOTS = 5;
-    static constexpr int kSlotBytes = NF * 1024, kLdsBytes = SLOTS * kSlotBytes;
+    static constexpr int NPW = NF / G;
+    // Three sets of numerators of 128 columns, queries and fragments do not fit 256 registers: half of the totals, which are
+    // touched once a chunk, takes a ring slot's place in LDS (two workgroups per compute unit, 80 KiB each).
+    static constexpr int TL = WHOLE && DT::HAS_LO && HD == 128 && G == 4 ? HT / 2 : 0;     // tiles of the totals in LDS
+    static constexpr int SLOTS = TL ? 4 : 5;
+    static constexpr int kSlotBytes = NF * 1024, kTotalsAt = SLOTS * kSlotBytes, kLdsBytes = kTotalsAt + G * TL * 1024;
     static_assert(NF % G == 0 && (G == 4 || G == 8), "");
 };
-template <class DT, int HD, int G>
-__global__ void __launch_bounds__(64 * G, 2) k_pf_attention(DevModel M, DevLayer Ly, PrefillBufs T, PrefillArgs P, int rt0, int nrt,
-                                                             int nch, int span) {
-    using C = PfAtt<DT, HD, G>;
+// WHOLE: a workgroup walks all keys of its row tile and keeps the rows' totals over the chunks in registers, which the merge
+// kernel would otherwise add up from the chunks' partials in memory; the row tiles with most keys begin first.
+// Totals of a row tile's chunks.  TL > 0: the last TL numerator tiles stand at `rest` in LDS (the wave's own).
+template <int HD, int TL>
+struct PfTotals : AttState<HD> {
+    __device__ __forceinline__ explicit PfTotals(v4f*) { this->clear(); }
+    __device__ __forceinline__ v4f get(int j) const { return this->o[j]; }
+};
+template <>
+struct PfTotals<128, 4> {
+    static constexpr int HD = 128, TL = 4, HT = HD / 16, TR = HT - TL;
+    float m = -INFINITY, l = 0.f;
+    v4f o[TR];
+    v4f* rest;
+    __device__ __forceinline__ explicit PfTotals(v4f* rest_) : rest(rest_) {
+#pragma unroll
+        for (int j = 0; j < HT; ++j) put(j, v4f{0.f, 0.f, 0.f, 0.f});
+    }
+    __device__ __forceinline__ v4f get(int j) const { return j < TR ? o[j < TR ? j : 0] : rest[(j - TR) * 64]; }
+    __device__ __forceinline__ void put(int j, v4f x) {
+        if (j < TR) o[j < TR ? j : 0] = x;
+        else rest[(j - TR) * 64] = x;
+    }
+    __device__ __forceinline__ void add(const AttState<HD>& s) {       // AttState::add
+        const bool up = att_outgrown(s.m, m), any = __builtin_amdgcn_ballot_w64(up) != 0;
+        const float a = up ? exp2_fast(m - s.m) : 1.f;
+        m = up ? s.m : m;
+        const float w = s.m == -INFINITY ? 0.f : exp2_fast(s.m - m);
+        if (any) l *= a;
+        l = fmaf(w, s.l, l);
+#pragma unroll
+        for (int j = 0; j < HT; ++j) {
+            v4f x = get(j);
+            if (any) x = x * a;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = fmaf(w, s.o[j][e], x[e]);
+            put(j, x);
+        }
+    }
+};
+template <class DT, int HD, int G, bool WHOLE>
+__device__ __forceinline__ void pf_attention(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PrefillArgs& P, int rt0,
+                                             int nrt, int nch, int span, char* smem) {
+    using C = PfAtt<DT, HD, G, WHOLE>;
     constexpr int FR = C::FR, HT = C::HT, BK = DT::BLOCK_KEYS, NPW = C::NPW, SLOTS = C::SLOTS;
     constexpr int PARTS = kWaves / G;
-    extern __shared__ float att_smem[];
-    char* smem = reinterpret_cast<char*>(att_smem);
+    constexpr bool kPairs = WHOLE && PARTS == 2 && HD == 64;
     const int lane = threadIdx.x & 63, hq = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int m = lane & 15, g = lane >> 4;
     // row tiles fastest: the workgroups that run together on an XCD (its kv head's, with 8 of them) walk the same keys
     const int kvh = blockIdx.x % M.Hkv, rest = blockIdx.x / M.Hkv;
-    const int t = rest % nrt, sp = rest / nrt;            // row tile, from rt0; stretch of chunks
+    const int t = WHOLE ? nrt - 1 - rest : rest % nrt, sp = WHOLE ? 0 : rest / nrt;   // row tile, from rt0; stretch of chunks
     const int row0 = 16 * (rt0 + t);
     const int L = P.L0 + row0, k = P.n - row0 < 16 ? P.n - row0 : 16;
     const int key0 = sp * span * M.chunk;
-    if (key0 >= L + k) return;
-    const int key1 = key0 + span * M.chunk < L + k ? key0 + span * M.chunk : L + k;
+    if (!WHOLE && key0 >= L + k) return;
+    const int key1 = !WHOLE && key0 + span * M.chunk < L + k ? key0 + span * M.chunk : L + k;
     const int b0 = key0 / BK, nb = (key1 - key0 + BK - 1) / BK;   // blocks with visible keys
     const int lim = m < k ? L + m : -1;
 
@@ -888,6 +931,7 @@ __global__ void __launch_bounds__(64 * G, 2) k_pf_attention(DevModel M, DevLayer
     AttState<HD> s, s0;                                   // the run at hand; the chunk's first run once it is done
     s.clear();
     s0.clear();
+    PfTotals<HD, C::TL> all(reinterpret_cast<v4f*>(smem + C::kTotalsAt) + hq * C::TL * 64 + lane);
     int run = 0, part = 0, c = sp * span, cslot = 0;     // run: blocks of it that are done
     // A chunk's result leaves in kStores stores.  They are younger than the loads that are under way, and the waits for
     // those must not include them (a store takes as long as a load).  The compiler must make exactly these stores of what
@@ -911,9 +955,10 @@ __global__ void __launch_bounds__(64 * G, 2) k_pf_attention(DevModel M, DevLayer
     };
     int freed = 0;                                        // ring slots whose blocks the step before used
     for (int ib = 0; ib < nb;) {
-        const int two = run + 1 < M.bpw && ib + 1 < nb ? 2 : 1;   // blocks of this step
+        const bool pair = kPairs && M.bpw == 1 && ib + 1 < nb;   // a chunk's two runs of one block each, in one step
+        const int two = pair || (run + 1 < M.bpw && ib + 1 < nb) ? 2 : 1;   // blocks of this step
         __builtin_amdgcn_s_waitcnt(0xC07F);               // no LDS read of the step before is pending
-        wait_blocks(next - ib - two, older >= two);
+        wait_blocks(next - ib - two, !WHOLE && older >= two);
         older -= two;
         __builtin_amdgcn_s_barrier();                     // .. of all waves; and all are done with the step before
         asm volatile("" ::: "memory");
@@ -925,7 +970,16 @@ __global__ void __launch_bounds__(64 * G, 2) k_pf_attention(DevModel M, DevLayer
         auto kf = [&](int bb, int tt, int i) { return *reinterpret_cast<const uint4*>((bb ? slot1 : slot0) + (tt * FR + i) * 1024); };
         auto vf = [&](int bb, int j) { return *reinterpret_cast<const uint4*>((bb ? slot1 : slot0) + (C::TPB * FR + j) * 1024); };
         const int p0 = (b0 + ib) * BK;
-        if (two == 2) {
+        if (kPairs && pair) {
+            cslot = cslot + 1 == SLOTS ? 0 : cslot + 1;
+            auto kf1 = [&](int, int tt, int i) { return kf(1, tt, i); };
+            auto vf1 = [&](int, int j) { return vf(1, j); };
+            s0.clear();
+            attention_step<DT, HD, 1, true>(s0, qh, ql, kf, vf, p0, lim, g, M.att_scale, true);
+            attention_step<DT, HD, 1, true>(s, qh, ql, kf1, vf1, p0 + BK, lim, g, M.att_scale, true);
+            s0.close();
+            part = 1;
+        } else if (two == 2) {
             cslot = cslot + 1 == SLOTS ? 0 : cslot + 1;
             if (p0 + 2 * BK - 1 > L) attention_step<DT, HD, 2, true>(s, qh, ql, kf, vf, p0, lim, g, M.att_scale, run == 0);
             else attention_step<DT, HD, 2, false>(s, qh, ql, kf, vf, p0, lim, g, M.att_scale, run == 0);
@@ -934,8 +988,9 @@ __global__ void __launch_bounds__(64 * G, 2) k_pf_attention(DevModel M, DevLayer
         }
         ib += two;
         run += two;
-        if (run == M.bpw || ib >= nb) {
+        if (run >= M.bpw || ib >= nb) {
             run = 0;
+            s.close();
             if (PARTS == 2 && part == 0 && ib < nb) {     // the chunk's second run follows
                 s0 = s;
                 s.clear();
@@ -943,30 +998,49 @@ __global__ void __launch_bounds__(64 * G, 2) k_pf_attention(DevModel M, DevLayer
                 continue;
             }
             // a chunk that ends with its first run: the second, without keys, counts for nothing
-            float Mx = s.m, den = s.l;
-            if (PARTS == 2 && part == 1) {
-                Mx = fmaxf(s0.m, s.m);
-                const float w0 = s0.m == -INFINITY ? 0.f : exp2_fast(s0.m - Mx);
-                const float w1 = s.m == -INFINITY ? 0.f : exp2_fast(s.m - Mx);
-                den = fmaf(w1, s.l, fmaf(w0, s0.l, 0.f));
+            if constexpr (WHOLE) {                        // (added to nothing, the first chunk stays what it is)
+                if (PARTS == 2 && part == 1) {
+                    s0.add(s);
+                    all.add(s0);
+                } else {
+                    all.add(s);
+                }
+            } else {
+                if (PARTS == 2 && part == 1) {
+                    s0.add(s);
+                    s = s0;
+                }
+                // rows past the tile's last one are written too (their places are there and nobody reads them), so that every
+                // wave issues all its stores
+                float* out = T.att_part + ((((size_t)t * M.Hkv + kvh) * nch + c) * G + hq) * (kRows * (HD + kPartRow)) + m * (HD + kPartRow);
 #pragma unroll
-                for (int j = 0; j < HT; ++j)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) s.o[j][e] = fmaf(w1, s.o[j][e], fmaf(w0, s0.o[j][e], 0.f));
+                for (int j = 0; j < HT; ++j) *reinterpret_cast<v4f*>(out + j * 16 + g * 4) = s.o[j];
+                if (g == 0) *reinterpret_cast<float2*>(out + HD) = float2{s.m, s.l};
             }
-            // rows past the tile's last one are written too (their places are there and nobody reads them), so that every
-            // wave issues all its stores
-            float* out = T.att_part + ((((size_t)t * M.Hkv + kvh) * nch + c) * G + hq) * (kRows * (HD + kPartRow)) + m * (HD + kPartRow);
-#pragma unroll
-            for (int j = 0; j < HT; ++j) *reinterpret_cast<v4f*>(out + j * 16 + g * 4) = s.o[j];
-            if (g == 0) *reinterpret_cast<float2*>(out + HD) = float2{Mx, den};
-            older = next - ib;
             s.clear();
+            if constexpr (!WHOLE) older = next - ib;
             part = 0;
             ++c;
         }
     }
     wait_vm<0>();
+    if constexpr (WHOLE) {
+        const float inv = 1.0f / all.l;
+        if (m < k)
+#pragma unroll
+            for (int j = 0; j < HT; ++j) PfAct<DT>::store4(T.O, M.qdim / DT::KB, row0 + m, (kvh * G + hq) * HD + j * 16 + g * 4, all.get(j) * inv);
+    }
+}
+template <class DT, int HD, int G>
+__global__ void __launch_bounds__(64 * G, 2) k_pf_attention(DevModel M, DevLayer Ly, PrefillBufs T, PrefillArgs P, int rt0, int nrt,
+                                                             int nch, int span) {
+    extern __shared__ float att_smem[];
+    pf_attention<DT, HD, G, false>(M, Ly, T, P, rt0, nrt, nch, span, reinterpret_cast<char*>(att_smem));
+}
+template <class DT, int HD, int G>
+__global__ void __launch_bounds__(64 * G, 2) k_pf_attention_rows(DevModel M, DevLayer Ly, PrefillBufs T, PrefillArgs P) {
+    extern __shared__ float att_smem[];
+    pf_attention<DT, HD, G, true>(M, Ly, T, P, 0, (P.n + 15) / 16, 0, 0, reinterpret_cast<char*>(att_smem));
 }
 
 constexpr int kPfSpanKeys = 256;     // keys a workgroup walks at least (whole chunks)
@@ -1188,6 +1262,16 @@ static hipError_t launch_pf_attention_g(const DevModel& M, const DevLayer& Ly, c
     return hipSuccess;
 }
 
+template <class DT, int HD, int G>
+static hipError_t launch_pf_attention_rows(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PrefillArgs& P, hipStream_t s) {
+    constexpr int lds = PfAtt<DT, HD, G, true>::kLdsBytes;
+    static const hipError_t set = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pf_attention_rows<DT, HD, G>),
+                                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (set != hipSuccess) return set;
+    hipLaunchKernelGGL((k_pf_attention_rows<DT, HD, G>), dim3((P.n + 15) / 16 * M.Hkv), dim3(64 * G), lds, s, M, Ly, T, P);
+    return hipSuccess;
+}
+
 template <class DT, int HD>
 static hipError_t launch_pf_attention(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PrefillArgs& P, int rt0, int nrt,
                                       int nch, hipStream_t s) {
@@ -1198,6 +1282,28 @@ static hipError_t launch_pf_attention(const DevModel& M, const DevLayer& Ly, con
                                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (set != hipSuccess) return set;
     hipLaunchKernelGGL((k_pf_attention_unit<DT, HD>), dim3(nrt * nch * M.Hkv), dim3(kThreads), lds, s, M, Ly, T, P, rt0, nch);
+    return hipSuccess;
+}
+
+// A layer's attention.  Where there are row tiles enough for the chip, or few keys, a workgroup per row tile and kv head walks
+// all keys; else the keys are split into stretches and the chunks' partials merged.  us, whole / split, 8B heads: 61 rows
+// behind 0 / 450 / 1500 keys 8.4 / 19 / 46 against 12 / 18 / 23; 250 rows 14 / 25 / 53 against 24 / 31 / 45; 400 rows 19 / 31 / 60
+// against 33 / 44 / 64, behind 6000 186 against 140; 2000 rows behind 14288 1180 against 1510.  The line follows the keys at
+// which the two are equal: 500 for 32 workgroups, 1250 for 128, 1900 for 200.
+template <class DT, int HD>
+static hipError_t pf_attention_all(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PrefillArgs& P, hipStream_t s) {
+    const int rts = (P.n + 15) / 16, wgs = rts * M.Hkv;
+    if ((M.G == 4 || M.G == 8) && (wgs >= T.cus + T.cus / 2 || P.L0 + P.n <= 250 + 8 * wgs))
+        return M.G == 4 ? launch_pf_attention_rows<DT, HD, 4>(M, Ly, T, P, s) : launch_pf_attention_rows<DT, HD, 8>(M, Ly, T, P, s);
+    for (int rt = 0; rt < rts; rt += T.att_tiles) {
+        const int nrt = rts - rt < T.att_tiles ? rts - rt : T.att_tiles;
+        const int last = P.n < (rt + nrt) * 16 ? P.n : (rt + nrt) * 16;     // rows below this one
+        const int nch = (P.L0 + last + M.chunk - 1) / M.chunk;
+        const hipError_t e = launch_pf_attention<DT, HD>(M, Ly, T, P, rt, nrt, nch, s);
+        if (e != hipSuccess) return e;
+        const int rows = last - rt * 16;
+        hipLaunchKernelGGL((k_pf_merge<DT, HD>), dim3((rows * M.Hq + 3) / 4), dim3(256), 0, s, M, T, P, rt, rows, nch);
+    }
     return hipSuccess;
 }
 
@@ -1212,14 +1318,7 @@ static hipError_t launch_prefill_t(const DevModel& M, const DevLayer* Ls, const 
         const float* gain_next = l + 1 < M.n_layers ? Ls[l + 1].g_attn : M.g_final;
         hipLaunchKernelGGL(k_pf_rstd, dim3(rstd_wgs), dim3(256), 0, s, M, T, P);
         if ((e = launch_pf_gemm<DT, kPfQKV>(M, Ls[l], T, tiles, P, nullptr, s)) != hipSuccess) return e;
-        for (int rt = 0; rt < rts; rt += T.att_tiles) {
-            const int nrt = rts - rt < T.att_tiles ? rts - rt : T.att_tiles;
-            const int last = P.n < (rt + nrt) * 16 ? P.n : (rt + nrt) * 16;     // rows below this one
-            const int nch = (P.L0 + last + M.chunk - 1) / M.chunk;
-            if ((e = launch_pf_attention<DT, HD>(M, Ls[l], T, P, rt, nrt, nch, s)) != hipSuccess) return e;
-            const int rows = last - rt * 16;
-            hipLaunchKernelGGL((k_pf_merge<DT, HD>), dim3((rows * M.Hq + 3) / 4), dim3(256), 0, s, M, T, P, rt, rows, nch);
-        }
+        if ((e = pf_attention_all<DT, HD>(M, Ls[l], T, P, s)) != hipSuccess) return e;
         if ((e = launch_pf_gemm<DT, kPfOproj>(M, Ls[l], T, tiles, P, Ls[l].g_mlp, s)) != hipSuccess) return e;
         hipLaunchKernelGGL(k_pf_rstd, dim3(rstd_wgs), dim3(256), 0, s, M, T, P);
         if ((e = launch_pf_gemm<DT, kPfGateUp>(M, Ls[l], T, tiles, P, nullptr, s)) != hipSuccess) return e;
