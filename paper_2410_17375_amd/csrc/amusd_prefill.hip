@@ -256,9 +256,10 @@ struct PfGemm {
     }
 
     // Slices first .. last - 1.  spill: where the total over the first K range waits while the second is summed (null:
-    // there is only one range in first .. last).
+    // there is only one range in first .. last).  begun(): called when the first blocks are under way.
+    template <class Begun>
     __device__ __forceinline__ void contract(const uint4* __restrict__ W, const uint4* __restrict__ act, const int* tiles, int rt0,
-                                             int kblocks, int kh, int wgs, int first, int last, float* spill, char* smem) {
+                                             int kblocks, int kh, int wgs, int first, int last, float* spill, char* smem, Begun&& begun) {
         const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         const int wn = wave % Sh::WN, wm = wave / Sh::WN;
         const int t0 = __builtin_amdgcn_readfirstlane(tiles[0]);   // all of the workgroup's tiles walk K alike
@@ -300,6 +301,7 @@ struct PfGemm {
 #pragma unroll
                 for (int q = NPW * (A - MID) / A; q < NPW; ++q) issue(q);
         }
+        begun();
 #pragma unroll
         for (int i = 0; i < A; ++i)
 #pragma unroll
@@ -455,6 +457,75 @@ __device__ __forceinline__ void pf_residual(const DevModel& M, const PrefillBufs
     if (on && g == 0) T.ssq[(size_t)tile * T.cap + row] = sq;
 }
 
+// 1 / rms of a workgroup's rows.  32 sums per row, of tiles s, s + 32, .., and then of each other, in the verify pass's order: a
+// thread takes a row and PER of the sums, the workgroup's waves have the rest.  load() before the contraction's first loads,
+// so that they are under way together; sum() is a thread's part; of() adds a row's parts, which all threads have put into LDS.
+// The contraction takes 0.3 (streaming form) to 2.4 us longer with it and a launch of 4.6 to 4.8 us in front of it goes, two a
+// layer: prompt of 61 rows, 4 layers of 8B shape 726 us -> 707, 509 rows of the 1B shape 3030 -> 2950, 333 rows of a small fp32
+// model 173 -> 161.
+template <int ROWS, int THREADS>
+struct PfScales {
+    static constexpr int Q = THREADS / ROWS, PER = 32 / Q, AHEAD = 4;
+    static_assert(Q >= 1 && Q <= 16 && (Q & (Q - 1)) == 0, "");
+    float raw[2][AHEAD][PER];
+    const float* at;
+    size_t step;                 // from a tile to the next
+    int ntp, q;
+    __device__ __forceinline__ void load(float (&v)[AHEAD][PER], int t0) {
+#pragma unroll
+        for (int t = 0; t < AHEAD; ++t)
+#pragma unroll
+            for (int p = 0; p < PER; ++p) {
+                const int i = q + Q * p + 32 * (t0 + t);
+                v[t][p] = at[(i < ntp ? i : ntp - 1) * step];
+            }
+    }
+    __device__ __forceinline__ void load(const DevModel& M, const PrefillBufs& T, const PrefillArgs& P, int rt0) {
+        const int row = rt0 * 16 + (int)threadIdx.x % ROWS;
+        q = threadIdx.x / ROWS;
+        ntp = M.d / 16;
+        step = T.cap;
+        at = T.ssq + (row < P.n ? row : P.n - 1);
+        load(raw[0], 0);
+        if (ntp > 32 * AHEAD) load(raw[1], AHEAD);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    __device__ __forceinline__ float sum() {
+        float a[PER];
+#pragma unroll
+        for (int p = 0; p < PER; ++p) a[p] = 0.f;
+        auto add = [&](const float (&v)[AHEAD][PER], int t0) {
+#pragma unroll
+            for (int t = 0; t < AHEAD; ++t)
+#pragma unroll
+                for (int p = 0; p < PER; ++p) a[p] += q + Q * p + 32 * (t0 + t) < ntp ? v[t][p] : 0.f;
+        };
+        add(raw[0], 0);
+        if (ntp > 32 * AHEAD) add(raw[1], AHEAD);
+        for (int t0 = 2 * AHEAD; 32 * t0 < ntp; t0 += AHEAD) {
+            load(raw[0], t0);
+            add(raw[0], t0);
+        }
+#pragma unroll
+        for (int h = PER / 2; h > 0; h /= 2)
+#pragma unroll
+            for (int p = 0; p < h; ++p) a[p] += a[p + h];
+        return a[0];
+    }
+    static __device__ __forceinline__ float of(const DevModel& M, const float* lds, int row) {
+        float a[Q];
+#pragma unroll
+        for (int p = 0; p < Q; ++p) a[p] = lds[p * ROWS + row];
+#pragma unroll
+        for (int h = Q / 2; h > 0; h /= 2)
+#pragma unroll
+            for (int p = 0; p < h; ++p) a[p] += a[p + h];
+        return 1.0f / sqrtf(a[0] / (float)M.d + M.eps);
+    }
+};
+template <int STAGE>
+constexpr bool kPfScaled = STAGE == kPfQKV || STAGE == kPfGateUp || STAGE == kPfLMHead;
+
 // What a stage does with a finished fragment (column tile `tile`, row tile rt).  fetch() asks for what finish() needs from
 // memory: a wave fetches for all of its fragments before it finishes the first, because the compiler moves no load in front
 // of another fragment's stores and the wave then waits for memory once per fragment (16 of them, 8B shape, 2048 rows: 26 us
@@ -463,7 +534,7 @@ __device__ __forceinline__ void pf_residual(const DevModel& M, const PrefillBufs
 template <class DT, int STAGE>
 struct PfEpilogue {
     v4f x, gain;                 // O-projection, down projection
-    float sc;                    // the others: the row's 1 / rms
+    float sc;                    // the others: the row's 1 / rms, set by the kernel
     float2 cs, sn;               // QKV: the rotation
     __device__ __forceinline__ void fetch(const DevModel& M, const PrefillBufs& T, const PrefillArgs& P, const float* gain_next, int tile, int rt) {
         const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
@@ -472,8 +543,6 @@ struct PfEpilogue {
         if constexpr (STAGE == kPfOproj || STAGE == kPfDown) {
             x = *pf_x_frag(M, T, tile, rt);
             gain = *reinterpret_cast<const v4f*>(gain_next + tile * 16 + 4 * g);
-        } else {
-            sc = T.rstd[row];
         }
         if constexpr (STAGE == kPfQKV) {
             const int hd = M.hd, tph = hd / 16;
@@ -565,7 +634,7 @@ struct PfEpilogue {
 
 template <class DT, int STAGE, class Sh>
 __global__ void __launch_bounds__(Sh::kThreads, Sh::kMinWaves) k_pf_gemm(DevModel M, DevLayer Ly, PrefillBufs T, PfTiles L, PrefillArgs P,
-                                                                          const float* gain_next, int shares) {
+                                                                          const float* gain_next, int shares, bool own_scales) {
     extern __shared__ char pf_smem[];
     using G = PfGemm<DT, STAGE, Sh>;
     constexpr int A = Sh::A, B = Sh::B;
@@ -585,10 +654,24 @@ __global__ void __launch_bounds__(Sh::kThreads, Sh::kMinWaves) k_pf_gemm(DevMode
     const int rt0 = rg * Sh::kRowTiles;
     const int kblocks = K / DT::KB, slices = ways * kWaves, per = slices / shares;   // shares: 1, `ways` or `slices`
     float* xch = T.xch + (size_t)idx * shares * (Sh::kThreads * A * B * 4);
+    using Scales = PfScales<Sh::kRowTiles * 16, Sh::kThreads>;
+    Scales scales;
+    float scale_part = 0.f;                             // in a register: the ring of PfMid leaves no LDS for a second workgroup's
+    if constexpr (kPfScaled<STAGE>)
+        if (own_scales) scales.load(M, T, P, rt0);
     G acc;
     acc.contract(W, reinterpret_cast<const uint4*>(act), tiles, rt0, kblocks, kblocks / ways, L.wgs, share * per, share * per + per,
-                 per > kWaves ? xch : nullptr, pf_smem);
+                 per > kWaves ? xch : nullptr, pf_smem, [&] {
+                     if constexpr (kPfScaled<STAGE>)
+                         if (own_scales) scale_part = scales.sum();
+                 });
     if (shares > 1 && !combine_shares<G>(acc, xch, T.ticket + idx, share, shares, shares == ways ? 1 : kWaves, pf_smem)) return;
+    float* scale_sums = reinterpret_cast<float*>(pf_smem) + 64;    // (combine_shares has its flag in front)
+    if constexpr (kPfScaled<STAGE>)
+        if (own_scales) {
+            scale_sums[threadIdx.x] = scale_part;
+            __syncthreads();
+        }
 
     float best_v[B];
     int best_i[B];
@@ -599,6 +682,14 @@ __global__ void __launch_bounds__(Sh::kThreads, Sh::kMinWaves) k_pf_gemm(DevMode
     for (int i = 0; i < A; ++i)
 #pragma unroll
         for (int j = 0; j < B; ++j) epi[i][j].fetch(M, T, P, gain_next, tiles[wn * A + i], rt0 + wm * B + j);
+    if constexpr (kPfScaled<STAGE>)
+#pragma unroll
+        for (int j = 0; j < B; ++j) {
+            const int row = (wm * B + j) * 16 + (lane & 15);
+            const float sc = own_scales ? Scales::of(M, scale_sums, row) : T.rstd[rt0 * 16 + row];
+#pragma unroll
+            for (int i = 0; i < A; ++i) epi[i][j].sc = sc;
+        }
     wait_vm<0>();                                       // fillers and rows past the last use nothing of it
 #pragma unroll
     for (int i = 0; i < A; ++i) {
@@ -651,6 +742,10 @@ __global__ void __launch_bounds__(kThreads, 2) k_pf_stream(DevModel M, DevLayer 
     static_assert(STAGE != kPfLMHead, "");
     float best_v = 0.f;       // (the LM head's)
     int best_i = 0;
+    using Scales = PfScales<RT * 16, kThreads>;
+    __shared__ float scale_sums[kPfScaled<STAGE> ? kThreads : 1];
+    Scales scales;
+    if constexpr (kPfScaled<STAGE>) scales.load(M, T, P, rt0);
     const uint4* W;
     const void* act;
     int K, ways;
@@ -696,6 +791,7 @@ __global__ void __launch_bounds__(kThreads, 2) k_pf_stream(DevModel M, DevLayer 
             };
 #pragma unroll
             for (int d = 0; d < D; ++d) fetch(d < last ? d : last, d);
+            if constexpr (kPfScaled<STAGE>) scale_sums[threadIdx.x] = scales.sum();    // (these stages have one K range)
             int s0 = 0;
             for (; s0 + D < S; s0 += D) {
 #pragma unroll
@@ -707,6 +803,8 @@ __global__ void __launch_bounds__(kThreads, 2) k_pf_stream(DevModel M, DevLayer 
 #pragma unroll
             for (int d = 0; d < D; ++d)
                 if (s0 + d < S) multiply(d);
+        } else if constexpr (kPfScaled<STAGE>) {
+            scale_sums[threadIdx.x] = scales.sum();
         }
         if (range != share) __syncthreads();        // the sums of the range before have been read
         v4f* lds = reinterpret_cast<v4f*>(pf_smem);   // [wave][fragment][lane]
@@ -738,6 +836,7 @@ __global__ void __launch_bounds__(kThreads, 2) k_pf_stream(DevModel M, DevLayer 
     for (int x = 0; x < F; ++x) {
         const int f = wave + x * kWaves < NT * RT ? wave + x * kWaves : 0;
         epi[x].fetch(M, T, P, gain_next, tiles[f / RT], rt0 + f % RT);
+        if constexpr (kPfScaled<STAGE>) epi[x].sc = Scales::of(M, scale_sums, f % RT * 16 + (lane & 15));
     }
     wait_vm<0>();
 #pragma unroll
@@ -781,19 +880,16 @@ __global__ void __launch_bounds__(256) k_pf_embed(DevModel M, PrefillBufs T, Pre
         if (first + t < ntiles) pf_residual<DT>(M, T, P, first + t, rt, x[t], gn[t]);
 }
 
-// 1 / rms of each row; 32 lanes per row sum tiles s, s + 32, .. and then each other, in the verify pass's order.
+// 1 / rms of each row, for the contractions that don't take it themselves: a workgroup has 16 rows.
 __global__ void __launch_bounds__(256) k_pf_rstd(DevModel M, PrefillBufs T, PrefillArgs P) {
-    const int row = blockIdx.x * 8 + (threadIdx.x >> 5), s = threadIdx.x & 31;
-    const int r = row < P.n ? row : P.n - 1;
-    const int ntp = M.d / 16;
-    float acc = 0.f;
-    for (int i = s; i < ntp; i += 32) acc += T.ssq[(size_t)i * T.cap + r];
-    acc = wave_xor_add<16>(acc);
-    acc = wave_xor_add<8>(acc);
-    acc = wave_xor_add<4>(acc);
-    acc = wave_xor_add<2>(acc);
-    acc = wave_xor_add<1>(acc);
-    if (s == 0 && row < P.n) T.rstd[row] = 1.0f / sqrtf(acc / (float)M.d + M.eps);
+    using Scales = PfScales<16, 256>;
+    __shared__ float sums[256];
+    Scales scales;
+    scales.load(M, T, P, blockIdx.x);
+    sums[threadIdx.x] = scales.sum();
+    __syncthreads();
+    const int row = blockIdx.x * 16 + threadIdx.x;
+    if (threadIdx.x < 16 && row < P.n) T.rstd[row] = Scales::of(M, sums, threadIdx.x);
 }
 
 // Attention of row tiles rt0 .. rt0 + nrt - 1 (16 rows each, at positions L0 + 16 rt ..) against all keys before them.
@@ -1148,7 +1244,13 @@ static hipError_t launch_pf_gemm_v(const DevModel& M, const DevLayer& Ly, const 
     const int groups = L.n / Sh::kTiles;
     const int grid = groups * ((P.n + Sh::kRowTiles * 16 - 1) / (Sh::kRowTiles * 16)) * shares;
     if (parts) *parts = groups * Sh::WN;
-    hipLaunchKernelGGL((k_pf_gemm<DT, STAGE, Sh>), dim3(grid), dim3(Sh::kThreads), lds, s, M, Ly, T, L, P, gain, shares);
+    // Its workgroups take 1 / rms of their rows themselves while they read less than this of the sums of squares per compute
+    // unit.  us more for the contraction (k_pf_rstd and its launch take 4.8): 8B shape 61 rows gate/up 64 KiB 2.3, LM head 2.4,
+    // 2048 rows QKV 384 KiB 5.3, gate/up 900 KiB 18, LM head 4 MiB 25; 1B shape 509 rows gate/up 64 KiB 1.3, QKV 24 KiB 1.3.
+    constexpr double kOwnScaleBytes = 320 << 10;
+    const bool own_scales = (double)grid / T.cus * Sh::kRowTiles * M.d * 4 <= kOwnScaleBytes;
+    if (kPfScaled<STAGE> && !own_scales) hipLaunchKernelGGL(k_pf_rstd, dim3((P.n + 15) / 16), dim3(256), 0, s, M, T, P);
+    hipLaunchKernelGGL((k_pf_gemm<DT, STAGE, Sh>), dim3(grid), dim3(Sh::kThreads), lds, s, M, Ly, T, L, P, gain, shares, own_scales);
     return hipSuccess;
 }
 
@@ -1311,20 +1413,16 @@ template <class DT, int HD>
 static hipError_t launch_prefill_t(const DevModel& M, const DevLayer* Ls, const PrefillBufs& T, const PfTileSet* tiles, const PrefillArgs& P,
                                    hipStream_t s) {
     const int rts = (P.n + 15) / 16;
-    const int rstd_wgs = (P.n + 7) / 8;
     hipError_t e;
     hipLaunchKernelGGL((k_pf_embed<DT>), dim3((M.d / 16 + 4 * kEmbedTiles - 1) / (4 * kEmbedTiles) * rts), dim3(256), 0, s, M, T, P, Ls[0].g_attn);
     for (int l = 0; l < M.n_layers; ++l) {
         const float* gain_next = l + 1 < M.n_layers ? Ls[l + 1].g_attn : M.g_final;
-        hipLaunchKernelGGL(k_pf_rstd, dim3(rstd_wgs), dim3(256), 0, s, M, T, P);
         if ((e = launch_pf_gemm<DT, kPfQKV>(M, Ls[l], T, tiles, P, nullptr, s)) != hipSuccess) return e;
         if ((e = pf_attention_all<DT, HD>(M, Ls[l], T, P, s)) != hipSuccess) return e;
         if ((e = launch_pf_gemm<DT, kPfOproj>(M, Ls[l], T, tiles, P, Ls[l].g_mlp, s)) != hipSuccess) return e;
-        hipLaunchKernelGGL(k_pf_rstd, dim3(rstd_wgs), dim3(256), 0, s, M, T, P);
         if ((e = launch_pf_gemm<DT, kPfGateUp>(M, Ls[l], T, tiles, P, nullptr, s)) != hipSuccess) return e;
         if ((e = launch_pf_gemm<DT, kPfDown>(M, Ls[l], T, tiles, P, gain_next, s)) != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k_pf_rstd, dim3(rstd_wgs), dim3(256), 0, s, M, T, P);
     int parts = 0;
     if ((e = launch_pf_gemm<DT, kPfLMHead>(M, Ls[0], T, tiles, P, nullptr, s, &parts)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_pf_greedy, dim3((P.n + 3) / 4), dim3(256), 0, s, T, P, parts);
