@@ -7,7 +7,7 @@
 namespace amusd {
 
 constexpr int kAttPad = 4;    // row padding of the attention partials (spreads LDS banks)
-constexpr int kPartRow = 4;   // floats appended to a partial's numerator: max, denominator, 2 pad (keeps 16-byte alignment)
+constexpr int kPartRow = 4;   // floats appended to a partial's numerator: reference, denominator, 2 pad (keeps 16-byte alignment)
 
 // Scores, maxima and weights are in units of log2: the score scale carries the factor log2(e), and every exponential is
 // the hardware's power of two.
@@ -140,8 +140,8 @@ __device__ __forceinline__ void attention_step(AttState<HD>& s, const uint4* qh,
     }
 }
 
-// The runs of a unit's heads, one per wave, through LDS to one partial per (head, row): [head][row][HD numerators, max,
-// denominator, pad] at part_out.  smem: kWaves * kRows * (HD + kAttPad + 2) floats, free to be written.
+// The runs of a unit's heads, one per wave, through LDS to one partial per (head, row): [head][row][HD numerators,
+// reference, denominator, pad] at part_out.  smem: kWaves * kRows * (HD + kAttPad + 2) floats, free to be written.
 template <int HD>
 __device__ __forceinline__ void merge_runs(AttState<HD>& s, int G, int parts, int hq, int part, int row0, int k, float* part_out,
                                            float* smem) {
@@ -190,8 +190,8 @@ __device__ __forceinline__ void merge_runs(AttState<HD>& s, int G, int parts, in
 
 // One unit: chunk c of kv head kvh (the 8/G runs of bpw key blocks that the waves of a workgroup walk) against the tile
 // rows row0 .. row0+k-1, which stand at positions L .. L+k-1.  q_hi / q_lo: the tile's query rows, row-major.
-// slot_frags: start of the sequence's cache, in 16-byte fragments.  Writes [head of the group][row][HD numerators, max,
-// denominator, pad] to part_out.  smem: kWaves * kRows * (HD + kAttPad + 2) floats.
+// slot_frags: start of the sequence's cache, in 16-byte fragments.  Writes [head of the group][row][HD numerators,
+// reference, denominator, pad] to part_out.  smem: kWaves * kRows * (HD + kAttPad + 2) floats.
 template <class DT, int HD>
 __device__ __forceinline__ void attention_unit(const DevModel& M, const DevLayer& Ly, const void* q_hi, const void* q_lo,
                                                size_t slot_frags, int kvh, int c, int L, int k, int row0, float* part_out,
@@ -365,8 +365,8 @@ __device__ __forceinline__ void attention_unit_staged(const DevModel& M, const D
 }
 
 // Merge of the chunk partials of one (head, row) in chunk order by one wave, with AttState::add's operations in its order:
-// lanes first hold one chunk each (reference, weight, denominator), then one slice of head_dim each.  base: the row's partial of chunk 0; cstride: floats from chunk
-// to chunk.  num[i]: normalised output of head_dim column lane + 64 i.
+// lanes first hold one chunk each (reference, weight, denominator), then one slice of head_dim each.  base: the row's
+// partial of chunk 0; cstride: floats from chunk to chunk.  num[i]: normalised output of head_dim column lane + 64 i.
 template <int HD>
 __device__ __forceinline__ void merge_chunks(const float* base, size_t cstride, int nch, int lane, float (&num)[HD / 64]) {
     constexpr int PER = HD / 64;

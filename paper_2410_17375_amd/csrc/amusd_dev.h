@@ -138,7 +138,7 @@ struct DevModel {
     float* ssq;           // [d/16][16] partial sums of squares of X rows
     void* Q_hi;           // [16][qdim]
     void* Q_lo;
-    float* att_part;      // [units][G][16][hd+4]: numerator[hd], max, denominator, 2 pad; units <= n_slots*Hkv*max_chunks
+    float* att_part;      // [units][G][16][hd+4]: numerator[hd], reference, denominator, 2 pad; units <= n_slots*Hkv*max_chunks
     float* xch;           // [group of tiles][K range][tile of the group][16 rows][16 columns]: partial tiles of a stage
                           // whose workgroups share K ranges in pairs (sized for the stage with most tiles)
     int* xch_ticket;      // [kSplitTickets]: workgroups of the pair that have delivered their partials

@@ -785,7 +785,7 @@ __device__ __forceinline__ void stage_lmhead(const DevModel& M, const PassArgs& 
 // Work unit = (sequence, kv head, chunk of 8/G runs of bpw key blocks; a block is 32 keys
 // bf16 / 16 keys fp32); tile rows of other sequences are masked out of the unit.  Wave w of
 // the workgroup serves query head w % G of the group and the w / G -th run, walking its
-// blocks in order with a running softmax (max, denominator, numerator) in registers.
+// blocks in order with a running softmax (reference, denominator, numerator) in registers.
 // STAGED (the group's 4 or 8 heads): the blocks come through LDS, two a step, fetched once
 // for all waves of a run while the step before is used; 0: each wave fetches its own next
 // block into registers.  Scores are computed transposed (keys x rows) so that the
@@ -793,7 +793,7 @@ __device__ __forceinline__ void stage_lmhead(const DevModel& M, const PassArgs& 
 // P.V product: nothing is transposed through LDS.  The 8/G runs of a head are merged through
 // LDS in run order.  Block, run and chunk boundaries sit at fixed absolute positions, so a
 // row's result does not depend on how many rows the pass has or where it starts.
-// Output per (unit, head, row): numerator[hd], running max, denominator.
+// Output per (unit, head, row): numerator[hd], reference, denominator.
 template <class DT, int HD, bool ONE, int STAGED>
 __device__ __forceinline__ void stage_attention(const DevModel& M, const DevLayer& Ly, const PassArgs& P, int wg, int nwg,
                                                 float* smem) {
@@ -857,7 +857,7 @@ __device__ __forceinline__ void stage_attention(const DevModel& M, const DevLaye
 
 // Merge of the chunk partials of each (head, row) in chunk order -> normalised
 // attention output as the O-projection's input.  One wave per (head, row):
-// lanes first hold one chunk each (max, weight, denominator), then one slice of
+// lanes first hold one chunk each (reference, weight, denominator), then one slice of
 // head_dim each.
 template <class DT, int HD, bool ONE>
 __device__ __forceinline__ void stage_attn_merge(const DevModel& M, const PassArgs& P, int wg, int nwg) {
