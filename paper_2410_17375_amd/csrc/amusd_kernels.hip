@@ -127,21 +127,9 @@ __device__ __forceinline__ void gemm_accumulate(v4f (&out)[kMaxTilesPerRound], c
                                                 const uint4* __restrict__ act, int lane) {
     auto blk = [&](int st) { const int x = st + rot; return (x >= S ? x - S : x) * kstride; };   // stage -> K block, from kb0
     constexpr int AF = MODE == kActHiLo ? 2 : 1;          // activation fragments per K block
-    v4f acc[NT];
+    v4f acc[NT * AF];
 #pragma unroll
-    for (int j = 0; j < NT; ++j) acc[j] = v4f{0.f, 0.f, 0.f, 0.f};
-    // One block's products: the hi halves' on every tile, then the lo halves'.  Eight packed rows have both in one fragment;
-    // with its lanes exchanged (slot ^ 8) the lo halves stand in the rows' own columns.
-    auto multiply = [&](const uint4 (&w)[NT], const uint4 (&a)[AF]) {
-#pragma unroll
-        for (int j = 0; j < NT; ++j) acc[j] = DT::mfma(w[j], a[0], acc[j]);
-        if constexpr (MODE != kActSingle) {
-            uint4 lo = a[AF - 1];
-            if constexpr (MODE == kActPacked8) lo = uint4{lane_xor_u<8>(lo.x), lane_xor_u<8>(lo.y), lane_xor_u<8>(lo.z), lane_xor_u<8>(lo.w)};
-#pragma unroll
-            for (int j = 0; j < NT; ++j) acc[j] = DT::mfma(w[j], lo, acc[j]);
-        }
-    };
+    for (int j = 0; j < NT * AF; ++j) acc[j] = v4f{0.f, 0.f, 0.f, 0.f};
     const uint4* wp[NT];
 #pragma unroll
     for (int j = 0; j < NT; ++j) wp[j] = W + ((size_t)(tile0 + tile_stride * j) * kblocks + kb0) * 64 + lane;
@@ -161,7 +149,10 @@ __device__ __forceinline__ void gemm_accumulate(v4f (&out)[kMaxTilesPerRound], c
     for (; s0 + D < S; s0 += D) {
 #pragma unroll
         for (int i = 0; i < D; ++i) {
-            multiply(wb[i], ab[i]);
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int f = 0; f < AF; ++f) acc[j * AF + f] = DT::mfma(wb[i][j], ab[i][f], acc[j * AF + f]);
             const int sn = blk(s0 + i + D < last ? s0 + i + D : last);
 #pragma unroll
             for (int j = 0; j < NT; ++j) wb[i][j] = load_stream(wp[j] + (size_t)sn * 64);
@@ -177,13 +168,28 @@ __device__ __forceinline__ void gemm_accumulate(v4f (&out)[kMaxTilesPerRound], c
     for (int i = 0; i < D; ++i) {
         const bool on = s0 + i < S;
         const uint4 z = uint4{0, 0, 0, 0};
-        uint4 a[AF];
 #pragma unroll
-        for (int f = 0; f < AF; ++f) a[f] = on ? ab[i][f] : z;
-        multiply(wb[i], a);
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int f = 0; f < AF; ++f) acc[j * AF + f] = DT::mfma(wb[i][j], on ? ab[i][f] : z, acc[j * AF + f]);
     }
+    // The wave's W.hi and W.lo sums are added here, in one fixed order for every k: two accumulators of a
+    // tile (kActHiLo), or result columns m and m+8 of one accumulator (kActPacked8; lanes m < 8 keep the sum).
 #pragma unroll
-    for (int j = 0; j < NT; ++j) out[j] = acc[j];
+    for (int j = 0; j < NT; ++j) {
+        if constexpr (MODE == kActHiLo) {
+            out[j] = acc[2 * j] + acc[2 * j + 1];
+        } else if constexpr (MODE == kActPacked8) {
+            v4f lo;
+            lo.x = lane_xor<8>(acc[j].x);
+            lo.y = lane_xor<8>(acc[j].y);
+            lo.z = lane_xor<8>(acc[j].z);
+            lo.w = lane_xor<8>(acc[j].w);
+            out[j] = acc[j] + lo;
+        } else {
+            out[j] = acc[j];
+        }
+    }
 }
 
 __device__ __forceinline__ int round_tiles(int left) { return left >= 8 ? 8 : left == 7 ? 7 : left >= 4 ? 4 : left >= 2 ? 2 : 1; }
@@ -263,7 +269,7 @@ __device__ __forceinline__ void gemm_stage_m(const uint4* __restrict__ W, int n_
             }
         }
         // partial tiles to LDS as [wave][slot][column m][n]; lane holds n = 4g..4g+3 of result column m
-        // (kActPacked8: columns 8..15 carry nothing)
+        // (kActPacked8: columns 8..15 carry nothing the reduction reads)
 #pragma unroll
         for (int j = 0; j < SLOTS; ++j)
             if (j < nt && (MODE != kActPacked8 || m < 8))

@@ -97,13 +97,11 @@ __device__ __forceinline__ void store_act(void* hi, void* lo, size_t idx, float 
 // selects the lane group's EPL columns of the K block.
 //   fp32        : one part, slot = row.
 //   bf16, k <= 8: one part; slots 0-7 hold the hi halves of rows 0-7 and slots
-//                 8-15 their lo halves (x = hi + lo); the lo halves are brought
-//                 under their rows' slots in registers for a second MFMA;
+//                 8-15 their lo halves (x = hi + lo), so one MFMA yields W.hi in
+//                 result columns 0-7 and W.lo in columns 8-15;
 //   bf16, k > 8 : two parts (hi, lo), slot = row.
-// In both bf16 forms a wave adds a block's W.hi and then its W.lo to the same
-// sum, so a row's value does not depend on which form carried it.  One sum per
-// output (there were two, added at the end of a slice) is what lets the prefill
-// pass keep slice and total of a 4 x 4 tile wave in 128 registers instead of 192.
+// In both bf16 forms a wave adds its W.hi and W.lo sums before the cross-wave
+// reduction, so a row's value does not depend on which form carried it.
 template <class DT>
 __device__ __forceinline__ void store_gemm_in(void* buf, int k_rows, int m, int col, float x) {
     const int kb = col / DT::KB, g = (col % DT::KB) / DT::EPL, e = col % DT::EPL;

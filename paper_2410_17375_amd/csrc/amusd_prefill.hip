@@ -5,9 +5,9 @@
 // for 64 rows of a wave, and the pass is bound by the matrix cores.
 //
 // A row gets the same bits as in the verify pass, whatever the number of rows: an output element is, as there, eight
-// chains of 16x16 matrix instructions over the same K slices in the same order (k_slice), a block's product with the hi
-// halves of the activations and then with the lo halves, slices added in wave order.  What eight waves do there side by
-// side a wave does here one after the other, with the slice's sum and the total in registers.  The order inside a
+// chains of 16x16 matrix instructions over the same K slices in the same order (k_slice), each for the hi and the lo
+// halves of the activations, W.hi + W.lo added per slice, slices added in wave order.  What eight waves do there side by
+// side a wave does here one after the other, with the slice's two sums and the total in registers.  The order inside a
 // slice depends on the tile (its workgroup there), so a workgroup here takes tiles whose walks start alike: tile lists
 // ordered by that start are made once per model.
 #include <algorithm>
@@ -133,10 +133,11 @@ struct KSequence {
 // ahead; the loop has no other vector-memory instruction, so its waits can count them), and each fragment is read from
 // there by the waves of its row or column.
 //   4 x 2 waves of 4 x 4 tiles (256 columns x 128 rows, 32 KiB per K block): per K block 1024 clocks of matrix instructions
-//       on each SIMD, 96 KiB of LDS reads (768 clocks) and 32 KiB of loads.  8B shape, 2048 rows: gate/up 867 us -> 780, down
-//       475 -> 410, O-projection 155 -> 120 (one card; others are 10 % faster).  With data that is all zero gate/up takes 600:
-//       the rest is the power that random data costs, and a bare loop of these instructions reaches 1.78 PFLOP/s with it (2.37
-//       with zeros).  Four waves of 8 x 4 tiles read a third less from LDS and take the same time (810, with 5 slots 790).
+//       on each SIMD, 96 KiB of LDS reads (768 clocks) and 32 KiB of loads.  A slice's two sums and the total fill 192 of a
+//       wave's 256 registers.  8B shape, 2048 rows: gate/up 782 us -> 742, down 393 -> 369, O-projection 149 -> 120 (loads all
+//       behind the barrier -> spread over the block).  With data that is all zero gate/up takes 600: the rest is the power that
+//       random data costs, and a bare loop of these instructions reaches 1.78 PFLOP/s with it (2.37 with zeros).  One sum for
+//       the hi and the lo products (gate/up 727, down 350) rounds the lo products to the hi sum's last place: not taken.
 //   smaller ones where that shape leaves compute units without a tile.  They are bound by what a compute unit can have under
 //       way, about 64 KiB whatever the ring's depth: 58 GB/s from HBM, 110 from L2, i.e. 0.28 us per K block of 16 KiB.
 //       (Touching the lines of later blocks, so that the loads find them in L2, was 3 to 20 % slower.)
@@ -146,7 +147,7 @@ struct PfShape {
     static constexpr int kTiles = WN * A, kRowTiles = WM * B, kThreads = WN * WM * 64;
     // accumulators in vector registers proper: with fewer waves the compiler keeps them in accumulation registers and
     // copies them back and forth around every slice
-    static constexpr int kMinWaves = A * B >= 32 ? 1 : A * B >= 8 ? 2 : 4;
+    static constexpr int kMinWaves = A * B >= 8 ? 2 : 4;
 };
 template <class DT, int STAGE, class Sh>
 struct PfGemm {
@@ -164,18 +165,26 @@ struct PfGemm {
     static constexpr int WR = A >= 4 ? 4 : 2, WD = WR / 2;
     static constexpr int MID = A / 2;
     static_assert(A % WR == 0 && MID + WD <= A, "");
-    v4f tot[A][B], acc[A][B];
+    v4f tot[A][B], acc[A][B][AF];
     uint4 wf[WR], af[B][AF];
 
     __device__ __forceinline__ uint4 lds_frag(const char* slot, int f, int lane) const {
         return *reinterpret_cast<const uint4*>(slot + f * 1024 + lane * 16);
     }
 
+    // The slice's sums go to the total, and the next slice's start at zero.
+    __device__ __forceinline__ void fold(int i, int j) {
+        if constexpr (AF == 2) tot[i][j] += acc[i][j][0] + acc[i][j][1];
+        else tot[i][j] += acc[i][j][0];
+#pragma unroll
+        for (int f = 0; f < AF; ++f) acc[i][j][f] = v4f{0.f, 0.f, 0.f, 0.f};
+    }
+
     // One K block from slot `cur`; the following one is in `nxt` after the barrier in the middle, where the loads of the block
     // SLOTS - 1 ahead begin (into the slot of the block before this one: every wave is past it).  They are issued a few per
-    // step, up to the middle of the next block: all at once they hold the wave up, and with it its matrix instructions (four
-    // waves of 8 x 4 tiles: 869 us, spread 810).  FIRST, at the first block of a slice: the sums of the slice before are
-    // added to the total, tile by tile between the matrix instructions, and the new ones start at zero.
+    // step, up to the middle of the next block: all at once they hold the wave up, and with it its matrix instructions.  FIRST,
+    // at the first block of a slice: the sums of the slice before are added to the total, tile by tile between the matrix
+    // instructions, and the new ones start at zero.
     template <bool FIRST, class Issue>
     __device__ __forceinline__ void block(const char* cur, const char* nxt, int wn, int wm, int lane, Issue&& issue) {
 #pragma unroll
@@ -195,13 +204,16 @@ struct PfGemm {
             else wf[(i + WD) % WR] = lds_frag(nxt, wn * A + i + WD - A, lane);
             if constexpr (FIRST) {
 #pragma unroll
-                for (int j = 0; j < B; ++j) { tot[i][j] += acc[i][j]; asm volatile("" : "+v"(tot[i][j])); acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f}; }
+                for (int j = 0; j < B; ++j) {
+                    fold(i, j);
+                    asm volatile("" : "+v"(tot[i][j]));
+                }
             }
 #pragma unroll
             for (int f = 0; f < AF; ++f)
 #pragma unroll
                 for (int j = 0; j < B; ++j) {
-                    acc[i][j] = DT::mfma(wf[i % WR], af[j][f], acc[i][j]);
+                    acc[i][j][f] = DT::mfma(wf[i % WR], af[j][f], acc[i][j][f]);
                     if (i == A - 1) {
                         __builtin_amdgcn_sched_barrier(0);
                         af[j][f] = lds_frag(nxt, WN * A + (wm * B + j) * AF + f, lane);
@@ -220,8 +232,9 @@ struct PfGemm {
         for (int i = 0; i < A; ++i)
 #pragma unroll
             for (int j = 0; j < B; ++j) {
-                *reinterpret_cast<v4f*>(hp + (i * B + j) * (Sh::kThreads * 4)) = tot[i][j] + acc[i][j];
-                tot[i][j] = acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+                fold(i, j);
+                *reinterpret_cast<v4f*>(hp + (i * B + j) * (Sh::kThreads * 4)) = tot[i][j];
+                tot[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
             }
     }
 
@@ -306,13 +319,15 @@ struct PfGemm {
         for (int i = 0; i < A; ++i)
 #pragma unroll
             for (int j = 0; j < B; ++j) {
-                tot[i][j] = acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+                tot[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int f = 0; f < AF; ++f) acc[i][j][f] = v4f{0.f, 0.f, 0.f, 0.f};
             }
         run_blocks(kh, t0 % wgs, first, last, wn, wm, lane, spill, smem, issue);
 #pragma unroll
         for (int i = 0; i < A; ++i)
 #pragma unroll
-            for (int j = 0; j < B; ++j) tot[i][j] += acc[i][j];
+            for (int j = 0; j < B; ++j) fold(i, j);
         if (spill) {
             const float* hp = spill + threadIdx.x * 4;
             asm volatile("" : "+v"(hp));
@@ -744,14 +759,25 @@ __global__ void __launch_bounds__(kThreads, 2) k_pf_stream(DevModel M, DevLayer 
     int best_i = 0;
     using Scales = PfScales<RT * 16, kThreads>;
     __shared__ float scale_sums[kPfScaled<STAGE> ? kThreads : 1];
+    // A form whose sums take half of a wave's registers adds its scales up before it fetches its first blocks: nothing of them
+    // is then held beside the fragments (held across the fetches they go to scratch: 24 rows of the 8B shape, gate/up 58 us
+    // against 47, 128 rows QKV 40 against 32).
+    constexpr bool kScalesFirst = NT * RT * AF >= 32;
     Scales scales;
-    if constexpr (kPfScaled<STAGE>) scales.load(M, T, P, rt0);
+    float scale_part = 0.f;
+    if constexpr (kPfScaled<STAGE>) {
+        scales.load(M, T, P, rt0);
+        if constexpr (kScalesFirst) {
+            scale_part = scales.sum();
+            asm volatile("" : "+v"(scale_part));
+        }
+    }
     const uint4* W;
     const void* act;
     int K, ways;
     pf_inputs<STAGE>(M, Ly, T, W, act, K, ways);
     const int kblocks = K / DT::KB, kh = kblocks / ways;
-    v4f acc[NT][RT];
+    v4f acc[NT][RT][AF], part[NT][RT];
     // K ranges of this workgroup: all of them one after the other, or its own
     for (int range = share; range < ways; range += shares) {
         const KSlice ks = k_slice_of<Walk>(kh, t0 % L.wgs, wave);
@@ -759,26 +785,29 @@ __global__ void __launch_bounds__(kThreads, 2) k_pf_stream(DevModel M, DevLayer 
 #pragma unroll
         for (int i = 0; i < NT; ++i)
 #pragma unroll
-            for (int j = 0; j < RT; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+            for (int j = 0; j < RT; ++j)
+#pragma unroll
+                for (int f = 0; f < AF; ++f) acc[i][j][f] = v4f{0.f, 0.f, 0.f, 0.f};
         if (S > 0) {
             const uint4* wp[NT];
 #pragma unroll
             for (int i = 0; i < NT; ++i) {
                 const int t = __builtin_amdgcn_readfirstlane(tiles[i]);
-                wp[i] = W + ((size_t)(t < 0 ? t0 : t) * kblocks + range * kh + ks.kb0) * 64 + lane;
+                wp[i] = W + ((size_t)(t < 0 ? t0 : t) * kblocks + range * kh + ks.kb0) * 64;
             }
-            const uint4* ap = reinterpret_cast<const uint4*>(act) + PfAct<DT>::frag(kblocks, rt0, range * kh + ks.kb0, 0) + lane;
+            const uint4* ap = reinterpret_cast<const uint4*>(act) + PfAct<DT>::frag(kblocks, rt0, range * kh + ks.kb0, 0);
             uint4 wb[D][NT], ab[D][RT][AF];
             const int last = S - 1;
+            const unsigned ln = lane;
             auto fetch = [&](int st, int to) {
                 const int x = st + ks.rot;
                 const int s = (x >= S ? x - S : x) * ks.stride;
 #pragma unroll
-                for (int i = 0; i < NT; ++i) wb[to][i] = load_stream(wp[i] + (size_t)s * 64);
+                for (int i = 0; i < NT; ++i) wb[to][i] = load_stream(wp[i] + (size_t)s * 64 + ln);
 #pragma unroll
                 for (int j = 0; j < RT; ++j)
 #pragma unroll
-                    for (int f = 0; f < AF; ++f) ab[to][j][f] = ap[(size_t)s * (PfAct<DT>::kBlockTiles * AF * 64) + (j * AF + f) * 64];
+                    for (int f = 0; f < AF; ++f) ab[to][j][f] = (ap + (size_t)s * (PfAct<DT>::kBlockTiles * AF * 64) + (j * AF + f) * 64)[ln];
                 __builtin_amdgcn_sched_barrier(0);      // the loads stay in this order, and behind the products before them
             };
             auto multiply = [&](int from) {
@@ -787,11 +816,11 @@ __global__ void __launch_bounds__(kThreads, 2) k_pf_stream(DevModel M, DevLayer 
 #pragma unroll
                     for (int i = 0; i < NT; ++i)
 #pragma unroll
-                        for (int j = 0; j < RT; ++j) acc[i][j] = DT::mfma(wb[from][i], ab[from][j][f], acc[i][j]);
+                        for (int j = 0; j < RT; ++j) acc[i][j][f] = DT::mfma(wb[from][i], ab[from][j][f], acc[i][j][f]);
             };
 #pragma unroll
             for (int d = 0; d < D; ++d) fetch(d < last ? d : last, d);
-            if constexpr (kPfScaled<STAGE>) scale_sums[threadIdx.x] = scales.sum();    // (these stages have one K range)
+            if constexpr (kPfScaled<STAGE>) scale_sums[threadIdx.x] = kScalesFirst ? scale_part : scales.sum();    // (these stages have one K range)
             int s0 = 0;
             for (; s0 + D < S; s0 += D) {
 #pragma unroll
@@ -804,14 +833,21 @@ __global__ void __launch_bounds__(kThreads, 2) k_pf_stream(DevModel M, DevLayer 
             for (int d = 0; d < D; ++d)
                 if (s0 + d < S) multiply(d);
         } else if constexpr (kPfScaled<STAGE>) {
-            scale_sums[threadIdx.x] = scales.sum();
+            scale_sums[threadIdx.x] = kScalesFirst ? scale_part : scales.sum();
         }
+#pragma unroll
+        for (int i = 0; i < NT; ++i)
+#pragma unroll
+            for (int j = 0; j < RT; ++j) {
+                if constexpr (AF == 2) part[i][j] = acc[i][j][0] + acc[i][j][1];
+                else part[i][j] = acc[i][j][0];
+            }
         if (range != share) __syncthreads();        // the sums of the range before have been read
         v4f* lds = reinterpret_cast<v4f*>(pf_smem);   // [wave][fragment][lane]
 #pragma unroll
         for (int i = 0; i < NT; ++i)
 #pragma unroll
-            for (int j = 0; j < RT; ++j) lds[(wave * (NT * RT) + i * RT + j) * 64 + lane] = acc[i][j];
+            for (int j = 0; j < RT; ++j) lds[(wave * (NT * RT) + i * RT + j) * 64 + lane] = part[i][j];
         __syncthreads();
 #pragma unroll
         for (int x = 0; x < F; ++x) {
@@ -1288,7 +1324,7 @@ static hipError_t launch_pf_stream_v(const DevModel& M, const DevLayer& Ly, cons
 // The streaming form where one round of workgroups does the stage: with the fewest column tiles (1, 2, 4) x 2 row tiles that
 // does it, else 8 x 2 for prompts of at most 32 rows, else 4 x 4.  More work per workgroup means fewer bytes, less means more
 // compute units that load.  us per launch (with 6 of timing), this form / the best plan of the other, 8B shape: 17 rows
-// QKV 19 / 33, O 16 / 32, gate/up 44 / 55, down 34 / 58; 61 rows 23 / 33, 20 / 32, (gate/up: 448 workgroups, 67 / 55), 41 / 58;
+// QKV 19 / 33, O 16 / 32, gate/up 49 / 55, down 34 / 58; 61 rows 23 / 33, 20 / 32, (gate/up: 448 workgroups, 67 / 55), 41 / 58;
 // 128 rows 31 / 35, 23 / 33, (115 / 86), 56 / 61; 250 rows (54 / 46), 31 / 34, (200 / 114), (95 / 81).  1B shape: 61 rows 12 / 22,
 // 11 / 21, 21 / 24, 22 / 37; 250 rows 19 / 23, 14 / 21, (60 / 45), 35 / 40; 509 rows (34 / 30), 19 / 23, (117 / 65), (57 / 53).
 // Between its own forms, 61 rows of the 8B shape: O with 1, 2, 4 column tiles 26, 20, 23, down 57, 57 (2), 41 (4).

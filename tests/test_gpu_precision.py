@@ -1,0 +1,69 @@
+"""What the sums of a pass keep: inputs on which a sum with fewer places, or in another unit, would give something else altogether."""
+import numpy as np
+import pytest
+
+from workload import SHAPES, WeightStore, prompt_tokens
+from workload.tensors import round_to_bf16_bits
+
+pytestmark = pytest.mark.gpu
+
+
+def _models_of(shape, max_ctx, store, n=1):
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2410_17375_amd as A
+    from paper_2410_17375_amd.harness import load_model
+    ms = [load_model(shape, max_ctx, store=store) for _ in range(n)]
+    for m in ms:
+        m.set_option(A.OPT_KEEP_LOGITS, 1)
+    return ms
+
+
+class _Cancelling(WeightStore):
+    """Layers that add nothing.  In every K block of the LM head one column's products are 4096, 4096, -4096, -4096 in turn, two more
+    cancel in their high halves, and what is left is the low half of one activation, 2^-14: less than half a unit in the last place
+    of a sum that holds 4096."""
+
+    def bits(self, name, layer=None):
+        b = super().bits(name, layer)
+        if name in ("wo", "wd"):
+            return np.zeros_like(b)
+        x = np.ones(b.shape, dtype=np.float32)
+        col = np.arange(self.shape.d_model)
+        if name == "embed":
+            x[:, col % 32 == 5] = 1 + 2.0 ** -7
+            x[:, col % 32 == 11] = 1 + 2.0 ** -6
+        elif name == "final_norm":
+            x[col % 32 == 5] = 1 + 2.0 ** -7                 # times the embedding: 1 + 2^-6 and the low half 2^-14
+        elif name == "lm_head":
+            x[:] = 0
+            big = np.where(col // 32 % 4 < 2, 4096.0, -4096.0)
+            x[:, col % 32 == 5], x[:, col % 32 == 11] = 1, -1
+            x[:, col % 32 == 20] = big[col % 32 == 20]
+            x *= 2.0 ** (np.arange(len(x)) % 5)[:, None]
+        else:
+            return b
+        return round_to_bf16_bits(x)
+
+
+# rows: a window with both halves packed, one with a part each, prompts on the two larger workgroup shapes
+@pytest.mark.parametrize("n", [3, 12, 40, 300])
+def test_low_halves_are_summed_apart(n):
+    shape = SHAPES["tiny_gqa_bf16"].with_(d_model=2048, vocab=16000 if n == 300 else 2048)
+    m, = _models_of(shape, 320, _Cancelling(shape))
+    toks = prompt_tokens(5, n + 1, shape.vocab)
+    rows = n
+    if n <= 16:
+        m.prefill(toks[:1])
+        m.set_next(int(toks[1]))
+        m.verify(1, toks[1:])
+    else:
+        m.prefill(toks[:n])
+        rows = (n - 1) % 8 + 1
+    got = m.get_logits(rows)
+    m.free()
+    # 64 blocks of 2^-14, over the row's root mean square; float32 holds all sums exactly, the rest rounds a few times
+    squares = (30 + (1 + 2.0 ** -7) ** 2 + (1 + 2.0 ** -6) ** 2) / 32
+    want = 64 * 2.0 ** -14 / np.sqrt(squares + shape.rms_eps) * 2.0 ** (np.arange(shape.vocab) % 5)
+    assert np.abs(got / want - 1).max() < 8 * 2.0 ** -24
