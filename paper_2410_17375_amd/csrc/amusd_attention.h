@@ -19,6 +19,12 @@ __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_ex
 constexpr float kAttSlack = 8.f;
 __device__ __forceinline__ bool att_outgrown(float m, float ref) { return m > ref + kAttSlack; }   // false for -inf against -inf
 
+// The scale of a score is taken into the subtraction of the reference where that is exact enough: a reference is a rounded
+// product, off by up to half its last place (at 2^28 by 16: weights would be 2^16 times too large or too small).  From
+// kAttFar on the product is rounded first, as the reference was.  A row's own reference decides, so that its bits do not
+// depend on its neighbours; references that large are rare, and a wave without one does nothing more than ask.
+constexpr float kAttFar = 1 << 20;
+
 // Running softmax of one wave: 16 rows of one query head, a run of key blocks.
 template <int HD>
 struct AttState {
@@ -106,6 +112,13 @@ __device__ __forceinline__ void attention_step(AttState<HD>& s, const uint4* qh,
         if (__builtin_amdgcn_ballot_w64(up)) s.rescale(up, top);
     }
     const float mref = s.m == -INFINITY ? 0.f : s.m;
+    const bool far = fabsf(mref) >= kAttFar;
+    if (__builtin_amdgcn_ballot_w64(far)) {
+        const float by = far ? scale : 1.f;
+#pragma unroll
+        for (int t = 0; t < NTL; ++t) sc[t] = sc[t] * by;
+        scale = far ? 1.f : scale;
+    }
 #pragma unroll
     for (int t = 0; t < NTL; ++t)
 #pragma unroll

@@ -764,20 +764,16 @@ __global__ void __launch_bounds__(kThreads, 2) k_pf_stream(DevModel M, DevLayer 
     // against 47, 128 rows QKV 40 against 32).
     constexpr bool kScalesFirst = NT * RT * AF >= 32;
     Scales scales;
-    float scale_part = 0.f;
     if constexpr (kPfScaled<STAGE>) {
         scales.load(M, T, P, rt0);
-        if constexpr (kScalesFirst) {
-            scale_part = scales.sum();
-            asm volatile("" : "+v"(scale_part));
-        }
+        if constexpr (kScalesFirst) scale_sums[threadIdx.x] = scales.sum();
     }
     const uint4* W;
     const void* act;
     int K, ways;
     pf_inputs<STAGE>(M, Ly, T, W, act, K, ways);
     const int kblocks = K / DT::KB, kh = kblocks / ways;
-    v4f acc[NT][RT][AF], part[NT][RT];
+    v4f acc[NT][RT][AF];
     // K ranges of this workgroup: all of them one after the other, or its own
     for (int range = share; range < ways; range += shares) {
         const KSlice ks = k_slice_of<Walk>(kh, t0 % L.wgs, wave);
@@ -820,7 +816,7 @@ __global__ void __launch_bounds__(kThreads, 2) k_pf_stream(DevModel M, DevLayer 
             };
 #pragma unroll
             for (int d = 0; d < D; ++d) fetch(d < last ? d : last, d);
-            if constexpr (kPfScaled<STAGE>) scale_sums[threadIdx.x] = kScalesFirst ? scale_part : scales.sum();    // (these stages have one K range)
+            if constexpr (kPfScaled<STAGE> && !kScalesFirst) scale_sums[threadIdx.x] = scales.sum();    // (these stages have one K range)
             int s0 = 0;
             for (; s0 + D < S; s0 += D) {
 #pragma unroll
@@ -832,22 +828,19 @@ __global__ void __launch_bounds__(kThreads, 2) k_pf_stream(DevModel M, DevLayer 
 #pragma unroll
             for (int d = 0; d < D; ++d)
                 if (s0 + d < S) multiply(d);
-        } else if constexpr (kPfScaled<STAGE>) {
-            scale_sums[threadIdx.x] = kScalesFirst ? scale_part : scales.sum();
+        } else if constexpr (kPfScaled<STAGE> && !kScalesFirst) {
+            scale_sums[threadIdx.x] = scales.sum();
         }
-#pragma unroll
-        for (int i = 0; i < NT; ++i)
-#pragma unroll
-            for (int j = 0; j < RT; ++j) {
-                if constexpr (AF == 2) part[i][j] = acc[i][j][0] + acc[i][j][1];
-                else part[i][j] = acc[i][j][0];
-            }
         if (range != share) __syncthreads();        // the sums of the range before have been read
         v4f* lds = reinterpret_cast<v4f*>(pf_smem);   // [wave][fragment][lane]
 #pragma unroll
         for (int i = 0; i < NT; ++i)
 #pragma unroll
-            for (int j = 0; j < RT; ++j) lds[(wave * (NT * RT) + i * RT + j) * 64 + lane] = part[i][j];
+            for (int j = 0; j < RT; ++j) {
+                v4f v = acc[i][j][0];
+                if constexpr (AF == 2) v += acc[i][j][1];
+                lds[(wave * (NT * RT) + i * RT + j) * 64 + lane] = v;
+            }
         __syncthreads();
 #pragma unroll
         for (int x = 0; x < F; ++x) {

@@ -3,7 +3,7 @@ import numpy as np
 import pytest
 
 from workload import SHAPES, WeightStore, prompt_tokens
-from workload.tensors import round_to_bf16_bits
+from workload.tensors import bf16_bits_to_f32, round_to_bf16_bits
 
 pytestmark = pytest.mark.gpu
 
@@ -67,3 +67,40 @@ def test_low_halves_are_summed_apart(n):
     squares = (30 + (1 + 2.0 ** -7) ** 2 + (1 + 2.0 ** -6) ** 2) / 32
     want = 64 * 2.0 ** -14 / np.sqrt(squares + shape.rms_eps) * 2.0 ** (np.arange(shape.vocab) % 5)
     assert np.abs(got / want - 1).max() < 8 * 2.0 ** -24
+
+
+class _Enormous(WeightStore):
+    """Queries and keys of one direction, up to the largest that the cache's type holds: a row's score with itself is 2^31 (16-bit
+    models) or 2^44 in units of log2, where a float's last place is worth 256 and more."""
+
+    def bits(self, name, layer=None):
+        if name not in ("wq", "wk"):
+            return super().bits(name, layer)
+        w = bf16_bits_to_f32(b) if (b := super().bits("wk", layer)).dtype == np.uint16 else b
+        w = np.tile(w.reshape(self.shape.n_kv_heads, 1, self.shape.head_dim, -1), (1, self.shape.group if name == "wq" else 1, 1, 1))
+        w = (w * np.float32(2.0 ** 15 if self.shape.dtype == "bf16" else 2.0 ** 20)).reshape(-1, self.shape.d_model)
+        return round_to_bf16_bits(w) if self.shape.dtype == "bf16" else w
+
+
+# groups of 2, 4, 8 and 1, both widths of a head; keys walked whole and, behind a context, in stretches
+@pytest.mark.parametrize("name,ctx,n", [("tiny_gqa_bf16", 0, 60), ("tiny_gqa128_bf16", 0, 60), ("tiny_gqa128_bf16", 700, 20),
+                                        ("tiny_g8_bf16", 0, 60), ("tiny_gqa_fp32", 0, 60), ("tiny_verify", 0, 60)])
+def test_enormous_scores(name, ctx, n):
+    from oracle import Decoder
+    shape = SHAPES[name]
+    store = _Enormous(shape)
+    toks = prompt_tokens(6, ctx + n, shape.vocab)
+    group = 16 if shape.dtype == "fp32" else 8
+    rows = (n - 1) % group + 1
+    out = []
+    for m, piece in zip(_models_of(shape, ctx + n + 16, store, 2), (n, group)):     # one prefill pass; verify passes
+        if ctx:
+            m.prefill(toks[:ctx])
+        for s in range(ctx, ctx + n, piece):
+            m.prefill(toks[s:min(s + piece, ctx + n)])
+        out.append(m.get_logits(rows))
+        m.free()
+    assert np.array_equal(out[0].view(np.uint32), out[1].view(np.uint32))
+    # every weight is 0 or 1 and an output is one value row: what is left is the tolerance of any pass
+    want = np.asarray(Decoder(shape, store, ctx + n).rows(toks, logits_from=ctx + n - rows))
+    assert np.abs(want - out[0]).max() < (2e-5 if shape.dtype == "fp32" else 3e-2)
