@@ -377,13 +377,15 @@ __device__ __forceinline__ void attention_unit_staged(const DevModel& M, const D
     merge_runs<HD>(s, G, PARTS, hq, part, row0, k, part_out, smem);
 }
 
-// Merge of the chunk partials of one (head, row) in chunk order by one wave, with AttState::add's operations in its order:
-// lanes first hold one chunk each (reference, weight, denominator), then one slice of head_dim each.  base: the row's
-// partial of chunk 0; cstride: floats from chunk to chunk.  num[i]: normalised output of head_dim column lane + 64 i.
+// Merge of the chunk partials of one (head, row) in chunk order by one wave, with the prefill pass's operations (PfTotals::add)
+// in its order: lanes first hold one chunk each (reference, weight, denominator), then one slice of head_dim each.  The
+// denominators, one after the other and hundreds of them in a long context, are added in 64 bits.  base: the row's partial of
+// chunk 0; cstride: floats from chunk to chunk.  num[i]: normalised output of head_dim column lane + 64 i.
 template <int HD>
 __device__ __forceinline__ void merge_chunks(const float* base, size_t cstride, int nch, int lane, float (&num)[HD / 64]) {
     constexpr int PER = HD / 64;
-    float ref = 0.f, den = 0.f;
+    float ref = 0.f;
+    double den = 0.;
     // numerators of the first chunks are fetched together with the references: one memory round trip
     constexpr int CPRE = 24;
     float pre[CPRE][PER];
@@ -410,12 +412,13 @@ __device__ __forceinline__ void merge_chunks(const float* base, size_t cstride, 
         }
         if (__builtin_amdgcn_ballot_w64(att_outgrown(mc, ref)) == 0) {      // the usual case: all against one reference
             const float wt = mc == -INFINITY ? 0.f : exp2_fast(mc - ref);
+            const double wd = (double)wt * (double)dc;                     // exact
             // (lanes past the last chunk hold weight and denominator 0, and what is fetched there is the last chunk's)
             if (c0 == 0) {
 #pragma unroll
                 for (int j = 1; j < CPRE; ++j) {
                     const float wj = lane_value(wt, j);
-                    den = fmaf(wj, lane_value(dc, j), den);
+                    den += lane_value(wd, j);
 #pragma unroll
                     for (int i = 0; i < PER; ++i) num[i] = fmaf(wj, pre[j][i], num[i]);
                 }
@@ -433,13 +436,13 @@ __device__ __forceinline__ void merge_chunks(const float* base, size_t cstride, 
 #pragma unroll
                 for (int u = 0; u < CB; ++u) {
                     const float wj = lane_value(wt, j + u);
-                    den = fmaf(wj, lane_value(dc, j + u), den);
+                    den += lane_value(wd, j + u);
 #pragma unroll
                     for (int i = 0; i < PER; ++i) num[i] = fmaf(wj, x[u][i], num[i]);
                 }
             }
         } else {
-            for (int j = j0; j < ng; ++j) {       // AttState::add
+            for (int j = j0; j < ng; ++j) {
                 const float mj = lane_value(mc, j);
                 const float* pj = base + (size_t)(c0 + j) * cstride;
                 if (att_outgrown(mj, ref)) {
@@ -450,13 +453,13 @@ __device__ __forceinline__ void merge_chunks(const float* base, size_t cstride, 
                     for (int i = 0; i < PER; ++i) num[i] *= a;
                 }
                 const float wj = mj == -INFINITY ? 0.f : exp2_fast(mj - ref);
-                den = fmaf(wj, lane_value(dc, j), den);
+                den = fma((double)wj, (double)lane_value(dc, j), den);
 #pragma unroll
                 for (int i = 0; i < PER; ++i) num[i] = fmaf(wj, pj[lane + 64 * i], num[i]);
             }
         }
     }
-    const float inv = 1.0f / den;
+    const float inv = 1.0f / (float)den;
 #pragma unroll
     for (int i = 0; i < PER; ++i) num[i] *= inv;
 }

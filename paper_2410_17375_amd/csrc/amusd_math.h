@@ -197,6 +197,11 @@ __device__ __forceinline__ float wave_sum_all(float v) {
 __device__ __forceinline__ float lane_value(float v, int j) {
     return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), j));
 }
+__device__ __forceinline__ double lane_value(double v, int j) {
+    const long long b = __double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, j), hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), j);
+    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
 
 // ---------------------------------------------------------------- loads that deliver into LDS
 // 16 bytes per lane from base + offset to LDS bytes dst + 16 lane.  In assembly, because the compiler takes the builtin

@@ -961,41 +961,44 @@ struct PfAtt {
 };
 // WHOLE: a workgroup walks all keys of its row tile and keeps the rows' totals over the chunks in registers, which the merge
 // kernel would otherwise add up from the chunks' partials in memory; the row tiles with most keys begin first.
-// Totals of a row tile's chunks.  TL > 0: the last TL numerator tiles stand at `rest` in LDS (the wave's own).
+// Totals of a row tile's chunks, the denominators in 64 bits (merge_chunks).  TL > 0: the last TL numerator tiles stand at
+// `rest` in LDS (the wave's own).
 template <int HD, int TL>
-struct PfTotals : AttState<HD> {
-    __device__ __forceinline__ explicit PfTotals(v4f*) { this->clear(); }
-    __device__ __forceinline__ v4f get(int j) const { return this->o[j]; }
-};
-template <>
-struct PfTotals<128, 4> {
-    static constexpr int HD = 128, TL = 4, HT = HD / 16, TR = HT - TL;
-    float m = -INFINITY, l = 0.f;
+struct PfTotals {
+    static constexpr int HT = HD / 16, TR = HT - TL;
+    float m = -INFINITY;
+    double l = 0.;
     v4f o[TR];
     v4f* rest;
     __device__ __forceinline__ explicit PfTotals(v4f* rest_) : rest(rest_) {
 #pragma unroll
-        for (int j = 0; j < HT; ++j) put(j, v4f{0.f, 0.f, 0.f, 0.f});
+        for (int j = 0; j < TR; ++j) o[j] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = TR; j < HT; ++j) rest[(j - TR) * 64] = v4f{0.f, 0.f, 0.f, 0.f};
     }
     __device__ __forceinline__ v4f get(int j) const { return j < TR ? o[j < TR ? j : 0] : rest[(j - TR) * 64]; }
-    __device__ __forceinline__ void put(int j, v4f x) {
-        if (j < TR) o[j < TR ? j : 0] = x;
-        else rest[(j - TR) * 64] = x;
-    }
-    __device__ __forceinline__ void add(const AttState<HD>& s) {       // AttState::add
+    __device__ __forceinline__ void add(const AttState<HD>& s) {
         const bool up = att_outgrown(s.m, m), any = __builtin_amdgcn_ballot_w64(up) != 0;
         const float a = up ? exp2_fast(m - s.m) : 1.f;
         m = up ? s.m : m;
         const float w = s.m == -INFINITY ? 0.f : exp2_fast(s.m - m);
-        if (any) l *= a;
-        l = fmaf(w, s.l, l);
+        if (any) {
+            l *= (double)a;
 #pragma unroll
-        for (int j = 0; j < HT; ++j) {
-            v4f x = get(j);
+            for (int j = 0; j < TR; ++j) o[j] = o[j] * a;
+        }
+        l = fma((double)w, (double)s.l, l);
+#pragma unroll
+        for (int j = 0; j < TR; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[j][e] = fmaf(w, s.o[j][e], o[j][e]);
+#pragma unroll
+        for (int j = TR; j < HT; ++j) {
+            v4f x = rest[(j - TR) * 64];
             if (any) x = x * a;
 #pragma unroll
             for (int e = 0; e < 4; ++e) x[e] = fmaf(w, s.o[j][e], x[e]);
-            put(j, x);
+            rest[(j - TR) * 64] = x;
         }
     }
 };
@@ -1149,7 +1152,7 @@ __device__ __forceinline__ void pf_attention(const DevModel& M, const DevLayer& 
     }
     wait_vm<0>();
     if constexpr (WHOLE) {
-        const float inv = 1.0f / all.l;
+        const float inv = 1.0f / (float)all.l;
         if (m < k)
 #pragma unroll
             for (int j = 0; j < HT; ++j) PfAct<DT>::store4(T.O, M.qdim / DT::KB, row0 + m, (kvh * G + hq) * HD + j * 16 + g * 4, all.get(j) * inv);

@@ -104,3 +104,51 @@ def test_enormous_scores(name, ctx, n):
     # every weight is 0 or 1 and an output is one value row: what is left is the tolerance of any pass
     want = np.asarray(Decoder(shape, store, ctx + n).rows(toks, logits_from=ctx + n - rows))
     assert np.abs(want - out[0]).max() < (2e-5 if shape.dtype == "fp32" else 3e-2)
+
+
+class _OneAmongMany(WeightStore):
+    """Token 1 stands out of a context of token 2 by 29 in units of log2: 16 of the others, a chunk's, are less than half a unit in
+    the last place of a float that holds the one, all of them 2^-17.  Its value is 1, theirs is 0; the output goes to the logits."""
+
+    def bits(self, name, layer=None):
+        s = self.shape
+        x = np.zeros_like(super().bits(name, layer))
+        if name.startswith("norm") or name == "final_norm":
+            x[:] = 1
+        elif name == "embed":
+            x[1, 0] = x[2, 1] = 16                           # 16 again behind the norm, of 256 columns
+        elif name == "wq":
+            x[31::64, :2] = 8 / 16
+        elif name == "wk":
+            x[31::64, 0] = 29.0 / np.log2(np.e) / 16
+        elif name == "wv":
+            x[0::64, 0] = 1 / 16
+        elif name == "wo":
+            x[2, 0] = 1
+        elif name == "lm_head":
+            x[:, 2] = 2.0 ** (np.arange(len(x)) % 4)
+        return x
+
+
+# groups of 8 (chunks of one run), 4 and 1 (of more keys: fewer)
+@pytest.mark.parametrize("heads,kv_heads,ctx", [(8, 1, 4080), (4, 1, 4080), (1, 1, 4080)])
+def test_denominators_of_many_chunks(heads, kv_heads, ctx):
+    from oracle import Decoder
+    # one pair of columns that the rotation leaves alone
+    shape = SHAPES["tiny_draft"].with_(d_model=256, n_q_heads=heads, n_kv_heads=kv_heads, d_ffn=16, vocab=64, rope_theta=1e30)
+    store = _OneAmongMany(shape)
+    toks = np.full(ctx + 16, 2, dtype=np.int32)
+    toks[0] = 1
+    out = []
+    for m, pieces in zip(_models_of(shape, ctx + 16, store, 3), ([ctx + 16], [ctx - 16, ctx + 16], [ctx, ctx + 16])):
+        start = 0
+        for stop in pieces:                                  # keys walked whole; behind a context in stretches; a verify pass
+            m.prefill(toks[start:stop])
+            start = stop
+        out.append(m.get_logits(16))
+        m.free()
+    for o in out[1:]:
+        assert np.array_equal(out[0].view(np.uint32), o.view(np.uint32))
+    want = np.asarray(Decoder(shape, store, ctx + 16).rows(toks, logits_from=ctx))
+    # 1 over the denominator, and what follows it: some ten roundings
+    assert np.abs(out[0] / want - 1).max() < 10 * 2.0 ** -24
