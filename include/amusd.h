@@ -280,15 +280,6 @@ int amusd_set_option(amusd_model *m, int32_t option, int32_t value);
  * Needs AMUSD_OPT_KEEP_LOGITS = 1 before that pass.  Errors: ARG, STATE. */
 int amusd_get_logits(amusd_model *m, float *out, int32_t rows);
 
-/* The same logits in one of the model's two blocks of pinned host memory, which
- * a copy from the device reaches up to 3 times faster: *data to its
- * [rows, vocab] floats, *block what amusd_return_logits takes.  Both NULL (and
- * AMUSD_OK) when the model has no free block: use amusd_get_logits.  The memory
- * is the caller's until it is returned, by any thread, also after
- * amusd_model_free.  Errors: as amusd_get_logits. */
-int amusd_borrow_logits(amusd_model *m, int32_t rows, float **data, void **block);
-int amusd_return_logits(void *block);
-
 /* g[0..rows) of the last pass (arg-max token of each row; after a prefill the
  * rows of amusd_get_logits) to host memory. */
 int amusd_get_greedy(amusd_model *m, int32_t *out, int32_t rows);

@@ -93,8 +93,6 @@ def _load():
         "amusd_generate_greedy": (C.c_int, [vp, i32p, i32, i32, i32p, C.POINTER(LoopStats)]),
         "amusd_set_option": (C.c_int, [vp, i32, i32]),
         "amusd_get_logits": (C.c_int, [vp, f32p, i32]),
-        "amusd_borrow_logits": (C.c_int, [vp, i32, C.POINTER(vp), C.POINTER(vp)]),
-        "amusd_return_logits": (C.c_int, [vp]),
         "amusd_get_greedy": (C.c_int, [vp, i32p, i32]),
         "amusd_last_pass_ms": (C.c_int, [vp, f32p]),
         "amusd_stage_time": (C.c_int, [vp, C.POINTER(C.c_double), C.POINTER(C.c_int64), C.POINTER(C.c_int64)]),
@@ -125,19 +123,6 @@ def _check(rc):
 def _i32(a):
     a = np.ascontiguousarray(a, dtype=np.int32)
     return a, a.ctypes.data_as(C.POINTER(C.c_int32))
-
-
-class _Lent:
-    """A block of amusd_borrow_logits, returned when nothing refers to its array any more."""
-
-    def __init__(self, block):
-        self.block = block
-
-    def __del__(self):
-        try:
-            lib.amusd_return_logits(self.block)
-        except Exception:
-            pass
 
 
 class Model:
@@ -260,12 +245,6 @@ class Model:
         _check(lib.amusd_set_option(self._h, option, value))
 
     def get_logits(self, rows):
-        data, block = C.c_void_p(), C.c_void_p()
-        _check(lib.amusd_borrow_logits(self._h, rows, C.byref(data), C.byref(block)))
-        if block.value:
-            buf = (C.c_float * (rows * self.cfg.vocab)).from_address(data.value)
-            buf.lent = _Lent(block.value)            # the array keeps buf
-            return np.frombuffer(buf, dtype=np.float32).reshape(rows, self.cfg.vocab)
         out = np.empty((rows, self.cfg.vocab), dtype=np.float32)
         _check(lib.amusd_get_logits(self._h, out.ctypes.data_as(C.POINTER(C.c_float)), rows))
         return out

@@ -41,16 +41,6 @@ struct HostStage {          // pinned: what one pass receives from the device
     PassResult res;
 };
 
-// Pinned host memory that logits are copied to and that a caller may keep (amusd_borrow_logits).  It belongs to its model
-// and, while it is lent, to the borrower too; who gives it up last frees it.
-struct LogitsBlock {
-    float* data = nullptr;
-    bool lent = false, orphan = false;     // orphan: the model is gone
-};
-std::mutex g_logits_mutex;                 // the two flags of every block
-constexpr int kLogitsBlocks = 2;           // a caller who replaces one result by the next holds both for a moment
-constexpr size_t kLogitsStaged = 256 << 10;
-
 }  // namespace
 
 // Workspace of the entry point that allocates nothing (amusd_verify_static): the buffers a pass keeps between its
@@ -115,7 +105,6 @@ struct amusd_model {
     size_t static_bytes = 0;               // bytes of the array that workspace takes
     uint64_t id = 0;
     HostStage* hstage = nullptr;
-    LogitsBlock* logits_blocks[kLogitsBlocks] = {};   // [max_k][V] each, from the first AMUSD_OPT_KEEP_LOGITS on
     PrefillBufs pf{};                      // workspace of the prefill pass; cap 0: prompts go through the verify pass
     PfTileSet pf_tiles[kPfStages];
     void* pf_mem = nullptr;                // the device allocation that its buffers are in
@@ -332,54 +321,6 @@ int run_pass(amusd_model* m, const SegReq* segs, int n_seg, bool force_accept, b
         q.p_next = h->res.next_token[i];
     }
     return AMUSD_OK;
-}
-
-// The blocks are only a faster way for logits to reach the host; without the memory for them there are none.
-void take_logits_blocks(amusd_model* m) {
-    for (LogitsBlock*& b : m->logits_blocks) {
-        if (b) continue;
-        void* p = nullptr;
-        if (hipHostMalloc(&p, (size_t)m->cfg.max_k * m->cfg.vocab * 4, hipHostMallocDefault) != hipSuccess) {
-            (void)hipGetLastError();
-            return;
-        }
-        b = new (std::nothrow) LogitsBlock;
-        if (!b) {
-            (void)hipHostFree(p);
-            return;
-        }
-        b->data = static_cast<float*>(p);
-    }
-}
-
-LogitsBlock* lend_logits_block(amusd_model* m) {
-    std::lock_guard<std::mutex> lock(g_logits_mutex);
-    for (LogitsBlock* b : m->logits_blocks)
-        if (b && !b->lent) {
-            b->lent = true;
-            return b;
-        }
-    return nullptr;
-}
-
-void return_logits_block(LogitsBlock* b) {
-    {
-        std::lock_guard<std::mutex> lock(g_logits_mutex);
-        b->lent = false;
-        if (!b->orphan) return;
-    }
-    (void)hipHostFree(b->data);
-    delete b;
-}
-
-void leave_logits_block(LogitsBlock* b) {      // its model is freed
-    {
-        std::lock_guard<std::mutex> lock(g_logits_mutex);
-        b->orphan = true;
-        if (b->lent) return;
-    }
-    (void)hipHostFree(b->data);
-    delete b;
 }
 
 // Gives the prefill workspace back: prompts go through the verify pass from here on.
@@ -826,7 +767,6 @@ int amusd_model_free(amusd_model* m) {
     for (void* p : m->allocs) (void)hipFree(p);
     if (m->staging) (void)hipFree(m->staging);
     if (m->hstage) (void)hipHostFree(m->hstage);
-    for (LogitsBlock* b : m->logits_blocks) if (b) leave_logits_block(b);
     release_prefill(m);
     if (m->ev0) (void)hipEventDestroy(m->ev0);
     if (m->ev1) (void)hipEventDestroy(m->ev1);
@@ -1023,10 +963,7 @@ int amusd_get_next(const amusd_model* m, int32_t* token) { return amusd_seq_get_
 int amusd_set_option(amusd_model* m, int32_t option, int32_t value) {
     if (!m) return fail(AMUSD_E_ARG, "null model");
     switch (option) {
-        case AMUSD_OPT_KEEP_LOGITS:
-            m->keep_logits = value != 0;
-            if (value) take_logits_blocks(m);
-            return AMUSD_OK;
+        case AMUSD_OPT_KEEP_LOGITS: m->keep_logits = value != 0; return AMUSD_OK;
         case AMUSD_OPT_TIME_STAGE: {
             if (value < -1 || value >= AMUSD_STAGE_COUNT) return fail(AMUSD_E_ARG, "unknown stage");
             if (value >= 0 && m->tev_begin.empty()) {
@@ -1065,49 +1002,12 @@ int64_t amusd_prefill_workspace_bytes(const amusd_model* m) {
     return (int64_t)m->pf_bytes;
 }
 
-static int check_logits(const amusd_model* m, const void* out, int32_t rows) {
-    const int rc = need_ready(m);
+int amusd_get_logits(amusd_model* m, float* out, int32_t rows) {
+    int rc = need_ready(m);
     if (rc) return rc;
     if (!out || rows < 1 || rows > kRows) return fail(AMUSD_E_ARG, "get_logits: bad argument");
     if (!m->logits_valid || rows > m->last_rows) return fail(AMUSD_E_STATE, "get_logits: the last pass kept no such logits");
-    return AMUSD_OK;
-}
-
-// A copy to pageable memory takes 18-25 us for 16 KB, 62 for 128 KB, 92 for 213 KB, 37 for 640 KB, 110 for 2 MB and 229 for
-// 4.1 MB, to pinned memory 10, 10, 13, 19, 44 and 80; the processor's copy out of the pinned memory then 1 us up to 256 KB, but
-// 17 for 640 KB and 60 for 2 MB (it is in no cache): beyond, only a caller who takes the pinned memory itself gains.
-int amusd_get_logits(amusd_model* m, float* out, int32_t rows) {
-    const int rc = check_logits(m, out, rows);
-    if (rc) return rc;
-    const size_t bytes = (size_t)rows * m->cfg.vocab * 4;
-    LogitsBlock* b = bytes <= kLogitsStaged ? lend_logits_block(m) : nullptr;
-    const hipError_t e = hipMemcpy(b ? b->data : out, m->dm.logits, bytes, hipMemcpyDeviceToHost);
-    if (b) {
-        if (e == hipSuccess) std::memcpy(out, b->data, bytes);
-        return_logits_block(b);
-    }
-    HIP_TRY(e);
-    return AMUSD_OK;
-}
-
-int amusd_borrow_logits(amusd_model* m, int32_t rows, float** data, void** block) {
-    if (data) *data = nullptr;
-    if (block) *block = nullptr;
-    const int rc = check_logits(m, data && block ? data : nullptr, rows);
-    if (rc) return rc;
-    LogitsBlock* b = lend_logits_block(m);
-    if (!b) return AMUSD_OK;
-    const hipError_t e = hipMemcpy(b->data, m->dm.logits, (size_t)rows * m->cfg.vocab * 4, hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return_logits_block(b);
-    HIP_TRY(e);
-    *data = b->data;
-    *block = b;
-    return AMUSD_OK;
-}
-
-int amusd_return_logits(void* block) {
-    if (!block) return fail(AMUSD_E_ARG, "null argument");
-    return_logits_block(static_cast<LogitsBlock*>(block));
+    HIP_TRY(hipMemcpy(out, m->dm.logits, (size_t)rows * m->cfg.vocab * 4, hipMemcpyDeviceToHost));
     return AMUSD_OK;
 }
 

@@ -1,6 +1,6 @@
-"""Logits on the host: arrays that the model lends its pinned blocks to, and those that are copied once none is free, hold what
-their pass computed for as long as they live."""
+"""Logits on the host: arrays of the caller's own, ordinary memory, which hold what their pass computed for as long as they live."""
 import ctypes as C
+import re
 
 import numpy as np
 import pytest
@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("name,rows,vocab", [("tiny_draft", 1, 4096), ("tiny_gqa_bf16", 16, 4096), ("tiny_gqa_bf16", 16, 4112)])
-def test_logits_are_the_callers(name, rows, vocab):      # 16 KB, and 256 KB on either side of the line to staged copies
+def test_logits_are_the_callers(name, rows, vocab):      # 16 KB and 256 KB
     torch = pytest.importorskip("torch")
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
@@ -29,7 +29,7 @@ def test_logits_are_the_callers(name, rows, vocab):      # 16 KB, and 256 KB on 
         return out
 
     kept = []
-    for r in range(4):                                       # the first two arrays have the model's blocks
+    for r in range(4):
         g.kv_rollback(20)
         g.set_next(int(toks[20 + r]))
         g.verify(20, toks[20 + r:20 + r + rows])
@@ -40,9 +40,19 @@ def test_logits_are_the_callers(name, rows, vocab):      # 16 KB, and 256 KB on 
         assert not np.array_equal(kept[0][0], kept[-1][0]) or r == 0
     kept[0][0][0, 0] = 5.0                                   # writable, and nobody else's
     assert kept[1][0][0, 0] != 5.0
-    address = kept[1][0].ctypes.data
+    own = kept[1][0]
     del kept[1], got
-    assert g.get_logits(rows).ctypes.data == address         # a block that is given back is lent again
+    assert own.base is None and own.flags.owndata
+    own.resize((rows + 1, vocab), refcheck=False)            # as any array that owns its data
+    # .. and a child process has its copy of (memory that the GPU's driver maps, it has not)
+    here, flags = False, None
+    for line in open("/proc/self/smaps"):
+        span = re.match(r"([0-9a-f]+)-([0-9a-f]+) ", line)
+        if span:
+            here = int(span.group(1), 16) <= kept[0][0].ctypes.data < int(span.group(2), 16)
+        elif here and line.startswith("VmFlags"):
+            flags = line.split()[1:]
+    assert flags and "dc" not in flags
     with pytest.raises(A.AmusdError):
         g.get_logits(rows + 1)
     with pytest.raises(A.AmusdError):
