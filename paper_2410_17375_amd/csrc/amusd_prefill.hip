@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "amusd_attention.h"
+#include "amusd_plan.h"
 
 namespace amusd {
 
@@ -1171,6 +1172,7 @@ __global__ void __launch_bounds__(64 * G, 2) k_pf_attention_rows(DevModel M, Dev
 }
 
 constexpr int kPfSpanKeys = 256;     // keys a workgroup walks at least (whole chunks)
+static int pf_span(const DevModel& M) { return kPfSpanKeys > M.chunk ? kPfSpanKeys / M.chunk : 1; }   // chunks of a stretch
 
 // One wave per (row, query head).
 template <class DT, int HD>
@@ -1407,7 +1409,7 @@ static hipError_t launch_pf_attention_g(const DevModel& M, const DevLayer& Ly, c
     static const hipError_t set = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pf_attention<DT, HD, G>),
                                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (set != hipSuccess) return set;
-    const int span = kPfSpanKeys > M.chunk ? kPfSpanKeys / M.chunk : 1;
+    const int span = pf_span(M);
     hipLaunchKernelGGL((k_pf_attention<DT, HD, G>), dim3(nrt * ((nch + span - 1) / span) * M.Hkv), dim3(64 * G), lds, s, M, Ly, T, P, rt0,
                        nrt, nch, span);
     return hipSuccess;
@@ -1436,15 +1438,11 @@ static hipError_t launch_pf_attention(const DevModel& M, const DevLayer& Ly, con
     return hipSuccess;
 }
 
-// A layer's attention.  Where there are row tiles enough for the chip, or few keys, a workgroup per row tile and kv head walks
-// all keys; else the keys are split into stretches and the chunks' partials merged.  us, whole / split, 8B heads: 61 rows
-// behind 0 / 450 / 1500 keys 8.4 / 19 / 46 against 12 / 18 / 23; 250 rows 14 / 25 / 53 against 24 / 31 / 45; 400 rows 19 / 31 / 60
-// against 33 / 44 / 64, behind 6000 186 against 140; 2000 rows behind 14288 1180 against 1510.  The line follows the keys at
-// which the two are equal: 500 for 32 workgroups, 1250 for 128, 1900 for 200.
+// A layer's attention: whole rows, or stretches of keys and a merge.
 template <class DT, int HD>
 static hipError_t pf_attention_all(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PrefillArgs& P, hipStream_t s) {
-    const int rts = (P.n + 15) / 16, wgs = rts * M.Hkv;
-    if ((M.G == 4 || M.G == 8) && (wgs >= T.cus + T.cus / 2 || P.L0 + P.n <= 250 + 8 * wgs))
+    const int rts = (P.n + 15) / 16;
+    if (pf_attention_walks_whole_rows(DT::HAS_LO, HD, M.G, M.Hkv, P.n, P.L0 + P.n, T.cus, M.chunk, M.bpw, pf_span(M) * M.chunk))
         return M.G == 4 ? launch_pf_attention_rows<DT, HD, 4>(M, Ly, T, P, s) : launch_pf_attention_rows<DT, HD, 8>(M, Ly, T, P, s);
     for (int rt = 0; rt < rts; rt += T.att_tiles) {
         const int nrt = rts - rt < T.att_tiles ? rts - rt : T.att_tiles;
