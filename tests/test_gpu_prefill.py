@@ -25,7 +25,7 @@ CASES = [
     # Attention runs of several key blocks: ceil(context / (256 / kv heads * runs * block)) blocks, 8 / G runs a chunk, so that
     # row tiles end after every number of blocks of the first and of the second run.  Odd runs end in a step of one block.
     ("tiny_gqa_bf16", {"d_model": 128, "n_q_heads": 128, "n_kv_heads": 32, "d_ffn": 128}, 33, 1030),     # G = 4: 3 blocks
-    ("tiny_gqa_bf16", {"d_model": 128, "n_q_heads": 128, "n_kv_heads": 32, "d_ffn": 128}, 0, 2100),      # 5, two stretches
+    ("tiny_gqa_bf16", {"d_model": 128, "n_q_heads": 128, "n_kv_heads": 32, "d_ffn": 128}, 0, 2100),      # 5, in two passes
     ("tiny_gqa128_bf16", {"d_model": 128, "n_q_heads": 64, "n_kv_heads": 16, "d_ffn": 128}, 7, 2050),    # head_dim 128: 3
     ("tiny_g8_bf16", {"d_model": 128, "n_q_heads": 256, "n_kv_heads": 32, "d_ffn": 128}, 0, 400),        # G = 8, one run: 2
     ("tiny_g8_bf16", {"d_model": 128, "n_q_heads": 256, "n_kv_heads": 32, "d_ffn": 128}, 40, 660),       # 3
