@@ -17,6 +17,7 @@ __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_ex
 // when it grows beyond.  (The true maximum grows in most steps of a run, for one of a wave's 16 rows or another.)  Numerators
 // stay far inside the half range, whose hi + lo pairs are as precise at 256 as at 1.
 constexpr float kAttSlack = 8.f;
+static_assert(kAttSlack < 15.f, "weights are converted to half unclamped");   // (and a reference is off by 2^-4 at most, kAttFar)
 __device__ __forceinline__ bool att_outgrown(float m, float ref) { return m > ref + kAttSlack; }   // false for -inf against -inf
 
 // The scale of a score is taken into the subtraction of the reference where that is exact enough: a reference is a rounded
@@ -251,7 +252,6 @@ __device__ __forceinline__ void attention_unit(const DevModel& M, const DevLayer
     load_block(b0, kf, vf);
     AttState<HD> s;
     s.clear();
-
     const int lim = mine ? L + m - row0 : -1;          // causal: the sequence's j-th row (tile row row0 + j) sees keys 0 .. L + j
     auto kfrag = [&](int, int t, int i) { return kf[t][i]; };
     auto vfrag = [&](int, int j) { return vf[j]; };
@@ -351,7 +351,6 @@ __device__ __forceinline__ void attention_unit_staged(const DevModel& M, const D
     wait_vm<0>();
     AttState<HD> s;
     s.clear();
-
     const int lim = mine ? L + m - row0 : -1;            // causal: the sequence's j-th row (tile row row0 + j) sees keys 0 .. L + j
     for (int st = 0; st < steps; ++st) {
         // The loads of this step are the only ones under way.  Behind the barrier they are there for all waves, and all

@@ -29,9 +29,9 @@ struct BF16 {
     static __device__ __forceinline__ v4f mfma(uint4 a, uint4 b, v4f c) {
         return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
     }
-    // Attention operands (cache, queries, probabilities) are IEEE half: the same 2 bytes per element as
-    // bf16 with three more mantissa bits; their magnitudes (keys, values, queries O(1), probabilities
-    // in [0,1]) sit well inside the half range, and stores clamp to it.
+    // Attention operands (cache, queries, softmax weights) are IEEE half: the same 2 bytes per element as
+    // bf16 with three more mantissa bits; their magnitudes (keys, values, queries O(1), weights up to
+    // 2^kAttSlack) sit well inside the half range, and stores of the cache and the queries clamp to it.
     static __device__ __forceinline__ v4f mfma_att(uint4 a, uint4 b, v4f c) {
         return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v8h, b), c, 0, 0, 0);
     }
@@ -40,7 +40,7 @@ struct BF16 {
         return (uint32_t)__half_as_ushort(__float2half_rn(c));
     }
     static __device__ __forceinline__ float att_float(uint32_t b) { return __half2float(__ushort_as_half((unsigned short)b)); }
-    // hi and lo halves of two probabilities (in [0, 1]: nothing to clamp), packed.  The subtraction of a half from its
+    // hi and lo halves of two softmax weights (at most 2^kAttSlack: nothing to clamp), packed.  The subtraction of a half from its
     // float is one mixed-precision instruction (an exact fused multiply-add by one; the compiler converts and subtracts).
     static __device__ __forceinline__ void att_split2(float a, float b, uint32_t& hi, uint32_t& lo) {
         typedef _Float16 h2 __attribute__((ext_vector_type(2)));
@@ -182,17 +182,6 @@ template <int OFF>
 __device__ __forceinline__ int lane_xor(int v) { return (int)lane_xor_u<OFF>((uint32_t)v); }
 template <int OFF>
 __device__ __forceinline__ float wave_xor_add(float v) { return v + lane_xor<OFF>(v); }
-// all 64 lanes, offsets 32, 16, .., 1 in that order
-__device__ __forceinline__ float wave_max_all(float v) {
-    v = fmaxf(v, lane_xor<32>(v)); v = fmaxf(v, lane_xor<16>(v)); v = fmaxf(v, lane_xor<8>(v));
-    v = fmaxf(v, lane_xor<4>(v)); v = fmaxf(v, lane_xor<2>(v)); v = fmaxf(v, lane_xor<1>(v));
-    return v;
-}
-__device__ __forceinline__ float wave_sum_all(float v) {
-    v = wave_xor_add<32>(v); v = wave_xor_add<16>(v); v = wave_xor_add<8>(v);
-    v = wave_xor_add<4>(v); v = wave_xor_add<2>(v); v = wave_xor_add<1>(v);
-    return v;
-}
 // lane j's value in every lane (j the same in all lanes)
 __device__ __forceinline__ float lane_value(float v, int j) {
     return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), j));

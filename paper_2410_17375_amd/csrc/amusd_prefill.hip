@@ -960,8 +960,6 @@ struct PfAtt {
     static constexpr int kSlotBytes = NF * 1024, kTotalsAt = SLOTS * kSlotBytes, kLdsBytes = kTotalsAt + G * TL * 1024;
     static_assert(NF % G == 0 && (G == 4 || G == 8), "");
 };
-// WHOLE: a workgroup walks all keys of its row tile and keeps the rows' totals over the chunks in registers, which the merge
-// kernel would otherwise add up from the chunks' partials in memory; the row tiles with most keys begin first.
 // Totals of a row tile's chunks, the denominators in 64 bits (merge_chunks).  TL > 0: the last TL numerator tiles stand at
 // `rest` in LDS (the wave's own).
 template <int HD, int TL>
@@ -1003,6 +1001,8 @@ struct PfTotals {
         }
     }
 };
+// WHOLE: a workgroup walks all keys of its row tile and keeps the rows' totals over the chunks in registers, which the merge
+// kernel would otherwise add up from the chunks' partials in memory; the row tiles with most keys begin first.
 template <class DT, int HD, int G, bool WHOLE>
 __device__ __forceinline__ void pf_attention(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PrefillArgs& P, int rt0,
                                              int nrt, int nch, int span, char* smem) {
