@@ -6,15 +6,15 @@ namespace amusd {
 // Attention of a prompt's rows: a workgroup per row tile and kv head that walks all keys (whole), or the keys split into
 // stretches and the chunks' partials merged.
 //
-// The whole form takes, per 1000 keys, `alone` us while each of its workgroups has a compute unit for itself, and `two` where
-// some share one: the largest tile's walk is its time.  The split form fills the chip whatever the number of tiles: `split` us
-// per 1000 keys and workgroup of the whole form per compute unit, the partials (stored and read back at 7.5 TB/s) on top, and at
-// least one stretch and 3 us.  A key block at the end of an odd run takes 0.8 of a step of two.  From 1.9 workgroups a compute
-// unit on the whole form is the faster one for any number of keys.
+// The whole form takes, per 1000 keys, `alone` us while each of its workgroups has a compute unit for itself (the last tile's
+// walk is its time), and `two` where some share one (a middling tile's; the longest begin first).  The split form fills the
+// chip whatever the number of tiles: `split` us per 1000 keys and workgroup of the whole form per compute unit, the partials
+// (stored and read back at 7.5 TB/s) on top, and a stretch and 2 us for its ends.  A key block at the end of an odd run takes
+// 0.75 of a step of two.  From 1.9 workgroups a compute unit on the whole form is the faster one for any number of keys.
 // Measured (MI355X, 1521 prompts of 17 to 2000 rows behind 0 to 14000 keys, 1 to 32 kv heads, the eight forms, contexts of 1000
-// to 16384): the choice is 0.6 % from the better form on average.  whole / split us: heads of 64 in fours, 8 kv heads, 768 rows
-// behind 8000 keys 185 / 152, float32 622 / 465; in eights, 4 kv heads, 192 / 233; heads of 128 in fours, 250 rows behind 1500 43 / 32,
-// 600 rows behind none 22 / 55.
+// to 16384): the choice is 0.4 % from the better form on average, 20 % and more in six.  whole / split us: heads of 64 in fours,
+// 8 kv heads, 768 rows behind 8000 keys 185 / 152, float32 622 / 465; in eights, 4 kv heads, 192 / 233; heads of 128 in fours, 250
+// rows behind 1500 43 / 32, 600 rows behind none 22 / 55.
 inline bool pf_attention_walks_whole_rows(bool bf16, int head_dim, int group, int kv_heads, int rows, int keys, int cus, int chunk, int run_blocks,
                                           int stretch) {
     struct Rates { double alone, two, split; };
@@ -26,9 +26,11 @@ inline bool pf_attention_walks_whole_rows(bool bf16, int head_dim, int group, in
     const double per_cu = (double)wgs / cus;
     if (per_cu >= 1.9) return true;
     const bool pairs = run_blocks == 1 && group == 4 && head_dim == 64;       // a chunk's two runs in one step
-    const double odd = run_blocks % 2 && !pairs ? (run_blocks - 1 + 2 * 0.8) / run_blocks : 1.;
+    const double odd = run_blocks % 2 && !pairs ? (run_blocks - 1 + 2 * 0.75) / run_blocks : 1.;
     const double partials = 1000. / chunk * 16 * group * wgs * (head_dim + 4) * 8 / 7.5e6;
-    return keys / 1000. * ((per_cu <= 1 ? r.alone : r.two) * odd - per_cu * r.split * odd - partials) <= 3 + r.alone * stretch / 1000;
+    const double whole = per_cu <= 1 ? keys * r.alone * odd : (keys - 0.4 * rows) * r.two * odd;    // ns
+    const double split = keys * (per_cu * r.split * odd + partials);
+    return whole <= split + r.alone * stretch + 2000;
 }
 
 }  // namespace amusd
