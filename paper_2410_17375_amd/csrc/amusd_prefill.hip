@@ -943,7 +943,7 @@ __global__ void __launch_bounds__(kThreads) k_pf_attention_unit(DevModel M, DevL
 // head) walk the blocks of `span` chunks together for one row tile, two blocks a step; a block is staged once, by loads
 // that deliver straight into an LDS ring, and read from there by all of them.  A wave does the runs of a chunk one after
 // the other and merges the two in registers, with the unit's operations in the unit's order.  8B heads, one layer: 2000 rows
-// behind 14288 keys 1560 us -> 1160-1190, 2048 rows 229 -> 105, 509 rows 44 -> 26; 1B heads, 509 rows 36 -> 16.  Matrix cores busy
+// behind 14288 keys 1560 us -> 1020-1190, 2048 rows 229 -> 105, 509 rows 44 -> 26; 1B heads, 509 rows 36 -> 16.  Matrix cores busy
 // for 36 % of the time, vector instructions for 32: the registers allow two waves per SIMD, and each is a chain of products,
 // softmax, products.  Measured slower: two heads or two row tiles per wave (no registers for either), eight waves on two row
 // tiles (26 %), fragments read a group ahead of their products (4 %), chunks before row tiles in the grid (9 %: the XCD's
@@ -1355,9 +1355,9 @@ using PfSmall = PfShape<2, 2, 2, 2, 6>;   // 64 x 64
 // to measurements of all choices on the 8B and 1B shapes at 17 to 2048 rows: 0.82 us per K block of a large tile; 0.30 and
 // 0.20 us of the smaller ones, 0.50 and 0.35 when two share a compute unit; 12, 7.5 and 6 us at the ends, 4 more for the large
 // tile's rotations; sharing 1.6 us per workgroup of a tile (its sums are written, counted and read back through the memory
-// side) and its bytes at 5 TB/s each way.  The choice is within 6 % of the best everywhere there.  For instance at 250 rows of the
-// 8B shape gate/up takes 114 us on 224 large tiles and 150 on 896 of the middle ones, at 128 rows 97 and 86.  Sharing
-// all slices is for few tiles and a long contraction (mostly the streaming form has those).
+// side) and its bytes at 5 TB/s each way.  The choice is within 6 % of the best at 166 of 170 sizes there, 12 % from it at
+// worst.  For instance at 250 rows of the 8B shape gate/up takes 114 us on 224 large tiles and 150 on 896 of the middle ones, at
+// 128 rows 97 and 86.  Sharing all slices is for few tiles and a long contraction (mostly the streaming form has those).
 struct PfPlan { int shape, shares; };
 static PfPlan plan_pf_gemm(const DevModel& M, const PrefillBufs& T, const PfTileSet* sets, int n, int stage) {
     struct Shape { int tiles, rows, per_cu; double alone, full, ends; };
