@@ -73,9 +73,13 @@ struct AttState {
 // share the former and fill the gaps of the latter.  Groups of 4 and 8 heads take
 // two (always the same two of a run), groups of 1 and 2 one.  A second block without a visible key is left out: it would add
 // zeros, but what rolled-back rows have left in it may be no number, and zero times that is none either.
-template <class DT, int HD, int NB, bool MASKED, class KF, class VF>
+// scored: called when the keys have been used.
+struct AttNothing {
+    __device__ __forceinline__ void operator()() const {}
+};
+template <class DT, int HD, int NB, bool MASKED, class KF, class VF, class Scored = AttNothing>
 __device__ __forceinline__ void attention_step(AttState<HD>& s, const uint4* qh, const uint4* ql, KF&& kf, VF&& vf, int p0, int lim,
-                                               int g, float scale, bool first) {
+                                               int g, float scale, bool first, Scored&& scored = Scored()) {
     constexpr int FR = HD / 4 / DT::EPL, HT = HD / 16, TPB = DT::TPB, NTL = NB * TPB;
     // Products are issued so that those of one accumulator are not neighbours; its own order stays (hi, lo, next fragment).
     v4f sc[NTL];
@@ -90,6 +94,7 @@ __device__ __forceinline__ void attention_step(AttState<HD>& s, const uint4* qh,
 #pragma unroll
             for (int t = 0; t < NTL; ++t) sc[t] = DT::mfma_att(k[t], ql[i], sc[t]);
     }
+    scored();
     __builtin_amdgcn_sched_barrier(0);
     // maxima and sums by tile: a chain over all of a lane's scores is as long as the products
     float mt[NTL];
@@ -374,6 +379,100 @@ __device__ __forceinline__ void attention_unit_staged(const DevModel& M, const D
     }
     __syncthreads();                                     // the runs' sums take the place of the blocks
     merge_runs<HD>(s, G, PARTS, hq, part, row0, k, part_out, smem);
+}
+
+// The same unit for a sequence with few rows: its rows times the group's heads fill one or two 16-row tiles instead of a tile
+// per head, of which a decoding step has one row each.  A unit is one such tile: lane m has the pair 16 t + m = row * G + head.
+// A run is a wave's, as its blocks are no one else's, and comes straight into registers: no block is waited for by more than
+// the wave that uses it, and several workgroups (of PARTS waves) share a compute unit.  smem: (HD + 8) * 64 floats.
+template <class DT, int HD, int G>
+struct AttPacked {
+    static constexpr int PARTS = kWaves / G, kThreads = PARTS * 64;
+    static constexpr int kLdsFloats = PARTS > 1 ? (HD / 4 + 2) * 64 : 1;
+};
+template <class DT, int HD, int G>
+__device__ __forceinline__ void attention_unit_packed(const DevModel& M, const DevLayer& Ly, const void* q_hi, const void* q_lo,
+                                                      size_t slot_frags, int kvh, int c, int t, int L, int k, int row0, float* part_out,
+                                                      float* smem) {
+    constexpr int FR = HD / 4 / DT::EPL, HT = HD / 16, BK = DT::BLOCK_KEYS, TPB = DT::TPB, PARTS = AttPacked<DT, HD, G>::PARTS;
+    const int lane = threadIdx.x & 63, part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int m = lane & 15, g = lane >> 4;
+    const int row = (16 * t + m) / G, hq = (16 * t + m) % G;
+    const bool mine = row < k;
+    const int T = L + k, bpw = M.bpw;
+    const int b0 = (c * PARTS + part) * bpw;             // first block of this wave's run
+    int steps = (T - b0 * BK + 2 * BK - 1) / (2 * BK);   // its steps with visible keys
+    if (steps > (bpw + 1) / 2) steps = (bpw + 1) / 2;
+    uint4 qh[FR], ql[FR], kb[2][TPB][FR], vb[2][HT];
+    const uint4* kc = reinterpret_cast<const uint4*>(Ly.kcache) + slot_frags + ((size_t)kvh * (M.ctx_pad / BK) + b0) * (TPB * FR * 64);
+    const uint4* vc = reinterpret_cast<const uint4*>(Ly.vcache) + slot_frags + ((size_t)kvh * (M.ctx_pad / BK) + b0) * (HT * 64);
+    auto two = [&](int st) { return 2 * st + 1 < bpw && (b0 + 2 * st + 1) * BK < T; };     // a second block with visible keys
+    auto load_keys = [&](int st) {
+#pragma unroll
+        for (int x = 0; x < TPB * FR; ++x) kb[0][x / FR][x % FR] = kc[(2 * st * (TPB * FR) + x) * 64 + lane];
+        if (two(st))
+#pragma unroll
+            for (int x = 0; x < TPB * FR; ++x) kb[1][x / FR][x % FR] = kc[((2 * st + 1) * (TPB * FR) + x) * 64 + lane];
+    };
+    auto load_values = [&](int st) {
+#pragma unroll
+        for (int j = 0; j < HT; ++j) vb[0][j] = vc[(2 * st * HT + j) * 64 + lane];
+        if (two(st))
+#pragma unroll
+            for (int j = 0; j < HT; ++j) vb[1][j] = vc[((2 * st + 1) * HT + j) * 64 + lane];
+        else
+#pragma unroll
+            for (int j = 0; j < HT; ++j) vb[1][j] = uint4{0, 0, 0, 0};
+    };
+    AttState<HD> s;
+    s.clear();
+    if (steps > 0) {
+        const size_t q0 = (size_t)(row0 + (mine ? row : 0)) * M.qdim + (kvh * G + hq) * HD + g * (HD / 4);
+#pragma unroll
+        for (int i = 0; i < FR; ++i) {
+            qh[i] = load_frag<DT>(q_hi, q0 + i * DT::EPL);
+            ql[i] = uint4{0, 0, 0, 0};
+            if constexpr (DT::HAS_LO) ql[i] = load_frag<DT>(q_lo, q0 + i * DT::EPL);
+        }
+        load_keys(0);
+        load_values(0);
+    }
+    const int lim = mine ? L + row : -1;                 // causal: the sequence's j-th row sees keys 0 .. L + j
+    auto kf = [&](int b, int tt, int i) { return kb[b][tt][i]; };
+    auto vf = [&](int b, int j) { return vb[b][j]; };
+#pragma unroll 1
+    for (int st = 0; st < steps; ++st) {
+        const int p0 = (b0 + 2 * st) * BK;
+        auto next_keys = [&] {
+            if (st + 1 < steps) load_keys(st + 1);
+        };
+        attention_step<DT, HD, 2, true>(s, qh, ql, kf, vf, p0, two(st) ? lim : lim < p0 + BK ? lim : p0 + BK - 1, g, M.att_scale, st == 0, next_keys);
+        if (st + 1 < steps) load_values(st + 1);
+    }
+    s.close();
+    if constexpr (PARTS == 2) {                          // the second run is added to the first, as merge_runs does
+        v4f* other = reinterpret_cast<v4f*>(smem);
+        float* other_ml = smem + HT * 256;
+        if (part == 1) {
+#pragma unroll
+            for (int j = 0; j < HT; ++j) other[j * 64 + lane] = s.o[j];
+            other_ml[lane] = s.m;
+            other_ml[64 + lane] = s.l;
+        }
+        __syncthreads();
+        if (part == 1) return;
+        AttState<HD> s1;
+#pragma unroll
+        for (int j = 0; j < HT; ++j) s1.o[j] = other[j * 64 + lane];
+        s1.m = other_ml[lane];
+        s1.l = other_ml[64 + lane];
+        s.add(s1);
+    }
+    if (!mine) return;
+    float* out = part_out + ((size_t)hq * kRows + row0 + row) * (HD + kPartRow);
+#pragma unroll
+    for (int j = 0; j < HT; ++j) *reinterpret_cast<v4f*>(out + j * 16 + g * 4) = s.o[j];
+    if (g == 0) *reinterpret_cast<float2*>(out + HD) = float2{s.m, s.l};
 }
 
 // Merge of the chunk partials of one (head, row) in chunk order by one wave, with the prefill pass's operations (PfTotals::add)

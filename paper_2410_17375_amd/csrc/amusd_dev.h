@@ -26,7 +26,7 @@ struct PassSeg {
     int slot;     // which key-value cache
     int unit0;    // first attention work unit of the sequence
     int nchunks;  // attention chunks covering positions 0 .. L+k-1
-    int pad;
+    int packed0;  // first unit of the sequence where units are tiles of (row, head) pairs; past the last sequence: above all units
 };
 
 // Per-pass values.  They travel as kernel arguments (no device round trip
@@ -43,6 +43,7 @@ struct PassArgs {
     int slot0;          // seg[0].slot
     int nchunks0;       // seg[0].nchunks
     int units;          // attention work units of the pass, all sequences together
+    int packed_units;   // the same with units that are tiles of (row, head) pairs
     int tokens[kRows];  // input token of each row
     int row_pos[kRows]; // position of each row in its sequence
     int row_seg[kRows]; // segment of each row

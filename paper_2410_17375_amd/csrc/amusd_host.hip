@@ -266,7 +266,7 @@ int run_pass(amusd_model* m, const SegReq* segs, int n_seg, bool force_accept, b
     const DevModel& D = use_static ? m->dm_static : m->dm;
     PassArgs P;
     std::memset(&P, 0, sizeof(P));
-    int rows = 0, units = 0;
+    int rows = 0, units = 0, packed = 0;
     int64_t positions = 0;
     for (int i = 0; i < n_seg; ++i) {
         const SegReq& r = segs[i];
@@ -284,7 +284,9 @@ int run_pass(amusd_model* m, const SegReq* segs, int n_seg, bool force_accept, b
             P.row_seg[rows + j] = i;
         }
         rows += r.k;
+        S.packed0 = packed;
         units += m->dm.Hkv * S.nchunks;
+        packed += (m->dm.Hkv * S.nchunks + 7) / 8 * 8 * ((r.k * m->dm.G + 15) / 16);   // (a multiple of 8: stage_attention_packed)
         positions += r.L + r.k;
     }
     P.k = rows;
@@ -293,6 +295,8 @@ int run_pass(amusd_model* m, const SegReq* segs, int n_seg, bool force_accept, b
     P.slot0 = P.seg[0].slot;
     P.nchunks0 = P.seg[0].nchunks;
     P.units = units;
+    P.packed_units = packed;
+    for (int i = n_seg; i < kMaxSegs; ++i) P.seg[i].packed0 = INT32_MAX;
     P.force_accept = force_accept ? 1 : 0;
     P.keep_logits = m->keep_logits ? 1 : 0;
     HIP_TRY(hipEventRecord(m->ev0, m->stream));

@@ -19,6 +19,7 @@
 // Every stage is a __device__ function over (workgroup id, workgroup count),
 // launched as one kernel per stage.
 #include "amusd_attention.h"
+#include "amusd_plan.h"
 
 namespace amusd {
 
@@ -861,6 +862,77 @@ __device__ __forceinline__ void stage_attention(const DevModel& M, const DevLaye
     prefetch_retire();
 }
 
+// The attention stage over tiles of (row, head) pairs (attention_unit_packed): one unit per workgroup, several of them on a
+// compute unit, so that their chains of loads, products, softmax and products overlap; the form above takes its units one after
+// the other, a workgroup a compute unit.  What bounds it: one such chain (3 us with the launch) while units are few, then the
+// load path.  Per launch, that form / this one: 8 sequences of the 1B shape to 1500, one row each, 13.3 us / 7.6 (16.4 MB of
+// cache), 4 sequences of the 8B shape to 3001 16.2 / 11.8 (36 MB), 1B shape, 1 row behind 512 4.4 / 3.2, 8B, 8 rows behind
+// 2048 8.2 / 5.4.
+// The workgroups behind the units fetch the O-projection's weights into L2, each for one workgroup of its own XCD, where
+// they are few enough to wait there (32 MiB in all): 1B shape (8 MB) 1 row behind 512 732 us a pass without, 714-722 with; 8B shape
+// (34 MB) 8 rows behind 2048 3000 without, 3082 with.
+constexpr size_t kPackedPfBytes = 24u << 20;
+template <class DT, int HD, bool ONE, int G>
+__device__ __forceinline__ void stage_attention_packed(const DevModel& M, const DevLayer& Ly, const PassArgs& P, int nwg, float* smem, float* sink) {
+    pin_scalar(M.Q_hi); pin_scalar(M.Q_lo); pin_scalar(Ly.kcache); pin_scalar(Ly.vcache); pin_scalar(M.att_part);
+    pin_scalar(Ly.wo); pin_scalar(M.d); pin_scalar(M.qdim); pin_scalar(M.Hkv); pin_scalar(M.ctx_pad);
+    pin_scalar(M.att_scale); pin_scalar(M.bpw); pin_scalar(P.L0); pin_scalar(P.k);
+    pin_scalar(P.nchunks0); pin_scalar(P.slot0); pin_scalar(P.packed_units);
+    constexpr int PARTS = AttPacked<DT, HD, G>::PARTS;
+    const int u = blockIdx.x;
+    if (u >= P.packed_units) {
+        const NextWeights wo{Ly.wo, M.d / 16, M.qdim / DT::KB};
+        const int consumers = wo.n_tiles < nwg ? wo.n_tiles : nwg;      // workgroups of the O-projection
+        const int x = u - P.packed_units;                                // same XCD as this one
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll 1
+        for (int w = wave; w < kWaves; w += PARTS) prefetch_frags<KWalkOproj, 0, kAttPf>(wo, x, consumers, w, lane, sink + wave * 64);
+        prefetch_retire();
+        return;
+    }
+    int L = P.L0, k = P.k, row0 = 0, nchunks = P.nchunks0, cslot = P.slot0, unit0 = 0, ul = u;
+    if constexpr (!ONE) {
+        int si = 0;
+#pragma unroll
+        for (int i = 1; i < kMaxSegs; ++i) si += u >= P.seg[i].packed0;
+        const PassSeg& S = P.seg[si];
+        L = S.L; k = S.k; row0 = S.row0; nchunks = S.nchunks; cslot = S.slot; unit0 = S.unit0;
+        ul = u - S.packed0;
+    }
+    // Eight (kv head, chunk) at a time, their tiles of pairs one after the other: the tiles that read the same keys run on one
+    // XCD, and with a multiple of 8 kv heads a kv head's chunks do, as in stage_attention.
+    int c = ul >> 3, t = 0;
+    const int tiles = (k * G + 15) / 16;
+    if (tiles > 1) {
+        t = c % tiles;
+        c /= tiles;
+    }
+    int kvh = ul & 7;
+    if (M.Hkv != 8) {
+        asm volatile("");   // a real branch, as above
+        if ((M.Hkv & 7) == 0) {
+            kvh += 8 * (c / nchunks);
+            c %= nchunks;
+        } else {
+            const int f = 8 * c + kvh;
+            kvh = f / nchunks;
+            c = f % nchunks;
+            if (kvh >= M.Hkv) return;
+        }
+    }
+    const size_t slot_frags = (size_t)cslot * M.Hkv * M.ctx_pad * HD / DT::EPL;
+    float* out = M.att_part + ((size_t)unit0 + (size_t)kvh * nchunks + c) * G * kRows * (HD + kPartRow);
+    attention_unit_packed<DT, HD, G>(M, Ly, M.Q_hi, M.Q_lo, slot_frags, kvh, c, t, L, k, row0, out, smem);
+}
+// Two waves a SIMD (registers for two blocks, 236 of 256).  Heads of 128 of several sequences: one, with registers to spare; each
+// wave then has more under way and fewer streams meet in a cache (4 sequences to 12000: 30.9 us a launch, two waves 33.4).
+template <class DT, int HD, bool ONE, int G>
+__global__ void __launch_bounds__(kWaves / G * 64, HD == 128 && !ONE ? 1 : 2) k_attention_packed(DevModel M, DevLayer Ly, PassArgs P, int nwg) {
+    __shared__ __attribute__((aligned(16))) float smem[AttPacked<DT, HD, G>::kLdsFloats];
+    __shared__ float sink[AttPacked<DT, HD, G>::PARTS * 64];
+    stage_attention_packed<DT, HD, ONE, G>(M, Ly, P, nwg, smem, sink);
+}
+
 // Merge of the chunk partials of each (head, row) in chunk order -> normalised
 // attention output as the O-projection's input.  One wave per (head, row):
 // lanes first hold one chunk each (reference, weight, denominator), then one slice of
@@ -1149,6 +1221,20 @@ hipError_t configure_kernels() {
     return hipSuccess;
 }
 
+template <class DT, int HD, int G>
+static void launch_attention_packed(const DevModel& M, const DevLayer& Ly, const PassArgs& P, int nwg, hipStream_t s, StageTimer* tm) {
+    const bool ahead = (size_t)M.d * M.qdim * DT::ESZ <= kPackedPfBytes;
+    const int o_wgs = !ahead ? 0 : M.d / 16 < nwg ? M.d / 16 : nwg;
+    const dim3 grid(P.packed_units + o_wgs), blk(AttPacked<DT, HD, G>::kThreads);
+    const auto kern = P.n_seg == 1 ? &k_attention_packed<DT, HD, true, G> : &k_attention_packed<DT, HD, false, G>;
+    if (tm && tm->stage == 2) {
+        hipExtLaunchKernelGGL(kern, grid, blk, 0, s, tm->begin[tm->used], tm->end[tm->used], 0, M, Ly, P, nwg);
+        ++tm->used;
+    } else {
+        hipLaunchKernelGGL(kern, grid, blk, 0, s, M, Ly, P, nwg);
+    }
+}
+
 template <class DT, int HD>
 static hipError_t launch_pass_t(const DevModel& M, const DevLayer* Ls, const PassArgs& P, int nwg, hipStream_t s,
                                 StageTimer* tm) {
@@ -1160,6 +1246,12 @@ static hipError_t launch_pass_t(const DevModel& M, const DevLayer* Ls, const Pas
     const int qkv_wgs = M.nqkv / 16 < nwg ? M.nqkv / 16 : nwg;
     const int d_wgs = M.d / 16 < nwg ? M.d / 16 : nwg;
     const int gu_wgs = 2 * M.F / 16 < nwg ? 2 * M.F / 16 : nwg;
+    int chunks = 0, tiles = 0;             // of all sequences: key chunks, and tiles of (row, head) pairs over them
+    for (int i = 0; i < P.n_seg; ++i) {
+        chunks += P.seg[i].nchunks;
+        tiles += P.seg[i].nchunks * ((P.seg[i].k * M.G + 15) / 16);
+    }
+    const bool packed = (M.G == 4 || M.G == 8) && attention_packs_rows(DT::HAS_LO, HD, M.G, P.units, (double)tiles / chunks, M.bpw, nwg);
     if (tm) tm->used = 0;
     // A timed stage is launched through the extended launch call, whose two events take the kernel's own
     // begin and end timestamps (no marker packets around it).
@@ -1190,7 +1282,9 @@ static hipError_t launch_pass_t(const DevModel& M, const DevLayer* Ls, const Pas
     for (int l = 0; l < M.n_layers; ++l) {
         const float* gain_next = l + 1 < M.n_layers ? Ls[l + 1].g_attn : M.g_final;
         AMUSD_LAUNCH_SEQ(1, k_qkv, qkv_wgs, blk, kSmemBytes, l)
-        if (M.G == 4) { AMUSD_LAUNCH_SEQ(2, k_attention_g4, att_wgs, blk, (kAttSmemBytes<DT, HD, 4>), l) }
+        if (packed && M.G == 4) launch_attention_packed<DT, HD, 4>(M, Ls[l], P, nwg, s, tm);
+        else if (packed) launch_attention_packed<DT, HD, 8>(M, Ls[l], P, nwg, s, tm);
+        else if (M.G == 4) { AMUSD_LAUNCH_SEQ(2, k_attention_g4, att_wgs, blk, (kAttSmemBytes<DT, HD, 4>), l) }
         else if (M.G == 8) { AMUSD_LAUNCH_SEQ(2, k_attention_g8, att_wgs, blk, (kAttSmemBytes<DT, HD, 8>), l) }
         else { AMUSD_LAUNCH_SEQ(2, k_attention, att_wgs, blk, kSmemBytes, l) }
         AMUSD_LAUNCH_SEQ(3, k_attn_merge, merge_wgs, dim3(64), 0, l)

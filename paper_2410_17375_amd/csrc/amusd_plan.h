@@ -33,4 +33,19 @@ inline bool pf_attention_walks_whole_rows(bool bf16, int head_dim, int group, in
     return whole <= split + r.alone * stretch + 2000;
 }
 
+// Attention of a verify pass, groups of 4 or 8 heads: tiles of (row, head) pairs (true) or a tile per head, whose units are one
+// (kv head, chunk) each.  units: of the latter; tiles: of pairs, per chunk on average; run_blocks: key blocks of a wave's run.
+//
+// A tile per head is a workgroup a compute unit, round after round, over blocks that are staged once for all heads.  Pairs need
+// fewer products while rows are few, and their workgroups share a compute unit; with many rows each tile fetches the keys for
+// itself.  So pairs where there is more than one round, or up to half as many tiles as heads (float32 heads of 128, twice the
+// registers a block: fewer).  Measured (MI355X, whole passes of 2 layers, us, tile per head / pairs): 8B, 8 rows behind 2000 keys 211 /
+// 208, behind 12000 224 / 219, 16 rows 238 / 241; 8 sequences of one row to 4000 260 / 235; heads in eights, 12 rows behind 7000 234 /
+// 238; float32, 8 rows behind 2000 359 / 365, 2 rows behind 7000 391 / 375; 1B (4 layers), 16 rows behind 4000 236 / 229.
+inline bool attention_packs_rows(bool bf16, int head_dim, int group, int units, double tiles, int run_blocks, int cus) {
+    if (units > cus) return true;
+    if (tiles <= group * (head_dim == 128 && !bf16 ? 0.375 : 0.5)) return true;
+    return bf16 && head_dim == 64 && run_blocks < 8;
+}
+
 }  // namespace amusd

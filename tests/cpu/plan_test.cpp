@@ -54,6 +54,26 @@ static const Point points[] = {
     {true, 128, 8, 1, 128, 1628, 64, 2, 256, 54, 24},
 };
 
+// Whether a verify pass's attention is tiles of (row, head) pairs or a tile per head, against measured times of a pass of two layers (us):
+// sizes that differ by 1 % and more.
+struct Pass {
+    bool bf16;
+    int head_dim, group, units;
+    double tiles;
+    int run_blocks;
+    double pairs, heads;
+};
+static const Pass passes[] = {
+    {true, 64, 4, 16, 1, 1, 194.4, 199.8},       {true, 64, 4, 256, 2, 8, 122.1, 124.2},      {true, 64, 4, 224, 4, 4, 131.7, 135.1},
+    {true, 64, 4, 808, 1, 4, 231.7, 268.6},      {true, 64, 4, 280, 1.5, 16, 142.6, 165.0},   {true, 64, 8, 256, 6, 16, 154.6, 152.3},
+    {true, 64, 8, 220, 8, 4, 141.2, 143.8},      {true, 128, 4, 128, 2, 2, 207.9, 211.0},     {true, 128, 4, 256, 2, 6, 219.4, 224.8},
+    {true, 128, 4, 256, 4, 6, 241.6, 238.1},     {true, 128, 4, 280, 1.5, 16, 259.9, 300.8},  {true, 128, 4, 1552, 1, 4, 298.8, 343.8},
+    {true, 128, 8, 220, 1, 4, 201.9, 207.5},     {true, 128, 8, 252, 4, 8, 219.0, 222.8},     {true, 128, 8, 220, 6, 4, 237.6, 233.5},
+    {true, 128, 8, 252, 8, 8, 252.8, 246.9},     {false, 64, 4, 256, 1, 7, 155.9, 163.3},     {false, 64, 4, 256, 4, 16, 202.2, 196.6},
+    {false, 64, 8, 252, 4, 16, 175.0, 188.9},    {false, 64, 8, 252, 8, 16, 211.0, 202.5},    {false, 128, 4, 168, 2, 3, 363.9, 357.6},
+    {false, 128, 4, 232, 1.45, 5, 372.6, 382.0}, {false, 128, 4, 256, 3, 16, 439.7, 430.8},   {false, 128, 4, 656, 1, 5, 387.7, 431.7},
+};
+
 extern "C" int whole_rows(int bf16, int head_dim, int group, int kv_heads, int rows, int keys, int cus, int chunk, int run_blocks, int stretch) {
     return amusd::pf_attention_walks_whole_rows(bf16, head_dim, group, kv_heads, rows, keys, cus, chunk, run_blocks, stretch);
 }
@@ -65,6 +85,13 @@ int main() {
         if (whole == (p.whole < p.split)) continue;
         std::printf("%s, heads of %d in groups of %d, %d kv heads, %d rows, %d keys: %.0f us, the other form %.0f\n", p.bf16 ? "bf16" : "float32", p.head_dim,
                     p.group, p.kv_heads, p.rows, p.keys, whole ? p.whole : p.split, whole ? p.split : p.whole);
+        ++wrong;
+    }
+    for (const Pass& p : passes) {
+        const bool pairs = amusd::attention_packs_rows(p.bf16, p.head_dim, p.group, p.units, p.tiles, p.run_blocks, 256);
+        if (pairs == (p.pairs < p.heads)) continue;
+        std::printf("verify pass, %s, heads of %d in groups of %d, %d units, %.2f tiles, %d blocks: pairs %.1f us, heads %.1f\n", p.bf16 ? "bf16" : "float32",
+                    p.head_dim, p.group, p.units, p.tiles, p.run_blocks, p.pairs, p.heads);
         ++wrong;
     }
     // groups of 1 and 2 have no such kernel
