@@ -36,6 +36,7 @@ struct PassArgs {
     int n_seg;          // sequences in the pass
     int force_accept;   // 1: prefill, every row is kept
     int keep_logits;    // 1: store fp32 logits
+    int export_bytes;   // of them, to DevModel::export_host as the pass ends (a multiple of 16)
     // The first sequence's values once more, next to k: a pass of ONE sequence (the usual case) then needs nothing
     // from the per-row and per-segment tables below, which a lane can only reach through dependent loads of the
     // argument memory (a memory round trip each, before the kernel's first useful address is known).
@@ -114,6 +115,7 @@ struct PrefillArgs {
     int L0;               // position of row 0
     int slot;             // which key-value cache
     int keep0;            // logits of rows keep0 .. n-1 are stored (n: none)
+    int export_bytes;     // as in PassArgs
 };
 
 struct DevModel {
@@ -149,6 +151,7 @@ struct DevModel {
     float* best_val;      // [lm_wgs][16]
     int* best_idx;
     PassResult* res;
+    char* export_host;    // pinned host memory, or null
 };
 
 }  // namespace amusd

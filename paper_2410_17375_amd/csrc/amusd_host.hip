@@ -105,6 +105,11 @@ struct amusd_model {
     size_t static_bytes = 0;               // bytes of the array that workspace takes
     uint64_t id = 0;
     HostStage* hstage = nullptr;
+    char* export_host = nullptr;           // pinned: logits on their way to the caller, kExportBytes at a time, and their chunks' flags
+    size_t export_bytes = 0;
+    int export_mark = 0;
+    size_t exported = 0;                   // bytes of the last pass's logits that are in the block already
+    std::mutex export_mutex;
     PrefillBufs pf{};                      // workspace of the prefill pass; cap 0: prompts go through the verify pass
     PfTileSet pf_tiles[kPfStages];
     void* pf_mem = nullptr;                // the device allocation that its buffers are in
@@ -248,6 +253,15 @@ float half_bits_to_float(uint16_t h) {      // IEEE binary16 -> float
 std::once_flag g_cfg_once;
 hipError_t g_cfg_err = hipSuccess;
 
+// Logits up to this size go to the host with the pass that makes them, next to its last kernel's own work.  us a call with its
+// logits fetched, so / when they are asked for: tiny draft step (16 KB) 70 / 77, 1B draft step (125 KB) 714 / 722, 333 rows of the tiny
+// model (208 KB) 162 / 171.
+constexpr size_t kExportWithPass = 256 << 10;
+int export_with_pass(const amusd_model* m, int rows) {
+    const size_t bytes = (size_t)rows * m->cfg.vocab * 4;
+    return m->keep_logits && m->export_host && bytes <= kExportWithPass ? (int)bytes : 0;
+}
+
 // Runs one pass: segment i feeds segs[i].k tokens of sequence segs[i].seq at cache length segs[i].L.
 // Everything is already validated (distinct sequences, lengths, capacity, tokens, row total).
 int run_pass(amusd_model* m, const SegReq* segs, int n_seg, bool force_accept, bool use_static = false) {
@@ -299,6 +313,8 @@ int run_pass(amusd_model* m, const SegReq* segs, int n_seg, bool force_accept, b
     for (int i = n_seg; i < kMaxSegs; ++i) P.seg[i].packed0 = INT32_MAX;
     P.force_accept = force_accept ? 1 : 0;
     P.keep_logits = m->keep_logits ? 1 : 0;
+    P.export_bytes = export_with_pass(m, rows);
+    m->exported = 0;
     HIP_TRY(hipEventRecord(m->ev0, m->stream));
     HIP_TRY(launch_pass(D, m->layers_host.data(), P, m->nwg, m->stream, m->timer.stage >= 0 ? &m->timer : nullptr));
     HIP_TRY(hipEventRecord(m->ev1, m->stream));
@@ -314,6 +330,7 @@ int run_pass(amusd_model* m, const SegReq* segs, int n_seg, bool force_accept, b
     }
     m->last_positions = positions;
     m->logits_valid = m->keep_logits;
+    m->exported = P.export_bytes;
     m->last_rows = rows;
     for (int i = 0; i < n_seg; ++i)
         if (h->res.accept_len[i] < 0 || h->res.accept_len[i] > segs[i].k)
@@ -323,6 +340,48 @@ int run_pass(amusd_model* m, const SegReq* segs, int n_seg, bool force_accept, b
         for (int j = 0; j < segs[i].k; ++j) q.greedy_at[segs[i].L + j + 1] = h->res.greedy[P.seg[i].row0 + j];
         q.kv_len = segs[i].L + h->res.accept_len[i];
         q.p_next = h->res.next_token[i];
+    }
+    return AMUSD_OK;
+}
+
+constexpr size_t kExportBytes = 4u << 20;     // the 16 rows of 65536 columns; more comes in several stretches
+
+int* export_flags(const amusd_model* m) { return reinterpret_cast<int*>(m->export_host + m->export_bytes); }
+
+// Device memory to memory of the caller's, through the model's pinned block: the device fills it chunk by chunk, the host
+// copies what has arrived and meanwhile touches the pages that follow, which the caller may never have used.  On the null stream,
+// as hipMemcpy would: it waits for what hipMemcpy waits for.
+int export_to(amusd_model* m, char* out, const char* src, size_t bytes) {
+    std::lock_guard<std::mutex> mine(m->export_mutex);
+    if (bytes <= m->exported) {
+        std::memcpy(out, m->export_host, bytes);
+        return AMUSD_OK;
+    }
+    size_t touched = 0;
+    for (size_t done = 0; done < bytes;) {
+        const size_t n = std::min(bytes - done, m->export_bytes);
+        const int mark = m->export_mark = m->export_mark == INT32_MAX ? 1 : m->export_mark + 1;
+        HIP_TRY(launch_export(m->dm.export_host, reinterpret_cast<int*>(m->dm.export_host + m->export_bytes), mark, src + done, n, nullptr));
+        for (size_t at = 0; at < n; at += kExportChunk) {
+            const int* flag = export_flags(m) + at / kExportChunk * kExportFlagStep;
+            for (unsigned spin = 1; __atomic_load_n(flag, __ATOMIC_ACQUIRE) != mark; ++spin) {
+                if (touched < bytes) {
+                    *static_cast<volatile char*>(out + touched) = 0;
+                    touched += 4096;
+                } else {
+                    __builtin_ia32_pause();
+                }
+                if (spin % 4096) continue;
+                const hipError_t e = hipStreamQuery(nullptr);
+                if (e == hipErrorNotReady) continue;
+                if (e == hipSuccess && __atomic_load_n(flag, __ATOMIC_ACQUIRE) == mark) break;
+                (void)hipGetLastError();
+                return fail(AMUSD_E_HIP, std::string("copy to the host: ") + hipGetErrorString(e));
+            }
+            std::memcpy(out + done + at, m->export_host + at, std::min(kExportChunk, n - at));
+            touched = std::max(touched, done + at + kExportChunk);
+        }
+        done += n;
     }
     return AMUSD_OK;
 }
@@ -414,7 +473,8 @@ int take_prefill(amusd_model* m) {
 // are what amusd_get_logits and amusd_get_greedy report.  Everything is already validated.
 int run_prefill(amusd_model* m, int seq, int L, const int32_t* tokens, int n, int tail) {
     HostStage* h = m->hstage;
-    const PrefillArgs P{n, L, seq, m->keep_logits ? n - tail : n};
+    const PrefillArgs P{n, L, seq, m->keep_logits ? n - tail : n, export_with_pass(m, tail)};
+    m->exported = 0;
     std::memcpy(m->pf_host, tokens, (size_t)n * 4);
     HIP_TRY(hipEventRecord(m->ev0, m->stream));
     HIP_TRY(launch_prefill(m->dm, m->layers_host.data(), m->pf, m->pf_tiles, P, m->stream));
@@ -429,6 +489,7 @@ int run_prefill(amusd_model* m, int seq, int L, const int32_t* tokens, int n, in
     q.p_next = greedy[n - 1];
     m->last_positions = L + n;
     m->logits_valid = m->keep_logits;
+    m->exported = P.export_bytes;
     m->last_rows = tail;
     return AMUSD_OK;
 }
@@ -592,6 +653,21 @@ int amusd_model_create(const amusd_config* cfg, void* hip_stream, amusd_model** 
         if (hipHostGetDevicePointer(&dev, m->hstage, 0) != hipSuccess)
             return bail(fail(AMUSD_E_HIP, "device address of the pinned result block"));
         D.res = reinterpret_cast<PassResult*>(dev);
+    }
+    // not needed either: without it logits reach the host by hipMemcpy
+    m->export_bytes = std::min(kExportBytes, (size_t)kRows * V * 4);
+    {
+        const size_t flags = (m->export_bytes + kExportChunk - 1) / kExportChunk * kExportFlagStep * sizeof(int);
+        if (hipHostMalloc(reinterpret_cast<void**>(&m->export_host), m->export_bytes + flags, hipHostMallocDefault) == hipSuccess) {
+            std::memset(export_flags(m), 0, flags);
+            void* dev = nullptr;
+            if (hipHostGetDevicePointer(&dev, m->export_host, 0) != hipSuccess)
+                return bail(fail(AMUSD_E_HIP, "device address of the pinned logits block"));
+            D.export_host = static_cast<char*>(dev);
+        } else {
+            m->export_host = nullptr;
+            (void)hipGetLastError();
+        }
     }
     if (hipEventCreate(&m->ev0) != hipSuccess || hipEventCreate(&m->ev1) != hipSuccess)
         return bail(fail(AMUSD_E_HIP, "event creation"));
@@ -771,6 +847,7 @@ int amusd_model_free(amusd_model* m) {
     for (void* p : m->allocs) (void)hipFree(p);
     if (m->staging) (void)hipFree(m->staging);
     if (m->hstage) (void)hipHostFree(m->hstage);
+    if (m->export_host) (void)hipHostFree(m->export_host);
     release_prefill(m);
     if (m->ev0) (void)hipEventDestroy(m->ev0);
     if (m->ev1) (void)hipEventDestroy(m->ev1);
@@ -1011,7 +1088,12 @@ int amusd_get_logits(amusd_model* m, float* out, int32_t rows) {
     if (rc) return rc;
     if (!out || rows < 1 || rows > kRows) return fail(AMUSD_E_ARG, "get_logits: bad argument");
     if (!m->logits_valid || rows > m->last_rows) return fail(AMUSD_E_STATE, "get_logits: the last pass kept no such logits");
-    HIP_TRY(hipMemcpy(out, m->dm.logits, (size_t)rows * m->cfg.vocab * 4, hipMemcpyDeviceToHost));
+    const size_t bytes = (size_t)rows * m->cfg.vocab * 4;
+    int device = -1;
+    // (a kernel runs on the calling thread's device; hipMemcpy finds the memory's)
+    if (m->export_host && hipGetDevice(&device) == hipSuccess && device == m->device)
+        return export_to(m, reinterpret_cast<char*>(out), reinterpret_cast<const char*>(m->dm.logits), bytes);
+    HIP_TRY(hipMemcpy(out, m->dm.logits, bytes, hipMemcpyDeviceToHost));
     return AMUSD_OK;
 }
 

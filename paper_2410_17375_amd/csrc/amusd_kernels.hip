@@ -1064,7 +1064,8 @@ AMUSD_STAGE_KERNEL(k_lmhead, (stage_lmhead<DT>(M, P, blockIdx.x, gridDim.x, smem
 
 __global__ void __launch_bounds__(kRows * 64) k_accept(DevModel M, PassArgs P) {
     __shared__ int sg[kRows];
-    stage_accept(M, P, sg);
+    if (blockIdx.x > 0) export_logits(M, P.export_bytes, blockIdx.x - 1);
+    else stage_accept(M, P, sg);
 }
 
 // ---------------------------------------------------------------- weight re-layout (model load)
@@ -1129,6 +1130,40 @@ hipError_t launch_fill_zero(uint4* dst, size_t n, hipStream_t stream) {
     if (n == 0) return hipSuccess;
     const size_t blocks = (n + 255) / 256;
     hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)(blocks < 1024 ? blocks : 1024)), dim3(256), 0, stream, dst, n);
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------- to pinned host memory, chunk by chunk
+// Four workgroups, so that the chunks arrive one after the other and the host copies the first while the rest is on its way:
+// bound by what one host core reads of memory that a device wrote (about 36 GB/s; the link does 53).  To memory of the
+// caller's, hipMemcpy / this: 16 KB 17 us / 7.5, 640 KB 34 / 25, 1.7 MB 88 / 50, 4.1 MB 215 / 115.  The stores are
+// system-scope atomics, which no cache of the device keeps, and a chunk's flag follows when all of them are acknowledged.
+__global__ void __launch_bounds__(kThreads) k_export(char* __restrict__ host, int* __restrict__ flags, int mark, const char* __restrict__ src,
+                                                     size_t bytes) {
+    constexpr int N = kExportChunk / (kThreads * 8);
+    for (size_t b0 = (size_t)blockIdx.x * kExportChunk; b0 < bytes; b0 += (size_t)gridDim.x * kExportChunk) {
+        uint64_t v[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const size_t at = b0 + ((size_t)i * kThreads + threadIdx.x) * 8;
+            v[i] = *reinterpret_cast<const uint64_t*>(src + (at < bytes ? at : bytes - 8));
+        }
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const size_t at = b0 + ((size_t)i * kThreads + threadIdx.x) * 8;
+            if (at < bytes) __hip_atomic_store(reinterpret_cast<uint64_t*>(host + at), v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (threadIdx.x == 0)
+            __hip_atomic_store(flags + b0 / kExportChunk * kExportFlagStep, mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
+hipError_t launch_export(char* host, int* flags, int mark, const void* src, size_t bytes, hipStream_t stream) {
+    const size_t chunks = (bytes + kExportChunk - 1) / kExportChunk;
+    hipLaunchKernelGGL(k_export, dim3((unsigned)(chunks < 4 ? chunks : 4)), dim3(kThreads), 0, stream, host, flags, mark,
+                       static_cast<const char*>(src), bytes);
     return hipGetLastError();
 }
 
@@ -1296,11 +1331,12 @@ static hipError_t launch_pass_t(const DevModel& M, const DevLayer* Ls, const Pas
 #undef AMUSD_LAUNCH_SEQ
 #undef AMUSD_LAUNCH
 #undef AMUSD_LAUNCH_T
+    const dim3 last(1 + export_wgs(P.export_bytes, kRows * 64));
     if (tm && tm->stage == 8) {
-        hipExtLaunchKernelGGL(k_accept, dim3(1), dim3(kRows * 64), 0, s, tm->begin[0], tm->end[0], 0, M, P);
+        hipExtLaunchKernelGGL(k_accept, last, dim3(kRows * 64), 0, s, tm->begin[0], tm->end[0], 0, M, P);
         tm->used = 1;
     } else {
-        hipLaunchKernelGGL(k_accept, dim3(1), dim3(kRows * 64), 0, s, M, P);
+        hipLaunchKernelGGL(k_accept, last, dim3(kRows * 64), 0, s, M, P);
     }
     return hipGetLastError();
 }

@@ -36,6 +36,12 @@ hipError_t launch_copy(uint4* dst, const uint4* src, size_t n, hipStream_t strea
 // Writes n zeroed 16-byte words (a kernel: usable where a memset node is not).
 hipError_t launch_fill_zero(uint4* dst, size_t n, hipStream_t stream);
 
+// Copies `bytes` (a multiple of 16) to pinned host memory in chunks of kExportChunk: as chunk c is there for the host to read,
+// flags[kExportFlagStep * c] becomes `mark`.
+constexpr size_t kExportChunk = 32 << 10;
+constexpr int kExportFlagStep = 16;
+hipError_t launch_export(char* host, int* flags, int mark, const void* src, size_t bytes, hipStream_t stream);
+
 // Enqueues n_kernels bare streaming kernels (256 workgroups, words_per_kernel 16-byte words each, regions of buf in
 // rotation), each depending on the one before.  io: 512 floats, fold: 256 words (device scratch of the caller).
 hipError_t launch_stream_chain(const uint4* buf, size_t buf_words, size_t words_per_kernel, int n_kernels, float* io,

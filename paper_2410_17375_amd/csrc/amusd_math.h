@@ -284,4 +284,14 @@ __device__ __forceinline__ void keep_better_xor(float& bv, int& bi) {
     if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
 }
 
+
+// Workgroup `wg` of those behind a pass's last kernel's own: its part of the logits to pinned host memory, a thread 16 bytes, while
+// the others finish the pass.  Fetching them afterwards takes a launch or a copy: 16 KB 17 us by hipMemcpy, 7.5 by k_export.
+__device__ __forceinline__ void export_logits(const DevModel& M, int bytes, int wg) {
+    const int at = (wg * (int)blockDim.x + (int)threadIdx.x) * 16;
+    if (at < bytes) *reinterpret_cast<uint4*>(M.export_host + at) = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(M.logits) + at);
+}
+// .. how many
+inline int export_wgs(int bytes, int threads) { return (bytes + threads * 16 - 1) / (threads * 16); }
+
 }  // namespace amusd

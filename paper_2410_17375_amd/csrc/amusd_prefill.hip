@@ -1196,7 +1196,12 @@ __global__ void __launch_bounds__(256) k_pf_merge(DevModel M, PrefillBufs T, Pre
 // Arg-max of each row over the workgroups' partials.  A workgroup takes 16 rows, so that a load's lanes share lines, in 32 walks
 // over the partials with eight loads under way each (a wave per row, one partial a lane: 5.3 us at 61 rows and 500 partials,
 // 14.5 at 2048).
-__global__ void __launch_bounds__(512) k_pf_greedy(PrefillBufs T, PrefillArgs P, int parts) {
+__global__ void __launch_bounds__(512) k_pf_greedy(DevModel M, PrefillBufs T, PrefillArgs P, int parts) {
+    const int own = (P.n + 15) / 16;
+    if ((int)blockIdx.x >= own) {
+        export_logits(M, P.export_bytes, blockIdx.x - own);
+        return;
+    }
     __shared__ float vals[8][16];
     __shared__ int idxs[8][16];
     constexpr int AHEAD = 8;
@@ -1476,7 +1481,7 @@ static hipError_t launch_prefill_t(const DevModel& M, const DevLayer* Ls, const 
     }
     int parts = 0;
     if ((e = launch_pf_gemm<DT, kPfLMHead>(M, Ls[0], T, tiles, P, nullptr, s, &parts)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_pf_greedy, dim3((P.n + 15) / 16), dim3(512), 0, s, T, P, parts);
+    hipLaunchKernelGGL(k_pf_greedy, dim3((P.n + 15) / 16 + export_wgs(P.export_bytes, 512)), dim3(512), 0, s, M, T, P, parts);
     return hipGetLastError();
 }
 
