@@ -159,11 +159,10 @@ __device__ __forceinline__ void attention_step(AttState<HD>& s, const uint4* qh,
     }
 }
 
-// The runs of a unit's heads, one per wave, through LDS to one partial per (head, row): [head][row][HD numerators,
-// reference, denominator, pad] at part_out.  smem: kWaves * kRows * (HD + kAttPad + 2) floats, free to be written.
-template <int HD>
-__device__ __forceinline__ void merge_runs(AttState<HD>& s, int G, int parts, int hq, int part, int row0, int k, float* part_out,
-                                           float* smem) {
+// The runs of a unit's heads, one per wave, through LDS to one partial per (head, row): out(head, row, column, four numerators,
+// reference, denominator).  smem: kWaves * kRows * (HD + kAttPad + 2) floats, free to be written.
+template <int HD, class Out>
+__device__ __forceinline__ void merge_runs(AttState<HD>& s, int G, int parts, int hq, int part, int row0, int k, Out&& out, float* smem) {
     constexpr int HT = HD / 16, HDP = HD + kAttPad;
     const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, g = lane >> 4;
     float* partO = smem;                               // [hq][part][16][HD + pad]
@@ -200,21 +199,29 @@ __device__ __forceinline__ void merge_runs(AttState<HD>& s, int G, int parts, in
 #pragma unroll
             for (int e = 0; e < 4; ++e) num[e] = fmaf(wt, x[e], num[e]);
         }
-        float* out = part_out + ((size_t)hh * kRows + mm) * (HD + kPartRow);
-        *reinterpret_cast<v4f*>(out + c4 * 4) = num;
-        if (c4 == 0) { out[HD] = Mx; out[HD + 1] = den; }
+        out(hh, mm, c4 * 4, num, Mx, den);
     }
     __syncthreads();
 }
 
+// .. to memory, for the merge of the chunks: [head][row][HD numerators, reference, denominator, pad]
+template <int HD>
+struct PartialOut {
+    float* part_out;
+    __device__ __forceinline__ void operator()(int hh, int mm, int col, v4f num, float ref, float den) const {
+        float* out = part_out + ((size_t)hh * kRows + mm) * (HD + kPartRow);
+        *reinterpret_cast<v4f*>(out + col) = num;
+        if (col == 0) { out[HD] = ref; out[HD + 1] = den; }
+    }
+};
+
 // One unit: chunk c of kv head kvh (the 8/G runs of bpw key blocks that the waves of a workgroup walk) against the tile
 // rows row0 .. row0+k-1, which stand at positions L .. L+k-1.  q_hi / q_lo: the tile's query rows, row-major.
-// slot_frags: start of the sequence's cache, in 16-byte fragments.  Writes [head of the group][row][HD numerators,
-// reference, denominator, pad] to part_out.  smem: kWaves * kRows * (HD + kAttPad + 2) floats.
-template <class DT, int HD>
+// slot_frags: start of the sequence's cache, in 16-byte fragments.  out: as in merge_runs, heads
+// counted in the group.  smem: kWaves * kRows * (HD + kAttPad + 2) floats.
+template <class DT, int HD, class Out>
 __device__ __forceinline__ void attention_unit(const DevModel& M, const DevLayer& Ly, const void* q_hi, const void* q_lo,
-                                               size_t slot_frags, int kvh, int c, int L, int k, int row0, float* part_out,
-                                               float* smem) {
+                                               size_t slot_frags, int kvh, int c, int L, int k, int row0, Out&& out, float* smem) {
     constexpr int FR = HD / 4 / DT::EPL;     // 16-byte fragments per lane along head_dim
     constexpr int HT = HD / 16;              // 16-wide head_dim tiles
     constexpr int BK = DT::BLOCK_KEYS, TPB = DT::TPB;
@@ -279,7 +286,7 @@ __device__ __forceinline__ void attention_unit(const DevModel& M, const DevLayer
 #pragma unroll
         for (int j = 0; j < HT; ++j) vf[j] = vn[j];
     }
-    merge_runs<HD>(s, G, parts, hq, part, row0, k, part_out, smem);
+    merge_runs<HD>(s, G, parts, hq, part, row0, k, out, smem);
 }
 
 // The same unit for groups of 4 or 8 heads: the blocks of a run are needed by all G waves that walk it, so they are staged
@@ -378,7 +385,7 @@ __device__ __forceinline__ void attention_unit_staged(const DevModel& M, const D
         }
     }
     __syncthreads();                                     // the runs' sums take the place of the blocks
-    merge_runs<HD>(s, G, PARTS, hq, part, row0, k, part_out, smem);
+    merge_runs<HD>(s, G, PARTS, hq, part, row0, k, PartialOut<HD>{part_out}, smem);
 }
 
 // The same unit for a sequence with few rows: its rows times the group's heads fill one or two 16-row tiles instead of a tile
@@ -388,91 +395,185 @@ __device__ __forceinline__ void attention_unit_staged(const DevModel& M, const D
 template <class DT, int HD, int G>
 struct AttPacked {
     static constexpr int PARTS = kWaves / G, kThreads = PARTS * 64;
-    static constexpr int kLdsFloats = PARTS > 1 ? (HD / 4 + 2) * 64 : 1;
-};
-template <class DT, int HD, int G>
-__device__ __forceinline__ void attention_unit_packed(const DevModel& M, const DevLayer& Ly, const void* q_hi, const void* q_lo,
-                                                      size_t slot_frags, int kvh, int c, int t, int L, int k, int row0, float* part_out,
-                                                      float* smem) {
-    constexpr int FR = HD / 4 / DT::EPL, HT = HD / 16, BK = DT::BLOCK_KEYS, TPB = DT::TPB, PARTS = AttPacked<DT, HD, G>::PARTS;
-    const int lane = threadIdx.x & 63, part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int m = lane & 15, g = lane >> 4;
-    const int row = (16 * t + m) / G, hq = (16 * t + m) % G;
-    const bool mine = row < k;
-    const int T = L + k, bpw = M.bpw;
-    const int b0 = (c * PARTS + part) * bpw;             // first block of this wave's run
-    int steps = (T - b0 * BK + 2 * BK - 1) / (2 * BK);   // its steps with visible keys
-    if (steps > (bpw + 1) / 2) steps = (bpw + 1) / 2;
+    static constexpr int FR = HD / 4 / DT::EPL, HT = HD / 16, BK = DT::BLOCK_KEYS, TPB = DT::TPB;
+    static constexpr int kRunFloats = (HD / 4 + 2) * 64;         // a run's sums in LDS: numerators, references, denominators
+    static constexpr int kLdsFloats = PARTS > 1 ? kRunFloats : 1;
+    AttState<HD> s;                                              // sums of the run that walk() walked
     uint4 qh[FR], ql[FR], kb[2][TPB][FR], vb[2][HT];
-    const uint4* kc = reinterpret_cast<const uint4*>(Ly.kcache) + slot_frags + ((size_t)kvh * (M.ctx_pad / BK) + b0) * (TPB * FR * 64);
-    const uint4* vc = reinterpret_cast<const uint4*>(Ly.vcache) + slot_frags + ((size_t)kvh * (M.ctx_pad / BK) + b0) * (HT * 64);
-    auto two = [&](int st) { return 2 * st + 1 < bpw && (b0 + 2 * st + 1) * BK < T; };     // a second block with visible keys
-    auto load_keys = [&](int st) {
-#pragma unroll
-        for (int x = 0; x < TPB * FR; ++x) kb[0][x / FR][x % FR] = kc[(2 * st * (TPB * FR) + x) * 64 + lane];
-        if (two(st))
-#pragma unroll
-            for (int x = 0; x < TPB * FR; ++x) kb[1][x / FR][x % FR] = kc[((2 * st + 1) * (TPB * FR) + x) * 64 + lane];
-    };
-    auto load_values = [&](int st) {
-#pragma unroll
-        for (int j = 0; j < HT; ++j) vb[0][j] = vc[(2 * st * HT + j) * 64 + lane];
-        if (two(st))
-#pragma unroll
-            for (int j = 0; j < HT; ++j) vb[1][j] = vc[((2 * st + 1) * HT + j) * 64 + lane];
-        else
-#pragma unroll
-            for (int j = 0; j < HT; ++j) vb[1][j] = uint4{0, 0, 0, 0};
-    };
-    AttState<HD> s;
-    s.clear();
-    if (steps > 0) {
-        const size_t q0 = (size_t)(row0 + (mine ? row : 0)) * M.qdim + (kvh * G + hq) * HD + g * (HD / 4);
+    const uint4* kc;                                             // the kv head's keys and values, this lane's of each fragment
+    const uint4* vc;
+    int lane, g, row, hq, lim, T, bpw, L;                        // row: of the sequence; lim: its last visible key, -1 if it has no such row
+    float scale;
+    __device__ __forceinline__ AttPacked(const DevModel& M, const DevLayer& Ly, size_t slot_frags, int kvh, int t, int L_, int k) {
+        lane = threadIdx.x & 63;
+        g = lane >> 4;
+        row = (16 * t + (lane & 15)) / G;
+        hq = (16 * t + (lane & 15)) % G;
+        L = L_;
+        T = L + k;
+        lim = row < k ? L + row : -1;
+        bpw = M.bpw;
+        scale = M.att_scale;
+        kc = reinterpret_cast<const uint4*>(Ly.kcache) + slot_frags + (size_t)kvh * (M.ctx_pad / BK) * (TPB * FR * 64) + lane;
+        vc = reinterpret_cast<const uint4*>(Ly.vcache) + slot_frags + (size_t)kvh * (M.ctx_pad / BK) * (HT * 64) + lane;
+    }
+    __device__ __forceinline__ void load_queries(const DevModel& M, const void* q_hi, const void* q_lo, int kvh, int row0) {
+        const size_t q0 = (size_t)(row0 + (lim >= 0 ? row : 0)) * M.qdim + (kvh * G + hq) * HD + g * (HD / 4);
 #pragma unroll
         for (int i = 0; i < FR; ++i) {
             qh[i] = load_frag<DT>(q_hi, q0 + i * DT::EPL);
             ql[i] = uint4{0, 0, 0, 0};
             if constexpr (DT::HAS_LO) ql[i] = load_frag<DT>(q_lo, q0 + i * DT::EPL);
         }
-        load_keys(0);
-        load_values(0);
     }
-    const int lim = mine ? L + row : -1;                 // causal: the sequence's j-th row sees keys 0 .. L + j
-    auto kf = [&](int b, int tt, int i) { return kb[b][tt][i]; };
-    auto vf = [&](int b, int j) { return vb[b][j]; };
-#pragma unroll 1
-    for (int st = 0; st < steps; ++st) {
-        const int p0 = (b0 + 2 * st) * BK;
-        auto next_keys = [&] {
-            if (st + 1 < steps) load_keys(st + 1);
-        };
-        attention_step<DT, HD, 2, true>(s, qh, ql, kf, vf, p0, two(st) ? lim : lim < p0 + BK ? lim : p0 + BK - 1, g, M.att_scale, st == 0, next_keys);
-        if (st + 1 < steps) load_values(st + 1);
+    // steps of the run from block b0 on with visible keys
+    __device__ __forceinline__ int steps(int b0) const {
+        const int n = (T - b0 * BK + 2 * BK - 1) / (2 * BK);
+        return n < (bpw + 1) / 2 ? n : (bpw + 1) / 2;
     }
-    s.close();
-    if constexpr (PARTS == 2) {                          // the second run is added to the first, as merge_runs does
-        v4f* other = reinterpret_cast<v4f*>(smem);
-        float* other_ml = smem + HT * 256;
-        if (part == 1) {
+    // whether step st of that run has a second block with visible keys
+    __device__ __forceinline__ bool two(int b0, int st) const { return 2 * st + 1 < bpw && (b0 + 2 * st + 1) * BK < T; }
+    __device__ __forceinline__ void load_keys(int b0, int st) {
+        const uint4* p = kc + (size_t)(b0 + 2 * st) * (TPB * FR * 64);
 #pragma unroll
-            for (int j = 0; j < HT; ++j) other[j * 64 + lane] = s.o[j];
-            other_ml[lane] = s.m;
-            other_ml[64 + lane] = s.l;
+        for (int x = 0; x < TPB * FR; ++x) kb[0][x / FR][x % FR] = p[x * 64];
+        if (two(b0, st))
+#pragma unroll
+            for (int x = 0; x < TPB * FR; ++x) kb[1][x / FR][x % FR] = p[(TPB * FR + x) * 64];
+    }
+    // (values of no visible block count as zero, with weights of zero: what is there may be no number)
+    __device__ __forceinline__ void load_values(int b0, int st) {
+        const uint4* p = vc + (size_t)(b0 + 2 * st) * (HT * 64);
+#pragma unroll
+        for (int j = 0; j < HT; ++j) vb[0][j] = p[j * 64];
+        if (two(b0, st))
+#pragma unroll
+            for (int j = 0; j < HT; ++j) vb[1][j] = p[(HT + j) * 64];
+        else
+#pragma unroll
+            for (int j = 0; j < HT; ++j) vb[1][j] = uint4{0, 0, 0, 0};
+    }
+    // Step st of the run from block b0 on.  next_keys: asks for the step to come; its values follow behind.
+    template <class Next>
+    __device__ __forceinline__ void step(int b0, int st, Next&& next_keys) {
+        const int p0 = (b0 + 2 * st) * BK, end = two(b0, st) ? lim : p0 + BK - 1;
+        auto kf = [&](int b, int tt, int i) { return kb[b][tt][i]; };
+        auto vf = [&](int b, int j) { return vb[b][j]; };
+        attention_step<DT, HD, 2, true>(s, qh, ql, kf, vf, p0, lim < end ? lim : end, g, scale, st == 0, next_keys);
+    }
+    // The run from block b0 on, to its end.
+    __device__ __forceinline__ void walk(const DevModel& M, const void* q_hi, const void* q_lo, int kvh, int row0, int b0) {
+        const int n = steps(b0);
+        s.clear();
+        if (n > 0) {
+            load_queries(M, q_hi, q_lo, kvh, row0);
+            load_keys(b0, 0);
+            load_values(b0, 0);
         }
+#pragma unroll 1
+        for (int st = 0; st < n; ++st) {
+            step(b0, st, [&] {
+                if (st + 1 < n) load_keys(b0, st + 1);
+            });
+            if (st + 1 < n) load_values(b0, st + 1);
+        }
+        s.close();
+    }
+    __device__ __forceinline__ void put(float* lds) const {
+#pragma unroll
+        for (int j = 0; j < HT; ++j) reinterpret_cast<v4f*>(lds)[j * 64 + lane] = s.o[j];
+        lds[HT * 256 + lane] = s.m;
+        lds[HT * 256 + 64 + lane] = s.l;
+    }
+};
+template <class DT, int HD, int G>
+__device__ __forceinline__ void attention_unit_packed(const DevModel& M, const DevLayer& Ly, const void* q_hi, const void* q_lo,
+                                                      size_t slot_frags, int kvh, int c, int t, int L, int k, int row0, float* part_out,
+                                                      float* smem) {
+    using A = AttPacked<DT, HD, G>;
+    constexpr int HT = A::HT, PARTS = A::PARTS;
+    const int part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    A at(M, Ly, slot_frags, kvh, t, L, k);
+    at.walk(M, q_hi, q_lo, kvh, row0, (c * PARTS + part) * at.bpw);
+    AttState<HD>& s = at.s;
+    if constexpr (PARTS == 2) {                          // the second run is added to the first, as merge_runs does
+        if (part == 1) at.put(smem);
         __syncthreads();
         if (part == 1) return;
         AttState<HD> s1;
 #pragma unroll
-        for (int j = 0; j < HT; ++j) s1.o[j] = other[j * 64 + lane];
-        s1.m = other_ml[lane];
-        s1.l = other_ml[64 + lane];
+        for (int j = 0; j < HT; ++j) s1.o[j] = reinterpret_cast<v4f*>(smem)[j * 64 + at.lane];
+        s1.m = smem[HT * 256 + at.lane];
+        s1.l = smem[HT * 256 + 64 + at.lane];
         s.add(s1);
     }
-    if (!mine) return;
-    float* out = part_out + ((size_t)hq * kRows + row0 + row) * (HD + kPartRow);
+    if (at.lim < 0) return;
+    float* out = part_out + ((size_t)at.hq * kRows + row0 + at.row) * (HD + kPartRow);
 #pragma unroll
-    for (int j = 0; j < HT; ++j) *reinterpret_cast<v4f*>(out + j * 16 + g * 4) = s.o[j];
-    if (g == 0) *reinterpret_cast<float2*>(out + HD) = float2{s.m, s.l};
+    for (int j = 0; j < HT; ++j) *reinterpret_cast<v4f*>(out + j * 16 + at.g * 4) = s.o[j];
+    if (at.g == 0) *reinterpret_cast<float2*>(out + HD) = float2{s.m, s.l};
+}
+
+// The same for a sequence whose keys are few (at most kWaves runs): a workgroup of eight waves walks all of a (kv head, tile of
+// pairs) and adds the runs and chunks up in LDS, in their order and with the operations of merge_runs and merge_chunks: no
+// partials, no launch to merge them.  smem: kRunFloats per run.
+template <class DT, int HD, int G>
+__device__ __forceinline__ void attention_whole_packed(const DevModel& M, const DevLayer& Ly, const void* q_hi, const void* q_lo,
+                                                       size_t slot_frags, int kvh, int t, int L, int k, int row0, int k_rows, float* smem) {
+    using A = AttPacked<DT, HD, G>;
+    constexpr int HT = A::HT, PARTS = A::PARTS;
+    const int run = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    A at(M, Ly, slot_frags, kvh, t, L, k);
+    const int bpw = at.bpw, runs = (at.T + bpw * A::BK - 1) / (bpw * A::BK), b0 = run * bpw;
+    if (run < runs) {
+        at.walk(M, q_hi, q_lo, kvh, row0, b0);
+        at.put(smem + run * A::kRunFloats);
+    }
+    __syncthreads();
+    const int j = threadIdx.x >> 6;                      // 16 columns of a pair: a lane has four of them
+    if (j >= HT || at.lim < 0) return;
+    auto part = [&](int r, float& m, float& l) {
+        const float* p = smem + r * A::kRunFloats;
+        m = p[HT * 256 + at.lane];
+        l = p[HT * 256 + 64 + at.lane];
+        return reinterpret_cast<const v4f*>(p)[j * 64 + at.lane];
+    };
+    float ref = 0.f;
+    double den = 0.;
+    v4f num;
+    const int chunks = at.lim / (PARTS * bpw * A::BK) + 1;                // with keys that the row sees
+    for (int c = 0; c < chunks; ++c) {
+        float m, l;
+        v4f o = part(c * PARTS, m, l);
+        if (PARTS == 2 && c * PARTS + 1 < runs) {        // AttState::add
+            float m1, l1;
+            const v4f o1 = part(c * PARTS + 1, m1, l1);
+            const bool up = att_outgrown(m1, m);
+            const float a = up ? exp2_fast(m - m1) : 1.f;
+            m = up ? m1 : m;
+            const float w = m1 == -INFINITY ? 0.f : exp2_fast(m1 - m);
+            l = fmaf(w, l1, l * a);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = fmaf(w, o1[e], o[e] * a);
+        }
+        if (c == 0) {
+            ref = m;
+            den = l;
+            num = o;
+            continue;
+        }
+        if (att_outgrown(m, ref)) {
+            const float a = exp2_fast(ref - m);
+            ref = m;
+            den *= a;
+            num = num * a;
+        }
+        const float w = m == -INFINITY ? 0.f : exp2_fast(m - ref);
+        den = fma((double)w, (double)l, den);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) num[e] = fmaf(w, o[e], num[e]);
+    }
+    store_gemm_in4<DT>(M.O, k_rows, row0 + at.row, (kvh * G + at.hq) * HD + j * 16 + at.g * 4, num * (1.0f / (float)den));
 }
 
 // Merge of the chunk partials of one (head, row) in chunk order by one wave, with the prefill pass's operations (PfTotals::add)

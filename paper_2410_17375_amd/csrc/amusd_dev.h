@@ -35,6 +35,7 @@ struct PassArgs {
     int k;              // rows of the pass, all sequences together
     int n_seg;          // sequences in the pass
     int force_accept;   // 1: prefill, every row is kept
+    int whole;          // 1: the attention stage's workgroups have all keys of their rows, nothing is left to merge (set by launch_pass)
     int keep_logits;    // 1: store fp32 logits
     int export_bytes;   // of them, to DevModel::export_host as the pass ends (a multiple of 16)
     // The first sequence's values once more, next to k: a pass of ONE sequence (the usual case) then needs nothing

@@ -855,9 +855,18 @@ __device__ __forceinline__ void stage_attention(const DevModel& M, const DevLaye
         }
         const int ucanon = unit0 + kvh * nchunks + c;      // where the merge stage looks for this unit's partials
         const size_t slot_frags = (size_t)cslot * M.Hkv * M.ctx_pad * HD / DT::EPL;   // 16-byte fragments per cache
-        float* out = M.att_part + (size_t)ucanon * G * kRows * (HD + kPartRow);
-        if constexpr (STAGED != 0) attention_unit_staged<DT, HD, STAGED>(M, Ly, M.Q_hi, M.Q_lo, slot_frags, kvh, c, L, k, row0, out, smem);
-        else attention_unit<DT, HD>(M, Ly, M.Q_hi, M.Q_lo, slot_frags, kvh, c, L, k, row0, out, smem);
+        float* part = M.att_part + (size_t)ucanon * G * kRows * (HD + kPartRow);
+        if constexpr (STAGED != 0) {
+            attention_unit_staged<DT, HD, STAGED>(M, Ly, M.Q_hi, M.Q_lo, slot_frags, kvh, c, L, k, row0, part, smem);
+        } else {
+            const int k_rows = P.k;
+            const bool whole = P.whole;
+            auto out = [&](int hh, int mm, int col, v4f num, float ref, float den) {
+                if (whole) store_gemm_in4<DT>(M.O, k_rows, mm, (kvh * G + hh) * HD + col, num * (1.0f / den));   // (merge_chunks of one chunk)
+                else PartialOut<HD>{part}(hh, mm, col, num, ref, den);
+            };
+            attention_unit<DT, HD>(M, Ly, M.Q_hi, M.Q_lo, slot_frags, kvh, c, L, k, row0, out, smem);
+        }
     }
     prefetch_retire();
 }
@@ -872,13 +881,13 @@ __device__ __forceinline__ void stage_attention(const DevModel& M, const DevLaye
 // they are few enough to wait there (32 MiB in all): 1B shape (8 MB) 1 row behind 512 732 us a pass without, 714-722 with; 8B shape
 // (34 MB) 8 rows behind 2048 3000 without, 3082 with.
 constexpr size_t kPackedPfBytes = 24u << 20;
-template <class DT, int HD, bool ONE, int G>
+// WHOLE: a unit is a (kv head, tile of pairs) with all its keys (attention_whole_packed) and no chunk of them.
+template <class DT, int HD, bool ONE, int G, bool WHOLE>
 __device__ __forceinline__ void stage_attention_packed(const DevModel& M, const DevLayer& Ly, const PassArgs& P, int nwg, float* smem, float* sink) {
-    pin_scalar(M.Q_hi); pin_scalar(M.Q_lo); pin_scalar(Ly.kcache); pin_scalar(Ly.vcache); pin_scalar(M.att_part);
+    pin_scalar(M.Q_hi); pin_scalar(M.Q_lo); pin_scalar(Ly.kcache); pin_scalar(Ly.vcache); pin_scalar(M.att_part); pin_scalar(M.O);
     pin_scalar(Ly.wo); pin_scalar(M.d); pin_scalar(M.qdim); pin_scalar(M.Hkv); pin_scalar(M.ctx_pad);
     pin_scalar(M.att_scale); pin_scalar(M.bpw); pin_scalar(P.L0); pin_scalar(P.k);
     pin_scalar(P.nchunks0); pin_scalar(P.slot0); pin_scalar(P.packed_units);
-    constexpr int PARTS = AttPacked<DT, HD, G>::PARTS;
     const int u = blockIdx.x;
     if (u >= P.packed_units) {
         const NextWeights wo{Ly.wo, M.d / 16, M.qdim / DT::KB};
@@ -886,7 +895,7 @@ __device__ __forceinline__ void stage_attention_packed(const DevModel& M, const 
         const int x = u - P.packed_units;                                // same XCD as this one
         const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll 1
-        for (int w = wave; w < kWaves; w += PARTS) prefetch_frags<KWalkOproj, 0, kAttPf>(wo, x, consumers, w, lane, sink + wave * 64);
+        for (int w = wave; w < kWaves; w += blockDim.x / 64) prefetch_frags<KWalkOproj, 0, kAttPf>(wo, x, consumers, w, lane, sink + wave * 64);
         prefetch_retire();
         return;
     }
@@ -899,6 +908,7 @@ __device__ __forceinline__ void stage_attention_packed(const DevModel& M, const 
         L = S.L; k = S.k; row0 = S.row0; nchunks = S.nchunks; cslot = S.slot; unit0 = S.unit0;
         ul = u - S.packed0;
     }
+    if constexpr (WHOLE) nchunks = 1;
     // Eight (kv head, chunk) at a time, their tiles of pairs one after the other: the tiles that read the same keys run on one
     // XCD, and with a multiple of 8 kv heads a kv head's chunks do, as in stage_attention.
     int c = ul >> 3, t = 0;
@@ -921,8 +931,12 @@ __device__ __forceinline__ void stage_attention_packed(const DevModel& M, const 
         }
     }
     const size_t slot_frags = (size_t)cslot * M.Hkv * M.ctx_pad * HD / DT::EPL;
-    float* out = M.att_part + ((size_t)unit0 + (size_t)kvh * nchunks + c) * G * kRows * (HD + kPartRow);
-    attention_unit_packed<DT, HD, G>(M, Ly, M.Q_hi, M.Q_lo, slot_frags, kvh, c, t, L, k, row0, out, smem);
+    if constexpr (WHOLE) {
+        attention_whole_packed<DT, HD, G>(M, Ly, M.Q_hi, M.Q_lo, slot_frags, kvh, t, L, k, row0, P.k, smem);
+    } else {
+        float* out = M.att_part + ((size_t)unit0 + (size_t)kvh * nchunks + c) * G * kRows * (HD + kPartRow);
+        attention_unit_packed<DT, HD, G>(M, Ly, M.Q_hi, M.Q_lo, slot_frags, kvh, c, t, L, k, row0, out, smem);
+    }
 }
 // Two waves a SIMD (registers for two blocks, 236 of 256).  Heads of 128 of several sequences: one, with registers to spare; each
 // wave then has more under way and fewer streams meet in a cache (4 sequences to 12000: 30.9 us a launch, two waves 33.4).
@@ -930,7 +944,13 @@ template <class DT, int HD, bool ONE, int G>
 __global__ void __launch_bounds__(kWaves / G * 64, HD == 128 && !ONE ? 1 : 2) k_attention_packed(DevModel M, DevLayer Ly, PassArgs P, int nwg) {
     __shared__ __attribute__((aligned(16))) float smem[AttPacked<DT, HD, G>::kLdsFloats];
     __shared__ float sink[AttPacked<DT, HD, G>::PARTS * 64];
-    stage_attention_packed<DT, HD, ONE, G>(M, Ly, P, nwg, smem, sink);
+    stage_attention_packed<DT, HD, ONE, G, false>(M, Ly, P, nwg, smem, sink);
+}
+template <class DT, int HD, bool ONE, int G>
+__global__ void __launch_bounds__(kThreads) k_attention_whole(DevModel M, DevLayer Ly, PassArgs P, int nwg) {
+    extern __shared__ __attribute__((aligned(16))) float smem[];
+    __shared__ float sink[kWaves * 64];
+    stage_attention_packed<DT, HD, ONE, G, true>(M, Ly, P, nwg, smem, sink);
 }
 
 // Merge of the chunk partials of each (head, row) in chunk order -> normalised
@@ -1229,6 +1249,12 @@ static hipError_t configure_one() {
     AMUSD_SET(k_attention, kSmemBytes)
     AMUSD_SET(k_attention_g4, (kAttSmemBytes<DT, HD, 4>))
     AMUSD_SET(k_attention_g8, (kAttSmemBytes<DT, HD, 8>))
+#define AMUSD_SET_WHOLE(one, g)                                                                                          \
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attention_whole<DT, HD, one, g>),                          \
+                            hipFuncAttributeMaxDynamicSharedMemorySize, kWaves * AttPacked<DT, HD, g>::kRunFloats * 4); \
+    if (e != hipSuccess) return e;
+    AMUSD_SET_WHOLE(true, 4) AMUSD_SET_WHOLE(false, 4) AMUSD_SET_WHOLE(true, 8) AMUSD_SET_WHOLE(false, 8)
+#undef AMUSD_SET_WHOLE
 #define AMUSD_SET_ONE(kern, bytes)                                                                                 \
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&kern<DT, HD, true>),                                     \
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)(bytes));                              \
@@ -1260,19 +1286,38 @@ template <class DT, int HD, int G>
 static void launch_attention_packed(const DevModel& M, const DevLayer& Ly, const PassArgs& P, int nwg, hipStream_t s, StageTimer* tm) {
     const bool ahead = (size_t)M.d * M.qdim * DT::ESZ <= kPackedPfBytes;
     const int o_wgs = !ahead ? 0 : M.d / 16 < nwg ? M.d / 16 : nwg;
-    const dim3 grid(P.packed_units + o_wgs), blk(AttPacked<DT, HD, G>::kThreads);
-    const auto kern = P.n_seg == 1 ? &k_attention_packed<DT, HD, true, G> : &k_attention_packed<DT, HD, false, G>;
+    const dim3 grid(P.packed_units + o_wgs), blk(P.whole ? kThreads : AttPacked<DT, HD, G>::kThreads);
+    const size_t lds = P.whole ? kWaves * AttPacked<DT, HD, G>::kRunFloats * 4 : 0;
+    auto kern = P.n_seg == 1 ? &k_attention_packed<DT, HD, true, G> : &k_attention_packed<DT, HD, false, G>;
+    if (P.whole) kern = P.n_seg == 1 ? &k_attention_whole<DT, HD, true, G> : &k_attention_whole<DT, HD, false, G>;
     if (tm && tm->stage == 2) {
-        hipExtLaunchKernelGGL(kern, grid, blk, 0, s, tm->begin[tm->used], tm->end[tm->used], 0, M, Ly, P, nwg);
+        hipExtLaunchKernelGGL(kern, grid, blk, lds, s, tm->begin[tm->used], tm->end[tm->used], 0, M, Ly, P, nwg);
         ++tm->used;
     } else {
-        hipLaunchKernelGGL(kern, grid, blk, 0, s, M, Ly, P, nwg);
+        hipLaunchKernelGGL(kern, grid, blk, lds, s, M, Ly, P, nwg);
     }
 }
 
 template <class DT, int HD>
-static hipError_t launch_pass_t(const DevModel& M, const DevLayer* Ls, const PassArgs& P, int nwg, hipStream_t s,
+static hipError_t launch_pass_t(const DevModel& M, const DevLayer* Ls, PassArgs& P, int nwg, hipStream_t s,
                                 StageTimer* tm) {
+    // Attention without a merge of chunks: a workgroup has all keys that its rows see.  Groups of 4 and 8 heads: up to a run a wave, and
+    // the 64 KB that a compute unit has under way.  us a layer less, 1B shape, 1 row behind 40 / 130 / 260 keys 3.1 / 0.5 / 0.7, 16
+    // rows 3.0 / 3.2 / 2.3 (at 520 keys, more runs than waves, 2.5 more); 8B shape, 8 rows 3.6 behind 40, 0.6 more behind 130.
+    const bool groups = M.G == 4 || M.G == 8;
+    P.whole = 1;
+    for (int i = 0; i < P.n_seg; ++i) {
+        const int keys = P.seg[i].L + P.seg[i].k;
+        P.whole &= groups ? keys <= kWaves * M.bpw * DT::BLOCK_KEYS && keys * HD * 2 * DT::ESZ <= 64 << 10 : keys <= M.chunk;
+    }
+    if (tm && tm->stage == 3) P.whole = 0;                   // the merge is to be timed
+    if (P.whole && groups) {
+        P.packed_units = 0;
+        for (int i = 0; i < P.n_seg; ++i) {
+            P.seg[i].packed0 = P.packed_units;
+            P.packed_units += (M.Hkv + 7) / 8 * 8 * ((P.seg[i].k * M.G + 15) / 16);
+        }
+    }
     const dim3 blk(kThreads);
     const int embed_wgs = (M.d / 16 + 3) / 4 < nwg ? (M.d / 16 + 3) / 4 : nwg;
     const int att_units = P.units;
@@ -1286,7 +1331,7 @@ static hipError_t launch_pass_t(const DevModel& M, const DevLayer* Ls, const Pas
         chunks += P.seg[i].nchunks;
         tiles += P.seg[i].nchunks * ((P.seg[i].k * M.G + 15) / 16);
     }
-    const bool packed = (M.G == 4 || M.G == 8) && attention_packs_rows(DT::HAS_LO, HD, M.G, P.units, (double)tiles / chunks, M.bpw, nwg);
+    const bool packed = groups && (P.whole || attention_packs_rows(DT::HAS_LO, HD, M.G, P.units, (double)tiles / chunks, M.bpw, nwg));
     if (tm) tm->used = 0;
     // A timed stage is launched through the extended launch call, whose two events take the kernel's own
     // begin and end timestamps (no marker packets around it).
@@ -1322,7 +1367,7 @@ static hipError_t launch_pass_t(const DevModel& M, const DevLayer* Ls, const Pas
         else if (M.G == 4) { AMUSD_LAUNCH_SEQ(2, k_attention_g4, att_wgs, blk, (kAttSmemBytes<DT, HD, 4>), l) }
         else if (M.G == 8) { AMUSD_LAUNCH_SEQ(2, k_attention_g8, att_wgs, blk, (kAttSmemBytes<DT, HD, 8>), l) }
         else { AMUSD_LAUNCH_SEQ(2, k_attention, att_wgs, blk, kSmemBytes, l) }
-        AMUSD_LAUNCH_SEQ(3, k_attn_merge, merge_wgs, dim3(64), 0, l)
+        if (!P.whole) { AMUSD_LAUNCH_SEQ(3, k_attn_merge, merge_wgs, dim3(64), 0, l) }
         AMUSD_LAUNCH(4, k_oproj, d_wgs, kSmemBytes, l, nogain)
         AMUSD_LAUNCH(5, k_gateup, gu_wgs, kSmemBytes, l, nogain)
         AMUSD_LAUNCH(6, k_down, (M.split_down == 1 ? 2 * d_wgs : d_wgs), kSmemBytes, l, gain_next)
@@ -1341,8 +1386,7 @@ static hipError_t launch_pass_t(const DevModel& M, const DevLayer* Ls, const Pas
     return hipGetLastError();
 }
 
-hipError_t launch_pass(const DevModel& M, const DevLayer* Ls, const PassArgs& P, int nwg, hipStream_t stream,
-                       StageTimer* tm) {
+hipError_t launch_pass(const DevModel& M, const DevLayer* Ls, PassArgs P, int nwg, hipStream_t stream, StageTimer* tm) {
     if (M.dtype)
         return M.hd == 128 ? launch_pass_t<BF16, 128>(M, Ls, P, nwg, stream, tm)
                            : launch_pass_t<BF16, 64>(M, Ls, P, nwg, stream, tm);

@@ -48,7 +48,7 @@ hipError_t launch_stream_chain(const uint4* buf, size_t buf_words, size_t words_
                                unsigned* fold, hipStream_t stream);
 
 // Enqueues one whole pass (all stages) on the stream.
-hipError_t launch_pass(const DevModel& M, const DevLayer* layers_host, const PassArgs& P, int nwg, hipStream_t stream,
+hipError_t launch_pass(const DevModel& M, const DevLayer* layers_host, PassArgs P, int nwg, hipStream_t stream,
                        StageTimer* timer);
 
 // One prefill pass: P.n rows (tokens in T.tokens) appended at P.L0; greedy tokens of all rows to T.greedy.

@@ -123,6 +123,25 @@ __device__ __forceinline__ void store_gemm_in(void* buf, int k_rows, int m, int 
     }
 }
 
+// four neighbouring columns (col a multiple of 4) of one row
+template <class DT>
+__device__ __forceinline__ void store_gemm_in4(void* buf, int k_rows, int m, int col, v4f x) {
+    const int kb = col / DT::KB, g = (col % DT::KB) / DT::EPL, e = col % DT::EPL;
+    if constexpr (DT::HAS_LO) {
+        uint32_t h[4], l[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            h[i] = bf16_rne(x[i]);
+            l[i] = bf16_rne(x[i] - bf16_to_f32(h[i]));
+        }
+        uint16_t* b = reinterpret_cast<uint16_t*>(buf) + ((size_t)kb * (k_rows <= 8 ? 64 : 128) + g * 16 + m) * 8 + e;
+        *reinterpret_cast<uint2*>(b) = uint2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
+        *reinterpret_cast<uint2*>(b + (k_rows <= 8 ? 8 : 64) * 8) = uint2{l[0] | (l[1] << 16), l[2] | (l[3] << 16)};
+    } else {
+        *reinterpret_cast<v4f*>(reinterpret_cast<float*>(buf) + ((size_t)kb * 64 + g * 16 + m) * 4 + e) = x;
+    }
+}
+
 // Element index of key `pos`, head_dim column `c` in a kv head's key cache.  Keys are kept in the operand
 // order of the score product: [16-key tile][fragment i][lane = g*16 + key%16][EPL], where lane group g owns
 // columns g*hd/4 .. (g+1)*hd/4 and fragment i its i-th run of EPL columns, so a wave fetches one

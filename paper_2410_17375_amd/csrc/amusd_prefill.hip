@@ -934,7 +934,7 @@ __global__ void __launch_bounds__(kThreads) k_pf_attention_unit(DevModel M, DevL
     const size_t q0 = (size_t)rt * 16 * M.qdim * DT::ESZ;
     const size_t slot_frags = (size_t)P.slot * M.Hkv * M.ctx_pad * HD / DT::EPL;
     attention_unit<DT, HD>(M, Ly, reinterpret_cast<const char*>(T.Q_hi) + q0, reinterpret_cast<const char*>(T.Q_lo) + q0, slot_frags,
-                           kvh, c, L, k, 0, T.att_part + (((size_t)t * M.Hkv + kvh) * nch + c) * M.G * kRows * (HD + kPartRow), att_smem);
+                           kvh, c, L, k, 0, PartialOut<HD>{T.att_part + (((size_t)t * M.Hkv + kvh) * nch + c) * M.G * kRows * (HD + kPartRow)}, att_smem);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // a wave must not end while its look-ahead fetch is in flight
 }
 

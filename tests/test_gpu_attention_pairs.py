@@ -25,6 +25,27 @@ def _heads(kv_heads, group, head_dim):
     ("tiny_gqa_fp32", _heads(32, 4, 128), (912,), (2,)), ("tiny_gqa_fp32", _heads(8, 8, 128), (960, 512), (3, 13)),
 ])
 def test_pairs_equal_prompt_rows(name, over, lens, rows):
+    _compare(name, over, lens, rows, max(lens) + 40)
+
+
+# few keys, which a workgroup has all of: up to eight runs and 64 KB of them, one more; runs of several blocks (long contexts that are not
+# used); groups of 1 and 2, one chunk and two
+@pytest.mark.parametrize("name,over,lens,rows,max_ctx", [
+    ("tiny_gqa_bf16", _heads(8, 4, 64), (256,), (1,), 300), ("tiny_gqa_bf16", _heads(8, 4, 64), (256, 16, 48, 136), (8, 1, 2, 5), 300),
+    ("tiny_gqa_bf16", _heads(8, 4, 64), (264, 16), (8, 2), 300), ("tiny_gqa_bf16", _heads(3, 8, 64), (256, 72), (1, 8), 300),
+    ("tiny_gqa_bf16", _heads(16, 4, 64), (200, 256), (8, 7), 4000), ("tiny_gqa_bf16", _heads(8, 4, 128), (128, 64), (8, 3), 200),
+    ("tiny_gqa_bf16", _heads(8, 4, 128), (136,), (1,), 200), ("tiny_gqa_bf16", _heads(16, 8, 128), (128, 48), (3, 8), 3000),
+    ("tiny_gqa_fp32", _heads(8, 4, 64), (128, 32), (13, 3), 200), ("tiny_gqa_fp32", _heads(8, 8, 64), (128, 64), (2, 14), 2000),
+    ("tiny_gqa_fp32", _heads(5, 4, 128), (64, 32), (9, 1), 200), ("tiny_gqa_fp32", _heads(8, 8, 128), (64,), (16,), 700),
+    ("tiny_gqa_fp32", _heads(4, 1, 64), (128, 112), (7, 9), 200), ("tiny_gqa_fp32", _heads(4, 1, 64), (144,), (16,), 200),
+    ("tiny_gqa_fp32", _heads(4, 2, 128), (64, 48), (7, 9), 200), ("tiny_gqa_bf16", _heads(4, 1, 128), (256, 40), (8, 8), 300),
+    ("tiny_gqa_bf16", _heads(4, 2, 64), (128, 40), (8, 1), 300),
+])
+def test_few_keys_equal_prompt_rows(name, over, lens, rows, max_ctx):
+    _compare(name, over, lens, rows, max_ctx)
+
+
+def _compare(name, over, lens, rows, max_ctx):
     torch = pytest.importorskip("torch")
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
@@ -32,7 +53,7 @@ def test_pairs_equal_prompt_rows(name, over, lens, rows):
     from paper_2410_17375_amd.harness import load_model
     shape = SHAPES[name].with_(**over)
     group = 16 if shape.dtype == "fp32" else 8               # rows whose logits a prompt leaves
-    m = load_model(shape, max(lens) + 40, store=WeightStore(shape), max_seqs=len(lens))
+    m = load_model(shape, max_ctx, store=WeightStore(shape), max_seqs=len(lens))
     m.set_option(A.OPT_KEEP_LOGITS, 1)
     want, new = [], []
     for i, (n, k) in enumerate(zip(lens, rows)):
