@@ -342,50 +342,17 @@ struct PfGemm {
     }
 };
 
-// The sums of `ranges` K ranges, PER each, added in order: all loads of a range first, then the additions (one trip to
-// memory per range and two fragments instead of one per sum).
-template <int PER, class G>
-__device__ __forceinline__ void add_shares(G& acc, const float* xch, int ranges) {
-    using Sh = typename G::Shape;
-    constexpr int N = Sh::A * Sh::B, XB = N % 2 == 0 ? 2 : 1;
-    constexpr size_t kFloats = (size_t)Sh::kThreads * N * 4;
-#pragma unroll
-    for (int x0 = 0; x0 < N; x0 += XB) {
-        for (int r = 0; r < ranges; ++r) {
-            uint64_t raw[XB][PER][2];
-#pragma unroll
-            for (int s = 0; s < PER; ++s)
-#pragma unroll
-                for (int x = 0; x < XB; ++x)
-#pragma unroll
-                    for (int h = 0; h < 2; ++h)
-                        raw[x][s][h] = __hip_atomic_load(reinterpret_cast<const uint64_t*>(xch + (r * PER + s) * kFloats + (x0 + x) * (Sh::kThreads * 4) + threadIdx.x * 4) + h,
-                                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-            for (int x = 0; x < XB; ++x) {
-                v4f v = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int s = 0; s < PER; ++s)
-                    v += v4f{__uint_as_float((uint32_t)raw[x][s][0]), __uint_as_float((uint32_t)(raw[x][s][0] >> 32)),
-                             __uint_as_float((uint32_t)raw[x][s][1]), __uint_as_float((uint32_t)(raw[x][s][1] >> 32))};
-                v4f& t = acc.tot[(x0 + x) / Sh::B][(x0 + x) % Sh::B];
-                t = r ? t + v : v;
-            }
-        }
-    }
-}
-
-// Adds the sums that `shares` workgroups have of the same tiles: each writes its own to device memory and counts itself;
-// the one that counts last adds all of them in the order of the slices and goes on (returns true).  per_range: sums per K
-// range (8: one per slice; 1: the range's total).  Nobody waits for anybody.  Relaxed device-scope accesses, counted after
-// every wave has seen its stores acknowledged, as in the verify pass's down projection.
+// Adds the sums that `shares` workgroups have of the same tiles, one per K range: each writes its own to device memory and counts
+// itself; the one that counts last adds all of them in the order of the ranges and goes on (returns true).  Nobody waits for
+// anybody.  Relaxed device-scope accesses, counted after every wave has seen its stores acknowledged, as in the verify pass's
+// down projection.
 template <class G>
-__device__ __forceinline__ bool combine_shares(G& acc, float* xch, int* ticket, int share, int shares, int per_range, char* smem) {
+__device__ __forceinline__ bool combine_shares(G& acc, float* xch, int* ticket, int share, int shares, char* smem) {
     using Sh = typename G::Shape;
-    constexpr int kFloats = Sh::kThreads * Sh::A * Sh::B * 4;
+    constexpr int N = Sh::A * Sh::B, kFloats = Sh::kThreads * N * 4, XB = N % 2 == 0 ? 2 : 1;
     auto at = [&](int sh, int x) { return reinterpret_cast<uint64_t*>(xch + (size_t)sh * kFloats + x * (Sh::kThreads * 4) + threadIdx.x * 4); };
 #pragma unroll
-    for (int x = 0; x < Sh::A * Sh::B; ++x) {
+    for (int x = 0; x < N; ++x) {
         const v4f v = acc.tot[x / Sh::B][x % Sh::B];
         uint64_t* p = at(share, x);
         __hip_atomic_store(p, (uint64_t)__float_as_uint(v.x) | (uint64_t)__float_as_uint(v.y) << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -401,8 +368,23 @@ __device__ __forceinline__ bool combine_shares(G& acc, float* xch, int* ticket, 
     }
     __syncthreads();
     if (!*flag) return false;
-    if (per_range == 1) add_shares<1>(acc, xch, shares);
-    else add_shares<kWaves>(acc, xch, shares / kWaves);
+#pragma unroll
+    for (int x0 = 0; x0 < N; x0 += XB) {                 // all loads of a range and two fragments first, then the additions
+        for (int r = 0; r < shares; ++r) {
+            uint64_t raw[XB][2];
+#pragma unroll
+            for (int x = 0; x < XB; ++x)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) raw[x][h] = __hip_atomic_load(at(r, x0 + x) + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int x = 0; x < XB; ++x) {
+                const v4f v = v4f{__uint_as_float((uint32_t)raw[x][0]), __uint_as_float((uint32_t)(raw[x][0] >> 32)),
+                                  __uint_as_float((uint32_t)raw[x][1]), __uint_as_float((uint32_t)(raw[x][1] >> 32))};
+                v4f& t = acc.tot[(x0 + x) / Sh::B][(x0 + x) % Sh::B];
+                t = r ? t + v : v;
+            }
+        }
+    }
     return true;
 }
 
@@ -681,8 +663,13 @@ __global__ void __launch_bounds__(Sh::kThreads, Sh::kMinWaves) k_pf_gemm(DevMode
                      if constexpr (kPfScaled<STAGE>)
                          if (own_scales) scale_part = scales.sum();
                  });
-    if (shares > 1 && !combine_shares<G>(acc, xch, T.ticket + idx, share, shares, shares == ways ? 1 : kWaves, pf_smem)) return;
-    float* scale_sums = reinterpret_cast<float*>(pf_smem) + 64;    // (combine_shares has its flag in front)
+    if (shares > 1) {                                    // k_pf_add goes on
+        v4f* out = reinterpret_cast<v4f*>(xch + (size_t)share * (Sh::kThreads * A * B * 4)) + threadIdx.x;
+#pragma unroll
+        for (int x = 0; x < A * B; ++x) out[x * Sh::kThreads] = acc.tot[x / B][x % B];
+        return;
+    }
+    float* scale_sums = reinterpret_cast<float*>(pf_smem);
     if constexpr (kPfScaled<STAGE>)
         if (own_scales) {
             scale_sums[threadIdx.x] = scale_part;
@@ -725,6 +712,68 @@ __global__ void __launch_bounds__(Sh::kThreads, Sh::kMinWaves) k_pf_gemm(DevMode
                 T.best_val[(size_t)(cg * Sh::WN + wn) * P.n + row] = best_v[j];
                 T.best_idx[(size_t)(cg * Sh::WN + wn) * P.n + row] = best_i[j];
             }
+        }
+    }
+}
+
+// The rest of a stage whose tiles `shares` workgroups of k_pf_gemm share: a wave adds a fragment's sums up in the order of the slices
+// and finishes it (LM head: the A fragments of a wave there, one after the other, for its best column).  All of a fragment's
+// sums are under way at once.  61 rows of the 8B shape's down projection, 16 slices on 512 workgroups and this: 40 us (43 in the
+// streaming form; 52 where the last workgroup of a tile added them all).
+template <class DT, int STAGE, class Sh>
+__global__ void __launch_bounds__(256) k_pf_add(DevModel M, DevLayer Ly, PrefillBufs T, PfTiles L, PrefillArgs P, const float* gain_next, int shares,
+                                                int total) {
+    constexpr int A = Sh::A, B = Sh::B, WAVES = Sh::WN * Sh::WM, FR = STAGE == kPfLMHead ? A : 1;     // fragments of a wave here
+    constexpr int kPlaces = WAVES * (A / FR) * B;
+    const int x = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+    const int idx = x / kPlaces, place = x % kPlaces;
+    if (idx >= total) return;
+    const int lane = threadIdx.x & 63, m = lane & 15;
+    const int row_groups = (P.n + Sh::kRowTiles * 16 - 1) / (Sh::kRowTiles * 16);
+    int cg, rg;
+    patch_order(idx, L.n / Sh::kTiles, row_groups, cg, rg);
+    const int wave = place / ((A / FR) * B), i0 = place % ((A / FR) * B) / B * FR, j = place % B;
+    const int wn = wave % Sh::WN, wm = wave / Sh::WN, rt = rg * Sh::kRowTiles + wm * B + j;
+    const int* tiles = L.order + cg * Sh::kTiles + wn * A;
+    constexpr size_t kFrags = (size_t)Sh::kThreads * A * B;
+    const v4f* in = reinterpret_cast<const v4f*>(T.xch) + (size_t)idx * shares * kFrags + wave * 64 + lane;
+    const int per = shares >= kWaves ? kWaves : 1;         // sums per K range
+    float best_v = -INFINITY;
+    int best_i = 0x7fffffff;
+#pragma unroll
+    for (int f = 0; f < FR; ++f) {
+        const int tile = __builtin_amdgcn_readfirstlane(tiles[i0 + f]);
+        PfEpilogue<DT, STAGE> epi;
+        epi.fetch(M, T, P, gain_next, tile, rt);
+        if constexpr (kPfScaled<STAGE>) epi.sc = T.rstd[rt * 16 + m];
+        const v4f* at = in + (size_t)((i0 + f) * B + j) * Sh::kThreads;
+        v4f raw[2 * kWaves];
+#pragma unroll
+        for (int s = 0; s < 2 * kWaves; ++s) raw[s] = at[(size_t)(s < shares ? s : shares - 1) * kFrags];
+        v4f sum = v4f{0.f, 0.f, 0.f, 0.f};
+        if (per == 1) {
+            sum = raw[0];
+            if (shares == 2) sum = sum + raw[1];
+        } else {
+#pragma unroll
+            for (int s = 0; s < kWaves; ++s) sum += raw[s];
+            if (shares == 2 * kWaves) {
+                v4f second = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int s = 0; s < kWaves; ++s) second += raw[kWaves + s];
+                sum = sum + second;
+            }
+        }
+        wait_vm<0>();                                      // fillers and rows past the last use nothing of it
+        if (tile >= 0) epi.finish(M, Ly, T, P, tile, rt, sum, best_v, best_i);
+    }
+    if constexpr (STAGE == kPfLMHead) {
+        const int row = rt * 16 + m;
+        keep_better_xor<16>(best_v, best_i);
+        keep_better_xor<32>(best_v, best_i);
+        if (lane < 16 && row < P.n) {
+            T.best_val[(size_t)(cg * Sh::WN + wn) * P.n + row] = best_v;
+            T.best_idx[(size_t)(cg * Sh::WN + wn) * P.n + row] = best_i;
         }
     }
 }
@@ -859,7 +908,7 @@ __global__ void __launch_bounds__(kThreads, 2) k_pf_stream(DevModel M, DevLayer 
     if (shares > 1) {
         __syncthreads();
         float* xch = T.xch + (size_t)idx * shares * (kThreads * F * 4);
-        if (!combine_shares<PfSums<F>>(sum, xch, T.ticket + idx, share, shares, 1, pf_smem)) return;
+        if (!combine_shares<PfSums<F>>(sum, xch, T.ticket + idx, share, shares, pf_smem)) return;
     }
     PfEpilogue<DT, STAGE> epi[F];
 #pragma unroll
@@ -1304,9 +1353,13 @@ static hipError_t launch_pf_gemm_v(const DevModel& M, const DevLayer& Ly, const 
     // unit.  us more for the contraction (k_pf_rstd and its launch take 4.8): 8B shape 61 rows gate/up 64 KiB 2.3, LM head 2.4,
     // 2048 rows QKV 384 KiB 5.3, gate/up 900 KiB 18, LM head 4 MiB 25; 1B shape 509 rows gate/up 64 KiB 1.3, QKV 24 KiB 1.3.
     constexpr double kOwnScaleBytes = 320 << 10;
-    const bool own_scales = (double)grid / T.cus * Sh::kRowTiles * M.d * 4 <= kOwnScaleBytes;
+    const bool own_scales = shares == 1 && (double)grid / T.cus * Sh::kRowTiles * M.d * 4 <= kOwnScaleBytes;
     if (kPfScaled<STAGE> && !own_scales) hipLaunchKernelGGL(k_pf_rstd, dim3((P.n + 15) / 16), dim3(256), 0, s, M, T, P);
     hipLaunchKernelGGL((k_pf_gemm<DT, STAGE, Sh>), dim3(grid), dim3(Sh::kThreads), lds, s, M, Ly, T, L, P, gain, shares, own_scales);
+    if (shares > 1) {
+        const int total = grid / shares, waves = total * Sh::WN * Sh::WM * Sh::B * (STAGE == kPfLMHead ? 1 : Sh::A);
+        hipLaunchKernelGGL((k_pf_add<DT, STAGE, Sh>), dim3((waves + 3) / 4), dim3(256), 0, s, M, Ly, T, L, P, gain, shares, total);
+    }
     return hipSuccess;
 }
 
@@ -1359,8 +1412,8 @@ using PfSmall = PfShape<2, 2, 2, 2, 6>;   // 64 x 64
 // rounds x (K blocks x time of a block + a workgroup's beginning and end), plus what the sharing costs.  The times were fitted
 // to measurements of all choices on the 8B and 1B shapes at 17 to 2048 rows: 0.82 us per K block of a large tile; 0.30 and
 // 0.20 us of the smaller ones, 0.50 and 0.35 when two share a compute unit; 12, 7.5 and 6 us at the ends, 4 more for the large
-// tile's rotations; sharing 1.6 us per workgroup of a tile (its sums are written, counted and read back through the memory
-// side) and its bytes at 5 TB/s each way.  The choice is within 6 % of the best at 166 of 170 sizes there, 12 % from it at
+// tile's rotations; sharing 1.6 us per workgroup of a tile (k_pf_add and its launch) and its
+// bytes at 5 TB/s each way.  The choice is within 6 % of the best at 166 of 170 sizes there, 12 % from it at
 // worst.  For instance at 250 rows of the 8B shape gate/up takes 114 us on 224 large tiles and 150 on 896 of the middle ones, at
 // 128 rows 97 and 86.  Sharing all slices is for few tiles and a long contraction (mostly the streaming form has those).
 struct PfPlan { int shape, shares; };
@@ -1378,7 +1431,7 @@ static PfPlan plan_pf_gemm(const DevModel& M, const PrefillBufs& T, const PfTile
             const Shape& h = shapes[s];
             const size_t tiles = (size_t)group_tiles(sets[stage], h.tiles).n / h.tiles * ((n + h.rows - 1) / h.rows);
             const size_t sum_bytes = tiles * h.tiles * h.rows * 16 * 4 * shares;
-            if (shares > 1 && (tiles > (size_t)kPfTickets || sum_bytes > T.xch_bytes)) continue;
+            if (shares > 1 && sum_bytes > T.xch_bytes) continue;
             const size_t wgs = tiles * shares, round = (size_t)T.cus * h.per_cu, rest = wgs % round;
             const double ends = h.ends + (s == 0 && stage == kPfQKV ? 4. : 0.), blocks = (double)kblocks / shares;
             const double full = blocks * h.full + ends, alone = blocks * h.alone + ends;
@@ -1395,6 +1448,21 @@ static PfPlan plan_pf_gemm(const DevModel& M, const PrefillBufs& T, const PfTile
 template <class DT, int STAGE>
 static hipError_t launch_pf_gemm(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PfTileSet* tiles, const PrefillArgs& P,
                                  const float* gain, hipStream_t s, int* parts = nullptr) {
+    // The down projection of one row group in all its 16 slices, where those are a workgroup a compute unit and no more than one round:
+    // each workgroup then loads a few hundred KB, where the streaming form's 1.8 MB are what its time is.  us per prompt of 4 layers,
+    // streaming / so: 8B shape 40 rows 678 / 654, 61 rows 659 / 647, 120 rows (256 x 128 tiles) 925 / 890 (17 rows: 4.7 a layer more);
+    // 16 layers of 1B, 35 rows 1108 / 1064, 61 rows 1134 / 1072 (120 rows: 128 workgroups, 1 a layer more).
+    if constexpr (STAGE == kPfDown)
+        if (M.split_down) {
+            auto one_round = [&](auto shape, int per_cu) {
+                using Sh = decltype(shape);
+                const size_t wgs = (size_t)group_tiles(tiles[STAGE], Sh::kTiles).n / Sh::kTiles * 2 * kWaves;
+                return P.n <= Sh::kRowTiles * 16 && wgs >= (size_t)T.cus && wgs <= (size_t)T.cus * per_cu &&
+                       wgs * Sh::kTiles * Sh::kRowTiles * 1024 <= T.xch_bytes;
+            };
+            if (P.n > 32 && one_round(PfMid(), 2)) return launch_pf_gemm_v<DT, STAGE, PfMid>(M, Ly, T, tiles, P, gain, s, parts, 2 * kWaves);
+            if (P.n > 64 && one_round(PfLarge(), 1)) return launch_pf_gemm_v<DT, STAGE, PfLarge>(M, Ly, T, tiles, P, gain, s, parts, 2 * kWaves);
+        }
     if constexpr (STAGE != kPfLMHead) {      // (its partial maxima would outgrow best_val, and it gains nothing)
         hipError_t e;
         if (launch_pf_stream<DT, STAGE>(M, Ly, T, tiles, P, gain, s, e)) return e;
