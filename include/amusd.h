@@ -77,7 +77,8 @@ enum {
 
 /* Options for amusd_set_option. */
 enum {
-    AMUSD_OPT_KEEP_LOGITS = 0, /* 1: each pass also stores its fp32 logits (test hook), default 0 */
+    AMUSD_OPT_KEEP_LOGITS = 0, /* 1: each pass also stores its fp32 logits (test hook), default 0.  The first time it takes a
+                                  pinned host block of at most 4 MB, which the model keeps */
     AMUSD_OPT_TIME_STAGE = 2,   /* AMUSD_STAGE_* to bracket with HIP events in every pass, -1: none (default) */
     AMUSD_OPT_PREFILL_WORKSPACE = 3 /* 0: the prefill workspace (amusd_prefill) is given back, or not taken by finalize;
                                        1: taken (default; HIP error if there is no memory for it) */

@@ -346,6 +346,28 @@ int run_pass(amusd_model* m, const SegReq* segs, int n_seg, bool force_accept, b
 
 constexpr size_t kExportBytes = 4u << 20;     // the 16 rows of 65536 columns; more comes in several stretches
 
+// Takes the pinned block for logits: the first time that a model is to keep any.  Without the memory for it logits reach the host
+// by hipMemcpy.  Coherent: the host reads flags and rows while the kernel that writes them runs.
+void take_export(amusd_model* m) {
+    std::lock_guard<std::mutex> mine(m->export_mutex);
+    int device = -1;
+    if (m->export_host || hipGetDevice(&device) != hipSuccess) return;
+    if (device != m->device && hipSetDevice(m->device) != hipSuccess) return;
+    const size_t bytes = std::min(kExportBytes, (size_t)kRows * m->cfg.vocab * 4);
+    const size_t flags = (bytes + kExportChunk - 1) / kExportChunk * kExportFlagStep * sizeof(int);
+    void *host = nullptr, *dev = nullptr;
+    if (hipHostMalloc(&host, bytes + flags, hipHostMallocCoherent) == hipSuccess && hipHostGetDevicePointer(&dev, host, 0) == hipSuccess) {
+        std::memset(host, 0, bytes + flags);      // (all of it: pages that the host has never touched cost the first logits 250 us)
+        m->export_bytes = bytes;
+        m->dm.export_host = m->dm_static.export_host = static_cast<char*>(dev);
+        m->export_host = static_cast<char*>(host);
+    } else {
+        if (host) (void)hipHostFree(host);
+        (void)hipGetLastError();
+    }
+    if (device != m->device) (void)hipSetDevice(device);
+}
+
 int* export_flags(const amusd_model* m) { return reinterpret_cast<int*>(m->export_host + m->export_bytes); }
 
 // Device memory to memory of the caller's, through the model's pinned block: the device fills it chunk by chunk, the host
@@ -653,22 +675,6 @@ int amusd_model_create(const amusd_config* cfg, void* hip_stream, amusd_model** 
         if (hipHostGetDevicePointer(&dev, m->hstage, 0) != hipSuccess)
             return bail(fail(AMUSD_E_HIP, "device address of the pinned result block"));
         D.res = reinterpret_cast<PassResult*>(dev);
-    }
-    // not needed either: without it logits reach the host by hipMemcpy
-    m->export_bytes = std::min(kExportBytes, (size_t)kRows * V * 4);
-    {
-        const size_t flags = (m->export_bytes + kExportChunk - 1) / kExportChunk * kExportFlagStep * sizeof(int);
-        if (hipHostMalloc(reinterpret_cast<void**>(&m->export_host), m->export_bytes + flags, hipHostMallocDefault) == hipSuccess) {
-            // (all of it: pages that the host has never touched cost the first logits 250 us)
-            std::memset(m->export_host, 0, m->export_bytes + flags);
-            void* dev = nullptr;
-            if (hipHostGetDevicePointer(&dev, m->export_host, 0) != hipSuccess)
-                return bail(fail(AMUSD_E_HIP, "device address of the pinned logits block"));
-            D.export_host = static_cast<char*>(dev);
-        } else {
-            m->export_host = nullptr;
-            (void)hipGetLastError();
-        }
     }
     if (hipEventCreate(&m->ev0) != hipSuccess || hipEventCreate(&m->ev1) != hipSuccess)
         return bail(fail(AMUSD_E_HIP, "event creation"));
@@ -1045,7 +1051,10 @@ int amusd_get_next(const amusd_model* m, int32_t* token) { return amusd_seq_get_
 int amusd_set_option(amusd_model* m, int32_t option, int32_t value) {
     if (!m) return fail(AMUSD_E_ARG, "null model");
     switch (option) {
-        case AMUSD_OPT_KEEP_LOGITS: m->keep_logits = value != 0; return AMUSD_OK;
+        case AMUSD_OPT_KEEP_LOGITS:
+            if (value) take_export(m);
+            m->keep_logits = value != 0;
+            return AMUSD_OK;
         case AMUSD_OPT_TIME_STAGE: {
             if (value < -1 || value >= AMUSD_STAGE_COUNT) return fail(AMUSD_E_ARG, "unknown stage");
             if (value >= 0 && m->tev_begin.empty()) {

@@ -1,0 +1,168 @@
+// The library's host side on a stand-in for the HIP runtime: memory is the host's, kernels are written down with their grids and
+// arguments and not run (except the copy of logits to the host, which is done here).  usage: host_test SCENARIO
+#include "../../include/amusd.h"
+#include "../../paper_2410_17375_amd/csrc/amusd_prefill.hip"
+
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <string>
+
+using namespace amusd;
+
+#define CHECK(cond)                                                             \
+    do {                                                                        \
+        if (!(cond)) {                                                          \
+            std::printf("line %d: %s (%s)\n", __LINE__, #cond, amusd_last_error()); \
+            std::exit(1);                                                       \
+        }                                                                       \
+    } while (0)
+
+// ---------------------------------------------------------------- the stand-in
+struct Launch {
+    std::string name;
+    dim3 grid;
+    PassArgs pass;
+    PrefillArgs prompt;
+};
+struct Pinned {
+    size_t bytes;
+    unsigned flags;
+};
+static std::vector<Launch> launches;
+static std::map<void*, Pinned> pinned;
+static size_t refuse_pinned = SIZE_MAX;      // blocks of this size and more find no memory
+static int copies = 0;                       // hipMemcpy to the host
+static int current_device = 0, pinned_device = -1;
+static std::map<const void*, std::string>& names() {
+    static auto& n = *new std::map<const void*, std::string>();
+    return n;
+}
+static bool has(const std::string& name, const char* kernel) { return name.find(std::to_string(std::strlen(kernel)) + kernel) != std::string::npos; }
+static int count(const char* kernel) {
+    int n = 0;
+    for (const Launch& l : launches) n += has(l.name, kernel);
+    return n;
+}
+
+extern "C" {
+void** __hipRegisterFatBinary(const void*) { return nullptr; }
+void __hipUnregisterFatBinary(void**) {}
+void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
+void __hipRegisterFunction(void**, const void* host, char*, const char* name, unsigned, uint3*, uint3*, dim3*, dim3*, int*) { names()[host] = name; }
+static thread_local struct { dim3 grid, block; size_t lds; hipStream_t stream; } config;
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, hipStream_t stream) {
+    config = {grid, block, lds, stream};
+    return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipStream_t* stream) {
+    *grid = config.grid; *block = config.block; *lds = config.lds; *stream = config.stream;
+    return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** args, size_t, hipStream_t) {
+    Launch l{names()[f], grid, {}, {}};
+    if (has(l.name, "k_accept")) l.pass = *static_cast<PassArgs*>(args[1]);
+    if (has(l.name, "k_pf_greedy")) l.prompt = *static_cast<PrefillArgs*>(args[2]);
+    if (has(l.name, "k_export")) {
+        const size_t bytes = *static_cast<size_t*>(args[4]);
+        std::memcpy(*static_cast<char**>(args[0]), *static_cast<const char**>(args[3]), bytes);
+        for (size_t c = 0; c * kExportChunk < bytes; ++c) (*static_cast<int**>(args[1]))[c * kExportFlagStep] = *static_cast<int*>(args[2]);
+    }
+    launches.push_back(l);
+    return hipSuccess;
+}
+hipError_t hipExtLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t lds, hipStream_t s, hipEvent_t, hipEvent_t, int) {
+    return hipLaunchKernel(f, grid, block, args, lds, s);
+}
+hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
+hipError_t hipMalloc(void** p, size_t bytes) { return (*p = std::calloc(1, bytes)) ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipFree(void* p) { std::free(p); return hipSuccess; }
+hipError_t hipHostMalloc(void** p, size_t bytes, unsigned flags) {
+    if (bytes >= refuse_pinned) return hipErrorOutOfMemory;
+    *p = std::calloc(1, bytes);
+    pinned[*p] = Pinned{bytes, flags};
+    pinned_device = current_device;
+    return hipSuccess;
+}
+hipError_t hipHostFree(void* p) { pinned.erase(p); std::free(p); return hipSuccess; }
+hipError_t hipHostGetDevicePointer(void** dev, void* host, unsigned) { *dev = host; return hipSuccess; }
+hipError_t hipGetSymbolAddress(void** p, const void* symbol) { *p = const_cast<void*>(symbol); return hipSuccess; }
+hipError_t hipMemcpy(void* dst, const void* src, size_t bytes, hipMemcpyKind kind) {
+    copies += kind == hipMemcpyDeviceToHost;
+    std::memcpy(dst, src, bytes);
+    return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void* dst, const void* src, size_t bytes, hipMemcpyKind, hipStream_t) { std::memcpy(dst, src, bytes); return hipSuccess; }
+hipError_t hipMemsetAsync(void* dst, int value, size_t bytes, hipStream_t) { std::memset(dst, value, bytes); return hipSuccess; }
+hipError_t hipGetDevice(int* device) { *device = current_device; return hipSuccess; }
+hipError_t hipSetDevice(int device) { current_device = device; return hipSuccess; }
+hipError_t hipGetDeviceCount(int* n) { *n = 2; return hipSuccess; }
+hipError_t hipGetDeviceProperties(hipDeviceProp_t* p, int) { *p = hipDeviceProp_t{}; p->multiProcessorCount = 256; return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t* e) { *e = nullptr; return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 1.f; return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamQuery(hipStream_t) { return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+const char* hipGetErrorString(hipError_t) { return "error"; }
+}
+
+static amusd_model* model(amusd_config c) {
+    static std::vector<char> zeros(64 << 20);
+    amusd_model* m = nullptr;
+    CHECK(amusd_model_create(&c, nullptr, &m) == AMUSD_OK);
+    for (int id = 0; id < AMUSD_T_COUNT; ++id)
+        for (int l = 0; l < (id <= AMUSD_T_FINAL_NORM ? 1 : c.n_layers); ++l) CHECK(amusd_model_set_tensor(m, id, l, zeros.data(), 0) == AMUSD_OK);
+    CHECK(amusd_model_finalize(m) == AMUSD_OK);
+    return m;
+}
+static amusd_config tiny(int vocab, int max_ctx) {
+    return amusd_config{2, 64, 8, 2, 64, 64, vocab, max_ctx, 16, AMUSD_DTYPE_BF16, 1e4f, 1e-5f, 2};
+}
+static size_t largest_pinned() {
+    size_t n = 0;
+    for (const auto& p : pinned) n = std::max(n, p.second.bytes);
+    return n;
+}
+
+// The pinned block that logits go through is for models that keep logits.
+static void logits_block() {
+    constexpr int kVocab = 65552;                 // 16 rows are 4 MB and a bit
+    amusd_model* m = model(tiny(kVocab, 256));
+    std::vector<int32_t> toks(16, 1);
+    std::vector<float> out(16 * kVocab, 7.f);
+    CHECK(largest_pinned() < 64 << 10);
+    CHECK(amusd_prefill(m, toks.data(), 8, nullptr) == AMUSD_OK);
+    CHECK(amusd_set_option(m, AMUSD_OPT_KEEP_LOGITS, 0) == AMUSD_OK && largest_pinned() < 64 << 10);
+    current_device = 1;                           // the calling thread's; the block is for the model's
+    CHECK(amusd_set_option(m, AMUSD_OPT_KEEP_LOGITS, 1) == AMUSD_OK && current_device == 1 && pinned_device == 0);
+    CHECK(largest_pinned() >= 4 << 20 && largest_pinned() < (4 << 20) + (64 << 10));
+    const size_t blocks = pinned.size();
+    for (const auto& p : pinned) CHECK(p.second.bytes < 4 << 20 || p.second.flags == hipHostMallocCoherent);
+    CHECK(amusd_set_option(m, AMUSD_OPT_KEEP_LOGITS, 1) == AMUSD_OK && pinned.size() == blocks);
+    CHECK(amusd_prefill(m, toks.data(), 16, nullptr) == AMUSD_OK);
+    CHECK(amusd_get_logits(m, out.data(), 8) == AMUSD_OK && copies == 1);      // another device's thread: a plain copy
+    current_device = 0;
+    int32_t n, next;
+    CHECK(amusd_verify(m, amusd_kv_len(m), toks.data(), 16, &n, &next) == AMUSD_OK);
+    CHECK(amusd_get_logits(m, out.data(), 16) == AMUSD_OK && copies == 1 && count("k_export") == 2);
+    for (float x : out) CHECK(x == 0.f);
+    CHECK(amusd_model_free(m) == AMUSD_OK);
+    refuse_pinned = 1 << 20;                      // no memory for the block: plain copies
+    m = model(tiny(kVocab, 256));
+    CHECK(amusd_set_option(m, AMUSD_OPT_KEEP_LOGITS, 1) == AMUSD_OK);
+    CHECK(amusd_prefill(m, toks.data(), 8, nullptr) == AMUSD_OK);
+    CHECK(amusd_get_logits(m, out.data(), 8) == AMUSD_OK && copies == 2 && count("k_export") == 2);
+    CHECK(amusd_model_free(m) == AMUSD_OK);
+    CHECK(pinned.empty());
+}
+
+int main(int argc, char** argv) {
+    const std::string scenario = argc > 1 ? argv[1] : "";
+    if (scenario == "logits_block") logits_block();
+    else return 2;
+    std::printf("OK\n");
+    return 0;
+}
