@@ -255,7 +255,7 @@ hipError_t g_cfg_err = hipSuccess;
 
 // Logits up to this size go to the host with the pass that makes them, next to its last kernel's own work.  us a call with its
 // logits fetched, so / when they are asked for: tiny draft step (16 KB) 70 / 77, 1B draft step (125 KB) 714 / 722, 333 rows of the tiny
-// model (208 KB) 162 / 171.
+// model (208 KB) 162 / 171.  A pass whose logits are kept and then not asked for takes 1.1 us more so (its last kernel 5.1 for 4.0).
 constexpr size_t kExportWithPass = 256 << 10;
 int export_with_pass(const amusd_model* m, int rows) {
     const size_t bytes = (size_t)rows * m->cfg.vocab * 4;
@@ -263,8 +263,9 @@ int export_with_pass(const amusd_model* m, int rows) {
 }
 
 // Runs one pass: segment i feeds segs[i].k tokens of sequence segs[i].seq at cache length segs[i].L.
+// last: its logits can be asked for (not those of a prompt's earlier passes).
 // Everything is already validated (distinct sequences, lengths, capacity, tokens, row total).
-int run_pass(amusd_model* m, const SegReq* segs, int n_seg, bool force_accept, bool use_static = false) {
+int run_pass(amusd_model* m, const SegReq* segs, int n_seg, bool force_accept, bool use_static = false, bool last = true) {
     HostStage* h = m->hstage;
     if (use_static) {
         // The array keeps what the last call on this GPU left in it.  A pass reads only what it has written itself
@@ -313,7 +314,7 @@ int run_pass(amusd_model* m, const SegReq* segs, int n_seg, bool force_accept, b
     for (int i = n_seg; i < kMaxSegs; ++i) P.seg[i].packed0 = INT32_MAX;
     P.force_accept = force_accept ? 1 : 0;
     P.keep_logits = m->keep_logits ? 1 : 0;
-    P.export_bytes = export_with_pass(m, rows);
+    P.export_bytes = last ? export_with_pass(m, rows) : 0;
     m->exported = 0;
     HIP_TRY(hipEventRecord(m->ev0, m->stream));
     HIP_TRY(launch_pass(D, m->layers_host.data(), P, m->nwg, m->stream, m->timer.stage >= 0 ? &m->timer : nullptr));
@@ -492,10 +493,11 @@ int take_prefill(amusd_model* m) {
 }
 
 // One prefill pass: n tokens of sequence seq appended at cache length L, all of them kept.  Of its rows the last `tail`
-// are what amusd_get_logits and amusd_get_greedy report.  Everything is already validated.
-int run_prefill(amusd_model* m, int seq, int L, const int32_t* tokens, int n, int tail) {
+// are what amusd_get_logits and amusd_get_greedy report.  last: of the prompt's passes, the one whose logits can be asked for.
+// Everything is already validated.
+int run_prefill(amusd_model* m, int seq, int L, const int32_t* tokens, int n, int tail, bool last) {
     HostStage* h = m->hstage;
-    const PrefillArgs P{n, L, seq, m->keep_logits ? n - tail : n, export_with_pass(m, tail)};
+    const PrefillArgs P{n, L, seq, m->keep_logits ? n - tail : n, last ? export_with_pass(m, tail) : 0};
     m->exported = 0;
     std::memcpy(m->pf_host, tokens, (size_t)n * 4);
     HIP_TRY(hipEventRecord(m->ev0, m->stream));
@@ -516,9 +518,9 @@ int run_prefill(amusd_model* m, int seq, int L, const int32_t* tokens, int n, in
     return AMUSD_OK;
 }
 
-int run_pass(amusd_model* m, int seq, int L, const int32_t* tokens, int k, bool force_accept) {
+int run_pass(amusd_model* m, int seq, int L, const int32_t* tokens, int k, bool force_accept, bool last) {
     const SegReq r{seq, L, tokens, k};
-    return run_pass(m, &r, 1, force_accept);
+    return run_pass(m, &r, 1, force_accept, false, last);
 }
 
 int check_tokens(const amusd_model* m, const int32_t* t, int n) {
@@ -885,7 +887,7 @@ int amusd_seq_prefill(amusd_model* m, int32_t seq, const int32_t* tokens, int32_
         for (int s = 0, k; s < n; s += k) {
             k = n - s < per ? n - s : per;
             if (n - s - k > 0 && n - s - k < tail) k -= kRows;
-            if ((rc = run_prefill(m, seq, q.kv_len, tokens + s, k, tail))) {
+            if ((rc = run_prefill(m, seq, q.kv_len, tokens + s, k, tail, s + k == n))) {
                 q.kv_len = len_before;
                 q.p_next = next_before;
                 return rc;
@@ -897,7 +899,7 @@ int amusd_seq_prefill(amusd_model* m, int32_t seq, const int32_t* tokens, int32_
     use.unlock();
     for (int s = 0; s < n; s += chunk) {
         const int k = n - s < chunk ? n - s : chunk;
-        if ((rc = run_pass(m, seq, q.kv_len, tokens + s, k, true))) {
+        if ((rc = run_pass(m, seq, q.kv_len, tokens + s, k, true, s + k == n))) {
             q.kv_len = len_before;          // the passes that succeeded are dropped again: an O(1) truncation
             q.p_next = next_before;
             return rc;

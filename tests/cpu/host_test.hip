@@ -159,9 +159,38 @@ static void logits_block() {
     CHECK(pinned.empty());
 }
 
+// Of a prompt's stretches only the last one's logits can be asked for: no other's go to the host.
+static void logits_of_stretches() {
+    amusd_model* m = model(tiny(512, 6000));
+    std::vector<int32_t> toks(5000, 1);
+    CHECK(amusd_set_option(m, AMUSD_OPT_KEEP_LOGITS, 1) == AMUSD_OK);
+    CHECK(amusd_prefill(m, toks.data(), 5000, nullptr) == AMUSD_OK);
+    std::vector<int> sent;
+    int last = 0;
+    for (const Launch& l : launches)
+        if (has(l.name, "k_pf_greedy")) {
+            sent.push_back(l.prompt.export_bytes);
+            last = l.prompt.n;
+            CHECK((int)l.grid.x == (l.prompt.n + 15) / 16 + export_wgs(l.prompt.export_bytes, 512));
+        }
+    CHECK((sent == std::vector<int>{0, 0, 8 * 512 * 4}) && last < 2048);
+    std::vector<float> out(8 * 512);
+    CHECK(amusd_get_logits(m, out.data(), 8) == AMUSD_OK && copies == 0 && count("k_export") == 0);
+    CHECK(amusd_set_option(m, AMUSD_OPT_PREFILL_WORKSPACE, 0) == AMUSD_OK);      // the same prompt in verify passes
+    launches.clear();
+    sent.clear();
+    CHECK(amusd_kv_rollback(m, 0) == AMUSD_OK && amusd_prefill(m, toks.data(), 19, nullptr) == AMUSD_OK);
+    for (const Launch& l : launches)
+        if (has(l.name, "k_accept")) sent.push_back(l.pass.export_bytes);
+    CHECK((sent == std::vector<int>{0, 0, 3 * 512 * 4}));
+    CHECK(amusd_get_logits(m, out.data(), 3) == AMUSD_OK && copies == 0 && count("k_export") == 0);
+    CHECK(amusd_model_free(m) == AMUSD_OK);
+}
+
 int main(int argc, char** argv) {
     const std::string scenario = argc > 1 ? argv[1] : "";
     if (scenario == "logits_block") logits_block();
+    else if (scenario == "logits_of_stretches") logits_of_stretches();
     else return 2;
     std::printf("OK\n");
     return 0;
