@@ -1338,6 +1338,12 @@ void prefill_tile_orders(const DevModel& M, int stage, int nwg, std::vector<int>
 
 static const PfTiles& group_tiles(const PfTileSet& set, int size) { return set.groups[__builtin_ctz(size)]; }
 
+// What workgroups that share tiles write of their sums, `fragments` each (T.xch holds T.xch_bytes).  Who chooses to share looks at it
+// first; a launch that would go past the buffer is refused all the same.
+static size_t shared_bytes(size_t workgroups, size_t fragments) { return workgroups * fragments * 1024; }
+// .. a workgroup of the streaming form: a slice's sums are spread over its waves
+static constexpr size_t stream_fragments(int nt, int rt) { return (size_t)(nt * rt + kWaves - 1) / kWaves * kWaves; }
+
 template <class DT, int STAGE, class Sh>
 static hipError_t launch_pf_gemm_v(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PfTileSet* tiles, const PrefillArgs& P,
                                    const float* gain, hipStream_t s, int* parts, int shares) {
@@ -1348,6 +1354,7 @@ static hipError_t launch_pf_gemm_v(const DevModel& M, const DevLayer& Ly, const 
     const PfTiles& L = group_tiles(tiles[STAGE], Sh::kTiles);
     const int groups = L.n / Sh::kTiles;
     const int grid = groups * ((P.n + Sh::kRowTiles * 16 - 1) / (Sh::kRowTiles * 16)) * shares;
+    if (shares > 1 && shared_bytes(grid, Sh::kTiles * Sh::kRowTiles) > T.xch_bytes) return hipErrorInvalidValue;
     if (parts) *parts = groups * Sh::WN;
     // Its workgroups take 1 / rms of their rows themselves while they read less than this of the sums of squares per compute
     // unit.  us more for the contraction (k_pf_rstd and its launch take 4.8): 8B shape 61 rows gate/up 64 KiB 2.3, LM head 2.4,
@@ -1371,9 +1378,9 @@ static hipError_t launch_pf_stream_v(const DevModel& M, const DevLayer& Ly, cons
                                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (set != hipSuccess) return set;
     const PfTiles& L = group_tiles(tiles[STAGE], NT);
-    const int groups = L.n / NT;
-    hipLaunchKernelGGL((k_pf_stream<DT, STAGE, NT, RT, D>), dim3(groups * ((P.n + RT * 16 - 1) / (RT * 16)) * shares), dim3(kThreads), lds, s,
-                       M, Ly, T, L, P, gain, shares);
+    const int wgs = L.n / NT * ((P.n + RT * 16 - 1) / (RT * 16));
+    if (shares > 1 && (wgs > kPfTickets || shared_bytes((size_t)wgs * shares, stream_fragments(NT, RT)) > T.xch_bytes)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_pf_stream<DT, STAGE, NT, RT, D>), dim3(wgs * shares), dim3(kThreads), lds, s, M, Ly, T, L, P, gain, shares);
     return hipSuccess;
 }
 
@@ -1393,8 +1400,7 @@ static bool launch_pf_stream(const DevModel& M, const DevLayer& Ly, const Prefil
     const int nt = round(1, 2) ? 1 : round(2, 2) ? 2 : round(4, 2) ? 4 : P.n <= 32 && round(8, 2) ? 8 : 4;
     const int rt = round(nt, 2) ? 2 : 4;
     if (!round(nt, rt)) return false;
-    const size_t sums = (size_t)wgs(nt, rt) * shares * (kThreads * ((nt * rt + kWaves - 1) / kWaves) * 16);
-    if (wgs(nt, rt) > kPfTickets || sums > T.xch_bytes) shares = 1;
+    if (wgs(nt, rt) > kPfTickets || shared_bytes((size_t)wgs(nt, rt) * shares, stream_fragments(nt, rt)) > T.xch_bytes) shares = 1;
     e = nt == 1 ? launch_pf_stream_v<DT, STAGE, 1, 2, 8>(M, Ly, T, tiles, P, gain, s, shares)
       : nt == 2 ? launch_pf_stream_v<DT, STAGE, 2, 2, 6>(M, Ly, T, tiles, P, gain, s, shares)
       : nt == 8 ? launch_pf_stream_v<DT, STAGE, 8, 2, 2>(M, Ly, T, tiles, P, gain, s, shares)
@@ -1430,7 +1436,7 @@ static PfPlan plan_pf_gemm(const DevModel& M, const PrefillBufs& T, const PfTile
         for (int shares : {1, ways, ways * kWaves}) {
             const Shape& h = shapes[s];
             const size_t tiles = (size_t)group_tiles(sets[stage], h.tiles).n / h.tiles * ((n + h.rows - 1) / h.rows);
-            const size_t sum_bytes = tiles * h.tiles * h.rows * 16 * 4 * shares;
+            const size_t sum_bytes = shared_bytes(tiles * shares, h.tiles * h.rows / 16);
             if (shares > 1 && sum_bytes > T.xch_bytes) continue;
             const size_t wgs = tiles * shares, round = (size_t)T.cus * h.per_cu, rest = wgs % round;
             const double ends = h.ends + (s == 0 && stage == kPfQKV ? 4. : 0.), blocks = (double)kblocks / shares;
@@ -1458,7 +1464,7 @@ static hipError_t launch_pf_gemm(const DevModel& M, const DevLayer& Ly, const Pr
                 using Sh = decltype(shape);
                 const size_t wgs = (size_t)group_tiles(tiles[STAGE], Sh::kTiles).n / Sh::kTiles * 2 * kWaves;
                 return P.n <= Sh::kRowTiles * 16 && wgs >= (size_t)T.cus && wgs <= (size_t)T.cus * per_cu &&
-                       wgs * Sh::kTiles * Sh::kRowTiles * 1024 <= T.xch_bytes;
+                       shared_bytes(wgs, Sh::kTiles * Sh::kRowTiles) <= T.xch_bytes;
             };
             if (P.n > 32 && one_round(PfMid(), 2)) return launch_pf_gemm_v<DT, STAGE, PfMid>(M, Ly, T, tiles, P, gain, s, parts, 2 * kWaves);
             if (P.n > 64 && one_round(PfLarge(), 1)) return launch_pf_gemm_v<DT, STAGE, PfLarge>(M, Ly, T, tiles, P, gain, s, parts, 2 * kWaves);

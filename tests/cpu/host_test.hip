@@ -187,10 +187,43 @@ static void logits_of_stretches() {
     CHECK(amusd_model_free(m) == AMUSD_OK);
 }
 
+// Workgroups that share tiles write their sums to a buffer: a launch that would go past its end, or past the counters, is refused.
+static void shared_sums() {
+    DevModel M{};
+    M.dtype = AMUSD_DTYPE_BF16;
+    M.d = 4096;
+    M.F = 14336;
+    M.split_down = 2;
+    PfTileSet tiles[kPfStages];
+    std::vector<int> orders;
+    prefill_tile_orders(M, kPfDown, 256, orders, tiles[kPfDown]);
+    PrefillBufs T{};
+    T.cus = 256;
+    const PrefillArgs P{61, 0, 0, 61, 0};
+    auto gemm = [&](int shares) { return launch_pf_gemm_v<BF16, kPfDown, PfMid>(M, DevLayer{}, T, tiles, P, nullptr, nullptr, nullptr, shares); };
+    T.xch_bytes = (size_t)4096 * 64 * 4 * 16 - 1;          // 64 rows of 4096 columns, 16 slices
+    CHECK(gemm(16) == hipErrorInvalidValue && launches.empty());
+    CHECK(gemm(2) == hipSuccess && count("k_pf_gemm") == 1 && count("k_pf_add") == 1);
+    ++T.xch_bytes;
+    CHECK(gemm(16) == hipSuccess && count("k_pf_gemm") == 2 && count("k_pf_add") == 2);
+    T.xch_bytes = 0;
+    CHECK(gemm(1) == hipSuccess && count("k_pf_gemm") == 3 && count("k_pf_add") == 2);
+    auto stream = [&](int shares) { return launch_pf_stream_v<BF16, kPfDown, 4, 2, 4>(M, DevLayer{}, T, tiles, P, nullptr, nullptr, shares); };
+    T.xch_bytes = (size_t)4096 * 64 * 4 * 2 - 1;
+    CHECK(stream(2) == hipErrorInvalidValue && stream(1) == hipSuccess && count("k_pf_stream") == 1);
+    ++T.xch_bytes;
+    CHECK(stream(2) == hipSuccess && count("k_pf_stream") == 2);
+    PrefillArgs many = P;                                   // more tiles than counters
+    many.n = (kPfTickets / 64 + 1) * 32;
+    T.xch_bytes = SIZE_MAX;
+    CHECK((launch_pf_stream_v<BF16, kPfDown, 4, 2, 4>(M, DevLayer{}, T, tiles, many, nullptr, nullptr, 2) == hipErrorInvalidValue));
+}
+
 int main(int argc, char** argv) {
     const std::string scenario = argc > 1 ? argv[1] : "";
     if (scenario == "logits_block") logits_block();
     else if (scenario == "logits_of_stretches") logits_of_stretches();
+    else if (scenario == "shared_sums") shared_sums();
     else return 2;
     std::printf("OK\n");
     return 0;
