@@ -292,7 +292,8 @@ int amusd_last_pass_ms(amusd_model *m, float *ms);
 
 /* Accumulated device time (HIP events on the model's stream, one pair around
  * every launch of the stage selected with AMUSD_OPT_TIME_STAGE) and number of
- * launches since the option was last set.  Also reports the algorithmic bytes
+ * launches since the option was last set (0 launches of a stage that the passes
+ * did without: keys that one workgroup has all of need no ATTN_MERGE).  Also reports the algorithmic bytes
  * one such launch reads from device memory (weights of the stage for one
  * layer; for the attention stage the cache rows of the last pass). */
 int amusd_stage_time(amusd_model *m, double *total_ms, int64_t *launches, int64_t *bytes_per_launch);

@@ -1310,7 +1310,6 @@ static hipError_t launch_pass_t(const DevModel& M, const DevLayer* Ls, PassArgs&
         const int keys = P.seg[i].L + P.seg[i].k;
         P.whole &= groups ? keys <= kWaves * M.bpw * DT::BLOCK_KEYS && keys * HD * 2 * DT::ESZ <= 64 << 10 : keys <= M.chunk;
     }
-    if (tm && tm->stage == 3) P.whole = 0;                   // the merge is to be timed
     if (P.whole && groups) {
         P.packed_units = 0;
         for (int i = 0; i < P.n_seg; ++i) {

@@ -219,11 +219,65 @@ static void shared_sums() {
     CHECK((launch_pf_stream_v<BF16, kPfDown, 4, 2, 4>(M, DevLayer{}, T, tiles, many, nullptr, nullptr, 2) == hipErrorInvalidValue));
 }
 
+// A pass launches the same kernels whichever of its stages is timed.
+static void timed_stages() {
+    for (const int ctx : {40, 700}) {                       // without a merge of chunks, with one
+        amusd_model* m = model(tiny(512, 800));
+        std::vector<int32_t> toks(ctx, 1);
+        std::vector<std::string> plain;
+        CHECK(amusd_prefill(m, toks.data(), ctx, nullptr) == AMUSD_OK);
+        for (int stage = -1; stage < AMUSD_STAGE_COUNT; ++stage) {
+            CHECK(amusd_set_option(m, AMUSD_OPT_TIME_STAGE, stage) == AMUSD_OK);
+            launches.clear();
+            int32_t n, next;
+            CHECK(amusd_verify(m, ctx - 4, toks.data(), 4, &n, &next) == AMUSD_OK);
+            std::vector<std::string> now;
+            for (const Launch& l : launches) now.push_back(l.name);
+            if (stage < 0) plain = now;
+            CHECK(now == plain && count("k_attn_merge") == (ctx == 40 ? 0 : 2));
+            double ms;
+            int64_t timed, bytes;
+            if (stage >= 0) CHECK(amusd_stage_time(m, &ms, &timed, &bytes) == AMUSD_OK);
+            if (stage == AMUSD_STAGE_ATTENTION) CHECK(timed == 2);
+            if (stage == AMUSD_STAGE_ATTN_MERGE) CHECK(timed == count("k_attn_merge") && (timed > 0) == (ms > 0));
+        }
+        CHECK(amusd_model_free(m) == AMUSD_OK);
+    }
+}
+
+// Prints the attention kernel that a verify pass takes.  usage: host_test form HEADS KV_HEADS HEAD_DIM CONTEXT ROWS TOKENS [ROWS TOKENS ..],
+// a pair for each sequence (16-bit models)
+static void form(int argc, char** argv) {
+    const int n_seq = (argc - 6) / 2;
+    amusd_config c = tiny(512, std::atoi(argv[5]));
+    c.n_q_heads = std::atoi(argv[2]);
+    c.n_kv_heads = std::atoi(argv[3]);
+    c.head_dim = std::atoi(argv[4]);
+    c.max_seqs = n_seq;
+    amusd_model* m = model(c);
+    std::vector<int32_t> toks(c.max_ctx, 1), ids, rows, ctx, accepted(n_seq), next(n_seq);
+    for (int i = 0; i < n_seq; ++i) {
+        ids.push_back(i);
+        rows.push_back(std::atoi(argv[6 + 2 * i]));
+        ctx.push_back(std::atoi(argv[7 + 2 * i]));
+        CHECK(amusd_seq_prefill(m, i, toks.data(), ctx[i], nullptr) == AMUSD_OK);
+    }
+    launches.clear();
+    CHECK(amusd_verify_batch(m, n_seq, ids.data(), ctx.data(), rows.data(), toks.data(), accepted.data(), next.data()) == AMUSD_OK);
+    std::vector<std::string> taken;
+    for (const char* k : {"k_attention", "k_attention_g4", "k_attention_g8", "k_attention_packed", "k_attention_whole"})
+        if (count(k)) taken.push_back(k);
+    CHECK(taken.size() == 1);
+    std::printf("%s\n", taken[0].c_str());
+}
+
 int main(int argc, char** argv) {
     const std::string scenario = argc > 1 ? argv[1] : "";
     if (scenario == "logits_block") logits_block();
     else if (scenario == "logits_of_stretches") logits_of_stretches();
     else if (scenario == "shared_sums") shared_sums();
+    else if (scenario == "timed_stages") timed_stages();
+    else if (scenario == "form" && argc >= 8 && argc % 2 == 0) form(argc, argv);
     else return 2;
     std::printf("OK\n");
     return 0;

@@ -33,7 +33,25 @@ def host_test(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("scenario", ["logits_block", "logits_of_stretches", "shared_sums"])
+@pytest.mark.parametrize("scenario", ["logits_block", "logits_of_stretches", "shared_sums", "timed_stages"])
 def test_host_side(host_test, scenario):
     r = subprocess.run([host_test, scenario], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and r.stdout == "OK\n", r.stdout + r.stderr
+
+
+def _attention(host_test, over, max_ctx, lens, rows):
+    args = [over["n_q_heads"], over["n_kv_heads"], over["head_dim"], max_ctx] + [x for pair in zip(rows, lens) for x in pair]
+    r = subprocess.run([host_test, "form"] + [str(x) for x in args], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, r.stdout + r.stderr
+    return r.stdout.split()[0]
+
+
+def test_windows_reach_the_attention_kernels_they_are_meant_for(host_test):
+    import test_gpu_attention_heads as heads
+    for over, max_ctx, blocks, lens, rows in heads.CASES:
+        group = over["n_q_heads"] // over["n_kv_heads"]
+        per_head = 256 // (over["n_kv_heads"] * (2 if len(lens) > 1 else 1)) * (8 // group) * 32   # keys of a head, one block a run
+        assert blocks == -(-max_ctx // per_head), (over, max_ctx)
+        assert _attention(host_test, over, max_ctx, lens, rows) == f"k_attention_g{group}", (over, max_ctx, lens, rows)
+        for n in lens:
+            assert _attention(host_test, over, max_ctx, (n,) * len(lens), (1,) * len(lens)) == "k_attention_packed", (over, max_ctx, n)
