@@ -391,7 +391,7 @@ __device__ __forceinline__ void attention_unit_staged(const DevModel& M, const D
 // The same unit for a sequence with few rows: its rows times the group's heads fill one or two 16-row tiles instead of a tile
 // per head, of which a decoding step has one row each.  A unit is one such tile: lane m has the pair 16 t + m = row * G + head.
 // A run is a wave's, as its blocks are no one else's, and comes straight into registers: no block is waited for by more than
-// the wave that uses it, and several workgroups (of PARTS waves) share a compute unit.  smem: (HD + 8) * 64 floats.
+// the wave that uses it, and several workgroups (of PARTS waves) share a compute unit.  smem: kLdsFloats.
 template <class DT, int HD, int G>
 struct AttPacked {
     static constexpr int PARTS = kWaves / G, kThreads = PARTS * 64;
@@ -477,6 +477,7 @@ struct AttPacked {
             });
             if (st + 1 < n) load_values(b0, st + 1);
         }
+        wait_vm<0>();                                            // (nothing is under way: the last step asks for no other)
         s.close();
     }
     __device__ __forceinline__ void put(float* lds) const {
