@@ -1,4 +1,4 @@
-"""Properties of the prefill kernels that a run does not show: read off the assembly that the build's compiler and flags
+"""Properties of the kernels that a run does not show: read off the assembly that the build's compiler and flags
 make of them."""
 import importlib.util
 import os
@@ -130,9 +130,13 @@ def test_stores_of_a_chunk_are_as_many_as_its_waits_count(prefill):
     assert seen == 8
 
 
-def test_one_form_of_attention_per_kernel(tmp_path):
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    return _compile(os.path.join(ROOT, "paper_2410_17375_amd", "csrc", "amusd_kernels.hip"), tmp_path_factory.mktemp("asm") / "kernels.s")
+
+
+def test_one_form_of_attention_per_kernel(kernels):
     """Forms of the attention unit that share a kernel also share the largest one's registers and LDS."""
-    kernels = _compile(os.path.join(ROOT, "paper_2410_17375_amd", "csrc", "amusd_kernels.hip"), tmp_path / "kernels.s")
     forms = {name: {m.group(0) for op in body for m in re.finditer(r"^global_load_lds_dwordx4|^global_load_dwordx4", op)}
              for name, body in kernels.items() if re.search(r"\d+k_attention(_g[48])?I", name)}
     assert len(forms) == 24                    # 3 forms x 2 types x 2 head dims x (one sequence, several)
@@ -142,3 +146,18 @@ def test_one_form_of_attention_per_kernel(tmp_path):
     units = {name: sum("ds_write_b128" in op for op in body) for name, body in kernels.items() if name in forms}
     for name, writes in units.items():         # the runs' numerators go to LDS once, in the form's own merge
         assert writes == (8 if "ELi128E" in name else 4), (name, writes)
+
+
+def test_attention_over_pairs_keeps_its_blocks_in_registers(kernels):
+    """k_attention_packed and _whole hold two key blocks, up to 236 of 256 registers where two waves share a SIMD, and ask for the next
+    ones under a condition: nothing of it may go to scratch, and no wave may end with a load under way."""
+    forms = {name: body for name, body in kernels.items() if re.search(r"\d+k_attention_(packed|whole)I", name)}
+    assert len(forms) == 32                    # 2 forms x 2 types x 2 head dims x (one sequence, several) x groups of 4 and 8
+    for name, body in forms.items():
+        assert not [op for op in body if op.startswith("scratch_")], name
+        assert not _ends_with_load_in_flight(body), name
+
+
+def test_no_kernel_of_a_verify_pass_spills(kernels):
+    assert len(kernels) > 90
+    assert [name for name, body in kernels.items() if any(op.startswith("scratch_") for op in body)] == []
