@@ -1386,11 +1386,12 @@ static hipError_t launch_pf_stream_v(const DevModel& M, const DevLayer& Ly, cons
 
 // The streaming form where one round of workgroups does the stage: with the fewest column tiles (1, 2, 4) x 2 row tiles that
 // does it, else 8 x 2 for prompts of at most 32 rows, else 4 x 4.  More work per workgroup means fewer bytes, less means more
-// compute units that load.  us per launch (with 6 of timing), this form / the best plan of the other, 8B shape: 17 rows
-// QKV 19 / 33, O 16 / 32, gate/up 49 / 55, down 34 / 58; 61 rows 23 / 33, 20 / 32, (gate/up: 448 workgroups, 67 / 55), 41 / 58;
-// 128 rows 31 / 35, 23 / 33, (115 / 86), 56 / 61; 250 rows (54 / 46), 31 / 34, (200 / 114), (95 / 81).  1B shape: 61 rows 12 / 22,
-// 11 / 21, 21 / 24, 22 / 37; 250 rows 19 / 23, 14 / 21, (60 / 45), 35 / 40; 509 rows (34 / 30), 19 / 23, (117 / 65), (57 / 53).
-// Between its own forms, 61 rows of the 8B shape: O with 1, 2, 4 column tiles 26, 20, 23, down 57, 57 (2), 41 (4).
+// compute units that load.  us a layer that the best plan of the other form, sharing included, takes more (minus: less).  8B shape: 17
+// rows QKV 9, O 4, gate/up 10, down 4; 61 rows 5, 0, (gate/up does not fit a round), -4 (launch_pf_gemm); 120 rows 4, 2, -, -1; 250 rows
+// O 3.  1B shape: 17 rows 6, 5, 9, 2; 61 rows 6, 2, 4, -2; 250 rows 4, 5, -, 3; 509 rows O 4.  Width 1024: 17 rows 5, 2, 6, 3; 250 rows
+// 7, 3, -, 4.  The down projection of widths whose K range is one would gain from 8 slices here as well and has no such rule: width 3072 at 61
+// rows -8, 5120 at 61 rows -13, at 120 -30.
+// Between its own forms, 61 rows of the 8B shape: O with 1, 2, 4 column tiles 26, 20, 23, down 57, 57 (2), 41 (4) (6 of timing in each).
 template <class DT, int STAGE>
 static bool launch_pf_stream(const DevModel& M, const DevLayer& Ly, const PrefillBufs& T, const PfTileSet* tiles, const PrefillArgs& P,
                              const float* gain, hipStream_t s, hipError_t& e) {
@@ -1418,10 +1419,17 @@ using PfSmall = PfShape<2, 2, 2, 2, 6>;   // 64 x 64
 // rounds x (K blocks x time of a block + a workgroup's beginning and end), plus what the sharing costs.  The times were fitted
 // to measurements of all choices on the 8B and 1B shapes at 17 to 2048 rows: 0.82 us per K block of a large tile; 0.30 and
 // 0.20 us of the smaller ones, 0.50 and 0.35 when two share a compute unit; 12, 7.5 and 6 us at the ends, 4 more for the large
-// tile's rotations; sharing 1.6 us per workgroup of a tile (k_pf_add and its launch) and its
-// bytes at 5 TB/s each way.  The choice is within 6 % of the best at 166 of 170 sizes there, 12 % from it at
-// worst.  For instance at 250 rows of the 8B shape gate/up takes 114 us on 224 large tiles and 150 on 896 of the middle ones, at
-// 128 rows 97 and 86.  Sharing all slices is for few tiles and a long contraction (mostly the streaming form has those).
+// tile's rotations.  For instance at 250 rows of the 8B shape gate/up takes 114 us on 224 large tiles and 150 on 896 of the middle
+// ones, at 128 rows 97 and 86.
+//
+// Sharing costs k_pf_add and its launch, less the epilogues that the tiles' own workgroups then do without: 3 us, 0.3 per workgroup of a
+// tile and the sums' bytes, written and read, at 13 TB/s; and k_pf_rstd, where those workgroups might have taken 1 / rms themselves.  us per
+// prompt, with the estimate's choice / another: down of a model 1024 wide (8 layers), 600 rows, over 2 workgroups 911, over 1 961;
+// 3072 wide (4 layers), 350 rows, 8 / 1 1041 / 1105; the 8B shape (4 layers), 160 rows, 2 / 16 1119 / 1128, 1370 rows 2 / 1 5445 / 5536.
+//
+// All choices of a stage were measured at 18 lengths from 17 to 2048 rows, where the forms above do not come first.  8B and 1B shapes: the
+// choice takes up to 2 % of the prompt's time more than the best at 122 of 124, 3.1 % at worst; widths 1024 to 8192: at 236 of 242, 5.9 %
+// at worst (gate/up of width 5120, 160 rows).  The rates are those of 16-bit models: float32, 66 of 82, 7.1 % at worst.
 struct PfPlan { int shape, shares; };
 static PfPlan plan_pf_gemm(const DevModel& M, const PrefillBufs& T, const PfTileSet* sets, int n, int stage) {
     struct Shape { int tiles, rows, per_cu; double alone, full, ends; };
@@ -1430,6 +1438,7 @@ static PfPlan plan_pf_gemm(const DevModel& M, const PrefillBufs& T, const PfTile
                                     {PfSmall::kTiles, PfSmall::kRowTiles * 16, 2, 0.20, 0.35, 6.}};
     const int K = stage == kPfOproj ? M.qdim : stage == kPfDown ? M.F : M.d;
     const int kblocks = K / (M.dtype ? BF16::KB : FP32::KB), ways = stage == kPfDown && M.split_down ? 2 : 1;
+    const bool scaled = stage == kPfQKV || stage == kPfGateUp || stage == kPfLMHead;
     PfPlan best{0, 1};
     double least = 0;
     for (int s = 0; s < 3; ++s)
@@ -1442,7 +1451,7 @@ static PfPlan plan_pf_gemm(const DevModel& M, const PrefillBufs& T, const PfTile
             const double ends = h.ends + (s == 0 && stage == kPfQKV ? 4. : 0.), blocks = (double)kblocks / shares;
             const double full = blocks * h.full + ends, alone = blocks * h.alone + ends;
             const double us = wgs / round * full + (rest > (size_t)T.cus ? full : rest ? alone : 0.) +
-                              (shares > 1 ? 1.6 * shares + 2e-6 / 5 * sum_bytes : 0.);
+                              (shares > 1 ? 3. + 0.3 * shares + 1.5e-7 * sum_bytes + (scaled ? 4.8 : 0.) : 0.);
             if (least == 0 || us < least) {
                 least = us;
                 best = PfPlan{s, shares};

@@ -219,6 +219,40 @@ static void shared_sums() {
     CHECK((launch_pf_stream_v<BF16, kPfDown, 4, 2, 4>(M, DevLayer{}, T, tiles, many, nullptr, nullptr, 2) == hipErrorInvalidValue));
 }
 
+// Over how many workgroups a prompt's contractions share the K slices of their tiles, against measured times: us a prompt (several layers)
+// as it is to be, and with the other number.
+static void shares_against_measured_times() {
+    struct Point {
+        int d, F, q, kv, dtype, split_down, stage, rows, shares, other;
+        double us, other_us;
+    };
+    static const Point points[] = {
+        {1024, 4096, 1024, 256, AMUSD_DTYPE_BF16, 1, kPfDown, 600, 2, 1, 910.6, 960.7},     {1024, 4096, 1024, 256, AMUSD_DTYPE_BF16, 1, kPfDown, 1300, 2, 1, 1494.9, 1583.8},
+        {2560, 6912, 2048, 512, AMUSD_DTYPE_BF16, 0, kPfDown, 425, 8, 1, 911.5, 963.3},     {3072, 8192, 2048, 512, AMUSD_DTYPE_BF16, 0, kPfDown, 350, 8, 1, 1040.5, 1104.6},
+        {5120, 13824, 5120, 1280, AMUSD_DTYPE_BF16, 0, kPfDown, 310, 8, 1, 1634.3, 1711.0}, {4096, 14336, 4096, 1024, AMUSD_DTYPE_BF16, 2, kPfDown, 160, 2, 16, 1119.4, 1127.7},
+        {4096, 14336, 4096, 1024, AMUSD_DTYPE_BF16, 2, kPfDown, 1370, 2, 1, 5444.9, 5536.2}, {8192, 8192, 4096, 512, AMUSD_DTYPE_BF16, 0, kPfQKV, 105, 8, 1, 699.3, 707.6},
+        {2048, 8192, 2048, 512, AMUSD_DTYPE_FP32, 1, kPfDown, 310, 16, 2, 2160.4, 2337.5},
+    };
+    for (const Point& p : points) {
+        DevModel M{};
+        M.dtype = p.dtype;
+        M.d = p.d;
+        M.F = p.F;
+        M.qdim = p.q;
+        M.nqkv = p.q + 2 * p.kv;
+        M.split_down = p.split_down;
+        PfTileSet tiles[kPfStages];
+        std::vector<int> orders;
+        prefill_tile_orders(M, p.stage, 256, orders, tiles[p.stage]);
+        PrefillBufs T{};
+        T.cus = 256;
+        T.xch_bytes = 2 * kPfShareBytes;
+        const int shares = plan_pf_gemm(M, T, tiles, p.rows, p.stage).shares;
+        if (shares != p.shares) std::printf("width %d, %d rows: over %d workgroups, not %d (%.0f us), %d: %.0f us\n", p.d, p.rows, shares, p.shares, p.us, p.other, p.other_us);
+        CHECK(p.us < p.other_us && shares == p.shares);
+    }
+}
+
 // A pass launches the same kernels whichever of its stages is timed.
 static void timed_stages() {
     for (const int ctx : {40, 700}) {                       // without a merge of chunks, with one
@@ -276,6 +310,7 @@ int main(int argc, char** argv) {
     if (scenario == "logits_block") logits_block();
     else if (scenario == "logits_of_stretches") logits_of_stretches();
     else if (scenario == "shared_sums") shared_sums();
+    else if (scenario == "shares_against_measured_times") shares_against_measured_times();
     else if (scenario == "timed_stages") timed_stages();
     else if (scenario == "form" && argc >= 8 && argc % 2 == 0) form(argc, argv);
     else return 2;

@@ -33,7 +33,7 @@ def host_test(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("scenario", ["logits_block", "logits_of_stretches", "shared_sums", "timed_stages"])
+@pytest.mark.parametrize("scenario", ["logits_block", "logits_of_stretches", "shared_sums", "shares_against_measured_times", "timed_stages"])
 def test_host_side(host_test, scenario):
     r = subprocess.run([host_test, scenario], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and r.stdout == "OK\n", r.stdout + r.stderr
