@@ -388,7 +388,7 @@ __device__ __forceinline__ void attention_unit_staged(const DevModel& M, const D
     merge_runs<HD>(s, G, PARTS, hq, part, row0, k, PartialOut<HD>{part_out}, smem);
 }
 
-// The same unit for a sequence with few rows: its rows times the group's heads fill one or two 16-row tiles instead of a tile
+// The same unit for a sequence with few rows: its rows times the group's heads fill fewer 16-row tiles than a tile
 // per head, of which a decoding step has one row each.  A unit is one such tile: lane m has the pair 16 t + m = row * G + head.
 // A run is a wave's, as its blocks are no one else's, and comes straight into registers: no block is waited for by more than
 // the wave that uses it, and several workgroups (of PARTS waves) share a compute unit.  smem: kLdsFloats.

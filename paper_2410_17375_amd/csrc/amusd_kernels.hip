@@ -1302,8 +1302,12 @@ template <class DT, int HD>
 static hipError_t launch_pass_t(const DevModel& M, const DevLayer* Ls, PassArgs& P, int nwg, hipStream_t s,
                                 StageTimer* tm) {
     // Attention without a merge of chunks: a workgroup has all keys that its rows see.  Groups of 4 and 8 heads: up to a run a wave, and
-    // the 64 KB that a compute unit has under way.  us a layer less, 1B shape, 1 row behind 40 / 130 / 260 keys 3.1 / 0.5 / 0.7, 16
-    // rows 3.0 / 3.2 / 2.3 (at 520 keys, more runs than waves, 2.5 more); 8B shape, 8 rows 3.6 behind 40, 0.6 more behind 130.
+    // 64 KB of keys and values, what a compute unit has under way (256 keys of 16-bit heads of 64, 128 of heads of 128; float32
+    // half as many).  us a layer, attention + merge / this: 1B shape, 1 row and 40 keys 4.8 + 4.7 / 5.4, 126 keys 5.1 + 4.8 / 6.1, 250 keys
+    // 5.1 + 4.7 / 7.4; 16 rows, 250 keys 5.2 + 4.8 / 7.2; 8B shape, 8 rows, 40 keys 5.9 + 4.7 / 6.1, 126 keys 5.8 + 4.8 / 7.0, 16 rows
+    // 10.3 + 4.7 / 7.0 (O-projection 9.3 / 10.2, not fetched ahead); float32, heads of 64, 1 row, 126 keys 5.4 + 4.9 / 8.3.  Past the line, in a build
+    // whose waves took several runs: 1B shape, 16 rows, 260 keys 2.3 less than with a merge, 520 keys 2.5 more; 8B, 8 rows, 130 keys 0.6 more.
+    // Other groups: one chunk (groups of 1, 1B width, 1 row, 250 keys 6.4 + 4.7 / 6.6).
     const bool groups = M.G == 4 || M.G == 8;
     P.whole = 1;
     for (int i = 0; i < P.n_seg; ++i) {

@@ -38,10 +38,19 @@ inline bool pf_attention_walks_whole_rows(bool bf16, int head_dim, int group, in
 //
 // A tile per head is a workgroup a compute unit, round after round, over blocks that are staged once for all heads.  Pairs need
 // fewer products while rows are few, and their workgroups share a compute unit; with many rows each tile fetches the keys for
-// itself.  So pairs where there is more than one round, or up to half as many tiles as heads (float32 heads of 128, twice the
-// registers a block: fewer).  Measured (MI355X, whole passes of 2 layers, us, tile per head / pairs): 8B, 8 rows behind 2000 keys 211 /
-// 208, behind 12000 224 / 219, 16 rows 238 / 241; 8 sequences of one row to 4000 260 / 235; heads in eights, 12 rows behind 7000 234 /
-// 238; float32, 8 rows behind 2000 359 / 365, 2 rows behind 7000 391 / 375; 1B (4 layers), 16 rows behind 4000 236 / 229.
+// itself.  So pairs
+//   where there is more than one round (168 sizes of the eight forms: all faster, by 0.2 to 154 us a layer.  Many rows to a unit do
+//     not occur there, as it takes three sequences and a pass has 16 rows: at most 0.47 tiles a head);
+//   up to half as many tiles as heads (float32 heads of 128, twice the registers a block: fewer);
+//   and for 16-bit heads of 64 in runs of up to 7 blocks whatever the rows: both of a unit's forms are then mostly its beginning and
+//     end (40 sizes, 0.8 us a layer less in the mean, 0.8 more at most; with 8 and more blocks and every compute unit taken
+//     1.2 more: 16 rows behind 16360 keys 18.8 / 20.0).
+// The line holds for full contexts, whose units are about the compute units.  With fewer than 200 of 256 pairs were faster for any number
+// of rows (191 sizes that this takes a tile per head for, 0.2 us a layer slower at worst, 1 to 10 faster in the mean of a form): not made use of.
+// Measured (MI355X): the attention's and the O-projection's kernels over 990 sizes, 1 to 8 sequences of 1 to 16 rows behind 100 to 16360
+// keys; where the rule says pairs they are 1 us a layer slower at worst.  Whole passes of 2 layers, us, tile per head / pairs: 8B, 8 rows
+// behind 2000 keys 211 / 208, behind 12000 224 / 219, 16 rows 238 / 241; 8 sequences of one row to 4000 260 / 235; heads in eights, 12 rows
+// behind 7000 234 / 238; float32, 8 rows behind 2000 359 / 365, 2 rows behind 7000 391 / 375; 1B (4 layers), 16 rows behind 4000 236 / 229.
 inline bool attention_packs_rows(bool bf16, int head_dim, int group, int units, double tiles, int run_blocks, int cus) {
     if (units > cus) return true;
     if (tiles <= group * (head_dim == 128 && !bf16 ? 0.375 : 0.5)) return true;

@@ -54,7 +54,7 @@ static const Point points[] = {
     {true, 128, 8, 1, 128, 1628, 64, 2, 256, 54, 24},
 };
 
-// Whether a verify pass's attention is tiles of (row, head) pairs or a tile per head, against measured times of a pass of two layers (us):
+// Whether a verify pass's attention is tiles of (row, head) pairs or a tile per head, against measured times of a pass of two layers (us; of four below):
 // sizes that differ by 1 % and more.
 struct Pass {
     bool bf16;
@@ -72,6 +72,13 @@ static const Pass passes[] = {
     {true, 128, 8, 252, 8, 8, 252.8, 246.9},     {false, 64, 4, 256, 1, 7, 155.9, 163.3},     {false, 64, 4, 256, 4, 16, 202.2, 196.6},
     {false, 64, 8, 252, 4, 16, 175.0, 188.9},    {false, 64, 8, 252, 8, 16, 211.0, 202.5},    {false, 128, 4, 168, 2, 3, 363.9, 357.6},
     {false, 128, 4, 232, 1.45, 5, 372.6, 382.0}, {false, 128, 4, 256, 3, 16, 439.7, 430.8},   {false, 128, 4, 656, 1, 5, 387.7, 431.7},
+    // more units than compute units, and the most rows a unit then has: a window of 13 rows and three of one
+    {true, 64, 4, 464, 1.83, 4, 248.7, 262.6},   {true, 64, 8, 448, 2.71, 1, 234.8, 246.8},   {true, 128, 4, 456, 1.84, 1, 229.9, 233.2},
+    {true, 128, 8, 448, 2.71, 1, 229.6, 234.8},  {false, 64, 4, 456, 1.84, 2, 130.1, 136.7},  {false, 64, 8, 448, 2.71, 2, 132.8, 142.1},
+    {false, 128, 4, 456, 1.84, 4, 164.5, 176.2}, {false, 128, 8, 448, 2.71, 2, 219.7, 235.2},
+    // 16-bit heads of 64 in short runs, many rows
+    {true, 64, 4, 104, 4, 2, 210.8, 214.6},      {true, 64, 4, 32, 4, 2, 205.0, 212.9},       {true, 64, 8, 104, 8, 2, 217.0, 223.2},
+    {true, 64, 8, 128, 8, 1, 226.2, 234.4},      {true, 64, 8, 244, 4.67, 1, 233.4, 240.8},   {true, 64, 4, 248, 2.55, 4, 235.7, 241.1},
 };
 
 extern "C" int whole_rows(int bf16, int head_dim, int group, int kv_heads, int rows, int keys, int cus, int chunk, int run_blocks, int stretch) {
